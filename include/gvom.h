@@ -188,7 +188,7 @@ int32_t map_insert_scan(map_t* m, const float* xyz_dev, int64_t n, const float p
 int32_t map_insert_scan_static(map_t* m, const float* xyz_dev, int64_t n,
                                const float pose[12], uint32_t flags);
 
-/* Writes the 2D maps of Sec. III-D into the caller's device arrays. *//* Writes the 2D maps of Sec. III-D into the caller's device arrays. */
+/* Writes the 2D maps of Sec. III-D into the caller's device arrays. */
 int32_t map_export_2d(map_t* m, const map_2d_t* out_dev);
 
 /* Writes the Sec. III-A lookup table and data array:
@@ -263,7 +263,9 @@ int32_t map_sync(map_t* m);
  * traversal grid (blocks of four waves), 1..32 (default 28, the most that fit
  * a compute unit); surface_tile: edge in
  * pixels of the tiles of the slope / roughness / negative-obstacle pass, 16
- * or 32 (default 32; other positive values are MAP_E_INVALID).  A field
+ * or 32 (default 32, which also lets the library take tiles of 16 or 64 where
+ * the launch has very few or very many; other positive values are
+ * MAP_E_INVALID).  A field
  * <= 0 keeps the current value.  The batch autotuner sets all three. */
 typedef struct {
   int32_t seg_len;

@@ -294,6 +294,7 @@ int32_t map_create(const map_params_t* p, void* stream, map_t** out) {
   if (e == hipSuccess) e = dmalloc(&m->minqz, V * 4);
   if (e == hipSuccess) e = dmalloc(&m->occ, C * m->d.W * 8);
   if (e == hipSuccess) e = dmalloc(&m->hq, C * 4);
+  if (e == hipSuccess) e = dmalloc(&m->defbits, nb * 8);
   if (e == hipSuccess) e = dmalloc(&m->block_base, nb * 4);
   if (e == hipSuccess) e = dmalloc(&m->colpre, C * 4);
   if (e == hipSuccess) e = dmalloc(&m->stats, kStatsBytes);
@@ -332,6 +333,7 @@ int32_t map_destroy(map_t* m) {
   (void)gvom::dev_free(m->minqz);
   (void)gvom::dev_free(m->occ);
   (void)gvom::dev_free(m->hq);
+  (void)gvom::dev_free(m->defbits);
   (void)gvom::dev_free(m->block_base);
   (void)gvom::dev_free(m->colpre);
   (void)gvom::dev_free(m->stats);
@@ -362,6 +364,7 @@ int32_t map_reset(map_t* m) {
   m->last_trace_blocks = 0;
   hipError_t e = clear_all(m);
   m->empty = true;
+  m->wild = false;
   if (e == hipSuccess) e = hipMemsetAsync(m->stats, 0, kStatsBytes, m->stream);
   // an insert that failed between the traversal and the fold leaves counts
   if (e == hipSuccess)
@@ -540,14 +543,21 @@ void column_args(const map_t* m, const map_2d_t* out, bool ranks, gvom::ColumnAr
   ca->density = out->density;
   ca->flags = out->flags;
   ca->hq = m->hq;
+  ca->defbits = m->defbits;
   ca->colpre = ranks ? m->colpre : nullptr;
   ca->block_base = ranks ? m->block_base : nullptr;
+}
+
+int64_t tiles64(const map_t* m) {
+  return (int64_t)((m->p.nx + 63) / 64) * ((m->p.ny + 63) / 64);
 }
 
 void surface_args(const map_t* m, const map_2d_t* out, gvom::SurfaceArgs* sa) {
   sa->nx = m->p.nx;
   sa->ny = m->p.ny;
   sa->hq = m->hq;
+  sa->defbits = (const uint32_t*)m->defbits;
+  sa->wild = m->wild;
   sa->half_fit = m->c.half_fit;
   sa->search_d = m->c.search_d;
   sa->tau_q = m->c.tau_neg_q;
@@ -721,7 +731,9 @@ int32_t map_export_2d(map_t* m, const map_2d_t* out) {
     gvom::SurfaceArgs sa;
     surface_args(m, out, &sa);
     pm = prof_begin(m, MAP_PROF_SURFACE);
-    e = gvom::launch_surface(sa, m->surf_tile, m->stream);
+    const int H = sa.search_d > sa.half_fit ? sa.search_d : sa.half_fit;
+    const int tile = gvom::surface_tile_for(H, m->surf_tile, tiles64(m), m->n_cu);
+    e = gvom::launch_surface(sa, tile, m->stream);
     prof_end(m, pm);
   }
   return dev_status(m, e);
@@ -803,11 +815,13 @@ int32_t map_import_voxels(map_t* m, const int32_t* lut_dev, const map_voxel_t* d
   hipError_t e = hipMemsetAsync(m->err, 0, 4, m->stream);
   if (e == hipSuccess)
     e = gvom::launch_import(m->d, lut_dev, data_dev, n_data, m->hits, m->passes, m->minqz,
-                            m->occ, m->err, m->stream);
+                            m->occ, m->origin[2], m->err, m->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(&err, m->err, 4, hipMemcpyDeviceToHost, m->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
   if (e != hipSuccess) return dev_status(m, e);
-  if (err) {
+  m->wild = (err & 2) != 0;
+  if (err & 1) {
+    m->wild = false;
     initial_origin(m);
     e = clear_all(m);
     m->empty = true;
@@ -873,7 +887,7 @@ int32_t map_sync(map_t* m) {
 int32_t map_set_tuning(map_t* m, const map_tuning_t* t) {
   if (!m || !t) return MAP_E_INVALID;
   if (t->seg_len > 1024 || t->trace_waves_per_cu > 32) return MAP_E_INVALID;
-  if (!(t->surface_tile <= 0 || t->surface_tile == 16 || t->surface_tile == 32))
+  if (!(t->surface_tile <= 0 || t->surface_tile == 16 || t->surface_tile == 32 ))
     return MAP_E_INVALID;
   // the wave-item buffer is sized for the segment length at the next insert
   if (t->seg_len > 0) m->seg_len = t->seg_len;
@@ -960,8 +974,10 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
   gvom::BatchTables* t = b->htab;
   gvom::BatchStep& st = t->st;
   st.nmaps = b->k;
-  st.pre_rays[0] = st.pre_trace[0] = st.pre_col[0] = st.pre_surf[0][0] = st.pre_surf[1][0] = 0;
+  st.pre_rays[0] = st.pre_trace[0] = st.pre_col[0] = st.pre_surf[0] = 0;
   st.pre_lcount[0] = st.pre_lscan[0] = st.pre_lwrite[0] = 0;
+  int64_t t64 = 0;
+  for (int i = 0; i < b->k; i++) t64 += tiles64(b->maps[i]);
   for (int i = 0; i < b->k; i++) {
     map_t* m = b->maps[i];
     bool full = false;
@@ -980,7 +996,9 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
     }
     const int64_t C = (int64_t)m->p.nx * m->p.ny;
     const int ray_blocks = (int)((n[i] + gvom::kRayBlock - 1) / gvom::kRayBlock);
-    const int tile = m->surf_tile, ti = tile == 16 ? 0 : 1;
+    st.surf_H[i] = m->c.search_d > m->c.half_fit ? m->c.search_d : m->c.half_fit;
+    const int tile = gvom::surface_tile_for(st.surf_H[i], m->surf_tile, t64, b->n_cu);
+    st.surf_tile[i] = tile;
     const int tiles_y = (m->p.ny + tile - 1) / tile;
     const int tiles = ((m->p.nx + tile - 1) / tile) * tiles_y;
     const int lw_by = (m->d.nby + 3) / 4;
@@ -988,13 +1006,11 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
     st.pre_rays[i + 1] = st.pre_rays[i] + (n[i] > 0 ? ray_blocks : 0);
     st.pre_trace[i + 1] = st.pre_trace[i] + t->ins[i].trace_blocks;
     st.pre_col[i + 1] = st.pre_col[i] + (int)((C + 255) / 256);
-    st.pre_surf[ti][i + 1] = st.pre_surf[ti][i] + tiles;
-    st.pre_surf[1 - ti][i + 1] = st.pre_surf[1 - ti][i];
+    st.pre_surf[i + 1] = st.pre_surf[i] + tiles;
     st.pre_lcount[i + 1] = st.pre_lcount[i] + (lut ? (int)((C + 255) / 256) : 0);
     st.pre_lscan[i + 1] = st.pre_lscan[i] + (lut ? 1 : 0);
     st.pre_lwrite[i + 1] = st.pre_lwrite[i] + (lut ? lw : 0);
     st.surf_tiles_y[i] = tiles_y;
-    st.surf_H[i] = m->c.search_d > m->c.half_fit ? m->c.search_d : m->c.half_fit;
     st.lw_by[i] = lw_by;
     st.lut_groups[i] = (int)((C + 63) / 64);
     st.nz_magic[i] = gvom::nz_magic(m->p.nz);
@@ -1101,19 +1117,24 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
     khz = 100000;
   b->clock_khz = khz;
   size_t surf = 0, lut = 0;
+  int64_t t64 = 0;
+  for (int i = 0; i < k; i++) t64 += tiles64(maps[i]);
   for (int i = 0; i < k; i++) {
     const map_t* m = maps[i];
     const int H = m->c.search_d > m->c.half_fit ? m->c.search_d : m->c.half_fit;
-    // either tile size (the maps' tuning may change before a step)
-    const size_t s32 = gvom::surface_lds(H, 32), s16 = gvom::surface_lds(H, 16);
-    const size_t s1 = s32 > s16 ? s32 : s16, s2 = gvom::lut_lds(m->p.nz);
-    surf = s1 > surf ? s1 : surf;
+    // any tile size (the maps' tuning may change before a step)
+    const size_t s2 = gvom::lut_lds(m->p.nz);
+    for (int tile = 16; tile <= 32; tile *= 2) {
+      const int t = gvom::surface_tile_for(H, tile, t64, b->n_cu);
+      const size_t s1 = gvom::surface_lds(H, t);
+      surf = s1 > surf ? s1 : surf;
+    }
     lut = s2 > lut ? s2 : lut;
   }
   const int cu = b->n_cu;
   // persistent grids; the bandwidth-bound column and table passes get eight
   // blocks per CU (the table pass's LDS regions allow it)
-  b->grid = gvom::BatchGrid{cu * 4, cu * 2, cu * 8, cu * 8, cu * 2, cu * 8, cu * 4, cu * 8,
+  b->grid = gvom::BatchGrid{cu * 4, cu * 2, cu * 8, cu * 8, cu * 2, cu * 4, cu * 8,
                             k * gvom::box_fold_blocks(), surf, lut};
   hipError_t e = gvom::dev_alloc((void**)&b->dtab, sizeof(gvom::BatchTables));
   if (e == hipSuccess) e = hipHostMalloc((void**)&b->htab, sizeof(gvom::BatchTables), 0);

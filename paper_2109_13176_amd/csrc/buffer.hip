@@ -941,6 +941,7 @@ int32_t map_buffer_combine(map_buffer_t* b, map_t* out) {
   gvom::set_origin(out, nw.origin);
   out->lut_counted = false;
   out->empty = false;
+  out->wild = false;  // (an update in place starts from a combination)
   gvom::CombineArgs a;
   a.d = out->d;
   for (int i = 0; i < 3; i++) a.O[i] = nw.origin[i];

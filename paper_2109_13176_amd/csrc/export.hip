@@ -10,9 +10,9 @@ namespace {
 
 __global__ __launch_bounds__(kBlock) void k_column(ColumnArgs a) { column_body(a, blockIdx.x); }
 
-template <int NT, int TILE>
-__global__ __launch_bounds__(NT) void k_surface(SurfaceArgs a, int H) {
-  surface_body<NT, TILE>(a, H, blockIdx.x, blockIdx.y);
+template <int TILE>
+__global__ __launch_bounds__(kSurfThreads, 8) void k_surface(SurfaceArgs a, int H) {
+  surface_body<kSurfThreads, TILE>(a, H, blockIdx.x, blockIdx.y);
 }
 
 __global__ __launch_bounds__(kBlock) void k_lut_count(LutArgs a) { lut_count_body(a, blockIdx.x); }
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kBlock) void k_import(Dims d, const int32_t* lut,
                                                    const map_voxel_t* data, int64_t n_data,
                                                    int32_t* hits, int32_t* passes,
                                                    int32_t* minqz, unsigned long long* occ,
-                                                   int32_t* err) {
+                                                   int32_t origin_z, int32_t* err) {
   const int lane = __lane_id();
   const int64_t c = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
   const int nx = d.nx, ny = d.ny, nz = d.nz;
@@ -153,6 +153,7 @@ __global__ __launch_bounds__(kBlock) void k_import(Dims d, const int32_t* lut,
           h = data[v].hits;
           p = data[v].passes;
           mq = data[v].min_qz;
+          if (mq >> 16 != origin_z + z) atomicOr(err, 2);
           occd = true;
         } else {
           atomicOr(err, 1);
@@ -223,20 +224,18 @@ __global__ __launch_bounds__(kBlock) void k_b_column(const BatchTables* __restri
   }
 }
 
-// The maps whose surface tile is TILE (index ti of pre_surf): tile 32 on
-// 1,024-thread blocks, tile 16 on 256-thread blocks.
-template <int NT, int TILE, int ti>
-__global__ __launch_bounds__(NT) void k_b_surface(const BatchTables* __restrict__ t,
-                                                  unsigned long long* stamps) {
+__global__ __launch_bounds__(kSurfThreads, 4) void k_b_surface(const BatchTables* __restrict__ t,
+                                                               unsigned long long* stamps) {
   const int n = t->st.nmaps;
-  const int32_t* pre = t->st.pre_surf[ti];
-  const int total = pre[n];
+  const int total = t->st.pre_surf[n];
   Stamper sp;
   for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {
-    const int m = find_map_e(pre, n, vb);
-    const int tile = vb - pre[m];
-    const int ty = t->st.surf_tiles_y[m];
-    surface_body<NT, TILE>(t->sur[m], t->st.surf_H[m], tile / ty, tile % ty);
+    const int m = find_map_e(t->st.pre_surf, n, vb);
+    const int b = vb - t->st.pre_surf[m];
+    const int ty = t->st.surf_tiles_y[m], H = t->st.surf_H[m], tile = t->st.surf_tile[m];
+    if (tile == 64) surface_body<kSurfThreads, 64>(t->sur[m], H, b / ty, b % ty);
+    else if (tile == 32) surface_body<kSurfThreads, 32>(t->sur[m], H, b / ty, b % ty);
+    else surface_body<kSurfThreads, 16>(t->sur[m], H, b / ty, b % ty);
     __syncthreads();
     sp.done(m, !t->st.last_is_lut[m], stamps);
   }
@@ -283,19 +282,13 @@ __global__ __launch_bounds__(kBlock) void k_b_lut_write(const BatchTables* __res
 hipError_t launch_batch_export(const BatchTables* tab, const BatchGrid& g,
                                unsigned long long* stamps, hipStream_t s) {
   if (g.surf_lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_b_surface<kSurfThreads, kTile, 1>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)g.surf_lds);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_b_surface<256, 16, 0>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.surf_lds);
+    const hipError_t e = hipFuncSetAttribute((const void*)k_b_surface,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)g.surf_lds);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_b_column, dim3(g.col), dim3(kBlock), 0, s, tab);
-  hipLaunchKernelGGL((k_b_surface<256, 16, 0>), dim3(g.surf16), dim3(256), g.surf_lds, s, tab,
-                     stamps);
-  hipLaunchKernelGGL((k_b_surface<kSurfThreads, kTile, 1>), dim3(g.surf), dim3(kSurfThreads),
-                     g.surf_lds, s, tab, stamps);
+  hipLaunchKernelGGL(k_b_surface, dim3(g.surf), dim3(kSurfThreads), g.surf_lds, s, tab, stamps);
   hipLaunchKernelGGL(k_b_lut_count, dim3(g.lcount), dim3(kBlock), 0, s, tab);
   hipLaunchKernelGGL(k_b_lut_scan, dim3(g.lcount), dim3(1024), 0, s, tab);
   hipLaunchKernelGGL(k_b_lut_write, dim3(g.lwrite), dim3(kBlock), g.lut_lds, s, tab, stamps);
@@ -308,13 +301,10 @@ hipError_t launch_column(const ColumnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-int surface_tile() { return kTile; }
-
 size_t surface_lds(int H, int tile) {
   const int T = tile + 2 * H;
-  const int MW = (T + 63) / 64;
-  return (size_t)((T * surface_stride(T) + 1) & ~1) * 4 + 2 * (size_t)T * MW * 8 +
-         2 * (size_t)T * tile;
+  return (size_t)T * surface_stride(T) * 4 + 2 * (size_t)T * surface_mask_stride(T) * 4 +
+         2 * (size_t)tile * surface_dist_stride(T) + 2 * (size_t)tile * tile;
 }
 
 size_t lut_lds(int nz) { return (size_t)kRegCols * lut_row(nz) * 4; }
@@ -323,8 +313,20 @@ uint32_t nz_magic(int nz) {
   return nz > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint64_t)nz - 1) / (uint64_t)nz) : 0u;
 }
 
-// tile 32: one pixel per thread (1,024-thread blocks); tile 16: 256 threads
-template <int NT, int TILE>
+// A tile's serial phases cost much the same for 16, 32 and 64 pixels, so the
+// tile follows the number of compute units: 16 while two blocks per unit hold
+// every tile, 64 (which stages 3.2 or, at D = 50, 6.6 cells per pixel where 32
+// stages 6.6 or 17) once every unit gets one, else 32.  Measured (us, tiles
+// of 16 / 32 / 64, with the events' ~3 us): 128 x 128, D = 13 10.0 / 12.0 / 24.5;
+// 354 x 278, D = 20 12.7 / 14.0 / 33; 512 x 512, D = 25 24.3 / 15.8 / 37;
+// 640 x 640, D = 50 45 / 35 / 53; 1024 x 1024, D = 50 97 / 72 / 55.
+int surface_tile_for(int H, int tile, int64_t tiles64, int n_cu) {
+  if (tile != 32) return tile;
+  if (8 * tiles64 <= n_cu) return 16;
+  return tiles64 >= n_cu && surface_lds(H, 64) <= 160 * 1024 ? 64 : 32;
+}
+
+template <int TILE>
 hipError_t launch_surface_t(const SurfaceArgs& a, hipStream_t s) {
   const int H = a.search_d > a.half_fit ? a.search_d : a.half_fit;
   const int T = TILE + 2 * H;
@@ -333,18 +335,19 @@ hipError_t launch_surface_t(const SurfaceArgs& a, hipStream_t s) {
   const size_t lds = surface_lds(H, TILE);
   if (lds > 160 * 1024) return hipErrorInvalidValue;
   if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute((const void*)k_surface<NT, TILE>,
+    const hipError_t e = hipFuncSetAttribute((const void*)k_surface<TILE>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize,
                                              (int)lds);
     if (e != hipSuccess) return e;
   }
   dim3 g((a.nx + TILE - 1) / TILE, (a.ny + TILE - 1) / TILE);
-  hipLaunchKernelGGL((k_surface<NT, TILE>), g, dim3(NT), lds, s, a, H);
+  hipLaunchKernelGGL((k_surface<TILE>), g, dim3(kSurfThreads), lds, s, a, H);
   return hipGetLastError();
 }
 
 hipError_t launch_surface(const SurfaceArgs& a, int tile, hipStream_t s) {
-  return tile == 16 ? launch_surface_t<256, 16>(a, s) : launch_surface_t<kSurfThreads, kTile>(a, s);
+  return tile == 64 ? launch_surface_t<64>(a, s)
+                    : tile == 16 ? launch_surface_t<16>(a, s) : launch_surface_t<32>(a, s);
 }
 
 hipError_t launch_lut(const LutArgs& a, bool counted, hipStream_t s) {
@@ -382,10 +385,11 @@ hipError_t launch_scan_i32(int32_t* base, int nb, int64_t* total, hipStream_t s)
 
 hipError_t launch_import(const Dims& d, const int32_t* lut, const map_voxel_t* data,
                          int64_t n_data, int32_t* hits, int32_t* passes, int32_t* minqz,
-                         unsigned long long* occ, int32_t* err, hipStream_t s) {
+                         unsigned long long* occ, int32_t origin_z, int32_t* err,
+                         hipStream_t s) {
   const int64_t threads = (int64_t)d.nx * d.ny * 64;
   hipLaunchKernelGGL(k_import, dim3((unsigned)((threads + kBlock - 1) / kBlock)), dim3(kBlock),
-                     0, s, d, lut, data, n_data, hits, passes, minqz, occ, err);
+                     0, s, d, lut, data, n_data, hits, passes, minqz, occ, origin_z, err);
   return hipGetLastError();
 }
 

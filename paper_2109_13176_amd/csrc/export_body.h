@@ -107,14 +107,13 @@ __device__ __forceinline__ void column_body(const ColumnArgs& a, const int blk) 
   }
   // every lane of the wave takes part in the rank scan
   if (a.colpre) column_counts(a, c, __popcll(m.lo) + __popcll(m.hi));
-  if (!valid) return;
   const int kg = lowest_bit(m);
-  float height = __uint_as_float(kQNaN), density = __uint_as_float(kQNaN);
+  const int64_t base = col_base(a.d, sx, sy);
   int32_t hq = INT32_MIN;
+  if (kg >= 0) hq = a.minqz[base + (wrap_add(kg + a.d.ro[2], nz) << 4)];
+  float height = __uint_as_float(kQNaN), density = __uint_as_float(kQNaN);
   uint8_t f = 0;
   if (kg >= 0) {
-    const int64_t base = col_base(a.d, sx, sy);
-    hq = a.minqz[base + (wrap_add(kg + a.d.ro[2], nz) << 4)];
     height = (float)((double)hq * a.res / 65536.0);
     f = 1;
     int64_t sh = 0, sa = 0;
@@ -149,6 +148,10 @@ __device__ __forceinline__ void column_body(const ColumnArgs& a, const int blk) 
       f |= 2 | (hard ? 4 : 8);
     }
   }
+  // the defined pixels of the wave's 64 columns, for the surface pass
+  const unsigned long long defined = __ballot(hq != INT32_MIN);
+  if (!valid) return;
+  if ((c & 63) == 0) a.defbits[c >> 6] = defined;
   a.height[c] = height;
   a.density[c] = density;
   a.flags[c] = f;
@@ -166,261 +169,532 @@ __device__ __forceinline__ void column_body(const ColumnArgs& a, const int blk) 
 // x+d over columns y-d..y+d; it holds a defined cell iff the distance along
 // that row from column y to the nearest defined cell is <= d.  These row
 // (and column) distances are precomputed for the tile's own columns (rows)
-// from per-line bit masks, so each ring costs one LDS byte; only the slice
-// where a cone stops is then read cell by cell.
+// from per-line bit masks, so each ring costs one LDS byte; the rings of all
+// four cones are looked up together, and so are the defined cells of the four
+// stopping slices (about seven in all).
+//
+// Bound: the latency and VALU issue of a tile's serial phases (there is about
+// one tile per compute unit at 512 x 512), not memory (14 bytes per pixel).
+// Measured (HIP events): 512 x 512 at 0.2 m 23.5 -> 15.8 us, 1024 x 1024 at
+// 0.1 m 108 -> 55 us, 128 x 128 at 0.4 m 15.3 -> 10.0 us, against masks built
+// from the staged heights, distances read ring by ring in a layout whose
+// column reads met in the same LDS banks, cones and their cells one after the
+// other, and 64-bit normal sums in every cell.
 constexpr int kTile = 32;
-constexpr int kSurfThreads = kTile * kTile;
+constexpr int kSurfThreads = 1024;
 constexpr int kMaxMaskWords = 3;  // staged edge <= 192 cells
 
-__device__ __forceinline__ unsigned long long span_bits(unsigned long long v, int w, int a,
-                                                        int b) {
-  // bits of word w that fall in the inclusive cell range [a, b]
-  const int lo = a - 64 * w, hi = b - 64 * w;
-  if (lo > 0) v &= ~0ull << lo;
-  if (hi < 63) v &= ~0ull >> (63 - hi);
-  return v;
+// LDS row stride of the staged heights: odd, so that the column reads of
+// the range pass hit distinct banks
+__host__ __device__ __forceinline__ int surface_stride(int T) { return T | 1; }
+// 32-bit words of a line mask: the cells' bits and 64 zero bits on each side;
+// odd, so that the lanes of a wave reading one word of many lines hit
+// distinct banks (as the strides below)
+__host__ __device__ __forceinline__ int surface_mask_stride(int T) {
+  return 2 * ((T + 63) >> 6) + 5;
+}
+// Distances are kept line-fastest, [tile column][line], so that the rings of a
+// cone are consecutive bytes.  Ring lookups run up to seven rings past D, in
+// whole words: bytes on each side of the lines, which hold "none" (the lookup
+// subtracts whole words, so every byte it reads has to be below 128).
+constexpr int kSurfPad = 12;
+__host__ __device__ __forceinline__ int surface_dist_stride(int T) {
+  return 4 * (((T + 2 * kSurfPad + 3) >> 2) | 1);
 }
 
-// distance from cell k of a line (bit mask of MW words, T cells) to its
-// nearest set bit, clamped to 255
-__device__ __forceinline__ int line_distance(const unsigned long long* L, int MW, int T, int k) {
-  int best = 255;
-  for (int w = 0; w < MW; w++) {
-    unsigned long long v = L[w];
-    if (!v) continue;
-    // nearest set bit at or below k, and at or above k, within this word
-    const int base = 64 * w;
-    if (k >= base) {
-      const int top = min(k - base, 63);
-      const unsigned long long below = top == 63 ? v : (v & ((2ull << top) - 1ull));
-      if (below) best = min(best, k - (base + 63 - __clzll((long long)below)));
+// 32 bits of a bit string starting at bit s.
+__device__ __forceinline__ uint32_t bits_at(const uint32_t* w, int s) {
+  const int i = s >> 5;
+  return __builtin_amdgcn_alignbit(w[i + 1], w[i], (uint32_t)s & 31u);
+}
+
+// Distance from cell k of a line mask to its nearest set bit; kSurfNone where
+// there is none within 31 (within 64 with FAR) cells.
+constexpr uint32_t kSurfNone = 127;
+template <bool FAR>
+__device__ __forceinline__ uint32_t line_distance(const uint32_t* m, int k) {
+  const uint32_t* w = m + (k >> 5);
+  const uint32_t sh = (uint32_t)k & 31u;
+  // cells k-32..k-1 (bit 31 = k-1) and k..k+31 (bit 0 = k)
+  const uint32_t lo = __builtin_amdgcn_alignbit(w[2], w[1], sh);
+  const uint32_t hi = __builtin_amdgcn_alignbit(w[3], w[2], sh);
+  uint32_t a = lo ? (uint32_t)__builtin_clz(lo) + 1u : kSurfNone;
+  uint32_t b = hi ? (uint32_t)__builtin_ctz(hi) : kSurfNone;
+  if (FAR) {  // cells k-64..k-33 and k+32..k+63, and k+64
+    const uint32_t lo2 = __builtin_amdgcn_alignbit(w[1], w[0], sh);
+    const uint32_t hi2 = __builtin_amdgcn_alignbit(w[4], w[3], sh);
+    const uint32_t a2 = lo2 ? (uint32_t)__builtin_clz(lo2) + 33u : kSurfNone;
+    const uint32_t b2 = hi2 ? (uint32_t)__builtin_ctz(hi2) + 32u
+                            : ((w[4] >> sh) & 1u ? 64u : kSurfNone);
+    a = min(a, a2);
+    b = min(b, b2);
+  }
+  return min(a, b);
+}
+
+// Normal equations of the N x N window of a defined pixel (heights relative
+// to the centre's).
+struct PlaneSums {
+  int32_t n, sx, sy, sxx, syy, sxy;
+  int64_t sz, sxz, syz, szz;
+};
+
+__device__ __forceinline__ void plane_sums(const int32_t* c, const int TS, const int h,
+                                           const int32_t hc, PlaneSums& s) {
+  s = {};
+  for (int dx = -h; dx <= h; dx++)
+    for (int dy = -h; dy <= h; dy++) {
+      const int32_t v = c[dx * TS + dy];
+      if (v == INT32_MIN) continue;
+      const int64_t dz = (int64_t)v - hc;
+      s.n++;
+      s.sx += dx;
+      s.sy += dy;
+      s.sxx += dx * dx;
+      s.syy += dy * dy;
+      s.sxy += dx * dy;
+      s.sz += dz;
+      s.sxz += dx * dz;
+      s.syz += dy * dz;
+      s.szz += dz * dz;
     }
-    if (k <= base + 63) {
-      const int bot = max(k - base, 0);
-      const unsigned long long above = v & (~0ull << bot);
-      if (above) best = min(best, base + __ffsll((long long)above) - 1 - k);
+}
+
+// The same for N = 5 and heights within 2^23 of each other (the first moments
+// stay below 30 * 2^23, so 32-bit sums are exact).  The counts are summed as
+// packed byte fields, offsets making every field non-negative: a row's
+// n | sum(dy+2) << 8 | sum(dy^2) << 16, then over the rows their sums (at most
+// 25, 50, 50), the sums weighted by dx+2 (at most 50, 100) and by dx^2 (50).
+__device__ __forceinline__ void plane_sums5(const int32_t* c, const int TS, const int32_t hc,
+                                            PlaneSums& s) {
+  uint32_t c0 = 0, c1 = 0, c2 = 0;
+  int32_t sz = 0, sxz = 0, syz = 0;
+  int64_t szz = 0;
+#pragma unroll
+  for (int dx = -2; dx <= 2; dx++) {
+    uint32_t r = 0;
+    int32_t rz = 0;
+#pragma unroll
+    for (int dy = -2; dy <= 2; dy++) {
+      const int32_t v = c[dx * TS + dy];
+      const bool def = v != INT32_MIN;
+      const int32_t dz = def ? v - hc : 0;
+      r += def ? 1u | (uint32_t)(dy + 2) << 8 | (uint32_t)(dy * dy) << 16 : 0u;
+      rz += dz;
+      syz += dy * dz;
+      szz += (int64_t)dz * dz;
+    }
+    c0 += r;
+    c1 += r * (uint32_t)(dx + 2);
+    c2 += (r & 0xFFu) * (uint32_t)(dx * dx);
+    sz += rz;
+    sxz += dx * rz;
+  }
+  s.n = (int32_t)(c0 & 0xFFu);
+  s.sy = (int32_t)((c0 >> 8) & 0xFFu) - 2 * s.n;
+  s.syy = (int32_t)(c0 >> 16);
+  s.sx = (int32_t)(c1 & 0xFFu) - 2 * s.n;
+  s.sxx = (int32_t)c2;
+  // sum (dx+2)(dy+2) = sxy + 2 sx + 2 sy + 4 n
+  s.sxy = (int32_t)((c1 >> 8) & 0xFFu) - 2 * (s.sx + s.sy) - 4 * s.n;
+  s.sz = sz;
+  s.sxz = sxz;
+  s.syz = syz;
+  s.szz = szz;
+}
+
+// Least-squares plane from the sums; I = integer type that holds the
+// determinant's terms (int32 for N = 5: at most 25 * 50 * 50 * 3, with factors
+// of at most 24 bits).
+__device__ __forceinline__ int32_t mul_i(int32_t a, int32_t b) { return __mul24(a, b); }
+__device__ __forceinline__ int64_t mul_i(int64_t a, int64_t b) { return a * b; }
+
+template <class I>
+__device__ __forceinline__ bool plane_solve(const PlaneSums& s, const double q2m, float& slope,
+                                            float& rough) {
+  const I n = s.n, sx = s.sx, sy = s.sy, sxx = s.sxx, syy = s.syy, sxy = s.sxy;
+  // adjugate of M = [[sxx sxy sx] [sxy syy sy] [sx sy n]] (symmetric)
+  const I c00 = mul_i(syy, n) - mul_i(sy, sy);
+  const I c01 = mul_i(sy, sx) - mul_i(sxy, n);
+  const I c02 = mul_i(sxy, sy) - mul_i(syy, sx);
+  const I c11 = mul_i(sxx, n) - mul_i(sx, sx);
+  const I c12 = mul_i(sxy, sx) - mul_i(sxx, sy);
+  const I c22 = mul_i(sxx, syy) - mul_i(sxy, sxy);
+  const I det = mul_i(sxx, c00) + mul_i(sxy, c01) + mul_i(sx, c02);
+  if (n < 3 || det == 0) return false;
+  const double inv = 1.0 / (double)det;
+  const double bx = (double)s.sxz, by = (double)s.syz, bz = (double)s.sz;
+  const double al = ((double)c00 * bx + (double)c01 * by + (double)c02 * bz) * inv;
+  const double be = ((double)c01 * bx + (double)c11 * by + (double)c12 * bz) * inv;
+  const double ga = ((double)c02 * bx + (double)c12 * by + (double)c22 * bz) * inv;
+  // residual sum of squares of the least-squares plane: z.z - beta.(X^T z)
+  // (integer sums exact; |dz| < 2^23 Q units as nz <= 128, so the double
+  // cancellation error stays far below the roughness tolerance)
+  const double ss = fmax((double)s.szz - (al * bx + be * by + ga * bz), 0.0);
+  slope = (float)(sqrt(al * al + be * be) / 65536.0);
+  rough = (float)(ss / (double)n * q2m * q2m);
+  return true;
+}
+
+// Stages the tile's heights row by row (a wave per row, lanes along y).  A
+// wave issues the loads of ROWS rows before it stores any (addresses clamped
+// into the map, so every load is in bounds; with EDGE the tile reaches past
+// the map and cells outside it take the empty value).
+template <int MW, int ROWS, int WAVES, bool EDGE>
+__device__ __forceinline__ void surface_stage(const SurfaceArgs& a, const int T, const int TS,
+                                              const int gx0, const int gy0, int32_t* th) {
+  const int lane = __lane_id(), wv = threadIdx.x >> 6;
+  int gy[MW];
+#pragma unroll
+  for (int w = 0; w < MW; w++) gy[w] = min(max(gy0 + 64 * w + lane, 0), a.ny - 1);
+  for (int r0 = wv; r0 < T; r0 += ROWS * WAVES) {
+    int32_t v[ROWS][MW];
+#pragma unroll
+    for (int j = 0; j < ROWS; j++) {
+      const int32_t* row = a.hq + (int64_t)min(max(gx0 + r0 + j * WAVES, 0), a.nx - 1) * a.ny;
+#pragma unroll
+      for (int w = 0; w < MW; w++) v[j][w] = row[gy[w]];
+    }
+#pragma unroll
+    for (int j = 0; j < ROWS; j++) {
+      const int r = r0 + j * WAVES;
+      if (r >= T) break;
+      const int gx = gx0 + r;
+#pragma unroll
+      for (int w = 0; w < MW; w++) {
+        const int k = 64 * w + lane;
+        const bool in = !EDGE || (gx >= 0 && gx < a.nx && gy0 + k == gy[w]);
+        if (k < T) th[r * TS + k] = in ? v[j][w] : INT32_MIN;
+      }
     }
   }
-  (void)T;
-  return best;
 }
 
-// LDS row stride of the staged heights: odd, so that the column reads of
-// the mask pass hit distinct banks
-__host__ __device__ __forceinline__ int surface_stride(int T) { return T | 1; }
+template <int WAVES, bool EDGE>
+__device__ __forceinline__ void surface_stage_w(const SurfaceArgs& a, const int T, const int TS,
+                                                const int gx0, const int gy0, int32_t* th) {
+  if (T <= 64) surface_stage<1, 4, WAVES, EDGE>(a, T, TS, gx0, gy0, th);
+  else if (T <= 128) surface_stage<2, 6, WAVES, EDGE>(a, T, TS, gx0, gy0, th);
+  else surface_stage<3, 5, WAVES, EDGE>(a, T, TS, gx0, gy0, th);
+}
+
+// The staged rows' masks from the column pass's bits (bit c of the bit string
+// = pixel c defined); cells outside the map are clear.
+template <int NT>
+__device__ __forceinline__ void surface_row_masks(const SurfaceArgs& a, const int T, const int MS,
+                                                  const int gx0, const int gy0, uint32_t* rmask) {
+  const int words = 2 * ((T + 63) >> 6);
+  const int last = ((a.nx * a.ny + 63) >> 6) * 2 - 1;  // words of the bit string - 1
+  for (int i = threadIdx.x; i < T * words; i += NT) {
+    const int r = i / words, w = i - r * words;
+    const int gx = gx0 + r, y0 = gy0 + 32 * w;  // cells y0 .. y0 + 31 of map row gx
+    uint32_t v = 0;
+    if (gx >= 0 && gx < a.nx && y0 + 31 >= 0 && y0 < a.ny) {
+      const int s = gx * a.ny + y0;  // may start before the bit string
+      const int q = s >> 5;
+      v = __builtin_amdgcn_alignbit(a.defbits[min(q + 1, last)], a.defbits[max(q, 0)],
+                                    (uint32_t)s & 31u);
+      if (y0 < 0) v &= ~0u << -y0;
+      const int n = min(a.ny - y0, T - 32 * w);  // cells of the word in the map and the tile
+      if (n < 32) v &= n > 0 ? (1u << n) - 1u : 0u;
+    }
+    rmask[r * MS + 2 + w] = v;
+  }
+}
+
+// Distances of every line at the tile's columns (col 0: rows; 1: columns),
+// four lines per thread.
+template <bool FAR, int TILE, int NT>
+__device__ __forceinline__ void surface_distances(const uint32_t* rmask, const uint32_t* cmask,
+                                                  const int MS, const int T, const int H,
+                                                  uint8_t* rdist, uint8_t* cdist, const int DS) {
+  const int nq = (T + 3) >> 2, nw = DS >> 2;
+  for (int i = threadIdx.x; i < 2 * TILE * nw; i += NT) {
+    const int jj = i / nw, q = i - jj * nw - kSurfPad / 4;
+    const bool col = jj >= TILE;
+    const int j = col ? jj - TILE : jj;
+    const uint32_t* m = col ? cmask : rmask;
+    uint32_t v = 0;
+    if (q < 0 || q >= nq) v = kSurfNone * 0x01010101u;
+    else
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      v |= line_distance<FAR>(m + min(4 * q + e, T - 1) * MS, H + j) << (8 * e);
+    *(uint32_t*)((col ? cdist : rdist) + j * DS + 4 * q) = v;
+  }
+}
+
+// Range of the defined cells of up to four slices: window 2k (2k + 1) holds
+// the bits of slice k's cells from cell[2k] (cell[2k + 1]) on, a word address
+// of th, consecutive cells 1 (k < 2) or TS words apart.  The eight windows
+// advance together, one cell each per round, so that their LDS reads overlap;
+// an empty window reads its last cell again, or another window's.
+__device__ __forceinline__ void slice_cells(const int32_t* th, const int cell[8], const int TS,
+                                            uint32_t win[8], int32_t& lo, int32_t& hi) {
+  int at[8], any = 0;
+#pragma unroll
+  for (int k = 0; k < 8; k++) any = win[k] ? cell[k] + __mul24(__builtin_ctz(win[k]), k < 4 ? 1 : TS) : any;
+#pragma unroll
+  for (int k = 0; k < 8; k++) at[k] = any;
+  while ((win[0] | win[1] | win[2]) | (win[3] | win[4] | win[5]) | (win[6] | win[7])) {
+    int32_t v[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+      const int i = __ffs(win[k]) - 1;
+      at[k] = win[k] ? cell[k] + (k < 4 ? i : __mul24(i, TS)) : at[k];
+      v[k] = th[at[k]];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+      lo = min(lo, v[k]);
+      hi = max(hi, v[k]);
+      win[k] &= win[k] - 1u;
+    }
+  }
+}
+
+// Spread (maximum - minimum) of the heights of the defined cells in the
+// stopping slices of the four cones of the undefined pixel at staged (tx, ty);
+// -1 without any.  rd, cd: its line distances (rows at its column, columns at
+// its row), pointing at its own line.
+__device__ __forceinline__ int64_t cone_spread(const int32_t* th, const uint32_t* rmask,
+                                               const uint32_t* cmask, const uint8_t* rd,
+                                               const uint8_t* cd, const int32_t* lds, const int TS,
+                                               const int MS, const int tx, const int ty,
+                                               const int D) {
+  // cones 0/1: +x/-x (slices on staged rows), 2/3: +y/-y (staged columns);
+  // first[k]: first ring holding a defined cell.  Eight rings of every cone
+  // per round, as aligned words shifted to the ring's byte (rings past D
+  // are read from the free bytes or other lines and rejected below: the
+  // first ring found is the smallest).
+  int wi[4];
+  uint32_t sh[4];
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    // byte offset of the lowest ring byte of the first round
+    const uint32_t o = (uint32_t)((k < 2 ? rd : cd) - (const uint8_t*)lds) + (k & 1 ? -8 : 1);
+    wi[k] = (int)(o >> 2);
+    sh[k] = o & 3u;
+  }
+  // A ring holds a defined cell iff its byte is at most the ring number: with
+  // both below 128, bit 7 of 128 + ring - byte.  hit / at: the bits of the
+  // first four rings with one, and the lowest of those rings.
+  uint32_t hit[4] = {0, 0, 0, 0};
+  int at[4] = {0, 0, 0, 0};
+  for (int d = 1, w = 0; d <= D; d += 8, w += 2) {
+    uint32_t v[4][3];
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+#pragma unroll
+      for (int e = 0; e < 3; e++) v[k][e] = (uint32_t)lds[wi[k] + (k & 1 ? -w : w) + e];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      const bool down = k & 1;  // ring numbers fall with the byte address
+      const uint32_t ramp = (uint32_t)d * 0x01010101u + (down ? 0x80818283u : 0x83828180u);
+      const uint32_t b0 = __builtin_amdgcn_alignbyte(v[k][1], v[k][0], sh[k]);
+      const uint32_t b1 = __builtin_amdgcn_alignbyte(v[k][2], v[k][1], sh[k]);
+      const uint32_t mn = (ramp - (down ? b1 : b0)) & 0x80808080u;
+      const uint32_t mf = (ramp + 0x04040404u - (down ? b0 : b1)) & 0x80808080u;
+      const bool open = hit[k] == 0;
+      at[k] = open ? (mn ? d : d + 4) : at[k];
+      hit[k] = open ? (mn ? mn : mf) : hit[k];
+    }
+    if (min(min(hit[0], hit[1]), min(hit[2], hit[3])) != 0) break;
+  }
+  int first[4];
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    const int e = (k & 1 ? __builtin_clz(hit[k] | 1u) : __builtin_ctz(hit[k] | 0x80000000u)) >> 3;
+    first[k] = hit[k] ? at[k] + e : 255;
+  }
+  // the slices' cells: offsets -31..0 and 1..32 from the centre
+  int32_t lo = INT32_MAX, hi = INT32_MIN;
+  uint32_t win[8];
+  int cell[8];
+  bool wide = false;
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    const int d = first[k];
+    const bool ok = d <= D;
+    const int dc = ok ? d : 0;
+    const int line = (k < 2 ? tx : ty) + (k & 1 ? -dc : dc), oth = k < 2 ? ty : tx;
+    const uint32_t* m = (k < 2 ? rmask : cmask) + __mul24(line, MS);
+    const uint32_t wl = bits_at(m, oth + 33), wr = bits_at(m, oth + 65);
+    const int dl = min(dc, 31);
+    win[2 * k] = ok ? wl & (~0u << (31 - dl)) : 0u;
+    win[2 * k + 1] = ok ? wr & (0x7FFFFFFFu >> (31 - dl)) : 0u;
+    const int mid = k < 2 ? __mul24(line, TS) + oth : __mul24(oth, TS) + line;
+    cell[2 * k] = mid - 31 * (k < 2 ? 1 : TS);
+    cell[2 * k + 1] = mid + (k < 2 ? 1 : TS);
+    wide |= ok & (d > 31);
+  }
+  slice_cells(th, cell, TS, win, lo, hi);
+  if (wide) {
+    // slices of rings past 31: offsets -63..-32 and 32..63, and +-64
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      const int d = first[k];
+      const bool ok = d <= D && d > 31;
+      const int st = k < 2 ? 1 : TS;
+      const int line = (k < 2 ? tx : ty) + (k & 1 ? -d : d), oth = k < 2 ? ty : tx;
+      const int lc = ok ? line : 0;
+      const uint32_t* m = (k < 2 ? rmask : cmask) + __mul24(lc, MS);
+      const int dw = ok ? min(d, 63) : 32;
+      win[2 * k] = ok ? bits_at(m, oth + 1) & (~0u << (63 - dw)) : 0u;
+      win[2 * k + 1] = ok ? bits_at(m, oth + 96) & (~0u >> (63 - dw)) : 0u;
+      const int mid = k < 2 ? __mul24(lc, TS) + oth : __mul24(oth, TS) + lc;
+      cell[2 * k] = mid - 63 * st;
+      cell[2 * k + 1] = mid + 32 * st;
+      if (ok && d == 64) {
+#pragma unroll
+        for (int e = -64; e <= 64; e += 128) {
+          const int32_t v = th[mid + e * st];
+          if (v != INT32_MIN) {
+            lo = min(lo, v);
+            hi = max(hi, v);
+          }
+        }
+      }
+    }
+    slice_cells(th, cell, TS, win, lo, hi);
+  }
+  return hi == INT32_MIN ? -1 : (int64_t)hi - lo;
+}
 
 template <int NT, int TILE>
 __device__ __forceinline__ void surface_body(const SurfaceArgs& a, const int H, const int bx,
                                              const int by) {
   constexpr int kPix = TILE * TILE;  // tile pixels
-  static_assert(kPix % NT == 0 && NT % 64 == 0 && kPix % 64 == 0, "tile pixels per thread");
-  extern __shared__ int32_t lds[];
-  const int T = TILE + 2 * H;          // staged tile edge
+  constexpr int kWaves = NT / 64;    // waves of the block
+  constexpr int kPer = kPix > NT ? kPix / NT : 1;  // tile pixels per thread
+  static_assert(kPix % 64 == 0 && NT % 64 == 0 && (kPix <= NT || kPer * NT == kPix), "whole waves");
+  static_assert(kWaves <= 16, "one entry per lane of a row");
+  extern __shared__ __attribute__((aligned(16))) int32_t lds[];
+  const int T = TILE + 2 * H;           // staged tile edge
   const int TS = surface_stride(T);     // LDS row stride of th
-  const int MW = (T + 63) >> 6;         // mask words per staged row / column
-  int32_t* th = lds;                                                    // [T][TS]
-  unsigned long long* rmask = (unsigned long long*)(lds + ((T * TS + 1) & ~1));  // [T][MW]
-  unsigned long long* cmask = rmask + T * MW;                            // [T][MW]
-  uint8_t* rdist = (uint8_t*)(cmask + T * MW);  // [T][TILE]: row r, tile column j
-  uint8_t* cdist = rdist + T * TILE;           // [T][TILE]: column c, tile row i
+  const int MS = surface_mask_stride(T);
+  const int DS = surface_dist_stride(T);
+  int32_t* th = lds;                                            // [T][TS]
+  uint32_t* rmask = (uint32_t*)(lds + T * TS);                  // [T][MS]
+  uint32_t* cmask = rmask + T * MS;                             // [T][MS]
+  uint8_t* rdist = (uint8_t*)(cmask + T * MS) + kSurfPad;       // [TILE][DS]: tile column, row
+  uint8_t* cdist = rdist + TILE * DS;                           // [TILE][DS]: tile row, column
+  int16_t* order = (int16_t*)(cdist + TILE * DS - kSurfPad);    // [kPix]
   const int gx0 = bx * TILE - H, gy0 = by * TILE - H;
   const int lane = __lane_id(), wv = threadIdx.x >> 6;
-  constexpr int kWaves = NT / 64;            // waves of the block
-  constexpr int kVW = kPix / 64;     // 64-pixel groups of the tile
-  constexpr int kPer = kPix / NT;    // tile pixels per thread
-  // stage the heights row by row (a wave per row, lanes along y); the
-  // ballot of each 64-cell piece is that row's mask word.  A wave issues the
-  // loads of kSurfRows rows before it stores any (addresses clamped into the
-  // map, so every load is in bounds; cells outside it take the empty value).
-  constexpr int kSurfRows = 4;
-  for (int r0 = wv; r0 < T; r0 += kSurfRows * kWaves) {
-    int32_t v[kSurfRows][kMaxMaskWords];
-#pragma unroll
-    for (int j = 0; j < kSurfRows; j++) {
-      const int64_t rowc = (int64_t)min(max(gx0 + r0 + j * kWaves, 0), a.nx - 1) * a.ny;
-#pragma unroll
-      for (int w = 0; w < kMaxMaskWords; w++)
-        v[j][w] = a.hq[rowc + min(max(gy0 + 64 * w + lane, 0), a.ny - 1)];
-    }
-#pragma unroll
-    for (int j = 0; j < kSurfRows; j++) {
-      const int r = r0 + j * kWaves;
-      if (r >= T) break;
-      const int gx = gx0 + r;
-      const bool rowok = gx >= 0 && gx < a.nx;
-#pragma unroll
-      for (int w = 0; w < kMaxMaskWords; w++) {
-        if (w >= MW) break;
-        const int k = 64 * w + lane;
-        const int gy = gy0 + k;
-        const int32_t x = rowok && k < T && gy >= 0 && gy < a.ny ? v[j][w] : INT32_MIN;
-        if (k < T) th[r * TS + k] = x;
-        const unsigned long long b = __ballot(x != INT32_MIN);
-        if (lane == 0) rmask[r * MW + w] = b;
-      }
-    }
-  }
-  __syncthreads();
-  // column masks: lanes along x
-  for (int c = wv; c < T; c += kWaves) {
-    for (int w = 0; w < MW; w++) {
-      const int k = 64 * w + lane;
-      const bool d = k < T && th[k * TS + c] != INT32_MIN;
-      const unsigned long long b = __ballot(d);
-      if (lane == 0) cmask[c * MW + w] = b;
-    }
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 2 * T * TILE; i += NT) {
-    const bool col = i >= T * TILE;
-    const int ii = col ? i - T * TILE : i;
-    const int line = ii / TILE, j = ii - line * TILE;
-    const int dd = line_distance((col ? cmask : rmask) + line * MW, MW, T, H + j);
-    (col ? cdist : rdist)[ii] = (uint8_t)dd;
-  }
-
-  // defined pixels (plane fit) and undefined ones (cone search) go to
-  // separate waves: the block's pixels are listed defined-first, ranks from
-  // ballots (deterministic order)
-  __shared__ int16_t order[kPix];
-  __shared__ int wcnt[kVW][2];
-  bool pdef[kPer], pund[kPer];
-#pragma unroll
-  for (int k = 0; k < kPer; k++) {
-    const int p = k * NT + (int)threadIdx.x;  // tile pixel; group p >> 6 = k * kWaves + wv
-    const int px = p / TILE, py = p - px * TILE;
-    const int gx = bx * TILE + px, gy = by * TILE + py;
-    const bool valid = gx < a.nx && gy < a.ny;
-    pdef[k] = valid && th[(px + H) * TS + py + H] != INT32_MIN;
-    pund[k] = valid && !pdef[k];
-    const unsigned long long bd = __ballot(pdef[k]), bu = __ballot(pund[k]);
-    if (lane == 0) {
-      wcnt[p >> 6][0] = __popcll(bd);
-      wcnt[p >> 6][1] = __popcll(bu);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < kPer; k++) {
-    const int p = k * NT + (int)threadIdx.x;
-    int pd = 0, pu = 0;
-    for (int w = 0; w < (p >> 6); w++) {
-      pd += wcnt[w][0];
-      pu += wcnt[w][1];
-    }
-    const unsigned long long bd = __ballot(pdef[k]), bu = __ballot(pund[k]);
-    const int below_d = __builtin_amdgcn_mbcnt_hi((uint32_t)(bd >> 32),
-                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)bd, 0));
-    const int below_u = __builtin_amdgcn_mbcnt_hi((uint32_t)(bu >> 32),
-                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)bu, 0));
-    if (pdef[k]) order[pd + below_d] = (int16_t)p;
-    if (pund[k]) order[kPix - 1 - (pu + below_u)] = (int16_t)p;
-  }
-  __syncthreads();
-  int nd = 0, nu = 0;
-  for (int w = 0; w < kVW; w++) {
-    nd += wcnt[w][0];
-    nu += wcnt[w][1];
-  }
-  // slots [0, nd): defined pixels, [kPix - nu, kPix): undefined
-  for (int slot = threadIdx.x; slot < kPix; slot += NT) {
-  if (slot >= nd && slot < kPix - nu) continue;
-  const int me = order[slot];
-  const int px = me / TILE, py = me - px * TILE;
-  const int gx = bx * TILE + px, gy = by * TILE + py;
   const int h = a.half_fit, D = a.search_d;
-  const int tx = px + H, ty = py + H;
-  const int32_t hc = th[tx * TS + ty];
-  const int64_t c = (int64_t)gx * a.ny + gy;
-  uint8_t fl = a.flags[c];
-  float slope = __uint_as_float(kQNaN), rough = __uint_as_float(kQNaN);
-  if (hc != INT32_MIN) {
-    int32_t n = 0, sx = 0, sy = 0, sxx = 0, syy = 0, sxy = 0;
-    int64_t sz = 0, sxz = 0, syz = 0, szz = 0;
-    for (int dx = -h; dx <= h; dx++)
-      for (int dy = -h; dy <= h; dy++) {
-        const int32_t v = th[(tx + dx) * TS + ty + dy];
-        if (v == INT32_MIN) continue;
-        const int64_t dz = (int64_t)v - hc;
-        n++;
-        sx += dx;
-        sy += dy;
-        sxx += dx * dx;
-        syy += dy * dy;
-        sxy += dx * dy;
-        sz += dz;
-        sxz += dx * dz;
-        syz += dy * dz;
-        szz += dz * dz;
-      }
-    // adjugate of M = [[sxx sxy sx] [sxy syy sy] [sx sy n]] (symmetric)
-    const int64_t c00 = (int64_t)syy * n - (int64_t)sy * sy;
-    const int64_t c01 = (int64_t)sy * sx - (int64_t)sxy * n;
-    const int64_t c02 = (int64_t)sxy * sy - (int64_t)syy * sx;
-    const int64_t c11 = (int64_t)sxx * n - (int64_t)sx * sx;
-    const int64_t c12 = (int64_t)sxy * sx - (int64_t)sxx * sy;
-    const int64_t c22 = (int64_t)sxx * syy - (int64_t)sxy * sxy;
-    const int64_t det = (int64_t)sxx * c00 + (int64_t)sxy * c01 + (int64_t)sx * c02;
-    if (n >= 3 && det != 0) {
-      const double inv = 1.0 / (double)det;
-      const double bx = (double)sxz, by = (double)syz, bz = (double)sz;
-      const double al = ((double)c00 * bx + (double)c01 * by + (double)c02 * bz) * inv;
-      const double be = ((double)c01 * bx + (double)c11 * by + (double)c12 * bz) * inv;
-      const double ga = ((double)c02 * bx + (double)c12 * by + (double)c22 * bz) * inv;
-      // residual sum of squares of the least-squares plane: z.z - beta.(X^T z)
-      // (integer sums exact; |dz| < 2^23 Q units as nz <= 128, so the double
-      // cancellation error stays far below the roughness tolerance)
-      const double ss = fmax((double)szz - (al * bx + be * by + ga * bz), 0.0);
-      slope = (float)(sqrt(al * al + be * be) / 65536.0);
-      rough = (float)(ss / (double)n * a.q2m * a.q2m);
-      fl |= 32;
-    }
-  } else {
-    int32_t lo = INT32_MAX, hi = INT32_MIN;
-    int found = 0;
-    // cones 0/1: +x/-x (slices on staged rows), 2/3: +y/-y (staged columns)
-    for (int cone = 0; cone < 4; cone++) {
-      const bool alongx = cone < 2;
-      const int dir = (cone & 1) ? -1 : 1;
-      const int ctr = alongx ? tx : ty;        // coordinate that moves with d
-      const int oth = alongx ? ty : tx;        // centre of the slice span
-      const uint8_t* dist = alongx ? rdist : cdist;
-      const int j = alongx ? py : px;
-      // first ring holding a defined cell: four rings per round (independent
-      // LDS reads; ring indexes clamped to D stay inside the staged tile)
-      int d = 1;
-      for (; d <= D; d += 4) {
-        const int d1 = min(d + 1, D), d2 = min(d + 2, D), d3 = min(d + 3, D);
-        const int b0 = dist[(ctr + dir * d) * TILE + j];
-        const int b1 = dist[(ctr + dir * d1) * TILE + j];
-        const int b2 = dist[(ctr + dir * d2) * TILE + j];
-        const int b3 = dist[(ctr + dir * d3) * TILE + j];
-        if (b0 <= d) break;
-        if (b1 <= d1) { d = d1; break; }
-        if (b2 <= d2) { d = d2; break; }
-        if (b3 <= d3) { d = d3; break; }
-      }
-      if (d > D) continue;
-      const int line = ctr + dir * d;
-      const int s0 = oth - d, s1 = oth + d;
-      const unsigned long long* L = (alongx ? rmask : cmask) + line * MW;
-      for (int w = s0 >> 6; w <= (s1 >> 6); w++) {
-        unsigned long long b = span_bits(L[w], w, s0, s1);
-        while (b) {
-          const int k = 64 * w + __ffsll((long long)b) - 1;
-          b &= b - 1;
-          const int32_t v = alongx ? th[line * TS + k] : th[k * TS + line];
-          lo = min(lo, v);
-          hi = max(hi, v);
-          found++;
-        }
-      }
-    }
-    if (found >= 2 && (int64_t)hi - lo > a.tau_q) fl |= 16;
+
+  // ---- heights and row masks
+  if (gx0 >= 0 && gy0 >= 0 && gx0 + T <= a.nx && gy0 + T <= a.ny)
+    surface_stage_w<kWaves, false>(a, T, TS, gx0, gy0, th);
+  else
+    surface_stage_w<kWaves, true>(a, T, TS, gx0, gy0, th);
+  surface_row_masks<NT>(a, T, MS, gx0, gy0, rmask);
+  for (int i = threadIdx.x; i < 2 * T; i += NT) {  // the masks' zero ends
+    uint32_t* m = rmask + i * MS;  // cmask follows rmask
+    m[0] = m[1] = m[MS - 3] = m[MS - 2] = 0u;
   }
-  a.slope[c] = slope;
-  a.rough[c] = rough;
-  a.flags[c] = fl;
+  __syncthreads();
+
+  // ---- pixel order: defined pixels (plane fit) and undefined ones (cone
+  // search) go to separate waves, listed defined-first.  Lane l counts tile
+  // row l; counts of defined | undefined << 16.
+  int nd, nu;
+  {
+    const int vy = min(TILE, a.ny - by * TILE);
+    const auto row_bits = [&](int row, unsigned long long& def, unsigned long long& und) {
+      const unsigned long long m = bx * TILE + row < a.nx ? ~0ull >> (64 - vy) : 0ull;
+      const uint32_t* w = rmask + (H + row) * MS;
+      def = bits_at(w, H + 64);
+      if (TILE == 64) def |= (unsigned long long)bits_at(w, H + 96) << 32;
+      def &= m;
+      und = ~def & m;
+    };
+    unsigned long long def, und;
+    row_bits(lane & (TILE - 1), def, und);
+    const int cnt = __popcll(def) | __popcll(und) << 16;
+    int x = cnt;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+    if (TILE >= 32) {
+      const int t0 = __builtin_amdgcn_readlane(x, 15);
+      const int t1 = TILE == 64 ? t0 + __builtin_amdgcn_readlane(x, 31) : 0;
+      const int t2 = TILE == 64 ? t1 + __builtin_amdgcn_readlane(x, 47) : 0;
+      const int q = (lane & (TILE - 1)) >> 4;
+      x += q == 0 ? 0 : q == 1 ? t0 : q == 2 ? t1 : t2;
+    }
+    const int tot = __builtin_amdgcn_readlane(x, TILE - 1);
+    nd = tot & 0xFFFF;
+    nu = tot >> 16;
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+      const int p = k * NT + threadIdx.x, row = p / TILE, col = p - row * TILE;
+      if (kPix < NT && p >= kPix) break;  // whole waves
+      const int before = __shfl(x - cnt, row);
+      row_bits(row, def, und);
+      const unsigned long long below = (1ull << col) - 1ull;
+      if ((def >> col) & 1u) order[(before & 0xFFFF) + __popcll(def & below)] = (int16_t)p;
+      if ((und >> col) & 1u) order[kPix - 1 - ((before >> 16) + __popcll(und & below))] = (int16_t)p;
+    }
+  }
+  if (nu) {
+    // column masks: lane = row, a ballot per column; a wave takes kChunk
+    // consecutive columns, whose bits are one word of each row
+    constexpr int kChunk = 6;
+    for (int w = 0; w < (T + 63) >> 6; w++) {
+      const int r = 64 * w + lane;
+      for (int c0 = wv * kChunk; c0 < T; c0 += kWaves * kChunk) {
+        const uint32_t v = r < T ? bits_at(rmask + r * MS, 64 + c0) : 0u;
+        uint32_t mword = 0;
+#pragma unroll
+        for (int e = 0; e < kChunk; e++) {
+          const unsigned long long b = __ballot((v >> e) & 1u);
+          mword = lane == 2 * e ? (uint32_t)b : mword;
+          mword = lane == 2 * e + 1 ? (uint32_t)(b >> 32) : mword;
+        }
+        const int c = c0 + (lane >> 1);
+        if (lane < 2 * kChunk && c < T) cmask[c * MS + 2 + 2 * w + (lane & 1)] = mword;
+      }
+    }
+    __syncthreads();
+    if (D <= 31) surface_distances<false, TILE, NT>(rmask, cmask, MS, T, H, rdist, cdist, DS);
+    else surface_distances<true, TILE, NT>(rmask, cmask, MS, T, H, rdist, cdist, DS);
+  }
+  __syncthreads();
+
+  // ---- slots [0, nd): defined pixels, [kPix - nu, kPix): undefined
+#pragma unroll 1
+  for (int k = 0; k < kPer; k++) {
+    const int slot = k * NT + threadIdx.x;
+    if (slot >= kPix || (slot >= nd && slot < kPix - nu)) continue;
+    const int me = order[slot];
+    const int px = me / TILE, py = me - px * TILE;
+    const int tx = px + H, ty = py + H;
+    const int64_t c = (int64_t)(bx * TILE + px) * a.ny + by * TILE + py;
+    uint8_t fl = a.flags[c];
+    float slope = __uint_as_float(kQNaN), rough = __uint_as_float(kQNaN);
+    if (slot < nd) {
+      const int32_t* tc = th + tx * TS + ty;
+      PlaneSums s;
+      bool ok;
+      if (h == 2 && !a.wild) {
+        plane_sums5(tc, TS, *tc, s);
+        ok = plane_solve<int32_t>(s, a.q2m, slope, rough);
+      } else {
+        plane_sums(tc, TS, h, *tc, s);
+        ok = plane_solve<int64_t>(s, a.q2m, slope, rough);
+      }
+      if (ok) fl |= 32;
+    } else {
+      if (cone_spread(th, rmask, cmask, rdist + py * DS + tx, cdist + px * DS + ty, lds, TS, MS, tx,
+                      ty, D) > a.tau_q)
+        fl |= 16;
+    }
+    a.slope[c] = slope;
+    a.rough[c] = rough;
+    a.flags[c] = fl;
   }
 }
 

@@ -115,6 +115,7 @@ struct ColumnArgs {
   float* density;
   uint8_t* flags;
   int32_t* hq;            // ground height Q per local pixel, INT32_MIN = undefined
+  unsigned long long* defbits;  // bit c % 64 of word c / 64: pixel c has a height
   int32_t* colpre;        // null, or the table export's counting pass (see LutArgs)
   int32_t* block_base;
 };
@@ -122,6 +123,8 @@ struct ColumnArgs {
 struct SurfaceArgs {
   int32_t nx, ny;
   const int32_t* hq;
+  const uint32_t* defbits;  // the column pass's bits, as 32-bit words
+  int32_t wild;           // heights may lie outside the window (imported data)
   int32_t half_fit;
   int32_t search_d;
   int64_t tau_q;
@@ -178,18 +181,17 @@ constexpr int kMaxBatch = 64;
 
 // Per-step table of a batch: virtual-block prefixes of every stage (block b of
 // stage S belongs to the map m with pre[m] <= b < pre[m+1]) and per-map
-// launch constants.  Lives in device memory, uploaded once per step.  The
-// surface pass has one prefix per tile size (index 0: 16, 1: 32); a map has
-// blocks only in the prefix of its own tile.
+// launch constants.  Lives in device memory, uploaded once per step.
 struct BatchStep {
   int32_t nmaps;
   int32_t pre_rays[kMaxBatch + 1];
   int32_t pre_trace[kMaxBatch + 1];
   int32_t pre_col[kMaxBatch + 1];
-  int32_t pre_surf[2][kMaxBatch + 1];
+  int32_t pre_surf[kMaxBatch + 1];
   int32_t pre_lcount[kMaxBatch + 1];
   int32_t pre_lscan[kMaxBatch + 1];
   int32_t pre_lwrite[kMaxBatch + 1];
+  int32_t surf_tile[kMaxBatch];    // 16, 32 or 64
   int32_t surf_tiles_y[kMaxBatch];
   int32_t surf_H[kMaxBatch];
   int32_t lw_by[kMaxBatch];
@@ -208,7 +210,7 @@ struct BatchTables {
 };
 
 struct BatchGrid {
-  int clear, rays, trace, col, surf, surf16, lcount, lwrite;  // persistent grid sizes
+  int clear, rays, trace, col, surf, lcount, lwrite;  // persistent grid sizes
   int fold;                                                   // maps x sensor-box fold blocks
   size_t surf_lds, lut_lds;
 };
@@ -220,8 +222,10 @@ hipError_t launch_batch_insert(const BatchTables* tab, const BatchGrid& g,
                                unsigned long long* stamps, hipStream_t s);
 hipError_t launch_batch_export(const BatchTables* tab, const BatchGrid& g,
                                unsigned long long* stamps, hipStream_t s);
-int surface_tile();
 size_t surface_lds(int H, int tile);
+// Tile edge of the surface pass for a map tuned to `tile`; tiles64 = tiles of
+// 64 pixels in the launch.
+int surface_tile_for(int H, int tile, int64_t tiles64, int n_cu);
 size_t lut_lds(int nz);
 uint32_t nz_magic(int nz);
 
@@ -230,12 +234,13 @@ hipError_t launch_clear(const ClearArgs& a, hipStream_t s);
 hipError_t launch_rays(const InsertArgs& a, bool distinct, hipStream_t s);
 hipError_t launch_trace(const InsertArgs& a, bool distinct, hipStream_t s);
 hipError_t launch_column(const ColumnArgs& a, hipStream_t s);
-hipError_t launch_surface(const SurfaceArgs& a, int tile, hipStream_t s);  // tile 16 or 32
+hipError_t launch_surface(const SurfaceArgs& a, int tile, hipStream_t s);  // tile 16, 32 or 64
 // counted: the column pass already wrote colpre / block_base for this state
 hipError_t launch_lut(const LutArgs& a, bool counted, hipStream_t s);
 hipError_t launch_import(const Dims& d, const int32_t* lut, const map_voxel_t* data,
                          int64_t n_data, int32_t* hits, int32_t* passes, int32_t* minqz,
-                         unsigned long long* occ, int32_t* err, hipStream_t s);
+                         unsigned long long* occ, int32_t origin_z, int32_t* err,
+                         hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 // out[0..3] = column sums of the ray pass's per-block counters parts[nblocks][4].
 hipError_t launch_sum_ray_parts(const unsigned long long* parts, int64_t nblocks,

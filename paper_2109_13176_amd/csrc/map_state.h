@@ -18,6 +18,7 @@ struct map_t {
   int32_t* minqz;
   unsigned long long* occ;
   int32_t* hq;
+  unsigned long long* defbits;  // pixels with a height (column pass to surface pass)
   int32_t* block_base;
   int32_t* colpre;
   unsigned long long* stats;  // 8 counters
@@ -49,6 +50,9 @@ struct map_t {
   // every voxel is empty and every occupancy word zero (a recentring then
   // needs no clears)
   bool empty;
+  // an import brought a lowest return that lies outside its voxel: ground
+  // heights may then differ by more than the window's height
+  bool wild;
   // a fresh value (from a process-wide counter) whenever the voxel state may
   // change: a combine can tell that a map still holds its previous result
   uint64_t version;
