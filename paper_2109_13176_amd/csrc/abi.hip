@@ -106,8 +106,9 @@ int32_t dev_status(map_t* m, hipError_t e) {
   return MAP_OK;
 }
 
-// Enqueues: every voxel empty, every occupancy word zero.
-hipError_t clear_all(map_t* m) {
+// Enqueues: every voxel empty, every occupancy word zero, whatever the memory
+// holds.
+hipError_t fill_all(map_t* m) {
   const int64_t V = n_store(m);
   hipError_t e = gvom::launch_fill_i32(m->hits, 0, V, m->stream);
   if (e == hipSuccess) e = gvom::launch_fill_i32(m->passes, 0, V, m->stream);
@@ -115,6 +116,12 @@ hipError_t clear_all(map_t* m) {
   if (e == hipSuccess)
     e = gvom::launch_fill_i32((int32_t*)m->occ, 0, n_col(m) * m->d.W * 2, m->stream);
   return e;
+}
+
+// The same for a map whose occupancy words agree with its voxels (every map
+// whose kernels all ran).
+hipError_t clear_all(map_t* m) {
+  return gvom::launch_thin(m->d, nullptr, m->hits, m->passes, m->minqz, m->occ, m->stream);
 }
 
 void initial_origin(map_t* m) {
@@ -310,7 +317,7 @@ int32_t map_create(const map_params_t* p, void* stream, map_t** out) {
     return MAP_E_OOM;
   }
   initial_origin(m);
-  e = clear_all(m);
+  e = fill_all(m);
   m->empty = true;
   m->version = gvom::next_version();
   if (e == hipSuccess) e = hipMemsetAsync(m->stats, 0, kStatsBytes, m->stream);
@@ -351,7 +358,9 @@ int32_t map_destroy(map_t* m) {
 
 int32_t map_reset(map_t* m) {
   if (!m) return MAP_E_INVALID;
-  (void)hipStreamSynchronize(m->stream);
+  // after an error the kernels that keep voxels and occupancy words in step
+  // may not have run
+  const bool intact = hipStreamSynchronize(m->stream) == hipSuccess && m->sticky == MAP_OK;
   (void)hipGetLastError();
   m->sticky = MAP_OK;
   initial_origin(m);
@@ -362,7 +371,7 @@ int32_t map_reset(map_t* m) {
   m->last_distinct = false;
   m->last_ray_blocks = 0;
   m->last_trace_blocks = 0;
-  hipError_t e = clear_all(m);
+  hipError_t e = intact ? clear_all(m) : fill_all(m);
   m->empty = true;
   m->wild = false;
   if (e == hipSuccess) e = hipMemsetAsync(m->stats, 0, kStatsBytes, m->stream);
@@ -777,6 +786,7 @@ int32_t map_export_density(map_t* m, float* density_dev) {
   a.d = m->d;
   a.hits = m->hits;
   a.passes = m->passes;
+  a.occ = m->occ;
   a.out = density_dev;
   return dev_status(m, gvom::launch_density(a, m->stream));
 }

@@ -26,82 +26,202 @@ __global__ __launch_bounds__(kBlock) void k_lut_write(LutArgs a, uint32_t nz_mag
 }
 
 // Density of every voxel (the voxel-map output, Fig. 1), in window-local
-// table order: the storage region of the table export (4 x 16 columns) is
-// read in storage order (16-byte loads, all of a thread's loads in flight
-// before its LDS stores), each voxel's density computed there and kept in
-// LDS rows in window-local z order; then every lane writes four consecutive
-// densities of one column.
+// table order, one region per block.  The hits are read for the occupied
+// voxels only, whose densities take the place of their passes in LDS.
+//
+// Bound: HBM, 4 V read (passes) + 4 V written.  Measured at 512 x 512 x 64:
+// 31.4 us (201 MB, the hits of every voxel read) -> 24.5 us (134 MB).
 __global__ __launch_bounds__(kBlock) void k_density(DensityArgs a, uint32_t nz_magic) {
-  extern __shared__ __attribute__((aligned(16))) float lden[];  // [64][lut_row(nz)]
-  __shared__ int64_t sout[kRegCols];
-  const int nx = a.d.nx, ny = a.d.ny, nz = a.d.nz, roz = a.d.ro[2];
-  const int nzp = lut_row(nz);
-  const int bxr = blockIdx.x, byr = blockIdx.y;
-  if (threadIdx.x < kRegCols) {
-    const int t = threadIdx.x;
-    const int sx = 4 * bxr + (t >> 4), sy = 16 * byr + (t & 15);
-    int64_t o = -1;
-    if (sx < nx && sy < ny) {
-      const int x = sx - a.d.ro[0] + (sx < a.d.ro[0] ? nx : 0);
-      const int y = sy - a.d.ro[1] + (sy < a.d.ro[1] ? ny : 0);
-      o = ((int64_t)x * ny + y) * nz;
-    }
-    sout[t] = o;
-  }
-  // 16-byte word k4 of the region: brick b, level zs, brick row iy
-  // (k4 = 4 (b nz + zs) + iy), voxels ix = 0..3 (slot 16 ix + 4 b + iy)
-  const int nbricks = min(4, a.d.nby - 4 * byr);
-  const int64_t r0 = col_base(a.d, 4 * bxr, 16 * byr);
-  const int nv4 = nbricks * nz * 4;
-  const int4* __restrict__ hsrc = (const int4*)(a.hits + r0);
-  const int4* __restrict__ psrc = (const int4*)(a.passes + r0);
-  for (int k0 = 0; k0 < nv4; k0 += kLutLoads * kBlock) {
-    int4 hv[kLutLoads], pv[kLutLoads];
-#pragma unroll
-    for (int u = 0; u < kLutLoads; u++) {
-      // clamped, not skipped: every lane loads (in bounds), the stores below
-      // skip the words past the region
-      const int k4 = min(k0 + u * kBlock + (int)threadIdx.x, nv4 - 1);
-      hv[u] = hsrc[k4];
-      pv[u] = psrc[k4];
-    }
-#pragma unroll
-    for (int u = 0; u < kLutLoads; u++) {
-      const int k4 = k0 + u * kBlock + threadIdx.x;
-      if (k4 < nv4) {
-        const int bz = k4 >> 2, iy = k4 & 3;
-        const int b = nz == 1 ? bz : (int)__umulhi((uint32_t)bz, nz_magic);
-        const int zs = bz - b * nz;
-        const int lz = zs >= roz ? zs - roz : zs - roz + nz;
-        const int32_t h4[4] = {hv[u].x, hv[u].y, hv[u].z, hv[u].w};
-        const int32_t p4[4] = {pv[u].x, pv[u].y, pv[u].z, pv[u].w};
-#pragma unroll
-        for (int ix = 0; ix < 4; ix++) {
-          const int32_t h = h4[ix], p = p4[ix];
-          float v;
-          if (h >= 1) v = (float)((double)h / ((double)h + (double)p));
-          else v = p >= 1 ? 0.0f : __uint_as_float(kQNaN);
-          lden[(16 * ix + 4 * b + iy) * nzp + lz] = v;
-        }
-      }
-    }
+  extern __shared__ __attribute__((aligned(16))) int32_t lpass[];  // [64][lut_row(nz)]
+  __shared__ RegionCols rc;
+  const int nz = a.d.nz, nzp = lut_row(nz);
+  region_load(a.d, a.passes, a.occ, nz_magic, blockIdx.x, blockIdx.y, lpass, rc,
+              [](int, int32_t) {});
+  __syncthreads();
+  const int nocc = rc.pre[kRegCols];
+  for (int o = threadIdx.x; o < nocc; o += kBlock) {
+    int r, z;
+    const int t = region_voxel(rc, o, r, z);
+    const double h = a.hits[rc.base[t] + ((int64_t)wrap_add(z + a.d.ro[2], nz) << 4)];
+    const double p = lpass[t * nzp + z];
+    lpass[t * nzp + z] = __float_as_int((float)(h / (h + p)));
   }
   __syncthreads();
-  const int nq = (nz + 3) >> 2;
-  const int qsh = nq > 1 ? 32 - __clz(nq - 1) : 0;
   const bool vec = (nz & 3) == 0 && ((uintptr_t)a.out & 15) == 0;
-  for (int i = threadIdx.x; i < (kRegCols << qsh); i += kBlock) {
-    const int t = i >> qsh, q = i & ((1 << qsh) - 1);
-    if (q >= nq || sout[t] < 0) continue;
+  region_quads(rc, nz, [&](int t, int q) {
+    const Mask128 mt = {rc.lo[t], rc.hi[t]};
     const int z0 = 4 * q;
-    float* __restrict__ out = a.out + sout[t] + z0;
-    const float* src = lden + t * nzp + z0;
-    if (vec) {
-      typedef float v4f __attribute__((ext_vector_type(4)));
-      __builtin_nontemporal_store(*(const v4f*)src, (v4f*)out);
-    } else {
-      for (int e = 0; e < 4; e++)
-        if (z0 + e < nz) __builtin_nontemporal_store(src[e], out + e);
+    const int4 pv = *(const int4*)(lpass + t * nzp + z0);
+    const int32_t p4[4] = {pv.x, pv.y, pv.z, pv.w};
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const bool occ = z0 + e < nz && test_bit(mt, z0 + e);
+      v[e] = occ ? __int_as_float(p4[e]) : p4[e] >= 1 ? 0.0f : __uint_as_float(kQNaN);
+    }
+    store_quad(a.out + (int64_t)rc.col[t] * nz + z0, v, nz - z0, vec);
+  });
+}
+
+// Per-column features (FeatArgs), one region per block: the passes summed from
+// the LDS rows (four threads per column), the occupied voxels' hits and lowest
+// returns added one thread per voxel (integer sums: any order), then four
+// features per thread.
+//
+// Bound: HBM, 4 V read + 64 C written.  Measured at 512 x 512 x 64: 87 us (one
+// lane per column, hits and passes of every voxel in 4-byte reads 16 bytes
+// apart) -> 22.8 us.
+__global__ __launch_bounds__(kBlock) void k_features(FeatArgs a, uint32_t nz_magic) {
+  extern __shared__ __attribute__((aligned(16))) int32_t lpass[];  // [64][lut_row(nz)]
+  __shared__ RegionCols rc;
+  __shared__ unsigned long long sh[kRegCols], sq[kRegCols];  // sums of hits, of lowest returns
+  __shared__ int32_t top_q[kRegCols], bot_h[kRegCols], bot_p[kRegCols];
+  static_assert(kBlock == 4 * kRegCols, "four threads per column");
+  const int nx = a.d.nx, ny = a.d.ny, nz = a.d.nz, nzp = lut_row(nz);
+  region_load(a.d, a.passes, a.occ, nz_magic, blockIdx.x, blockIdx.y, lpass, rc,
+              [&](int t, int32_t) { sh[t] = sq[t] = 0ull; });
+  __syncthreads();
+  const int nocc = rc.pre[kRegCols];
+  for (int o = threadIdx.x; o < nocc; o += kBlock) {
+    int r, z;
+    const int t = region_voxel(rc, o, r, z);
+    const int64_t e = rc.base[t] + ((int64_t)wrap_add(z + a.d.ro[2], nz) << 4);
+    const int32_t h = a.hits[e], q = a.minqz[e];
+    atomicAdd(&sh[t], (unsigned long long)(int64_t)h);
+    atomicAdd(&sq[t], (unsigned long long)(int64_t)q);
+    if (r == 0) {
+      bot_h[t] = h;
+      bot_p[t] = lpass[t * nzp + z];
+    }
+    if (o + 1 == rc.pre[t + 1]) top_q[t] = q;
+  }
+  const int t = threadIdx.x >> 2, part = threadIdx.x & 3;
+  int64_t sp = 0;
+  for (int q = part; 4 * q < nz; q += 4) {
+    const int4 v = *(const int4*)(lpass + t * nzp + 4 * q);
+    sp += v.x;
+    if (4 * q + 1 < nz) sp += v.y;
+    if (4 * q + 2 < nz) sp += v.z;
+    if (4 * q + 3 < nz) sp += v.w;
+  }
+  sp += __shfl_xor(sp, 1);
+  sp += __shfl_xor(sp, 2);
+  __syncthreads();
+  const int32_t c = rc.col[t];
+  if (c < 0) return;
+  const int x = c / ny, y = c - x * ny;
+  (void)nx;
+  const int cnt = rc.pre[t + 1] - rc.pre[t];
+  const bool thinned = a.thin && a.thin[c];
+  const double q2m = a.res / 65536.0;
+  float f[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  const uint8_t fl = thinned ? 0 : a.flags[c];
+  if (part == 0) {
+    if (!thinned) {
+      f[0] = (float)(double)(int64_t)sh[t];
+      f[1] = (float)(double)sp;
+      f[2] = (float)cnt;
+      f[3] = (float)((double)cnt / (double)nz);
+    }
+  } else if (part == 1) {
+    if (fl & 1) {
+      f[0] = a.height[c];
+      f[3] = 1.0f;
+    }
+    if (!thinned && cnt > 0) {
+      f[1] = (float)((double)top_q[t] * q2m);
+      f[2] = (float)(((double)(int64_t)sq[t] / (double)cnt) * q2m);
+    }
+  } else if (part == 2) {
+    if (!thinned && cnt > 0) {
+      const double hb = bot_h[t], pb = bot_p[t];
+      f[0] = (float)(hb / (hb + pb));
+    }
+    if (fl & 2) f[1] = a.density[c];
+    if (fl & 32) {
+      f[2] = a.slope[c];
+      f[3] = a.rough[c];
+    }
+  } else {
+    if (fl & 32) f[0] = 1.0f;
+    const double cx = ((double)(a.O[0] + x) + 0.5) * a.res - a.sx;
+    const double cy = ((double)(a.O[1] + y) + 0.5) * a.res - a.sy;
+    f[1] = (float)sqrt(cx * cx + cy * cy);
+    if (fl & 1) f[2] = (float)(a.sz - (double)a.height[c]);
+    if (thinned) f[3] = 1.0f;
+  }
+  float* o = a.feat + (int64_t)c * 16 + 4 * part;
+  if (((uintptr_t)a.feat & 15) == 0) {
+    *(float4*)o = make_float4(f[0], f[1], f[2], f[3]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; e++) o[e] = f[e];
+  }
+}
+
+// Empties the columns marked in `thin` (window-local; null: every column),
+// one storage region per block: the passes words that hold a count are
+// zeroed, hits and lowest returns only where the occupancy words have a
+// voxel (they are empty elsewhere), then the columns' words.
+//
+// Bound: HBM, 4 V read.  Measured at 512 x 512 x 64: half the columns 141 us
+// (4-byte stores to every voxel) -> 14.5 us; the whole map 3 x 18.3 us (three
+// fills) -> 14.5 us.
+__global__ __launch_bounds__(kBlock) void k_thin(Dims d, const uint8_t* thin, int32_t* hits,
+                                                 int32_t* passes, int32_t* minqz,
+                                                 unsigned long long* occ, uint32_t nz_magic) {
+  __shared__ unsigned long long lo[kRegCols], hi[kRegCols];  // storage z order, marked columns
+  __shared__ unsigned long long marked;
+  const int nz = d.nz, tid = threadIdx.x, bxr = blockIdx.x, byr = blockIdx.y;
+  const int64_t r0 = col_base(d, 4 * bxr, 16 * byr);
+  const int nv4 = min(4, d.nby - 4 * byr) * nz * 4;
+  if (tid < kRegCols) {
+    int sx, sy;
+    const int32_t c = region_col(d, bxr, byr, tid, sx, sy);
+    const bool on = c >= 0 && (!thin || thin[c]);
+    unsigned long long w0 = 0ull, w1 = 0ull;
+    if (on) {
+      const int64_t col = ((int64_t)sx * d.ny + sy) * d.W;
+      w0 = occ[col];
+      if (d.W > 1) w1 = occ[col + 1];
+      if (w0) occ[col] = 0ull;
+      if (w1) occ[col + 1] = 0ull;
+    }
+    lo[tid] = w0;
+    hi[tid] = w1;
+    const unsigned long long b = __ballot(on);
+    if (tid == 0) marked = b;
+  }
+  __syncthreads();
+  const unsigned long long mk = marked;
+  if (!mk) return;
+  for (int k0 = 0; k0 < nv4; k0 += kLutLoads * kBlock) {
+    int4 v[kLutLoads];
+#pragma unroll
+    for (int u = 0; u < kLutLoads; u++)
+      v[u] = ((const int4*)(passes + r0))[min(k0 + u * kBlock + tid, nv4 - 1)];
+#pragma unroll
+    for (int u = 0; u < kLutLoads; u++) {
+      const int k4 = k0 + u * kBlock + tid;
+      if (k4 >= nv4) continue;
+      int zs;
+      const int t = region_word(k4, nz, nz_magic, zs);
+      const unsigned long long m = mk >> t;  // bits 0, 16, 32, 48: the word's columns
+      const bool on[4] = {(m & 1ull) != 0, ((m >> 16) & 1ull) != 0, ((m >> 32) & 1ull) != 0,
+                          ((m >> 48) & 1ull) != 0};
+      const int32_t p[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+      const int32_t n[4] = {on[0] ? 0 : p[0], on[1] ? 0 : p[1], on[2] ? 0 : p[2], on[3] ? 0 : p[3]};
+      const int64_t s = r0 + 4 * (int64_t)k4;
+      if ((p[0] ^ n[0]) | (p[1] ^ n[1]) | (p[2] ^ n[2]) | (p[3] ^ n[3]))
+        *(int4*)(passes + s) = make_int4(n[0], n[1], n[2], n[3]);
+      const unsigned long long* w = zs < 64 ? lo : hi;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        if ((w[t + 16 * e] >> (zs & 63)) & 1ull) {
+          hits[s + e] = 0;
+          minqz[s + e] = INT32_MAX;
+        }
+      }
     }
   }
 }
@@ -125,61 +245,109 @@ __global__ __launch_bounds__(kBlock) void k_costmap(CostArgs a) {
   a.cost[i] = c;
 }
 
-// Import: one wave per window-local column; lane = local z.
-__global__ __launch_bounds__(kBlock) void k_import(Dims d, const int32_t* lut,
-                                                   const map_voxel_t* data, int64_t n_data,
-                                                   int32_t* hits, int32_t* passes,
+// Import, one region per block: the table's columns are read in 16-byte words
+// into the LDS rows, then the region is written in storage order, the records
+// of occupied voxels gathered on the way.  Hits and lowest returns are written
+// where the old or the new map has an occupied voxel (they are empty
+// elsewhere).  err: bit 0 = invalid content (the caller empties the map), bit
+// 1 = a lowest return outside its voxel.
+//
+// Bound: HBM, 4 V read + 4 V written.  Measured at 512 x 512 x 64: 237 us (a
+// lane per voxel of a column, each storing to lines of its own) -> 38.7 us.
+__global__ __launch_bounds__(kBlock) void k_import(Dims d, const int32_t* __restrict__ lut,
+                                                   const map_voxel_t* __restrict__ data,
+                                                   int64_t n_data, int32_t* hits, int32_t* passes,
                                                    int32_t* minqz, unsigned long long* occ,
-                                                   int32_t origin_z, int32_t* err) {
-  const int lane = __lane_id();
-  const int64_t c = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-  const int nx = d.nx, ny = d.ny, nz = d.nz;
-  if (c >= (int64_t)nx * ny) return;
-  const int x = (int)(c / ny), y = (int)(c - (int64_t)x * ny);
-  const int sx = wrap_add(x + d.ro[0], nx), sy = wrap_add(y + d.ro[1], ny);
-  const int64_t scol = (int64_t)sx * ny + sy;
-  const int64_t cb = col_base(d, sx, sy);
-  unsigned long long w0 = 0, w1 = 0;
-  for (int zb = 0; zb < nz; zb += 64) {
-    const int z = zb + lane;
-    bool occd = false;
-    if (z < nz) {
-      const int32_t v = lut[c * nz + z];
-      const int sz = wrap_add(z + d.ro[2], nz);
-      const int64_t e = cb + ((int64_t)sz << 4);
-      int32_t h = 0, p = 0, mq = INT32_MAX;
+                                                   int32_t origin_z, int32_t* err,
+                                                   uint32_t nz_magic) {
+  extern __shared__ __attribute__((aligned(16))) int32_t lval[];  // [64][lut_row(nz)]
+  __shared__ unsigned long long oldw[2][kRegCols], neww[2][kRegCols];  // storage z order
+  __shared__ int32_t scol[kRegCols];
+  const int nz = d.nz, roz = d.ro[2], nzp = lut_row(nz);
+  const int tid = threadIdx.x, bxr = blockIdx.x, byr = blockIdx.y;
+  int64_t wcol = -1;
+  if (tid < kRegCols) {
+    int sx, sy;
+    const int32_t c = region_col(d, bxr, byr, tid, sx, sy);
+    scol[tid] = c;
+    wcol = c >= 0 ? ((int64_t)sx * d.ny + sy) * d.W : -1;
+    oldw[0][tid] = wcol >= 0 ? occ[wcol] : 0ull;
+    oldw[1][tid] = wcol >= 0 && d.W > 1 ? occ[wcol + 1] : 0ull;
+    neww[0][tid] = neww[1][tid] = 0ull;
+  }
+  __syncthreads();
+  // table words (column slot t, quad q), as region_quads; columns outside the
+  // map read as empty voxels
+  const int nq = (nz + 3) >> 2;
+  const int qsh = nq > 1 ? 32 - __clz(nq - 1) : 0;
+  const bool vec = (nz & 3) == 0 && ((uintptr_t)lut & 15) == 0;
+  for (int i0 = 0; i0 < (kRegCols << qsh); i0 += kLutLoads * kBlock) {
+    int4 v[kLutLoads];
+#pragma unroll
+    for (int u = 0; u < kLutLoads; u++) {
+      const int i = i0 + u * kBlock + tid;
+      const int t = (i >> qsh) & (kRegCols - 1), q = min(i & ((1 << qsh) - 1), nq - 1);
+      const int32_t* src = lut + (int64_t)max(scol[t], 0) * nz + 4 * q;
+      if (vec) {
+        v[u] = *(const int4*)src;
+      } else {
+        const int last = nz - 1 - 4 * q;  // clamped: every lane loads in bounds
+        v[u] = make_int4(src[0], src[min(1, last)], src[min(2, last)], src[min(3, last)]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kLutLoads; u++) {
+      const int i = i0 + u * kBlock + tid;
+      const int t = i >> qsh, q = i & ((1 << qsh) - 1);
+      if (t < kRegCols && q < nq)
+        *(int4*)(lval + t * nzp + 4 * q) = scol[t] >= 0 ? v[u] : make_int4(-1, -1, -1, -1);
+    }
+  }
+  __syncthreads();
+  const int64_t r0 = col_base(d, 4 * bxr, 16 * byr);
+  const int nv4 = min(4, d.nby - 4 * byr) * nz * 4;
+  for (int k4 = tid; k4 < nv4; k4 += kBlock) {
+    int zs;
+    const int t = region_word(k4, nz, nz_magic, zs);
+    const int lz = zs >= roz ? zs - roz : zs - roz + nz;
+    const int32_t* row = lval + t * nzp + lz;
+    int32_t h[4] = {0, 0, 0, 0}, p[4], mq[4] = {INT32_MAX, INT32_MAX, INT32_MAX, INT32_MAX};
+    bool write = false;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int32_t v = row[16 * e * nzp];
+      p[e] = 0;
+      write |= (oldw[zs >> 6][t + 16 * e] >> (zs & 63)) & 1ull;
       if (v >= 0) {
-        if (v < n_data && data[v].hits >= 1) {
-          h = data[v].hits;
-          p = data[v].passes;
-          mq = data[v].min_qz;
-          if (mq >> 16 != origin_z + z) atomicOr(err, 2);
-          occd = true;
+        map_voxel_t r = {0, 0, 0};
+        if (v < n_data) r = data[v];
+        if (r.hits >= 1) {
+          h[e] = r.hits;
+          p[e] = r.passes;
+          mq[e] = r.min_qz;
+          write = true;
+          atomicOr(&neww[zs >> 6][t + 16 * e], 1ull << (zs & 63));
+          if (r.min_qz >> 16 != origin_z + lz) atomicOr(err, 2);
         } else {
           atomicOr(err, 1);
         }
       } else if (v == INT32_MIN) {
         atomicOr(err, 1);
       } else {
-        p = -1 - v;
-      }
-      hits[e] = h;
-      passes[e] = p;
-      minqz[e] = mq;
-      if (occd) {
-        if (sz < 64) w0 |= 1ull << sz; else w1 |= 1ull << (sz - 64);
+        p[e] = -1 - v;
       }
     }
+    const int64_t s = r0 + 4 * (int64_t)k4;
+    *(int4*)(passes + s) = make_int4(p[0], p[1], p[2], p[3]);
+    if (write) {
+      *(int4*)(hits + s) = make_int4(h[0], h[1], h[2], h[3]);
+      *(int4*)(minqz + s) = make_int4(mq[0], mq[1], mq[2], mq[3]);
+    }
   }
-  // combine the lanes' bits
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    w0 |= __shfl_xor(w0, o);
-    w1 |= __shfl_xor(w1, o);
-  }
-  if (lane == 0) {
-    occ[scol * d.W] = w0;
-    if (d.W > 1) occ[scol * d.W + 1] = w1;
+  __syncthreads();
+  if (wcol >= 0) {
+    occ[wcol] = neww[0][tid];
+    if (d.W > 1) occ[wcol + 1] = neww[1][tid];
   }
 }
 
@@ -365,9 +533,24 @@ hipError_t launch_lut(const LutArgs& a, bool counted, hipStream_t s) {
   return hipGetLastError();
 }
 
+dim3 region_grid(const Dims& d) { return dim3((d.nx + 3) / 4, (d.nby + 3) / 4); }
+
 hipError_t launch_density(const DensityArgs& a, hipStream_t s) {
-  dim3 g((a.d.nx + 3) / 4, (a.d.nby + 3) / 4);
-  hipLaunchKernelGGL(k_density, g, dim3(kBlock), lut_lds(a.d.nz), s, a, nz_magic(a.d.nz));
+  hipLaunchKernelGGL(k_density, region_grid(a.d), dim3(kBlock), lut_lds(a.d.nz), s, a,
+                     nz_magic(a.d.nz));
+  return hipGetLastError();
+}
+
+hipError_t launch_features(const FeatArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(k_features, region_grid(a.d), dim3(kBlock), lut_lds(a.d.nz), s, a,
+                     nz_magic(a.d.nz));
+  return hipGetLastError();
+}
+
+hipError_t launch_thin(const Dims& d, const uint8_t* thin, int32_t* hits, int32_t* passes,
+                       int32_t* minqz, unsigned long long* occ, hipStream_t s) {
+  hipLaunchKernelGGL(k_thin, region_grid(d), dim3(kBlock), 0, s, d, thin, hits, passes, minqz, occ,
+                     nz_magic(d.nz));
   return hipGetLastError();
 }
 
@@ -387,9 +570,8 @@ hipError_t launch_import(const Dims& d, const int32_t* lut, const map_voxel_t* d
                          int64_t n_data, int32_t* hits, int32_t* passes, int32_t* minqz,
                          unsigned long long* occ, int32_t origin_z, int32_t* err,
                          hipStream_t s) {
-  const int64_t threads = (int64_t)d.nx * d.ny * 64;
-  hipLaunchKernelGGL(k_import, dim3((unsigned)((threads + kBlock - 1) / kBlock)), dim3(kBlock),
-                     0, s, d, lut, data, n_data, hits, passes, minqz, occ, origin_z, err);
+  hipLaunchKernelGGL(k_import, region_grid(d), dim3(kBlock), lut_lds(d.nz), s, d, lut, data, n_data,
+                     hits, passes, minqz, occ, origin_z, err, nz_magic(d.nz));
   return hipGetLastError();
 }
 

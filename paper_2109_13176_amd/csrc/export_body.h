@@ -785,36 +785,60 @@ __device__ __forceinline__ void lut_scan_body(int32_t* base, const int nb, int64
 }
 
 
-// Pass 3: block = a storage region of 4 x 16 columns (four 4 x 4 bricks,
-// contiguous in memory).  The passes of the region are read in storage order
-// (16-byte loads, all of a thread's loads in flight before its LDS stores)
-// into LDS rows in window-local z order.  The occupied voxels' records are
-// written one thread per voxel (the region's occupied voxels are numbered
-// column by column, so a voxel's rank is its column base plus its number
-// within the column, and every gather is issued at once).  Then every lane
-// writes four consecutive table entries of one column (a transpose through
-// LDS keeps both sides coalesced; one 16-byte LDS read and one 16-byte store
-// per lane).
+// ---- storage regions: 4 x 16 columns (four 4 x 4 bricks, contiguous in
+// memory).  The kernels that turn the whole map between storage order and
+// window-local order (the table, density and feature exports, the import)
+// take one region per block: the passes (or table entries) go through LDS
+// rows in window-local z order, so that both sides are read and written in
+// 16-byte words; hits and lowest returns, which only occupied voxels have, are
+// touched one voxel at a time where the occupancy words say so.
 constexpr int kRegCols = 64;
 constexpr int kLutLoads = 4;  // 16-byte region loads per thread per batch
 
 // LDS row stride of a column's passes: a multiple of 4 words.
 __host__ __device__ __forceinline__ int lut_row(int nz) { return ((nz + 3) & ~3) + 4; }
 
-__device__ __forceinline__ void lut_write_body(const LutArgs& a, const uint32_t nz_magic,
-                                               const int bxr, const int byr) {
-  extern __shared__ __attribute__((aligned(16))) int32_t lpass[];  // [64][lut_row(nz)]
-  __shared__ unsigned long long slo[kRegCols], shi[kRegCols];
-  __shared__ int32_t sbase[kRegCols], spre[kRegCols + 1];
-  __shared__ int64_t scb[kRegCols], slut[kRegCols];
-  const int nx = a.d.nx, ny = a.d.ny, nz = a.d.nz, W = a.d.W, roz = a.d.ro[2];
-  const int nzp = lut_row(nz);
+// The columns of a region (slot t = 16 ix + 4 b + iy: brick b, column (ix, iy)
+// of the brick): occupancy in window-local z order, storage index of z = 0,
+// window-local column index (-1 outside the map) and prefix of the occupied
+// voxels in slot order.
+struct RegionCols {
+  unsigned long long lo[kRegCols], hi[kRegCols];
+  int32_t base[kRegCols], col[kRegCols], pre[kRegCols + 1];
+};
+
+__device__ __forceinline__ int32_t region_col(const Dims& d, const int bxr, const int byr,
+                                              const int t, int& sx, int& sy) {
+  sx = 4 * bxr + (t >> 4);
+  sy = 16 * byr + (t & 15);
+  if (sx >= d.nx || sy >= d.ny) return -1;
+  const int x = sx - d.ro[0] + (sx < d.ro[0] ? d.nx : 0);
+  const int y = sy - d.ro[1] + (sy < d.ro[1] ? d.ny : 0);
+  return x * d.ny + y;
+}
+
+// 16-byte word k4 of a region holds brick b, level zs, brick row iy
+// (k4 = 4 (b nz + zs) + iy), voxels ix = 0..3; slot of voxel ix = 16 ix + 4 b + iy.
+__device__ __forceinline__ int region_word(const int k4, const int nz, const uint32_t nz_magic,
+                                           int& zs) {
+  const int bz = k4 >> 2, iy = k4 & 3;
+  const int b = nz == 1 ? bz : (int)__umulhi((uint32_t)bz, nz_magic);
+  zs = bz - b * nz;
+  return 4 * b + iy;
+}
+
+// Loads the passes of region (bxr, byr) into the LDS rows and describes its
+// columns (wave 0, while the first loads are in flight; extra(t, c) for slot t
+// = window-local column c, -1 outside the map).  Ends without a barrier.
+template <class Extra>
+__device__ __forceinline__ void region_load(const Dims& d, const int32_t* passes,
+                                            const unsigned long long* occ, const uint32_t nz_magic,
+                                            const int bxr, const int byr, int32_t* lpass,
+                                            RegionCols& rc, Extra extra) {
+  const int nz = d.nz, roz = d.ro[2], nzp = lut_row(nz);
   const int tid = threadIdx.x;
-  // storage-order read of the region: 16-byte word k4 holds brick b, level
-  // zs, brick row iy (k4 = 4 (b nz + zs) + iy), voxels ix = 0..3
-  const int nbricks = min(4, a.d.nby - 4 * byr);
-  const int nv4 = nbricks * nz * 4;
-  const int4* __restrict__ src = (const int4*)(a.passes + col_base(a.d, 4 * bxr, 16 * byr));
+  const int nv4 = min(4, d.nby - 4 * byr) * nz * 4;
+  const int4* __restrict__ src = (const int4*)(passes + col_base(d, 4 * bxr, 16 * byr));
   for (int k0 = 0; k0 < nv4; k0 += kLutLoads * kBlock) {
     int4 v[kLutLoads];
 #pragma unroll
@@ -824,21 +848,11 @@ __device__ __forceinline__ void lut_write_body(const LutArgs& a, const uint32_t 
       v[u] = src[min(k0 + u * kBlock + tid, nv4 - 1)];
     }
     if (k0 == 0 && tid < kRegCols) {
-      // wave 0, after the first region loads are issued: the region's columns
-      // (masks, rank bases, occupied-count prefix)
       Mask128 m = {0ull, 0ull};
-      int32_t base = 0;
-      int64_t cb = -1, lrow = 0;
-      const int sx = 4 * bxr + (tid >> 4), sy = 16 * byr + (tid & 15);
-      if (sx < nx && sy < ny) {
-        const int x = sx - a.d.ro[0] + (sx < a.d.ro[0] ? nx : 0);
-        const int y = sy - a.d.ro[1] + (sy < a.d.ro[1] ? ny : 0);
-        const int c = x * ny + y;
-        base = a.block_base[c >> 6] + a.colpre[c];
-        m = local_mask(a.occ, (int64_t)sx * ny + sy, W, nz, roz);
-        cb = col_base(a.d, sx, sy);
-        lrow = (int64_t)c * nz;
-      }
+      int sx, sy;
+      const int32_t c = region_col(d, bxr, byr, tid, sx, sy);
+      extra(tid, c);
+      if (c >= 0) m = local_mask(occ, (int64_t)sx * d.ny + sy, d.W, nz, roz);
       const int cnt = __popcll(m.lo) + __popcll(m.hi);
       int incl = cnt;
 #pragma unroll
@@ -846,23 +860,21 @@ __device__ __forceinline__ void lut_write_body(const LutArgs& a, const uint32_t 
         const int y = __shfl_up(incl, o);
         if (tid >= o) incl += y;
       }
-      slo[tid] = m.lo;
-      shi[tid] = m.hi;
-      sbase[tid] = base;
-      scb[tid] = cb;
-      slut[tid] = lrow;
-      spre[tid] = incl - cnt;
-      if (tid == kRegCols - 1) spre[kRegCols] = incl;
+      rc.lo[tid] = m.lo;
+      rc.hi[tid] = m.hi;
+      rc.base[tid] = col_base(d, sx, sy);
+      rc.col[tid] = c;
+      rc.pre[tid] = incl - cnt;
+      if (tid == kRegCols - 1) rc.pre[kRegCols] = incl;
     }
 #pragma unroll
     for (int u = 0; u < kLutLoads; u++) {
       const int k4 = k0 + u * kBlock + tid;
       if (k4 < nv4) {
-        const int bz = k4 >> 2, iy = k4 & 3;
-        const int b = nz == 1 ? bz : (int)__umulhi((uint32_t)bz, nz_magic);
-        const int zs = bz - b * nz;
+        int zs;
+        const int t = region_word(k4, nz, nz_magic, zs);
         const int lz = zs >= roz ? zs - roz : zs - roz + nz;
-        int32_t* row = lpass + (4 * b + iy) * nzp + lz;  // slot = 16 ix + 4 b + iy
+        int32_t* row = lpass + t * nzp + lz;
         row[0] = v[u].x;
         row[16 * nzp] = v[u].y;
         row[32 * nzp] = v[u].z;
@@ -870,20 +882,67 @@ __device__ __forceinline__ void lut_write_body(const LutArgs& a, const uint32_t 
       }
     }
   }
-  __syncthreads();
-  // records of the occupied voxels: voxel o of the region lies in the column t
-  // with spre[t] <= o < spre[t + 1], at the set bit of rank o - spre[t]
-  const int nocc = spre[kRegCols];
-  for (int o = tid; o < nocc; o += kBlock) {
-    int t = 0;
+}
+
+// Occupied voxel o of a region (o < rc.pre[kRegCols]): its slot (the one with
+// pre[t] <= o < pre[t + 1]) and number r within its column; its level is the
+// set bit of rank r.
+__device__ __forceinline__ int region_voxel(const RegionCols& rc, const int o, int& r, int& z) {
+  int t = 0;
 #pragma unroll
-    for (int step = kRegCols / 2; step >= 1; step >>= 1)
-      if (spre[t + step] <= o) t += step;
-    const int r = o - spre[t];
+  for (int step = kRegCols / 2; step >= 1; step >>= 1)
+    if (rc.pre[t + step] <= o) t += step;
+  r = o - rc.pre[t];
+  z = select_bit(Mask128{rc.lo[t], rc.hi[t]}, r);
+  return t;
+}
+
+// Calls item(t, q) for the quads q (window-local z = 4q .. 4q + 3) of every
+// column of the region inside the map; quads per column rounded up to a power
+// of two so that t and q are shifts.
+template <class Item>
+__device__ __forceinline__ void region_quads(const RegionCols& rc, const int nz, Item item) {
+  const int nq = (nz + 3) >> 2;
+  const int qsh = nq > 1 ? 32 - __clz(nq - 1) : 0;
+  for (int i = threadIdx.x; i < (kRegCols << qsh); i += kBlock) {
+    const int t = i >> qsh, q = i & ((1 << qsh) - 1);
+    if (q < nq && rc.col[t] >= 0) item(t, q);
+  }
+}
+
+// Four consecutive words of the output, streaming (written once, not read back).
+template <class T>
+__device__ __forceinline__ void store_quad(T* out, const T v[4], const int n, const bool vec) {
+  typedef T v4t __attribute__((ext_vector_type(4)));
+  if (vec) {
+    const v4t vv = {v[0], v[1], v[2], v[3]};
+    __builtin_nontemporal_store(vv, (v4t*)out);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      if (e < n) __builtin_nontemporal_store(v[e], out + e);
+  }
+}
+
+// Pass 3: the table, and the records of the occupied voxels one thread per
+// voxel (every gather issued at once).
+__device__ __forceinline__ void lut_write_body(const LutArgs& a, const uint32_t nz_magic,
+                                               const int bxr, const int byr) {
+  extern __shared__ __attribute__((aligned(16))) int32_t lpass[];  // [64][lut_row(nz)]
+  __shared__ RegionCols rc;
+  __shared__ int32_t sbase[kRegCols];  // rank of the column's first occupied voxel
+  const int nz = a.d.nz, roz = a.d.ro[2], nzp = lut_row(nz);
+  region_load(a.d, a.passes, a.occ, nz_magic, bxr, byr, lpass, rc, [&](int t, int32_t c) {
+    sbase[t] = c >= 0 ? a.block_base[c >> 6] + a.colpre[c] : 0;
+  });
+  __syncthreads();
+  const int nocc = rc.pre[kRegCols];
+  for (int o = threadIdx.x; o < nocc; o += kBlock) {
+    int r, z;
+    const int t = region_voxel(rc, o, r, z);
     const int32_t rank = sbase[t] + r;
     if (rank < a.cap) {
-      const int z = select_bit(Mask128{slo[t], shi[t]}, r);
-      const int64_t idx = scb[t] + ((int64_t)wrap_add(z + roz, nz) << 4);
+      const int64_t idx = rc.base[t] + ((int64_t)wrap_add(z + roz, nz) << 4);
       map_voxel_t d;
       d.hits = a.hits[idx];
       d.passes = lpass[t * nzp + z];
@@ -891,15 +950,9 @@ __device__ __forceinline__ void lut_write_body(const LutArgs& a, const uint32_t 
       a.data[rank] = d;
     }
   }
-  // items (column t, quad q): window-local z = 4q .. 4q+3; qs quads per column
-  // rounded up to a power of two so that t and q are shifts
-  const int nq = (nz + 3) >> 2;
-  const int qsh = nq > 1 ? 32 - __clz(nq - 1) : 0;
   const bool vec = (nz & 3) == 0 && ((uintptr_t)a.lut & 15) == 0;
-  for (int i = tid; i < (kRegCols << qsh); i += kBlock) {
-    const int t = i >> qsh, q = i & ((1 << qsh) - 1);
-    if (q >= nq || scb[t] < 0) continue;
-    const Mask128 mt = {slo[t], shi[t]};
+  region_quads(rc, nz, [&](int t, int q) {
+    const Mask128 mt = {rc.lo[t], rc.hi[t]};
     const int z0 = 4 * q;
     const int4 pv = *(const int4*)(lpass + t * nzp + z0);
     const int32_t p4[4] = {pv.x, pv.y, pv.z, pv.w};
@@ -912,18 +965,8 @@ __device__ __forceinline__ void lut_write_body(const LutArgs& a, const uint32_t 
       v[e] = occ ? rank : -1 - p4[e];
       rank += occ;
     }
-    // the table is written once and not read back here: streaming stores
-    int32_t* __restrict__ lut = a.lut + slut[t] + z0;
-    if (vec) {
-      typedef int32_t v4i __attribute__((ext_vector_type(4)));
-      const v4i vv = {v[0], v[1], v[2], v[3]};
-      __builtin_nontemporal_store(vv, (v4i*)lut);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; e++)
-        if (z0 + e < nz) __builtin_nontemporal_store(v[e], lut + e);
-    }
-  }
+    store_quad(a.lut + (int64_t)rc.col[t] * nz + z0, v, nz - z0, vec);
+  });
 }
 
 }  // namespace

@@ -152,7 +152,34 @@ struct DensityArgs {
   Dims d;
   const int32_t* hits;
   const int32_t* passes;
+  const unsigned long long* occ;
   float* out;             // [nx*ny*nz], window-local table order
+};
+
+// Per-column features of the gap-fill surrogate ([nx][ny][16]; undefined values
+// are 0):
+//  0 sum of hits, 1 sum of passes, 2 occupied voxels, 3 occupied fraction,
+//  4 ground height, 5 height of the highest occupied voxel, 6 mean of the
+//  occupied voxels' lowest returns, 7 height defined, 8 density of the ground
+//  voxel, 9 obstacle-band density, 10 slope, 11 roughness, 12 slope defined,
+//  13 horizontal distance of the column centre to the sensor, 14 sensor height
+//  above the ground, 15 column thinned.  A thinned column keeps only 13, 15.
+struct FeatArgs {
+  Dims d;
+  const int32_t* hits;
+  const int32_t* passes;
+  const int32_t* minqz;
+  const unsigned long long* occ;
+  int32_t O[3];
+  double res;
+  double sx, sy, sz;  // sensor position, m
+  const float* height;
+  const float* density;
+  const float* slope;
+  const float* rough;
+  const uint8_t* flags;
+  const uint8_t* thin;  // may be null
+  float* feat;
 };
 
 struct CostArgs {
@@ -246,6 +273,11 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_sum_ray_parts(const unsigned long long* parts, int64_t nblocks,
                                 unsigned long long* out, hipStream_t s);
 hipError_t launch_density(const DensityArgs& a, hipStream_t s);
+hipError_t launch_features(const FeatArgs& a, hipStream_t s);
+// Empties the window-local columns marked in `thin` (null: all of them) of a
+// map whose occupancy words agree with its voxels.
+hipError_t launch_thin(const Dims& d, const uint8_t* thin, int32_t* hits, int32_t* passes,
+                       int32_t* minqz, unsigned long long* occ, hipStream_t s);
 hipError_t launch_costmap(const CostArgs& a, hipStream_t s);
 // Exclusive prefix of base[0..nb) in place (one block); *total = the sum.
 hipError_t launch_scan_i32(int32_t* base, int nb, int64_t* total, hipStream_t s);

@@ -18,9 +18,6 @@
 
 #include "map_state.h"
 
-using gvom::col_base;
-using gvom::Dims;
-
 namespace {
 
 constexpr int kNL = 5;
@@ -43,114 +40,6 @@ __host__ __device__ inline uint16_t to_bf16(float f) {
 }
 
 __device__ inline float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-__device__ __forceinline__ int32_t wrap_add(int32_t s, int32_t n) { return s >= n ? s - n : s; }
-
-// ---------------------------------------------------------------- features
-struct FeatArgs {
-  Dims d;
-  const int32_t* hits;
-  const int32_t* passes;
-  const int32_t* minqz;
-  const unsigned long long* occ;
-  int32_t O[3];
-  double res;
-  double sx, sy, sz;  // sensor position, m
-  const float* height;
-  const float* density;
-  const float* slope;
-  const float* rough;
-  const uint8_t* flags;
-  const uint8_t* thin;  // may be null
-  float* feat;          // [nx][ny][16]
-};
-
-// One lane per window-local column.  Features (undefined values are 0):
-//  0 sum of hits, 1 sum of passes, 2 occupied voxels, 3 occupied fraction,
-//  4 ground height, 5 height of the highest occupied voxel, 6 mean of the
-//  occupied voxels' lowest returns, 7 height defined, 8 density of the ground
-//  voxel, 9 obstacle-band density, 10 slope, 11 roughness, 12 slope defined,
-//  13 horizontal distance of the column centre to the sensor, 14 sensor height
-//  above the ground, 15 column thinned.  A thinned column keeps only 13, 15.
-__global__ __launch_bounds__(256) void k_features(FeatArgs a) {
-  const int nx = a.d.nx, ny = a.d.ny, nz = a.d.nz;
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= nx * ny) return;
-  const int x = c / ny, y = c - x * ny;
-  float f[kFeat];
-  for (int k = 0; k < kFeat; k++) f[k] = 0.0f;
-  const double cx = ((double)(a.O[0] + x) + 0.5) * a.res - a.sx;
-  const double cy = ((double)(a.O[1] + y) + 0.5) * a.res - a.sy;
-  f[13] = (float)sqrt(cx * cx + cy * cy);
-  const bool thinned = a.thin && a.thin[c];
-  if (thinned) {
-    f[15] = 1.0f;
-  } else {
-    const int sxs = wrap_add(x + a.d.ro[0], nx), sys = wrap_add(y + a.d.ro[1], ny);
-    const int64_t cb = col_base(a.d, sxs, sys);
-    int64_t sh = 0, sp = 0, sq = 0;
-    int cnt = 0, top = -1, bottom = -1;
-    for (int z = 0; z < nz; z++) {
-      const int64_t e = cb + ((int64_t)wrap_add(z + a.d.ro[2], nz) << 4);
-      const int32_t h = a.hits[e];
-      sh += h;
-      sp += a.passes[e];
-      if (h >= 1) {
-        cnt++;
-        sq += a.minqz[e];
-        if (bottom < 0) bottom = z;
-        top = z;
-      }
-    }
-    const double q2m = a.res / 65536.0;
-    f[0] = (float)(double)sh;
-    f[1] = (float)(double)sp;
-    f[2] = (float)cnt;
-    f[3] = (float)((double)cnt / (double)nz);
-    const uint8_t fl = a.flags[c];
-    if (fl & 1) {
-      f[4] = a.height[c];
-      f[7] = 1.0f;
-      f[14] = (float)(a.sz - (double)a.height[c]);
-    }
-    if (cnt > 0) {
-      const int64_t et = cb + ((int64_t)wrap_add(top + a.d.ro[2], nz) << 4);
-      f[5] = (float)((double)a.minqz[et] * q2m);
-      f[6] = (float)(((double)sq / (double)cnt) * q2m);
-      const int64_t eb = cb + ((int64_t)wrap_add(bottom + a.d.ro[2], nz) << 4);
-      const double hb = a.hits[eb], pb = a.passes[eb];
-      f[8] = (float)(hb / (hb + pb));
-    }
-    if (fl & 2) f[9] = a.density[c];
-    if (fl & 32) {
-      f[10] = a.slope[c];
-      f[11] = a.rough[c];
-      f[12] = 1.0f;
-    }
-  }
-  float* o = a.feat + (int64_t)c * kFeat;
-  for (int k = 0; k < kFeat; k++) o[k] = f[k];
-}
-
-// Clears the voxels and occupancy of window-local columns marked in `thin`.
-__global__ __launch_bounds__(256) void k_thin(Dims d, const uint8_t* thin, int32_t* hits,
-                                              int32_t* passes, int32_t* minqz,
-                                              unsigned long long* occ) {
-  const int nx = d.nx, ny = d.ny, nz = d.nz;
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= nx * ny || !thin[c]) return;
-  const int x = c / ny, y = c - x * ny;
-  const int sxs = wrap_add(x + d.ro[0], nx), sys = wrap_add(y + d.ro[1], ny);
-  const int64_t cb = col_base(d, sxs, sys);
-  for (int z = 0; z < nz; z++) {
-    hits[cb + ((int64_t)z << 4)] = 0;
-    passes[cb + ((int64_t)z << 4)] = 0;
-    minqz[cb + ((int64_t)z << 4)] = INT32_MAX;
-  }
-  const int64_t col = (int64_t)sxs * ny + sys;
-  occ[col * d.W] = 0;
-  if (d.W > 1) occ[col * d.W + 1] = 0;
-}
 
 // Per-block sums and sums of squares of the 16 features (normalisation).
 __global__ __launch_bounds__(256) void k_feat_sums(const float* feat, int64_t P, double* part) {
@@ -1302,12 +1191,9 @@ int32_t sgt_set_norm(sgt_net_t* n, const float* mean, const float* stdv) {
 int32_t sgt_thin(map_t* m, const uint8_t* thin_dev) {
   if (!m || !thin_dev) return MAP_E_INVALID;
   if (m->sticky) return m->sticky;
-  const int64_t C = (int64_t)m->p.nx * m->p.ny;
   m->lut_counted = false;
   m->version = gvom::next_version();
-  hipLaunchKernelGGL(k_thin, dim3(blocks_for(C)), dim3(256), 0, m->stream, m->d, thin_dev, m->hits,
-                     m->passes, m->minqz, m->occ);
-  return st_of(hipGetLastError());
+  return st_of(gvom::launch_thin(m->d, thin_dev, m->hits, m->passes, m->minqz, m->occ, m->stream));
 }
 
 int32_t sgt_features(map_t* m, const map_2d_t* plain, const float sensor_xyz[3],
@@ -1316,7 +1202,7 @@ int32_t sgt_features(map_t* m, const map_2d_t* plain, const float sensor_xyz[3],
       !plain->flags || !sensor_xyz || !feat_dev)
     return MAP_E_INVALID;
   if (m->sticky) return m->sticky;
-  FeatArgs a;
+  gvom::FeatArgs a;
   a.d = m->d;
   a.hits = m->hits;
   a.passes = m->passes;
@@ -1334,9 +1220,7 @@ int32_t sgt_features(map_t* m, const map_2d_t* plain, const float sensor_xyz[3],
   a.flags = plain->flags;
   a.thin = thin_dev;
   a.feat = feat_dev;
-  const int64_t C = (int64_t)m->p.nx * m->p.ny;
-  hipLaunchKernelGGL(k_features, dim3(blocks_for(C)), dim3(256), 0, m->stream, a);
-  return st_of(hipGetLastError());
+  return st_of(gvom::launch_features(a, m->stream));
 }
 
 int32_t sgt_feature_sums(sgt_net_t* n, const float* feat_dev, double* sums_host) {

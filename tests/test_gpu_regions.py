@@ -1,0 +1,107 @@
+"""The kernels that take a map region by region (import, table, density and
+feature exports, thinning, reset) against the oracle, on windows whose columns,
+levels and scroll offsets do not fill the regions (needs an MI355X).  Everything
+compared here is exact: integers, and floats by their bits (slope and roughness
+features excepted, which follow the plain maps' tolerance and are not compared)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sgt as osgt
+
+pytestmark = pytest.mark.gpu
+
+
+def _state(nx, ny, nz, seed, fill):
+    """A random table and data array: occupied, passed and unseen voxels."""
+    rng = np.random.default_rng(seed)
+    V = nx * ny * nz
+    occ = rng.uniform(size=V) < fill
+    lut = np.where(rng.uniform(size=V) < 0.4, -1 - rng.integers(1, 1000, V), -1).astype(np.int32)
+    lut[occ] = np.arange(occ.sum())
+    data = np.stack([rng.integers(1, 50, occ.sum()), rng.integers(0, 90, occ.sum()),
+                     rng.integers(-2 ** 20, 2 ** 20, occ.sum())], 1).astype(np.int32)
+    return lut, data
+
+
+@pytest.mark.parametrize("nx,ny,nz,origin", [
+    (2, 2, 1, (0, 0, 0)),             # one voxel per column, one partial brick
+    (6, 10, 3, (-3, 5, -1)),
+    (18, 34, 41, (7, -11, 13)),       # odd levels: no 16-byte table words
+    (64, 48, 64, (5, 2, -31)),
+    (66, 94, 96, (-35, 17, 40)),      # two occupancy words per column
+    (30, 130, 128, (1, 1, 127)),      # the most levels
+])
+def test_region_kernels_match_oracle(nx, ny, nz, origin):
+    import oracle
+    from paper_2109_13176_amd import gvom
+    p = dict(nx=nx, ny=ny, nz=nz, res_m=0.25, sensor_z_voxel=nz // 2, obs_min_m=0.3, obs_max_m=2.0,
+             dens_num=1, dens_den=2, fit_n=5, neg_thresh_m=0.5, neg_search_m=2.0)
+    m, o = gvom.VoxelMap(p), oracle.OracleMap(p)
+    origin = np.array(origin, np.int32)
+    V = nx * ny * nz
+    sensor = np.array([0.3, -0.2, 1.1], np.float32)
+    # each state over the one before it (other occupied voxels, other offsets)
+    for k, fill in enumerate((0.1, 0.0, 0.02, 0.6)):
+        org = origin + np.array([k, -2 * k, 3 * k], np.int32)
+        lut, data = _state(nx, ny, nz, 10 * k + nz, fill)
+        off = k & 1  # a table that is not 16-byte aligned
+        lt = torch.zeros(V + 4, dtype=torch.int32, device="cuda")[off:off + V]
+        lt.copy_(torch.from_numpy(lut))
+        dt = torch.from_numpy(data).cuda() if len(data) else None
+        assert gvom.map_import_voxels(m.h, lt, dt, org) == 0
+        assert o.import_voxels(lut, data, org) == oracle.OK
+        out = torch.zeros(V + 4, dtype=torch.int32, device="cuda")[off:off + V]
+        back = torch.zeros((len(data) + 1, 3), dtype=torch.int32, device="cuda")
+        st, n, org_g = gvom.map_export_voxels(m.h, out, back)
+        assert st == 0 and n == len(data) and np.array_equal(org_g, org)
+        assert np.array_equal(out.cpu().numpy(), lut)
+        assert np.array_equal(back.cpu().numpy()[:n], data)
+        den = m.export_density().cpu().numpy()
+        assert np.array_equal(den.view(np.uint32), o.export_density().view(np.uint32).reshape(-1))
+        mask = (np.random.default_rng(k).uniform(size=(nx, ny)) < 0.5).astype(np.uint8)
+        thin = torch.from_numpy(mask).cuda()
+        for step in range(2):  # features before and after the columns go
+            plain = m.export_2d()
+            f = gvom.sgt_features(m, plain, sensor, thin if step else None).cpu().numpy()
+            of = osgt.features(o, o.export_2d(), sensor, mask if step else np.zeros_like(mask))
+            exact = [i for i in range(16) if i not in (10, 11)]
+            assert np.array_equal(f[..., exact].view(np.uint32), of[..., exact].view(np.uint32))
+            if step == 0:
+                assert gvom.sgt_thin(m, thin) == 0
+                osgt.thin(o, mask)
+        st, lut_o, data_o, n_o, _ = o.export_voxels()
+        st, n, _ = gvom.map_export_voxels(m.h, out, back)
+        assert n == n_o and np.array_equal(out.cpu().numpy(), lut_o.reshape(-1))
+        assert np.array_equal(back.cpu().numpy()[:n], np.asarray(data_o).reshape(-1, 3)[:n])
+    assert gvom.map_reset(m.h) == 0
+    st, n, _ = gvom.map_export_voxels(m.h, out, back)
+    assert st == 0 and n == 0 and bool((out == -1).all())
+    assert bool(torch.isnan(m.export_density()).all())
+    m.close()
+    o.close()
+
+
+def test_import_of_invalid_content_empties_the_map():
+    from paper_2109_13176_amd import gvom
+    nx, ny, nz = 34, 18, 9
+    p = dict(nx=nx, ny=ny, nz=nz, res_m=0.25, sensor_z_voxel=4, obs_min_m=0.3, obs_max_m=2.0,
+             dens_num=1, dens_den=2, fit_n=5, neg_thresh_m=0.5, neg_search_m=2.0)
+    m = gvom.VoxelMap(p)
+    org = np.zeros(3, np.int32)
+    good, data = _state(nx, ny, nz, 3, 0.2)
+    out = torch.zeros(nx * ny * nz, dtype=torch.int32, device="cuda")
+    for kind in ("index", "hits", "min"):
+        lut, d = good.copy(), data.copy()
+        if kind == "index":
+            lut[np.argmax(lut)] = len(d)
+        elif kind == "hits":
+            d[7, 0] = 0
+        else:
+            lut[5] = -2 ** 31
+        assert gvom.map_import_voxels(m.h, torch.from_numpy(good).cuda(), torch.from_numpy(data).cuda(), org) == 0
+        st = gvom.map_import_voxels(m.h, torch.from_numpy(lut).cuda(), torch.from_numpy(d).cuda(), org)
+        assert st == gvom.MAP_E_INVALID, kind
+        st, n, _ = gvom.map_export_voxels(m.h, out, None)
+        assert n == 0 and bool((out == -1).all()), kind
+    m.close()
