@@ -302,8 +302,9 @@ int32_t map_create(const map_params_t* p, void* stream, map_t** out) {
   if (e == hipSuccess) e = dmalloc(&m->occ, C * m->d.W * 8);
   if (e == hipSuccess) e = dmalloc(&m->hq, C * 4);
   if (e == hipSuccess) e = dmalloc(&m->defbits, nb * 8);
-  if (e == hipSuccess) e = dmalloc(&m->block_base, nb * 4);
+  if (e == hipSuccess) e = dmalloc(&m->group_cnt, nb * 4);
   if (e == hipSuccess) e = dmalloc(&m->colpre, C * 4);
+  if (e == hipSuccess) e = dmalloc(&m->super_sum, (nb + 63) / 64 * 4);
   if (e == hipSuccess) e = dmalloc(&m->stats, kStatsBytes);
   if (e == hipSuccess) e = dmalloc(&m->err, 4);
   if (e == hipSuccess) e = dmalloc(&m->nocc, 8);
@@ -341,8 +342,9 @@ int32_t map_destroy(map_t* m) {
   (void)gvom::dev_free(m->occ);
   (void)gvom::dev_free(m->hq);
   (void)gvom::dev_free(m->defbits);
-  (void)gvom::dev_free(m->block_base);
+  (void)gvom::dev_free(m->group_cnt);
   (void)gvom::dev_free(m->colpre);
+  (void)gvom::dev_free(m->super_sum);
   (void)gvom::dev_free(m->stats);
   (void)gvom::dev_free(m->err);
   (void)gvom::dev_free(m->nocc);
@@ -364,7 +366,7 @@ int32_t map_reset(map_t* m) {
   (void)hipGetLastError();
   m->sticky = MAP_OK;
   initial_origin(m);
-  m->lut_counted = false;
+  m->ranked = false;
   m->version = gvom::next_version();
   m->last_points = 0;
   m->last_cleared = 0;
@@ -554,14 +556,18 @@ void column_args(const map_t* m, const map_2d_t* out, bool ranks, gvom::ColumnAr
   ca->hq = m->hq;
   ca->defbits = m->defbits;
   ca->colpre = ranks ? m->colpre : nullptr;
-  ca->block_base = ranks ? m->block_base : nullptr;
+  ca->group_cnt = ranks ? m->group_cnt : nullptr;
 }
 
 int64_t tiles64(const map_t* m) {
   return (int64_t)((m->p.nx + 63) / 64) * ((m->p.ny + 63) / 64);
 }
 
-void surface_args(const map_t* m, const map_2d_t* out, gvom::SurfaceArgs* sa) {
+// ranks: the launch also sums the group counts of the column pass
+void surface_args(const map_t* m, const map_2d_t* out, bool ranks, gvom::SurfaceArgs* sa) {
+  sa->rank_cnt = m->group_cnt;
+  sa->rank_n = ranks ? (int32_t)((n_col(m) + 63) / 64) : 0;
+  sa->rank_sum = m->super_sum;
   sa->nx = m->p.nx;
   sa->ny = m->p.ny;
   sa->hq = m->hq;
@@ -586,8 +592,11 @@ void lut_args(const map_t* m, int32_t* lut_dev, map_voxel_t* data_dev, int64_t c
   a->lut = lut_dev;
   a->data = data_dev;
   a->cap = cap;
-  a->block_base = m->block_base;
+  a->group_cnt = m->group_cnt;
   a->colpre = m->colpre;
+  a->super_sum = m->super_sum;
+  a->nsuper = (int32_t)((n_col(m) + 4095) / 4096);
+  a->scanned = 0;
   a->n_occupied = n_occupied_dev;
 }
 
@@ -657,7 +666,7 @@ int32_t map_insert_scan(map_t* m, const float* xyz_dev, int64_t n, const float p
   gvom::InsertArgs a;
   gvom::ClearArgs plan;
   bool full = false;
-  m->lut_counted = false;
+  m->ranked = false;
   m->version = gvom::next_version();
   const int pm0 = prof_begin(m, MAP_PROF_SCROLL);
   st = prepare_insert(m, xyz_dev, n, pose, flags, S, &a, &plan, &full);
@@ -709,7 +718,7 @@ int32_t map_insert_scan_static(map_t* m, const float* xyz_dev, int64_t n, const 
   a.witems = (int2*)base;
   base += align256((size_t)need * sizeof(int2));
   a.part_rays = (unsigned long long*)base;
-  m->lut_counted = false;
+  m->ranked = false;
   m->version = gvom::next_version();
   st = fill_insert(m, xyz_dev, n, pose, flags, S, &a, &plan, &full, need);
   if (st) return st;
@@ -735,15 +744,15 @@ int32_t map_export_2d(map_t* m, const map_2d_t* out) {
   int pm = prof_begin(m, MAP_PROF_COLUMN);
   hipError_t e = gvom::launch_column(ca, m->stream);
   prof_end(m, pm);
-  m->lut_counted = e == hipSuccess;
   if (e == hipSuccess) {
     gvom::SurfaceArgs sa;
-    surface_args(m, out, &sa);
+    surface_args(m, out, true, &sa);
     pm = prof_begin(m, MAP_PROF_SURFACE);
     const int H = sa.search_d > sa.half_fit ? sa.search_d : sa.half_fit;
     const int tile = gvom::surface_tile_for(H, m->surf_tile, tiles64(m), m->n_cu);
     e = gvom::launch_surface(sa, tile, m->stream);
     prof_end(m, pm);
+    m->ranked = e == hipSuccess;
   }
   return dev_status(m, e);
 }
@@ -756,10 +765,11 @@ int32_t map_export_voxels_async(map_t* m, int32_t* lut_dev, map_voxel_t* data_de
   gvom::LutArgs a;
   lut_args(m, lut_dev, data_dev, cap, n_occupied_dev, &a);
   const int pm = prof_begin(m, MAP_PROF_LUT);
-  // the ranks of a 2D export since the last change of the map are reused
-  // (the scan below turns block_base into prefixes: a later export recounts)
-  hipError_t e = gvom::launch_lut(a, m->lut_counted, m->stream);
-  m->lut_counted = false;
+  // the ranks of a 2D export since the last change of the map are used once: an
+  // export on its own always makes them, so that a captured one replays on
+  // whatever the map then holds
+  hipError_t e = gvom::launch_lut(a, m->ranked, m->stream);
+  m->ranked = false;
   prof_end(m, pm);
   for (int i = 0; i < 3; i++) origin_vox[i] = m->origin[i];
   return dev_status(m, e);
@@ -818,7 +828,7 @@ int32_t map_import_voxels(map_t* m, const int32_t* lut_dev, const map_voxel_t* d
   if (m->sticky) return m->sticky;
   for (int i = 0; i < 3; i++) m->origin[i] = origin_vox[i];
   set_ring(m);
-  m->lut_counted = false;
+  m->ranked = false;
   m->empty = false;
   m->version = gvom::next_version();
   int32_t err = 0;
@@ -985,7 +995,7 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
   gvom::BatchStep& st = t->st;
   st.nmaps = b->k;
   st.pre_rays[0] = st.pre_trace[0] = st.pre_col[0] = st.pre_surf[0] = 0;
-  st.pre_lcount[0] = st.pre_lscan[0] = st.pre_lwrite[0] = 0;
+  st.pre_lwrite[0] = 0;
   int64_t t64 = 0;
   for (int i = 0; i < b->k; i++) t64 += tiles64(b->maps[i]);
   for (int i = 0; i < b->k; i++) {
@@ -994,12 +1004,12 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
     const int32_t s = prepare_insert(m, xyz_dev[i], n[i], poses + 12 * i, flags[i], S[i],
                                      &t->ins[i], &t->clr[i], &full);
     if (s) return s;  // allocation failure
-    column_args(m, &out2d[i], false, &t->col[i]);
-    m->lut_counted = false;
+    const bool lut = lut_dev && lut_dev[i];
+    column_args(m, &out2d[i], lut, &t->col[i]);
+    m->ranked = false;
     m->empty = false;
     m->version = gvom::next_version();
-    surface_args(m, &out2d[i], &t->sur[i]);
-    const bool lut = lut_dev && lut_dev[i];
+    surface_args(m, &out2d[i], lut, &t->sur[i]);
     if (lut) {
       lut_args(m, lut_dev[i], data_dev ? data_dev[i] : nullptr, cap ? cap[i] : 0,
                n_occupied_dev[i], &t->lut[i]);
@@ -1017,12 +1027,9 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
     st.pre_trace[i + 1] = st.pre_trace[i] + t->ins[i].trace_blocks;
     st.pre_col[i + 1] = st.pre_col[i] + (int)((C + 255) / 256);
     st.pre_surf[i + 1] = st.pre_surf[i] + tiles;
-    st.pre_lcount[i + 1] = st.pre_lcount[i] + (lut ? (int)((C + 255) / 256) : 0);
-    st.pre_lscan[i + 1] = st.pre_lscan[i] + (lut ? 1 : 0);
     st.pre_lwrite[i + 1] = st.pre_lwrite[i] + (lut ? lw : 0);
     st.surf_tiles_y[i] = tiles_y;
     st.lw_by[i] = lw_by;
-    st.lut_groups[i] = (int)((C + 63) / 64);
     st.nz_magic[i] = gvom::nz_magic(m->p.nz);
     st.last_is_lut[i] = lut ? 1 : 0;
     (void)full;  // a whole-window clear is the plan's single full box
@@ -1144,7 +1151,7 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
   const int cu = b->n_cu;
   // persistent grids; the bandwidth-bound column and table passes get eight
   // blocks per CU (the table pass's LDS regions allow it)
-  b->grid = gvom::BatchGrid{cu * 4, cu * 2, cu * 8, cu * 8, cu * 2, cu * 4, cu * 8,
+  b->grid = gvom::BatchGrid{cu * 4, cu * 2, cu * 8, cu * 8, cu * 2, cu * 8,
                             k * gvom::box_fold_blocks(), surf, lut};
   hipError_t e = gvom::dev_alloc((void**)&b->dtab, sizeof(gvom::BatchTables));
   if (e == hipSuccess) e = hipHostMalloc((void**)&b->htab, sizeof(gvom::BatchTables), 0);

@@ -893,7 +893,7 @@ int32_t map_buffer_push(map_buffer_t* b, const float* xyz_dev, int64_t n, const 
     return buf_fail(b, e);
   }
   m->empty = true;
-  m->lut_counted = false;
+  m->ranked = false;
   m->version = gvom::next_version();
   s.origin[0] = m->origin[0];
   s.origin[1] = m->origin[1];
@@ -939,7 +939,7 @@ int32_t map_buffer_combine(map_buffer_t* b, map_t* out) {
   hipError_t e = hipStreamWaitEvent(out->stream, b->pushed, 0);
   const map_buffer_t::Slot& nw = slot_of(b, b->npush - 1);
   gvom::set_origin(out, nw.origin);
-  out->lut_counted = false;
+  out->ranked = false;
   out->empty = false;
   out->wild = false;  // (an update in place starts from a combination)
   gvom::CombineArgs a;

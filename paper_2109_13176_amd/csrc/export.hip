@@ -10,12 +10,25 @@ namespace {
 
 __global__ __launch_bounds__(kBlock) void k_column(ColumnArgs a) { column_body(a, blockIdx.x); }
 
+// Block b of a surface pass sums super group b of the table export's ranks in
+// its last wave (a pass has at least one tile per 64 x 64 columns).
+__device__ __forceinline__ void surface_rank_sums(const SurfaceArgs& a, const int b) {
+  if (64 * b < a.rank_n && threadIdx.x >= kSurfThreads - 64)
+    super_sum_body(a.rank_cnt, a.rank_n, a.rank_sum, b);
+}
+
 template <int TILE>
 __global__ __launch_bounds__(kSurfThreads, 8) void k_surface(SurfaceArgs a, int H) {
+  surface_rank_sums(a, blockIdx.x * gridDim.y + blockIdx.y);
   surface_body<kSurfThreads, TILE>(a, H, blockIdx.x, blockIdx.y);
 }
 
 __global__ __launch_bounds__(kBlock) void k_lut_count(LutArgs a) { lut_count_body(a, blockIdx.x); }
+
+__global__ __launch_bounds__(kBlock) void k_lut_sums(int32_t* cnt, int n, int32_t* sum) {
+  const int g = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (64 * g < n) super_sum_body(cnt, n, sum, g);
+}
 
 __global__ __launch_bounds__(1024) void k_lut_scan(int32_t* base, int nb, int64_t* n_occupied) {
   lut_scan_body<1024>(base, nb, n_occupied);
@@ -400,6 +413,7 @@ __global__ __launch_bounds__(kSurfThreads, 4) void k_b_surface(const BatchTables
   for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {
     const int m = find_map_e(t->st.pre_surf, n, vb);
     const int b = vb - t->st.pre_surf[m];
+    surface_rank_sums(t->sur[m], b);
     const int ty = t->st.surf_tiles_y[m], H = t->st.surf_H[m], tile = t->st.surf_tile[m];
     if (tile == 64) surface_body<kSurfThreads, 64>(t->sur[m], H, b / ty, b % ty);
     else if (tile == 32) surface_body<kSurfThreads, 32>(t->sur[m], H, b / ty, b % ty);
@@ -408,25 +422,6 @@ __global__ __launch_bounds__(kSurfThreads, 4) void k_b_surface(const BatchTables
     sp.done(m, !t->st.last_is_lut[m], stamps);
   }
   sp.flush(stamps);
-}
-
-__global__ __launch_bounds__(kBlock) void k_b_lut_count(const BatchTables* __restrict__ t) {
-  const int n = t->st.nmaps;
-  const int total = t->st.pre_lcount[n];
-  for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {
-    const int m = find_map_e(t->st.pre_lcount, n, vb);
-    lut_count_body(t->lut[m], vb - t->st.pre_lcount[m]);
-  }
-}
-
-__global__ __launch_bounds__(1024) void k_b_lut_scan(const BatchTables* __restrict__ t) {
-  const int n = t->st.nmaps;
-  const int total = t->st.pre_lscan[n];
-  for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {
-    const int m = find_map_e(t->st.pre_lscan, n, vb);
-    lut_scan_body<1024>(t->lut[m].block_base, t->st.lut_groups[m], t->lut[m].n_occupied);
-    __syncthreads();
-  }
 }
 
 __global__ __launch_bounds__(kBlock) void k_b_lut_write(const BatchTables* __restrict__ t,
@@ -457,8 +452,6 @@ hipError_t launch_batch_export(const BatchTables* tab, const BatchGrid& g,
   }
   hipLaunchKernelGGL(k_b_column, dim3(g.col), dim3(kBlock), 0, s, tab);
   hipLaunchKernelGGL(k_b_surface, dim3(g.surf), dim3(kSurfThreads), g.surf_lds, s, tab, stamps);
-  hipLaunchKernelGGL(k_b_lut_count, dim3(g.lcount), dim3(kBlock), 0, s, tab);
-  hipLaunchKernelGGL(k_b_lut_scan, dim3(g.lcount), dim3(1024), 0, s, tab);
   hipLaunchKernelGGL(k_b_lut_write, dim3(g.lwrite), dim3(kBlock), g.lut_lds, s, tab, stamps);
   return hipGetLastError();
 }
@@ -518,16 +511,25 @@ hipError_t launch_surface(const SurfaceArgs& a, int tile, hipStream_t s) {
                     : tile == 16 ? launch_surface_t<16>(a, s) : launch_surface_t<32>(a, s);
 }
 
-hipError_t launch_lut(const LutArgs& a, bool counted, hipStream_t s) {
+hipError_t launch_lut(const LutArgs& args, bool ranked, hipStream_t s) {
+  LutArgs a = args;
   const int C = a.d.nx * a.d.ny;
   const int ng = (C + kGroup - 1) / kGroup;
   // b / nz == umulhi(b, ceil(2^32 / nz)) for every b < 2^20 (here b < 4 * 128)
   const uint32_t magic =
       a.d.nz > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint64_t)a.d.nz - 1) / (uint64_t)a.d.nz) : 0u;
   const size_t lds = lut_lds(a.d.nz);
-  if (!counted)
+  if (!ranked) {
     hipLaunchKernelGGL(k_lut_count, dim3((C + kBlock - 1) / kBlock), dim3(kBlock), 0, s, a);
-  hipLaunchKernelGGL(k_lut_scan, dim3(1), dim3(1024), 0, s, a.block_base, ng, a.n_occupied);
+    hipLaunchKernelGGL(k_lut_sums, dim3((a.nsuper + 3) / 4), dim3(kBlock), 0, s, a.group_cnt, ng,
+                       a.super_sum);
+  }
+  // every region scans the sums of the super groups in a wave, four of them a
+  // lane at most; more of them are scanned first
+  if (a.nsuper > 256) {
+    hipLaunchKernelGGL(k_lut_scan, dim3(1), dim3(1024), 0, s, a.super_sum, a.nsuper, a.n_occupied);
+    a.scanned = 1;
+  }
   dim3 g((a.d.nx + 3) / 4, (a.d.nby + 3) / 4);
   hipLaunchKernelGGL(k_lut_write, g, dim3(kBlock), lds, s, a, magic);
   return hipGetLastError();

@@ -20,10 +20,9 @@ struct Mask128 {
   unsigned long long lo, hi;
 };
 
-__device__ __forceinline__ Mask128 local_mask(const unsigned long long* occ, int64_t col,
-                                              int W, int nz, int roz) {
-  unsigned __int128 m = occ[col * W];
-  if (W > 1) m |= (unsigned __int128)occ[col * W + 1] << 64;
+__device__ __forceinline__ Mask128 rotate_mask(const unsigned long long w0,
+                                               const unsigned long long w1, int nz, int roz) {
+  unsigned __int128 m = w0 | (unsigned __int128)w1 << 64;
   if (roz != 0) {
     const unsigned __int128 full =
         nz == 128 ? ~(unsigned __int128)0 : (((unsigned __int128)1 << nz) - 1);
@@ -33,6 +32,12 @@ __device__ __forceinline__ Mask128 local_mask(const unsigned long long* occ, int
   r.lo = (unsigned long long)m;
   r.hi = (unsigned long long)(m >> 64);
   return r;
+}
+
+__device__ __forceinline__ Mask128 local_mask(const unsigned long long* occ, int64_t col,
+                                              int W, int nz, int roz) {
+  const unsigned long long w0 = occ[col * W], w1 = W > 1 ? occ[col * W + 1] : 0ull;
+  return rotate_mask(w0, w1, nz, roz);
 }
 
 __device__ __forceinline__ int lowest_bit(const Mask128& m) {
@@ -72,6 +77,18 @@ __device__ __forceinline__ int select_bit(const Mask128& m, int r) {
   return pos;
 }
 
+// Inclusive prefix sum over the lanes of a wave (row shifts within 16 lanes,
+// then the broadcasts of lanes 15 and 31 of each half).
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, true);
+  return x;
+}
+
 // One lane per map column (window-local pixel).  Ground voxel = lowest
 // occupied voxel; height = its lowest return.  The positive-obstacle band is
 // the occupied voxels n_lo..n_hi above the ground voxel; its density is
@@ -82,15 +99,10 @@ __device__ __forceinline__ int select_bit(const Mask128& m, int r) {
 // see lut_count_body), from the occupancy mask it loads anyway.
 __device__ __forceinline__ void column_counts(const ColumnArgs& a, const int c, const int cnt) {
   const int lane = __lane_id();
-  int incl = cnt;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(incl, o);
-    if (lane >= o) incl += u;
-  }
+  const int incl = wave_scan(cnt);
   const int C = a.d.nx * a.d.ny;
   if (c < C) a.colpre[c] = incl - cnt;
-  if (lane == 63 && (c >> 6) * 64 < C) a.block_base[c >> 6] = incl;
+  if (lane == 63 && (c >> 6) * 64 < C) a.group_cnt[c >> 6] = incl;
 }
 
 __device__ __forceinline__ void column_body(const ColumnArgs& a, const int blk) {
@@ -701,8 +713,13 @@ __device__ __forceinline__ void surface_body(const SurfaceArgs& a, const int H, 
 
 // Lookup-table export.  Ranks follow window-local column order: pass 1 gives
 // every local column its occupied-voxel count prefix within its group of 64
-// columns and each group its total, pass 2 scans the group totals, pass 3
-// writes the table and the data array region by region.
+// columns and each group its count, pass 2 sums the counts of every super
+// group of 64 groups (and makes them prefixes within it), pass 3 writes the
+// table and the data array region by region, scanning the sums of the super
+// groups in a wave.  After a 2D export the first two passes are already done, by its column pass and by one
+// wave in each of the first blocks of its surface pass: a scan of all groups in
+// a launch of its own took 5 us at 4,096 groups and 20 us at 16,384, and a
+// block more in the surface pass 7 us (a compute unit with two of its blocks).
 constexpr int kGroup = 64;
 
 __device__ __forceinline__ void lut_count_body(const LutArgs& a, const int blk) {
@@ -716,19 +733,25 @@ __device__ __forceinline__ void lut_count_body(const LutArgs& a, const int blk) 
     cnt = __popcll(a.occ[scol * a.d.W]);
     if (a.d.W > 1) cnt += __popcll(a.occ[scol * a.d.W + 1]);
   }
-  int incl = cnt;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(incl, o);
-    if (lane >= o) incl += u;
-  }
+  const int incl = wave_scan(cnt);
   if (c < nx * ny) a.colpre[c] = incl - cnt;
   const int g = c >> 6;
-  if (lane == 63 && g * kGroup < nx * ny) a.block_base[g] = incl;
+  if (lane == 63 && g * kGroup < nx * ny) a.group_cnt[g] = incl;
 }
 
 
-// Pass 2 (one block): exclusive scan of the group counts; writes M.
+// Pass 2: the counts of super group g become exclusive prefixes within it, and
+// sum[g] their sum, by one wave.
+__device__ __forceinline__ void super_sum_body(int32_t* cnt, const int n, int32_t* sum,
+                                               const int g) {
+  const int i = 64 * g + __lane_id();
+  const int v = i < n ? cnt[i] : 0;
+  const int s = wave_scan(v);
+  if (i < n) cnt[i] = s - v;
+  if (__lane_id() == 63) sum[g] = s;
+}
+
+// Exclusive prefix of base[0..nb) in place (one block); *n_occupied = the sum.
 template <int NT>
 __device__ __forceinline__ void lut_scan_body(int32_t* base, const int nb, int64_t* n_occupied) {
   __shared__ int64_t wsum[NT / 64];
@@ -829,7 +852,8 @@ __device__ __forceinline__ int region_word(const int k4, const int nz, const uin
 
 // Loads the passes of region (bxr, byr) into the LDS rows and describes its
 // columns (wave 0, while the first loads are in flight; extra(t, c) for slot t
-// = window-local column c, -1 outside the map).  Ends without a barrier.
+// = window-local column c, -1 outside the map, called by the whole wave).  Ends
+// without a barrier.
 template <class Extra>
 __device__ __forceinline__ void region_load(const Dims& d, const int32_t* passes,
                                             const unsigned long long* occ, const uint32_t nz_magic,
@@ -848,18 +872,16 @@ __device__ __forceinline__ void region_load(const Dims& d, const int32_t* passes
       v[u] = src[min(k0 + u * kBlock + tid, nv4 - 1)];
     }
     if (k0 == 0 && tid < kRegCols) {
-      Mask128 m = {0ull, 0ull};
       int sx, sy;
       const int32_t c = region_col(d, bxr, byr, tid, sx, sy);
+      // the occupancy words and extra()'s loads in one round trip: the words
+      // are loaded first (from a clamped column) and used last
+      const int64_t ow = c >= 0 ? ((int64_t)sx * d.ny + sy) * d.W : 0;
+      const unsigned long long w0 = occ[ow], w1 = occ[ow + d.W - 1];
       extra(tid, c);
-      if (c >= 0) m = local_mask(occ, (int64_t)sx * d.ny + sy, d.W, nz, roz);
+      const Mask128 m = c >= 0 ? rotate_mask(w0, d.W > 1 ? w1 : 0ull, nz, roz) : Mask128{0ull, 0ull};
       const int cnt = __popcll(m.lo) + __popcll(m.hi);
-      int incl = cnt;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o);
-        if (tid >= o) incl += y;
-      }
+      const int incl = wave_scan(cnt);
       rc.lo[tid] = m.lo;
       rc.hi[tid] = m.hi;
       rc.base[tid] = col_base(d, sx, sy);
@@ -933,7 +955,25 @@ __device__ __forceinline__ void lut_write_body(const LutArgs& a, const uint32_t 
   __shared__ int32_t sbase[kRegCols];  // rank of the column's first occupied voxel
   const int nz = a.d.nz, roz = a.d.ro[2], nzp = lut_row(nz);
   region_load(a.d, a.passes, a.occ, nz_magic, bxr, byr, lpass, rc, [&](int t, int32_t c) {
-    sbase[t] = c >= 0 ? a.block_base[c >> 6] + a.colpre[c] : 0;
+    const int g = max(c, 0) >> 6, sg = g >> 6;
+    const int32_t cp = a.colpre[max(c, 0)], gp = a.group_cnt[g];
+    const int32_t s0 = a.super_sum[a.scanned ? sg : min(t, a.nsuper - 1)];
+    int32_t base = c >= 0 ? cp + gp : 0;
+    if (a.scanned) {
+      base += s0;
+    } else {
+      int before = 0;
+      for (int k = 0; 64 * k < a.nsuper; k++) {
+        int v = k == 0 ? s0 : a.super_sum[min(64 * k + t, a.nsuper - 1)];
+        v = 64 * k + t < a.nsuper ? v : 0;
+        const int s = wave_scan(v);
+        const int e = __shfl(s - v, sg & 63);
+        base += sg >> 6 == k ? before + e : 0;
+        before += __builtin_amdgcn_readlane(s, 63);
+      }
+      if (bxr == 0 && byr == 0 && t == 0) *a.n_occupied = before;
+    }
+    sbase[t] = base;
   });
   __syncthreads();
   const int nocc = rc.pre[kRegCols];

@@ -117,7 +117,7 @@ struct ColumnArgs {
   int32_t* hq;            // ground height Q per local pixel, INT32_MIN = undefined
   unsigned long long* defbits;  // bit c % 64 of word c / 64: pixel c has a height
   int32_t* colpre;        // null, or the table export's counting pass (see LutArgs)
-  int32_t* block_base;
+  int32_t* group_cnt;
 };
 
 struct SurfaceArgs {
@@ -132,6 +132,11 @@ struct SurfaceArgs {
   float* slope;
   float* rough;
   uint8_t* flags;
+  // the table export's group counts (see LutArgs), turned into prefixes and sums
+  // of super groups by this launch; rank_n = groups, 0: none
+  int32_t* rank_cnt;
+  int32_t rank_n;
+  int32_t* rank_sum;
 };
 
 struct LutArgs {
@@ -143,8 +148,14 @@ struct LutArgs {
   int32_t* lut;
   map_voxel_t* data;
   int64_t cap;
-  int32_t* block_base;    // per group of 64 window-local columns: exclusive rank base
+  // a column's first rank = the sums of the super groups before its own + its
+  // group's prefix within that + its rank within its group
+  int32_t* group_cnt;     // per group of 64 window-local columns: its prefix within its
+                          // super group
+  int32_t* super_sum;     // per super group of 64 groups: their sum, or the exclusive
+                          // prefix of the sums (scanned != 0)
   int32_t* colpre;        // per window-local column: exclusive rank within its group
+  int32_t nsuper, scanned;
   int64_t* n_occupied;
 };
 
@@ -215,14 +226,11 @@ struct BatchStep {
   int32_t pre_trace[kMaxBatch + 1];
   int32_t pre_col[kMaxBatch + 1];
   int32_t pre_surf[kMaxBatch + 1];
-  int32_t pre_lcount[kMaxBatch + 1];
-  int32_t pre_lscan[kMaxBatch + 1];
   int32_t pre_lwrite[kMaxBatch + 1];
   int32_t surf_tile[kMaxBatch];    // 16, 32 or 64
   int32_t surf_tiles_y[kMaxBatch];
   int32_t surf_H[kMaxBatch];
   int32_t lw_by[kMaxBatch];
-  int32_t lut_groups[kMaxBatch];
   uint32_t nz_magic[kMaxBatch];
   int32_t last_is_lut[kMaxBatch];
 };
@@ -237,7 +245,7 @@ struct BatchTables {
 };
 
 struct BatchGrid {
-  int clear, rays, trace, col, surf, lcount, lwrite;  // persistent grid sizes
+  int clear, rays, trace, col, surf, lwrite;  // persistent grid sizes
   int fold;                                                   // maps x sensor-box fold blocks
   size_t surf_lds, lut_lds;
 };
@@ -262,8 +270,9 @@ hipError_t launch_rays(const InsertArgs& a, bool distinct, hipStream_t s);
 hipError_t launch_trace(const InsertArgs& a, bool distinct, hipStream_t s);
 hipError_t launch_column(const ColumnArgs& a, hipStream_t s);
 hipError_t launch_surface(const SurfaceArgs& a, int tile, hipStream_t s);  // tile 16, 32 or 64
-// counted: the column pass already wrote colpre / block_base for this state
-hipError_t launch_lut(const LutArgs& a, bool counted, hipStream_t s);
+// ranked: colpre, group_cnt and super_sum already hold this state's ranks;
+// otherwise they are made first
+hipError_t launch_lut(const LutArgs& a, bool ranked, hipStream_t s);
 hipError_t launch_import(const Dims& d, const int32_t* lut, const map_voxel_t* data,
                          int64_t n_data, int32_t* hits, int32_t* passes, int32_t* minqz,
                          unsigned long long* occ, int32_t origin_z, int32_t* err,

@@ -19,8 +19,9 @@ struct map_t {
   unsigned long long* occ;
   int32_t* hq;
   unsigned long long* defbits;  // pixels with a height (column pass to surface pass)
-  int32_t* block_base;
+  int32_t* group_cnt;
   int32_t* colpre;
+  int32_t* super_sum;
   unsigned long long* stats;  // 8 counters
   int32_t* err;
   int64_t* nocc;              // occupied-voxel count of a synchronous table export
@@ -44,9 +45,9 @@ struct map_t {
   // counters were summed into stats[0..3] (the per-block ones are not kept)
   bool last_static;
   int32_t prof_mask;          // profiled phases (bit p = phase p)
-  // the last 2D export left the table export's per-column ranks (colpre,
-  // block_base) for the current map state; any change of the map clears it
-  bool lut_counted;
+  // the last 2D export left the table export's ranks (colpre, group_cnt,
+  // super_sum) for the current map state; any change of the map clears it
+  bool ranked;
   // every voxel is empty and every occupancy word zero (a recentring then
   // needs no clears)
   bool empty;

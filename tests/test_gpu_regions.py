@@ -31,6 +31,8 @@ def _state(nx, ny, nz, seed, fill):
     (64, 48, 64, (5, 2, -31)),
     (66, 94, 96, (-35, 17, 40)),      # two occupancy words per column
     (30, 130, 128, (1, 1, 127)),      # the most levels
+    (514, 530, 4, (3, -9, 2)),        # 67 super groups of ranks
+    (1026, 1030, 2, (-513, 0, 1)),    # 258 of them: scanned first
 ])
 def test_region_kernels_match_oracle(nx, ny, nz, origin):
     import oracle
