@@ -153,12 +153,25 @@ bool move_window(map_t* m, const int32_t o[3], gvom::ClearArgs* plan) {
   for (int a = 0; a < 3; a++) m->origin[a] = o[a];
   set_ring(m);
   plan->d = m->d;
+  plan->nslab = 0;
+  plan->keep[0] = plan->keep[1] = ~0ull;
+  plan->pre[0] = 0;
+  // a box of storage range [s0, s1) along axis a (all of the other axes)
+  const auto add_box = [&](int a, int32_t s0, int32_t s1) {
+    int32_t* b = plan->box[plan->nbox];
+    for (int k = 0; k < 3; k++) {
+      b[2 * k] = k == a ? s0 : 0;
+      b[2 * k + 1] = k == a ? s1 : n[k];
+    }
+    const int64_t words = (int64_t)(((b[1] + 3) >> 2) - (b[0] >> 2)) *
+                          (((b[3] + 3) >> 2) - (b[2] >> 2)) * (b[5] - b[4]) * 4;
+    plan->pre[plan->nbox + 1] = plan->pre[plan->nbox] + (int32_t)words;
+    plan->nbox++;
+    if (a < 2) plan->nslab++;
+  };
   if (all) {
     m->last_cleared = n_vox(m);
-    int32_t* b = plan->box[0];
-    b[0] = 0; b[1] = n[0]; b[2] = 0; b[3] = n[1]; b[4] = 0; b[5] = n[2];
-    plan->keep[0][0] = plan->keep[0][1] = 0ull;
-    plan->nbox = 1;
+    add_box(0, 0, n[0]);
     return true;
   }
   int64_t keep = 1;
@@ -170,21 +183,16 @@ bool move_window(map_t* m, const int32_t o[3], gvom::ClearArgs* plan) {
     const int32_t s0 = delta[a] > 0 ? pos_mod((int64_t)n[a] - delta[a] + m->d.ro[a], n[a])
                                     : m->d.ro[a];
     const int32_t cnt = (int32_t)(delta[a] > 0 ? delta[a] : -delta[a]);
-    int32_t* b = plan->box[plan->nbox];
-    b[0] = 0; b[1] = n[0]; b[2] = 0; b[3] = n[1]; b[4] = 0; b[5] = n[2];
-    b[2 * a] = s0;
-    b[2 * a + 1] = cnt;
-    unsigned long long k0 = 0ull, k1 = 0ull;
+    // the range in one or, where it wraps, two pieces
+    const int32_t s1 = s0 + cnt < n[a] ? s0 + cnt : n[a];
+    add_box(a, s0, s1);
+    if (s0 + cnt > n[a]) add_box(a, 0, s0 + cnt - n[a]);
     if (a == 2) {
-      k0 = k1 = ~0ull;
       for (int j = 0; j < cnt; j++) {
         const int z = (s0 + j) % n[2];
-        if (z < 64) k0 &= ~(1ull << z); else k1 &= ~(1ull << (z - 64));
+        plan->keep[z >> 6] &= ~(1ull << (z & 63));
       }
     }
-    plan->keep[plan->nbox][0] = k0;
-    plan->keep[plan->nbox][1] = k1;
-    plan->nbox++;
   }
   return false;
 }
@@ -671,8 +679,11 @@ int32_t map_insert_scan(map_t* m, const float* xyz_dev, int64_t n, const float p
   const int pm0 = prof_begin(m, MAP_PROF_SCROLL);
   st = prepare_insert(m, xyz_dev, n, pose, flags, S, &a, &plan, &full);
   if (st) return st;
-  // an empty map moves its window without clearing anything
-  hipError_t e = m->empty ? hipSuccess : full ? clear_all(m) : gvom::launch_clear(plan, m->stream);
+  // an empty map moves its window without clearing anything; the slabs of a
+  // moved one are cleared beside the ray pass
+  hipError_t e = hipSuccess;
+  if (m->empty || full) plan.nbox = 0;
+  if (full && !m->empty) e = clear_all(m);
   if (n > 0) m->empty = false;
   prof_end(m, pm0);
   const bool distinct = (flags & MAP_STATS_DISTINCT) != 0;
@@ -685,9 +696,10 @@ int32_t map_insert_scan(map_t* m, const float* xyz_dev, int64_t n, const float p
     if (e == hipSuccess) e = hipMemsetAsync(m->touch, 0, words * 2 * 4, m->stream);
     a.touch = m->touch;
   }
+  if (e == hipSuccess && n == 0) e = gvom::launch_clear(plan, m->stream);
   if (e == hipSuccess && n > 0) {
     int pm = prof_begin(m, MAP_PROF_RAYS);
-    e = gvom::launch_rays(a, distinct, m->stream);
+    e = gvom::launch_rays(a, plan, m->stream);
     prof_end(m, pm);
     if (e == hipSuccess) {
       pm = prof_begin(m, MAP_PROF_TRACE);
@@ -724,12 +736,15 @@ int32_t map_insert_scan_static(map_t* m, const float* xyz_dev, int64_t n, const 
   if (st) return st;
   m->last_static = true;
   // kernels only (no memset, no allocation): callers may capture this call
-  hipError_t e = m->empty ? hipSuccess : full ? clear_all(m) : gvom::launch_clear(plan, m->stream);
+  hipError_t e = hipSuccess;
+  if (m->empty || full) plan.nbox = 0;
+  if (full && !m->empty) e = clear_all(m);
   if (n > 0) m->empty = false;
+  if (e == hipSuccess && n == 0) e = gvom::launch_clear(plan, m->stream);
   if (e == hipSuccess)
     e = gvom::launch_fill_i32((int32_t*)m->stats, 0, (int64_t)(kStatsBytes / 4), m->stream);
   if (e == hipSuccess && n > 0) {
-    e = gvom::launch_rays(a, false, m->stream);
+    e = gvom::launch_rays(a, plan, m->stream);
     if (e == hipSuccess) e = gvom::launch_trace(a, false, m->stream);
     if (e == hipSuccess) e = gvom::launch_sum_ray_parts(a.part_rays, ray_blocks, m->stats, m->stream);
   }
@@ -873,12 +888,12 @@ int32_t map_get_stats(map_t* m, map_stats_t* out) {
     c[0] += (int64_t)pr[4 * b + 0];
     c[1] += (int64_t)pr[4 * b + 1];
     c[2] += (int64_t)pr[4 * b + 2];
-    c[5] += (int64_t)pr[4 * b + 3];
   }
   for (int64_t b = 0; b < m->last_trace_blocks; b++) {
     c[3] += (int64_t)pt[4 * b + 0];
     c[4] += (int64_t)pt[4 * b + 1];
     c[6] += (int64_t)pt[4 * b + 2];
+    c[5] += (int64_t)pt[4 * b + 3];
   }
   out->n_points = m->last_points;
   out->n_nonfinite = c[0];
@@ -1023,7 +1038,8 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
     const int tiles = ((m->p.nx + tile - 1) / tile) * tiles_y;
     const int lw_by = (m->d.nby + 3) / 4;
     const int lw = ((m->p.nx + 3) / 4) * lw_by;
-    st.pre_rays[i + 1] = st.pre_rays[i] + (n[i] > 0 ? ray_blocks : 0);
+    st.ray_blocks[i] = n[i] > 0 ? ray_blocks : 0;
+    st.pre_rays[i + 1] = st.pre_rays[i] + st.ray_blocks[i] + gvom::clear_blocks(t->clr[i]);
     st.pre_trace[i + 1] = st.pre_trace[i] + t->ins[i].trace_blocks;
     st.pre_col[i + 1] = st.pre_col[i] + (int)((C + 255) / 256);
     st.pre_surf[i + 1] = st.pre_surf[i] + tiles;
@@ -1151,7 +1167,7 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
   const int cu = b->n_cu;
   // persistent grids; the bandwidth-bound column and table passes get eight
   // blocks per CU (the table pass's LDS regions allow it)
-  b->grid = gvom::BatchGrid{cu * 4, cu * 2, cu * 8, cu * 8, cu * 2, cu * 8,
+  b->grid = gvom::BatchGrid{cu * 4, cu * 8, cu * 8, cu * 2, cu * 8,
                             k * gvom::box_fold_blocks(), surf, lut};
   hipError_t e = gvom::dev_alloc((void**)&b->dtab, sizeof(gvom::BatchTables));
   if (e == hipSuccess) e = hipHostMalloc((void**)&b->htab, sizeof(gvom::BatchTables), 0);

@@ -68,8 +68,9 @@ struct InsertArgs {
   unsigned long long* occ;
   unsigned long long* stats;   // [8 global counters][kStripes segment counters]
   uint32_t* touch;             // distinct-voxel bitmaps [2][V/32] or null
-  unsigned long long* part_rays;   // per ray block: nonfinite, range, hits, distinct hits
-  unsigned long long* part_trace;  // per trace block: passes, distinct passes, updates, 0
+  unsigned long long* part_rays;   // per ray block: nonfinite, range, hits, 0
+  unsigned long long* part_trace;  // per trace block: passes, distinct passes, updates,
+                                   // distinct hits
   int4* rays;                  // per ray (ray-pass lane): {Qx, Qy, Qz, segments}
   int2* witems;                // wave items {ray wave, segment index}, per stripe
   int64_t stripe_off[kStripes];  // wave-item region of each stripe of ray blocks
@@ -203,15 +204,20 @@ struct CostArgs {
   float* cost;
 };
 
+// The slabs a moved window takes over (storage coordinates, cut where they
+// wrap), and which of every column's levels stay.
+constexpr int kClearBoxes = 6;
 struct ClearArgs {
   Dims d;
   int32_t* hits;
   int32_t* passes;
   int32_t* minqz;
   unsigned long long* occ;
-  int32_t nbox;
-  int32_t box[3][6];              // x0, cx, y0, cy, z0, cz (storage coordinates)
-  unsigned long long keep[3][2];  // occupancy bits kept in the box's columns
+  int32_t nbox;                        // 0: nothing to clear
+  int32_t box[kClearBoxes][6];         // [x0, x1) x [y0, y1) x [z0, z1)
+  int32_t pre[kClearBoxes + 1];        // words (16 bytes of passes) of the boxes before
+  int32_t nslab;                       // the boxes that span every level come first
+  unsigned long long keep[2];          // occupancy bits outside the z boxes
 };
 
 // ---- batches of maps ------------------------------------------------------
@@ -222,7 +228,8 @@ constexpr int kMaxBatch = 64;
 // launch constants.  Lives in device memory, uploaded once per step.
 struct BatchStep {
   int32_t nmaps;
-  int32_t pre_rays[kMaxBatch + 1];
+  int32_t pre_rays[kMaxBatch + 1];   // ray blocks and, after them, clear blocks
+  int32_t ray_blocks[kMaxBatch];
   int32_t pre_trace[kMaxBatch + 1];
   int32_t pre_col[kMaxBatch + 1];
   int32_t pre_surf[kMaxBatch + 1];
@@ -245,7 +252,7 @@ struct BatchTables {
 };
 
 struct BatchGrid {
-  int clear, rays, trace, col, surf, lwrite;  // persistent grid sizes
+  int rays, trace, col, surf, lwrite;  // persistent grid sizes
   int fold;                                                   // maps x sensor-box fold blocks
   size_t surf_lds, lut_lds;
 };
@@ -266,7 +273,11 @@ uint32_t nz_magic(int nz);
 
 // Launchers (all enqueue on `s`, return the launch status).
 hipError_t launch_clear(const ClearArgs& a, hipStream_t s);
-hipError_t launch_rays(const InsertArgs& a, bool distinct, hipStream_t s);
+// The ray pass and, beside it, the clears of the moved window (which nothing in
+// it touches).
+hipError_t launch_rays(const InsertArgs& a, const ClearArgs& c, hipStream_t s);
+// Blocks of kRayBlock threads that clear c's boxes.
+int clear_blocks(const ClearArgs& c);
 hipError_t launch_trace(const InsertArgs& a, bool distinct, hipStream_t s);
 hipError_t launch_column(const ColumnArgs& a, hipStream_t s);
 hipError_t launch_surface(const SurfaceArgs& a, int tile, hipStream_t s);  // tile 16, 32 or 64

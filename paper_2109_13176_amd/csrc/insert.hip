@@ -11,9 +11,15 @@ namespace {
 
 
 
-template <bool DISTINCT>
-__global__ __launch_bounds__(kRayBlock) void k_rays(InsertArgs a) {
-  rays_body<DISTINCT>(a, blockIdx.x);
+// Blocks [0, ray_blocks): the ray pass; the others clear the moved window.
+__global__ __launch_bounds__(kRayBlock) void k_rays(InsertArgs a, ClearArgs c, int ray_blocks) {
+  const int b = (int)blockIdx.x - ray_blocks;
+  if (b < 0) {
+    rays_body(a, blockIdx.x);
+  } else {
+    clear_body(c, (int64_t)b * kRayBlock + threadIdx.x,
+               (int64_t)((int)gridDim.x - ray_blocks) * kRayBlock);
+  }
 }
 
 template <bool DISTINCT>
@@ -28,8 +34,8 @@ __global__ __launch_bounds__(kBlock) void k_box_fold(InsertArgs a) {
   box_fold_body<DISTINCT>(a, blockIdx.x, blockIdx.y);
 }
 
-__global__ __launch_bounds__(kBlock) void k_clear(ClearArgs a) {
-  clear_body(a, (int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
+__global__ __launch_bounds__(kRayBlock) void k_clear(ClearArgs a) {
+  clear_body(a, (int64_t)blockIdx.x * kRayBlock + threadIdx.x, (int64_t)gridDim.x * kRayBlock);
 }
 
 // ---------------------------------------------------------------------------
@@ -44,24 +50,25 @@ __device__ __forceinline__ int find_map(const int32_t* pre, int n, int vb) {
   return lo;
 }
 
-__global__ __launch_bounds__(kBlock) void k_b_clear(const BatchTables* __restrict__ t,
-                                                    unsigned long long* stamps) {
-  const int n = t->st.nmaps;
-  const int64_t gid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  if (gid == 0) stamps[0] = wall_clock64();
-  constexpr int kWords = 8 + kStripes;
-  for (int64_t i = gid; i < (int64_t)n * kWords; i += stride) t->ins[i / kWords].stats[i % kWords] = 0;
-  for (int64_t i = gid; i < n; i += stride) stamps[1 + i] = 0;  // per-map completion maxima
-  for (int m = 0; m < n; m++) clear_body(t->clr[m], gid, stride);
-}
-
-__global__ __launch_bounds__(kRayBlock) void k_b_rays(const BatchTables* __restrict__ t) {
+__global__ __launch_bounds__(kRayBlock) void k_b_rays(const BatchTables* __restrict__ t,
+                                                      unsigned long long* stamps) {
   const int n = t->st.nmaps;
   const int total = t->st.pre_rays[n];
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) stamps[0] = wall_clock64();
+    // per-map completion maxima, taken by the last stages
+    for (int i = threadIdx.x; i < n; i += kRayBlock) stamps[1 + i] = 0;
+  }
   for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {
     const int m = find_map(t->st.pre_rays, n, vb);
-    rays_body<false>(t->ins[m], vb - t->st.pre_rays[m]);
+    const int b = vb - t->st.pre_rays[m], nr = t->st.ray_blocks[m];
+    if (b < nr) {
+      rays_body(t->ins[m], b);
+      __syncthreads();
+    } else {
+      const int nc = t->st.pre_rays[m + 1] - t->st.pre_rays[m] - nr;
+      clear_body(t->clr[m], (int64_t)(b - nr) * kRayBlock + threadIdx.x, (int64_t)nc * kRayBlock);
+    }
   }
 }
 
@@ -103,21 +110,23 @@ int grid_for(int64_t n) {
 
 }  // namespace
 
+int clear_blocks(const ClearArgs& c) {
+  if (c.nbox == 0) return 0;
+  // two words per thread: the blocks share the device with the ray pass, whose
+  // records the next kernel waits for
+  const int64_t g = ((int64_t)c.pre[c.nbox] + 2 * kRayBlock - 1) / (2 * kRayBlock);
+  return (int)(g < 1 ? 1 : g > 1024 ? 1024 : g);
+}
+
 hipError_t launch_clear(const ClearArgs& a, hipStream_t s) {
-  int64_t total = 0;
-  for (int k = 0; k < a.nbox; k++) {
-    const int64_t t = (int64_t)a.box[k][1] * a.box[k][3] * a.box[k][5];
-    total = t > total ? t : total;
-  }
-  if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_clear, dim3(grid_for(total)), dim3(kBlock), 0, s, a);
+  if (a.nbox == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_clear, dim3(clear_blocks(a)), dim3(kRayBlock), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_batch_insert(const BatchTables* tab, const BatchGrid& g,
                                unsigned long long* stamps, hipStream_t s) {
-  hipLaunchKernelGGL(k_b_clear, dim3(g.clear), dim3(kBlock), 0, s, tab, stamps);
-  hipLaunchKernelGGL(k_b_rays, dim3(g.rays), dim3(kRayBlock), 0, s, tab);
+  hipLaunchKernelGGL(k_b_rays, dim3(g.rays), dim3(kRayBlock), 0, s, tab, stamps);
   hipLaunchKernelGGL(k_b_trace, dim3(g.trace), dim3(kTraceBlock), 0, s, tab);
   hipLaunchKernelGGL(k_b_box_fold, dim3(g.fold), dim3(kBlock), 0, s, tab);
   return hipGetLastError();
@@ -135,13 +144,10 @@ int64_t max_segments(const Dims& d, int32_t seg_len) {
   return (m - 1) / seg_len + 1;
 }
 
-hipError_t launch_rays(const InsertArgs& a, bool distinct, hipStream_t s) {
-  if (a.n <= 0) return hipSuccess;
+hipError_t launch_rays(const InsertArgs& a, const ClearArgs& c, hipStream_t s) {
+  if (a.n <= 0) return launch_clear(c, s);
   const int g = (a.n + kRayBlock - 1) / kRayBlock;
-  if (distinct)
-    hipLaunchKernelGGL(k_rays<true>, dim3(g), dim3(kRayBlock), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_rays<false>, dim3(g), dim3(kRayBlock), 0, s, a);
+  hipLaunchKernelGGL(k_rays, dim3(g + clear_blocks(c)), dim3(kRayBlock), 0, s, a, c, g);
   return hipGetLastError();
 }
 

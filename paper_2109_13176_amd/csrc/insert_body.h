@@ -14,8 +14,11 @@ namespace {
 
 
 // ---------------------------------------------------------------------------
-// Pass 1, one lane per point: transform, record the return in its voxel, and
-// cut the ray into segments for the traversal pass.
+// Pass 1, one lane per point: transform, and cut the ray into segments for the
+// traversal pass.  It touches nothing of the map, so the clears of the moved
+// window run beside it (in a launch of their own before it they took 3-6 us, on
+// 1024 x 1024 x 96 34 us); the traversal pass records the returns.  With the
+// clears: 5.8 + 8.2 -> 7.1 us for 131,072 points on 512 x 512 x 64.
 //
 // A ray's voxel path is monotone in every axis.  Along its dominant axis (the
 // axis with the most voxel steps) the path is cut every seg_len voxels:
@@ -57,9 +60,8 @@ __device__ __forceinline__ int block_excl_scan(int v, int* wtot) {
   return x - v + wtot[wv];
 }
 
-template <bool DISTINCT>
 __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
-  __shared__ unsigned int wcount[kRayWaves][5];
+  __shared__ unsigned int wcount[kRayWaves][4];
   __shared__ unsigned long long wbase[kRayWaves];
   __shared__ int bin_pre[kSegBins * kRayWaves];  // [bin][wave]: count, then prefix
   __shared__ int wtot[kRayWaves];
@@ -69,11 +71,10 @@ __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
   const int32_t dims[3] = {a.d.nx, a.d.ny, a.d.nz};
   int32_t q[3];
   PointFlags pf;
-  const bool ray = point_pass<DISTINCT>(a, i, q, pf);
-  const HitReads hr = record_hit_issue(a, pf);  // completed after the block's returning atomic
-  const bool nonfinite = pf.nonfinite, outrange = pf.outrange, hit = pf.hit, dhit = pf.dhit;
+  const bool ray = point_pass(a, i, q, pf);
+  const bool nonfinite = pf.nonfinite, outrange = pf.outrange, hit = pf.hit;
 
-  int nseg = 0;
+  int nseg = 0;  // of a ray at least 1 (one that ends in the sensor's voxel has no steps)
   if (ray) {
     int32_t n[3];
 #pragma unroll
@@ -81,13 +82,11 @@ __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
       const int32_t sv = a.S[k] >> 16, ev = q[k] >> 16;
       n[k] = ev > sv ? ev - sv : sv - ev;
     }
-    if (n[0] + n[1] + n[2] > 0) {
-      const int dom = dominant_axis(n);
-      const int32_t Sd = sel3(dom, a.S[0], a.S[1], a.S[2]);
-      const int32_t lc = (Sd >> 16) - sel3(dom, a.O[0], a.O[1], a.O[2]);
-      const int32_t room = sel3(dom, q[0], q[1], q[2]) > Sd ? sel3(dom, dims[0], dims[1], dims[2]) - 1 - lc : lc;
-      nseg = min(sel3(dom, n[0], n[1], n[2]), room) / a.seg_len + 1;
-    }
+    const int dom = dominant_axis(n);
+    const int32_t Sd = sel3(dom, a.S[0], a.S[1], a.S[2]);
+    const int32_t lc = (Sd >> 16) - sel3(dom, a.O[0], a.O[1], a.O[2]);
+    const int32_t room = sel3(dom, q[0], q[1], q[2]) > Sd ? sel3(dom, dims[0], dims[1], dims[2]) - 1 - lc : lc;
+    nseg = min(sel3(dom, n[0], n[1], n[2]), room) / a.seg_len + 1;
   }
 
   // ---- stable counting sort of the block's rays by bin (most segments first)
@@ -120,24 +119,21 @@ __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
   const int c0 = __popcll(__ballot(nonfinite));
   const int c1 = __popcll(__ballot(outrange));
   const int c2 = __popcll(__ballot(hit));
-  const int c5 = DISTINCT ? __popcll(__ballot(dhit)) : 0;
   if (lane == 0) {
     wcount[wv][0] = maxseg;
     wcount[wv][1] = c0;
     wcount[wv][2] = c1;
     wcount[wv][3] = c2;
-    wcount[wv][4] = c5;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    unsigned long long sum = 0, s0 = 0, s1 = 0, s2 = 0, s5 = 0;
+    unsigned long long sum = 0, s0 = 0, s1 = 0, s2 = 0;
     for (int w = 0; w < kRayWaves; w++) {
       wbase[w] = sum;
       sum += wcount[w][0];
       s0 += wcount[w][1];
       s1 += wcount[w][2];
       s2 += wcount[w][3];
-      s5 += wcount[w][4];
     }
     // blocks are spread over kStripes counters, each with its own item region
     const int st = blk % kStripes;
@@ -147,18 +143,19 @@ __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
     pr[0] = s0;
     pr[1] = s1;
     pr[2] = s2;
-    pr[3] = s5;
+    pr[3] = 0;
   }
   __syncthreads();
-  record_hit_finish(a, pf, hr, q[2]);
   const int gw = blk * kRayWaves + wv;  // this group's rays: 64 gw .. 64 gw + 63
   const unsigned long long off = wbase[wv];
   for (int j = lane; j < maxseg; j += 64) a.witems[off + j] = make_int2(gw, j);
 }
 
 // ---------------------------------------------------------------------------
-// Pass 2, one lane per ray segment: walk the segment voxel by voxel and add
-// one pass to every window voxel before the ray's end voxel.
+// Pass 2: record the returns, one lane per ray, then, one lane per ray segment,
+// walk the segment voxel by voxel and add one pass to every window voxel before
+// the ray's end voxel.  (The returns' reads and atomics overlap the set-up of
+// the blocks' tables and the stripe counts' round trip.)
 //
 // Start voxel of segment j > 0: the instant the dominant axis enters cell
 // c = c_sensor +- j*seg_len, at exact time t = num / |D_dom|.  Another axis b
@@ -236,6 +233,10 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
                                            int32_t* box_cnt, WaveTable* wtab) {
   const int lane = __lane_id();
   WaveTable& wt = wtab[threadIdx.x >> 6];
+  const int64_t slots = ((int64_t)a.n + kRayBlock - 1) / kRayBlock * kRayBlock;  // ray records
+  const int slot0 = blk * NT + (int)threadIdx.x;
+  int4 ray0 = make_int4(0, 0, 0, 0);
+  if (slot0 < slots) ray0 = a.rays[slot0];
   wt.tag[lane] = kWtEmpty;
   for (int i = lane; i < kWtSlots * kWtStride; i += 64) wt.cnt[i] = 0;
   if (BOX) {
@@ -249,6 +250,8 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
   // (in registers it would cost the kernel its last wave per SIMD).
   __shared__ int64_t s_pre[kStripes + 1];
   __shared__ int64_t s_base[kStripes];  // stripe_off[t] - s_pre[t]
+  const Hit hit0 = find_hit(a, ray0);
+  const HitReads reads0 = record_hit_issue(a, hit0);
   if (threadIdx.x == 0) {
     int64_t p = 0;
 #pragma unroll
@@ -265,6 +268,15 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
   uint32_t* touch_p = DISTINCT ? a.touch + ((a.d.vs + 31) >> 5) : nullptr;
   int32_t* const passes = a.passes;  // kept in registers across the loop
   int n_pass = 0, n_dpass = 0, n_upd = 0;  // n_pass is wave-uniform
+  int n_dhit = 0;
+  record_hit_finish(a, hit0, reads0, ray0.z);
+  if (DISTINCT) n_dhit += distinct_hit(a, hit0);
+  for (int64_t i = (int64_t)slot0 + (int64_t)nblk * NT; i < slots; i += (int64_t)nblk * NT) {
+    const int4 r = a.rays[i];
+    const Hit h = find_hit(a, r);
+    record_hit_finish(a, h, record_hit_issue(a, h), r.z);
+    if (DISTINCT) n_dhit += distinct_hit(a, h);
+  }
 
   for (int64_t u = (int64_t)blk * (NT / 64) + (threadIdx.x >> 6); u < count; u += stride) {
     bool active = false, near = false;
@@ -423,27 +435,30 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
     }
   }
   // per-block counters, written without atomics (summed by the host)
-  __shared__ int wsum[NT / 64][3];
+  __shared__ int wsum[NT / 64][4];
   const int c3 = n_pass;
+  const int c5 = DISTINCT ? wave_sum(n_dhit) : 0;
   const int c4 = DISTINCT ? wave_sum(n_dpass) : 0;
   const int c6 = wave_sum(n_upd);
   if (lane == 0) {
     wsum[threadIdx.x >> 6][0] = c3;
     wsum[threadIdx.x >> 6][1] = c4;
     wsum[threadIdx.x >> 6][2] = c6;
+    wsum[threadIdx.x >> 6][3] = c5;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    unsigned long long p = 0, q = 0, u = 0;
+    unsigned long long p = 0, q = 0, u = 0, h = 0;
     for (int w = 0; w < NT / 64; w++) {
       p += wsum[w][0];
       q += wsum[w][1];
       u += wsum[w][2];
+      h += wsum[w][3];
     }
     a.part_trace[4 * blk] = p;
     a.part_trace[4 * blk + 1] = q;
     a.part_trace[4 * blk + 2] = u;
-    a.part_trace[4 * blk + 3] = 0;
+    a.part_trace[4 * blk + 3] = h;
   }
 }
 
@@ -510,62 +525,70 @@ __device__ __forceinline__ void box_fold_body(const InsertArgs& a, const int bx,
   }
 }
 
-// Window scroll: box k resets the storage voxels of
-// [x0, x0+cx) x [y0, y0+cy) x [z0, z0+cz) (each coordinate modulo the axis
-// size).  Occupancy: a box spanning all z (an x or y slab) zeroes the words
-// of its columns; a z slab (spanning all columns) clears its bits in every
-// column, where one thread combines all boxes of the column so that no two
-// threads update one word.
+// Window scroll.  (One voxel per thread, three arrays and eight integer
+// divisions for each, took 34 us for the slabs of a 1.2 m step on 1024 x 1024 x
+// 96.)  The boxes' passes are zeroed in 16-byte words (four voxels of
+// one brick row; words that reach past a box one voxel at a time); hits and
+// lowest returns only where the columns' occupancy words have a voxel, then
+// the words' bits.  The boxes of a column are combined by one thread, so that
+// no two threads update one word.
 __device__ __forceinline__ void clear_body(const ClearArgs& a, const int64_t first,
                                            const int64_t stride) {
   const Dims& d = a.d;
-  bool zslab = false;
-  for (int k = 0; k < a.nbox; k++) {
-    const int32_t* bx = a.box[k];
-    const uint32_t cx = bx[1], cy = bx[3], cz = bx[5];
-    zslab = zslab || (int)cz < d.nz;
-    const uint32_t total = cx * cy * cz;
-    for (int64_t i = first; i < total; i += stride) {
-      const uint32_t kz = (uint32_t)i % cz;
-      const uint32_t t = (uint32_t)i / cz;
-      const uint32_t ky = t % cy;
-      const uint32_t kx = t / cy;
-      const uint32_t sx = (bx[0] + kx) % (uint32_t)d.nx;
-      const uint32_t sy = (bx[2] + ky) % (uint32_t)d.ny;
-      const uint32_t sz = (bx[4] + kz) % (uint32_t)d.nz;
-      const uint32_t e = (uint32_t)col_base(d, sx, sy) + (sz << 4);
-      a.hits[e] = 0;
-      a.passes[e] = 0;
-      a.minqz[e] = INT32_MAX;
+  if (a.nbox == 0) return;
+  int k = 0;
+  for (int64_t i = first; i < a.pre[a.nbox]; i += stride) {
+    while (i >= a.pre[k + 1]) k++;
+    const int32_t* b = a.box[k];
+    // word (brick column bx, by, level z, brick row iy) of the box, in storage order
+    const uint32_t nby = (uint32_t)((b[3] + 3) >> 2) - (uint32_t)(b[2] >> 2);
+    const uint32_t nz = b[5] - b[4];
+    const uint32_t w = (uint32_t)(i - a.pre[k]), t = w >> 2, u = t / nz;
+    const int iy = w & 3, z = b[4] + (int)(t - u * nz);
+    const int bx = (b[0] >> 2) + (int)(u / nby), by = (b[2] >> 2) + (int)(u % nby);
+    const int sy = 4 * by + iy;
+    if (sy < b[2] || sy >= b[3]) continue;
+    int32_t* p = a.passes + col_base(d, 4 * bx, sy) + (z << 4);
+    if (4 * bx >= b[0] && 4 * bx + 3 < b[1]) {
+      *(int4*)p = make_int4(0, 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int ix = 0; ix < 4; ix++)
+        if (4 * bx + ix >= b[0] && 4 * bx + ix < b[1]) p[ix] = 0;
     }
   }
-  if (!zslab) {
-    for (int k = 0; k < a.nbox; k++) {
-      const int32_t* bx = a.box[k];
-      const uint32_t cx = bx[1], cy = bx[3];
-      for (int64_t i = first; i < (int64_t)cx * cy; i += stride) {
-        const uint32_t sx = (bx[0] + (uint32_t)i / cy) % (uint32_t)d.nx;
-        const uint32_t sy = (bx[2] + (uint32_t)i % cy) % (uint32_t)d.ny;
-        const uint32_t col = sx * d.ny + sy;
-        a.occ[(size_t)col * d.W] = 0;
-        if (d.W > 1) a.occ[(size_t)col * d.W + 1] = 0;
+  const auto clear_column = [&](int sx, int sy, unsigned long long k0, unsigned long long k1) {
+    unsigned long long* o = a.occ + ((int64_t)sx * d.ny + sy) * d.W;
+    const int32_t base = col_base(d, sx, sy);
+    for (int h = 0; h < d.W; h++) {
+      const unsigned long long keep = h ? k1 : k0, m = o[h];
+      unsigned long long gone = m & ~keep;
+      if (!gone) continue;
+      o[h] = m & keep;
+      while (gone) {
+        const int32_t e = base + ((64 * h + __ffsll((long long)gone) - 1) << 4);
+        gone &= gone - 1;
+        a.hits[e] = 0;
+        a.minqz[e] = INT32_MAX;
       }
     }
-  } else {
+  };
+  if (a.nslab < a.nbox) {  // some levels of every column go
     for (int64_t i = first; i < (int64_t)d.nx * d.ny; i += stride) {
-      const uint32_t sx = (uint32_t)i / d.ny, sy = (uint32_t)i % d.ny;
-      unsigned long long k0 = ~0ull, k1 = ~0ull;
-      for (int k = 0; k < a.nbox; k++) {
-        const int32_t* bx = a.box[k];
-        const uint32_t rx = (sx + d.nx - bx[0]) % (uint32_t)d.nx;
-        const uint32_t ry = (sy + d.ny - bx[2]) % (uint32_t)d.ny;
-        if (rx < (uint32_t)bx[1] && ry < (uint32_t)bx[3]) {
-          k0 &= a.keep[k][0];
-          k1 &= a.keep[k][1];
-        }
-      }
-      a.occ[(size_t)i * d.W] &= k0;
-      if (d.W > 1) a.occ[(size_t)i * d.W + 1] &= k1;
+      const int sx = (int)((uint32_t)i / (uint32_t)d.ny), sy = (int)((uint32_t)i % (uint32_t)d.ny);
+      bool all = false;
+      for (int j = 0; j < a.nslab; j++)
+        all |= sx >= a.box[j][0] && sx < a.box[j][1] && sy >= a.box[j][2] && sy < a.box[j][3];
+      clear_column(sx, sy, all ? 0ull : a.keep[0], all ? 0ull : a.keep[1]);
+    }
+  } else {
+    // (a column of two slabs is emptied by both: the same stores)
+    for (int j = 0; j < a.nslab; j++) {
+      const uint32_t cy = a.box[j][3] - a.box[j][2];
+      const int64_t cols = (int64_t)(a.box[j][1] - a.box[j][0]) * cy;
+      for (int64_t i = first; i < cols; i += stride)
+        clear_column(a.box[j][0] + (int)((uint32_t)i / cy), a.box[j][2] + (int)((uint32_t)i % cy),
+                     0ull, 0ull);
     }
   }
 }

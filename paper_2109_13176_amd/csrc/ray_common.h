@@ -34,19 +34,13 @@ __device__ __forceinline__ int dominant_axis(const int32_t n[3]) {
   return (n[1] > n[0]) ? (n[2] > n[1] ? 2 : 1) : (n[2] > n[0] ? 2 : 0);
 }
 
-// Transform of point i (in firing order) and its return: q = Q16 world
-// coordinates.  When the return lies in the window, f.hit is set and f.e /
-// f.ow / f.ob locate its voxel (storage index, occupancy word and bit); the
-// caller records the hit (record_hit_*).  Returns true when the ray can be
+// Transform of point i (in firing order): q = Q16 world coordinates; f.hit is
+// set when the return lies in the window.  Returns true when the ray can be
 // traversed.
 struct PointFlags {
-  bool nonfinite = false, outrange = false, hit = false, dhit = false;
-  int32_t e = 0;
-  int64_t ow = 0;
-  unsigned long long ob = 0;
+  bool nonfinite = false, outrange = false, hit = false;
 };
 
-template <bool DISTINCT>
 __device__ __forceinline__ bool point_pass(const InsertArgs& a, const int i, int32_t q[3],
                                            PointFlags& f) {
   q[0] = q[1] = q[2] = 0;
@@ -81,30 +75,40 @@ __device__ __forceinline__ bool point_pass(const InsertArgs& a, const int i, int
     f.outrange = true;
     return false;
   }
-  int32_t l[3];
-  bool win = true;
+  f.hit = true;
 #pragma unroll
   for (int k = 0; k < 3; k++) {
-    l[k] = (q[k] >> 16) - a.O[k];
-    win = win && l[k] >= 0 && l[k] < dims[k];
+    const int32_t l = (q[k] >> 16) - a.O[k];
+    f.hit = f.hit && l >= 0 && l < dims[k];
   }
-  if (win) {  // the return
+  return true;
+}
+
+// The return of ray record {q, segments} (segments 0: no ray): f.e / f.ow /
+// f.ob locate its voxel (storage index, occupancy word and bit).
+struct Hit {
+  bool on = false;
+  int32_t e = 0;
+  int64_t ow = 0;
+  unsigned long long ob = 0;
+};
+
+__device__ __forceinline__ Hit find_hit(const InsertArgs& a, const int4 ray) {
+  Hit f;
+  const int32_t dims[3] = {a.d.nx, a.d.ny, a.d.nz};
+  const int32_t l[3] = {(ray.x >> 16) - a.O[0], (ray.y >> 16) - a.O[1], (ray.z >> 16) - a.O[2]};
+  f.on = ray.w > 0;
+#pragma unroll
+  for (int k = 0; k < 3; k++) f.on = f.on && l[k] >= 0 && l[k] < dims[k];
+  if (f.on) {
     const int32_t ex = wrap_add(l[0] + a.d.ro[0], dims[0]);
     const int32_t ey = wrap_add(l[1] + a.d.ro[1], dims[1]);
     const int32_t ez = wrap_add(l[2] + a.d.ro[2], dims[2]);
-    const int32_t col = ex * dims[1] + ey;
-    const int32_t e = col_base(a.d, ex, ey) + (ez << 4);
-    f.e = e;
-    f.ow = (int64_t)col * a.d.W + (ez >> 6);
+    f.e = col_base(a.d, ex, ey) + (ez << 4);
+    f.ow = (int64_t)(ex * dims[1] + ey) * a.d.W + (ez >> 6);
     f.ob = 1ull << (ez & 63);
-    f.hit = true;
-    if (DISTINCT) {
-      const uint32_t bit = 1u << (e & 31);
-      const uint32_t old = atomicOr(&a.touch[(uint32_t)e >> 5], bit);
-      f.dhit = !(old & bit);
-    }
   }
-  return true;
+  return f;
 }
 
 // Recording a hit takes a count, a minimum and an or.  The minimum and the or
@@ -118,9 +122,9 @@ struct HitReads {
   unsigned long long ow = 0;
 };
 
-__device__ __forceinline__ HitReads record_hit_issue(const InsertArgs& a, const PointFlags& f) {
+__device__ __forceinline__ HitReads record_hit_issue(const InsertArgs& a, const Hit& f) {
   HitReads r;
-  if (f.hit) {
+  if (f.on) {
     r.mz = a.minqz[f.e];
     r.ow = a.occ[f.ow];
     atomicAdd(&a.hits[f.e], 1);
@@ -128,12 +132,19 @@ __device__ __forceinline__ HitReads record_hit_issue(const InsertArgs& a, const 
   return r;
 }
 
-__device__ __forceinline__ void record_hit_finish(const InsertArgs& a, const PointFlags& f,
+__device__ __forceinline__ void record_hit_finish(const InsertArgs& a, const Hit& f,
                                                   const HitReads& r, const int32_t qz) {
-  if (f.hit) {
+  if (f.on) {
     if (qz < r.mz) atomicMin(&a.minqz[f.e], qz);
     if (!(r.ow & f.ob)) atomicOr(&a.occ[f.ow], f.ob);
   }
+}
+
+// With distinct counting: whether the hit is the first in its voxel this insert.
+__device__ __forceinline__ int distinct_hit(const InsertArgs& a, const Hit& f) {
+  if (!f.on) return 0;
+  const uint32_t bit = 1u << (f.e & 31);
+  return !(atomicOr(&a.touch[(uint32_t)f.e >> 5], bit) & bit);
 }
 
 // Voxel at which the ray S -> q enters world cell c along axis dm (c is not

@@ -126,3 +126,45 @@ def test_fill_at_tile_edges(H, W):
     oh, orr = osgt.fill(pred, ph, pr, 0.04)
     assert np.array_equal(gh.cpu().numpy().view(np.uint32), oh.view(np.uint32))
     assert np.array_equal(gr.cpu().numpy().view(np.uint32), orr.view(np.uint32))
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(6, 10, 3), (18, 34, 41), (64, 48, 64), (66, 94, 96)])
+def test_scrolled_window_keeps_and_clears(nx, ny, nz):
+    """The window moved over a random map by every kind of step (slabs that wrap
+    in storage, that cut bricks, along one axis, all axes, past the window), with
+    and without points in the same call."""
+    import oracle
+    from paper_2109_13176_amd import gvom
+    p = dict(nx=nx, ny=ny, nz=nz, res_m=0.5, sensor_z_voxel=nz // 2, obs_min_m=0.5, obs_max_m=2.0,
+             dens_num=1, dens_den=2, fit_n=5, neg_thresh_m=0.5, neg_search_m=2.0)
+    rng = np.random.default_rng(nz)
+    m, o = gvom.VoxelMap(p), oracle.OracleMap(p)
+    V = nx * ny * nz
+    out = torch.zeros(V, dtype=torch.int32, device="cuda")
+    steps = [(0, 0, 0), (1, 0, 0), (0, -3, 0), (0, 0, 1), (-2, 1, 0), (nx // 2, -1, -nz // 2),
+             (3, ny - 1, 1), (-nx + 1, 2, -1), (nx + 5, 0, 0), (0, 0, nz - 1), (5, 4, -2)]
+    vox = np.array([0, 0, 0])
+    for k, d in enumerate(steps):
+        if k % 5 == 0:
+            lut, data = _state(nx, ny, nz, k + nx, 0.3)
+            org = vox - np.array([nx // 2, ny // 2, nz // 2])
+            org = org.astype(np.int32)
+            assert gvom.map_import_voxels(m.h, torch.from_numpy(lut).cuda(),
+                                          torch.from_numpy(data).cuda(), org) == 0
+            assert o.import_voxels(lut, data, org) == oracle.OK
+        vox = vox + np.array(d)
+        pose = np.eye(3, 4, dtype=np.float32)
+        pose[:, 3] = (vox + 0.5) * 0.5
+        pts = rng.uniform(-nx / 5, nx / 5, (0 if k & 1 else 700, 3)).astype(np.float32)
+        x = torch.from_numpy(pts).cuda() if len(pts) else None
+        assert gvom.map_insert_scan(m.h, x, pose.reshape(12), gvom.MAP_RECENTER) == 0
+        assert o.insert_scan(pts, pose.reshape(12), oracle.RECENTER) == oracle.OK
+        n_o = o.export_voxels()
+        back = torch.zeros((n_o[3] + 1, 3), dtype=torch.int32, device="cuda")
+        st, n, org_g = gvom.map_export_voxels(m.h, out, back)
+        assert st == 0 and n == n_o[3] and np.array_equal(org_g, n_o[4]), k
+        assert np.array_equal(out.cpu().numpy(), n_o[1].reshape(-1)), k
+        assert np.array_equal(back.cpu().numpy()[:n], np.asarray(n_o[2]).reshape(-1, 3)[:n]), k
+        assert m.stats()["n_cleared"] == o.stats()["n_cleared"], k
+    m.close()
+    o.close()
