@@ -279,11 +279,10 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
   }
 
   for (int64_t u = (int64_t)blk * (NT / 64) + (threadIdx.x >> 6); u < count; u += stride) {
-    bool active = false, near = false;
+    bool active = false, near = false, wraps = false;
     Walk w = {};
-    int32_t cnt[3] = {0, 0, 0};
-    bool stop[3] = {false, false, false};
-    int32_t sc[3] = {0, 0, 0};
+    // storage coordinates of the current voxel (sx, 4 sy, 16 sz), their steps
+    int32_t sc[3] = {0, 0, 0}, st[3] = {0, 0, 0};
     int32_t sidx = 0;
     {
       // last stripe t with s_pre[t] <= u (empty stripes share their prefix)
@@ -318,12 +317,17 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
         inside = inside && l[k] >= 0 && l[k] < dims[k];
       }
       if (inside) {
-        walk_init(a, q, v, l, w);
-        budget_init(w, dom, a.seg_len, cnt, stop);
+        int32_t most[3];
+        walk_init(a, q, v, l, sg, ad, dom, w, most);
 #pragma unroll
-        for (int k = 0; k < 3; k++) sc[k] = wrap_add(l[k] + a.d.ro[k], dims[k]);
-        sidx = col_base24(a.d, sc[0], sc[1]) + (sc[2] << 4);
-        active = (cnt[0] | cnt[1] | cnt[2]) != 0;
+        for (int k = 0; k < 3; k++) {
+          const int32_t s = wrap_add(l[k] + a.d.ro[k], dims[k]);
+          wraps |= sg[k] > 0 ? s + most[k] >= dims[k] : s < most[k];
+          sc[k] = s << (2 * k);
+          st[k] = sg[k] * (1 << (2 * k));
+        }
+        sidx = index24(a.d, sc[0], sc[1], sc[2]);
+        active = !walk_ended(w);
         if (BOX) {
           // the segment's dominant-axis cells (window-local) against the box's
           const int32_t c0 = sel3(dom, l[0], l[1], l[2]), c1 = c0 + sgd * (a.seg_len - 1);
@@ -336,10 +340,8 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
     // box lookups only in waves that can reach the box
     const bool wnear = BOX && __any(near);
 
-    // per-lane constants of the storage wrap
-    const bool px = w.sg[0] > 0, py = w.sg[1] > 0, pz = w.sg[2] > 0;
-    const int32_t trig0 = px ? nx : -1, trig1 = py ? ny : -1, trig2 = pz ? nz : -1;
-    const int32_t wv0 = px ? 0 : nx - 1, wv1 = py ? 0 : ny - 1, wv2 = pz ? 0 : nz - 1;
+    // the storage wrap only in waves where a walk can reach it
+    const bool wwrap = __any(wraps);
     int32_t cur_line = kWtEmpty;  // this lane's current line and its slot
     int cur_slot = -1;
     for (;;) {
@@ -352,8 +354,8 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
         if (BOX && wnear) {
           // storage offsets from the box's first cell (unsigned: wrapped)
           const uint32_t d0 = (uint32_t)wrap_add(sc[0] - a.box_s[0] + nx, nx);
-          const uint32_t d1 = (uint32_t)wrap_add(sc[1] - a.box_s[1] + ny, ny);
-          const uint32_t d2 = (uint32_t)wrap_add(sc[2] - a.box_s[2] + nz, nz);
+          const uint32_t d1 = (uint32_t)wrap_add((sc[1] >> 2) - a.box_s[1] + ny, ny);
+          const uint32_t d2 = (uint32_t)wrap_add((sc[2] >> 4) - a.box_s[2] + nz, nz);
           if (d0 < (uint32_t)a.box_e[0] && d1 < (uint32_t)a.box_e[1] && d2 < (uint32_t)a.box_e[2])
             bidx = (int)((d0 * kBoxXY + d1) * kBoxZ + d2);
         }
@@ -366,7 +368,8 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
             cur_slot = wt_lookup(wt, line);
           }
           if (cur_slot >= 0) {
-            atomicAdd(&wt.cnt[cur_slot * kWtStride + ((sidx & 15) >> 1)], 1u << ((sidx & 1) << 4));
+            // counter pair (sidx & 15) / 2, half sidx & 1 (a shift takes 5 bits)
+            atomicAdd(&wt.cnt[cur_slot * kWtStride + ((sidx & 15) >> 1)], 1u << ((sidx << 4) & 31));
           } else {
             n_upd++;
             atomicAdd(&passes[sidx], 1);
@@ -380,15 +383,17 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
       }
       // ---- step
       bool mx, my, mz;
-      const bool out = budget_step(w, cnt, stop, px, py, pz, mx, my, mz);
-      const int32_t t0 = sc[0] + (mx ? w.sg[0] : 0);
-      const int32_t t1 = sc[1] + (my ? w.sg[1] : 0);
-      const int32_t t2 = sc[2] + (mz ? w.sg[2] : 0);
-      sc[0] = t0 == trig0 ? wv0 : t0;
-      sc[1] = t1 == trig1 ? wv1 : t1;
-      sc[2] = t2 == trig2 ? wv2 : t2;
-      sidx = col_base24(a.d, sc[0], sc[1]) + (sc[2] << 4);
-      active = active & !out & ((cnt[0] | cnt[1] | cnt[2]) != 0);
+      walk_step(w, mx, my, mz);
+      sc[0] += mx ? st[0] : 0;
+      sc[1] += my ? st[1] : 0;
+      sc[2] += mz ? st[2] : 0;
+      if (wwrap) {
+        sc[0] = sc[0] < 0 ? nx - 1 : sc[0] == nx ? 0 : sc[0];
+        sc[1] = sc[1] < 0 ? 4 * (ny - 1) : sc[1] == 4 * ny ? 0 : sc[1];
+        sc[2] = sc[2] < 0 ? 16 * (nz - 1) : sc[2] == 16 * nz ? 0 : sc[2];
+      }
+      sidx = index24(a.d, sc[0], sc[1], sc[2]);
+      active = active & !walk_ended(w);
     }
     // ---- flush the wave's table: 16 lanes per claimed line
     wave_lds_sync();

@@ -190,116 +190,98 @@ __device__ __forceinline__ void entry_voxel(const int32_t S[3], const int32_t sg
   }
 }
 
-// Exact traversal state of one segment: remaining steps to the end voxel and
-// to the window edge per axis, and the crossing-time differences.
+// Exact traversal state of one segment: which axis crosses into its next cell
+// first, and the moves left.
 //
-// E_ab = num_a |D_b| - num_b |D_a| (num = distance from the sensor to the
-// next boundary along the axis, Q units) decides which axis crosses first.
-// It only changes by multiples of 2^16 (|D| << 16 per step), so its low 16
-// bits are fixed and f = floor(E / 2^16) carries the rest: E >= 0 iff
-// f >= 0, and E <= 0 iff f <= c with c = -1 when the low bits are not zero,
-// else 0.  While both axes still move, the next crossings lie within one
-// cell of the current point, so |E| <= 2^16 max(|D_a|, |D_b|) < 2^43 and f
-// fits in 32 bits (|D| < 2^27); f of a finished axis is never consulted.
+// Axis k crosses its next cell boundary at time num_k / |D_k| (num = distance
+// from the sensor to that boundary along the axis, Q units).  The order of two
+// axes is the sign of E_ab = num_a |D_b| - num_b |D_a|, which only changes by
+// multiples of 2^16 (|D| << 16 per step): its low 16 bits are fixed, and
+// floor(E / 2^16) carries the rest.  When several axes cross at one instant,
+// the axes moving up step first, together (the shared boundary belongs to the
+// upper cell), the axes moving down in the next step, together.  So a steps
+// (before or with b) iff E < 0, or E = 0 and not (a down and b up); b steps iff
+// E > 0, or E = 0 and not (a up and b down).  With f = floor(E / 2^16) - d,
+// d = 1 when a moves up, b down and the low bits are zero (E = 0 then has to
+// read as negative), and g = 1 when both move the same way and the low bits are
+// zero: a steps iff f < g, b steps iff f >= 0.
+//
+// The next boundary of every axis lies within one cell of the current point,
+// so |E| <= 2^16 max(|D_a|, |D_b|) < 2^43 and f fits in 32 bits; an axis without
+// motion counts as one cell away for ever (num = 2^16).  An axis that has
+// reached the end voxel's coordinate needs no check of its own: its next
+// crossing comes after the ray's end, at t > 1 (or, moving down with the end on
+// a boundary, at t = 1), while an axis with moves left crosses at t < 1 (moving
+// up, at t <= 1, which steps first in a tie).
+//
+// cnt: an axis whose moves to the end voxel reach the move that leaves the
+// window or the segment (the walk ends before that voxel) holds the moves
+// before that one, and ends the walk by going negative; any other axis holds
+// its moves to the end voxel, and they end the walk by all being zero, if no
+// axis of the first kind exists (thr: -1 with one, else 0).
 struct Walk {
-  int32_t rem[3], room[3], sg[3], ad[3];
-  int32_t fxy, fxz, fyz;
-  int32_t cxy, cxz, cyz;
+  int32_t fxy, fxz, fyz, gxy, gxz, gyz;
+  int32_t ad[3], cnt[3], thr;
 };
 
-__device__ __forceinline__ void split_e(int64_t e, int32_t& f, int32_t& c) {
-  f = (int32_t)(e >> 16);
-  c = (e & 0xFFFF) ? -1 : 0;
+__device__ __forceinline__ void pair_init(const int32_t num_a, const int32_t ad_a, const bool up_a,
+                                          const int32_t num_b, const int32_t ad_b, const bool up_b,
+                                          int32_t& f, int32_t& g) {
+  const int64_t e = (int64_t)num_a * ad_b - (int64_t)num_b * ad_a;
+  const bool exact = (e & 0xFFFF) == 0;
+  f = (int32_t)(e >> 16) - (exact & up_a & !up_b);
+  g = exact & (up_a == up_b);
 }
 
-// Starts the walk at world voxel v (inside the window, local l).
+__device__ __forceinline__ bool walk_ended(const Walk& w) {
+  return (w.cnt[0] | w.cnt[1] | w.cnt[2]) <= w.thr;
+}
+
+// Starts the walk of a ray to q at world voxel v (inside the window, local l).
+// sg, ad: signs and sizes of the ray's displacement.  most[k]: an upper bound
+// of the walk's moves along axis k (the dominant axis moves seg_len times at
+// most, another one no faster than twice as fast).
 __device__ __forceinline__ void walk_init(const InsertArgs& a, const int32_t q[3],
-                                          const int32_t v[3], const int32_t l[3], Walk& w) {
+                                          const int32_t v[3], const int32_t l[3],
+                                          const int32_t sg[3], const int32_t ad[3], const int dom,
+                                          Walk& w, int32_t most[3]) {
   const int32_t dims[3] = {a.d.nx, a.d.ny, a.d.nz};
   int32_t num[3];  // |num| < 2^28: v lies on the ray, which spans fewer than 2^11 cells
+  bool stopped = false;
 #pragma unroll
   for (int k = 0; k < 3; k++) {
     const int32_t ev = q[k] >> 16;
-    const int32_t dq = q[k] - a.S[k];
-    w.sg[k] = dq > 0 ? 1 : (dq < 0 ? -1 : 0);
-    w.ad[k] = dq < 0 ? -dq : dq;
-    w.rem[k] = ev > v[k] ? ev - v[k] : v[k] - ev;
-    w.room[k] = w.sg[k] > 0 ? dims[k] - 1 - l[k] : l[k];
+    const int32_t rem = ev > v[k] ? ev - v[k] : v[k] - ev;
+    int32_t T = (sg[k] > 0 ? dims[k] - 1 - l[k] : l[k]) + 1;  // the move that leaves the window
+    T = k == dom ? min(T, a.seg_len) : T;                     // or the segment
+    const bool stop = rem >= T;
+    stopped |= stop;
+    w.cnt[k] = stop ? T - 1 : rem;
+    w.ad[k] = ad[k];
+    most[k] = min(stop ? T : rem, 2 * a.seg_len + 2);
     const int32_t off = v[k] - (a.S[k] >> 16), fr = a.S[k] & 0xFFFF;
-    num[k] = w.sg[k] > 0 ? ((off + 1) << 16) - fr : fr - (off << 16);
+    num[k] = sg[k] > 0 ? ((off + 1) << 16) - fr : fr - (off << 16);
+    num[k] = sg[k] == 0 ? 1 << 16 : num[k];
   }
-  split_e((int64_t)num[0] * w.ad[1] - (int64_t)num[1] * w.ad[0], w.fxy, w.cxy);
-  split_e((int64_t)num[0] * w.ad[2] - (int64_t)num[2] * w.ad[0], w.fxz, w.cxz);
-  split_e((int64_t)num[1] * w.ad[2] - (int64_t)num[2] * w.ad[1], w.fyz, w.cyz);
+  w.thr = stopped ? -1 : 0;
+  pair_init(num[0], ad[0], sg[0] > 0, num[1], ad[1], sg[1] > 0, w.fxy, w.gxy);
+  pair_init(num[0], ad[0], sg[0] > 0, num[2], ad[2], sg[2] > 0, w.fxz, w.gxz);
+  pair_init(num[1], ad[1], sg[1] > 0, num[2], ad[2], sg[2] > 0, w.fyz, w.gyz);
 }
 
-// One step: the axes with the smallest crossing time move; when several
-// share it, the axes moving up step first (the shared boundary belongs to
-// the upper cell) and the axes moving down in the next step.  Sets mx/my/mz
-// and returns whether a moving axis left the window.
-__device__ __forceinline__ bool walk_step(Walk& w, bool& mx, bool& my, bool& mz) {
-  const bool ax = w.rem[0] > 0, ay = w.rem[1] > 0, az = w.rem[2] > 0;
-  const bool px = w.sg[0] > 0, py = w.sg[1] > 0, pz = w.sg[2] > 0;
-  mx = ax & (!ay | (w.fxy <= w.cxy)) & (!az | (w.fxz <= w.cxz));
-  my = ay & (!ax | (w.fxy >= 0)) & (!az | (w.fyz <= w.cyz));
-  mz = az & (!ax | (w.fxz >= 0)) & (!ay | (w.fyz >= 0));
-  const bool up = (mx & px) | (my & py) | (mz & pz);
-  mx = mx & (!up | px);
-  my = my & (!up | py);
-  mz = mz & (!up | pz);
-  const bool out = (mx & (w.room[0] == 0)) | (my & (w.room[1] == 0)) | (mz & (w.room[2] == 0));
-  w.rem[0] -= mx;
-  w.rem[1] -= my;
-  w.rem[2] -= mz;
-  w.room[0] -= mx;
-  w.room[1] -= my;
-  w.room[2] -= mz;
-  // wrapping unsigned adds: f of an axis that no longer moves may drift
-  w.fxy = (int32_t)((uint32_t)w.fxy + (mx ? (uint32_t)w.ad[1] : 0u) - (my ? (uint32_t)w.ad[0] : 0u));
-  w.fxz = (int32_t)((uint32_t)w.fxz + (mx ? (uint32_t)w.ad[2] : 0u) - (mz ? (uint32_t)w.ad[0] : 0u));
-  w.fyz = (int32_t)((uint32_t)w.fyz + (my ? (uint32_t)w.ad[2] : 0u) - (mz ? (uint32_t)w.ad[1] : 0u));
-  return out;
-}
-
-// Budgeted stepping for the segmented traversal.  cnt[k] = moves left along
-// axis k before it either reaches the end voxel's coordinate (the axis stops
-// moving) or, when stop[k], makes the move that leaves the window or the
-// segment (the walk ends before that voxel).  While the walk is on,
-// cnt[k] > 0 iff the axis still has steps to the end voxel, so the axis
-// choice is the one of walk_step.
-__device__ __forceinline__ void budget_init(const Walk& w, const int dom, const int32_t seg_len,
-                                            int32_t cnt[3], bool stop[3]) {
-#pragma unroll
-  for (int k = 0; k < 3; k++) {
-    int32_t T = w.room[k] + 1;                   // the move that leaves the window
-    if (k == dom && seg_len < T) T = seg_len;    // the move that leaves the segment
-    stop[k] = w.rem[k] >= T;
-    cnt[k] = stop[k] ? T : w.rem[k];
-  }
-}
-
-// One step of walk_step's rule under the budgets; returns whether the walk
-// ends (a stopping axis spent its budget).
-__device__ __forceinline__ bool budget_step(Walk& w, int32_t cnt[3], const bool stop[3],
-                                            const bool px, const bool py, const bool pz,
-                                            bool& mx, bool& my, bool& mz) {
-  const bool ax = cnt[0] > 0, ay = cnt[1] > 0, az = cnt[2] > 0;
-  mx = ax & (!ay | (w.fxy <= w.cxy)) & (!az | (w.fxz <= w.cxz));
-  my = ay & (!ax | (w.fxy >= 0)) & (!az | (w.fyz <= w.cyz));
-  mz = az & (!ax | (w.fxz >= 0)) & (!ay | (w.fyz >= 0));
-  const bool up = (mx & px) | (my & py) | (mz & pz);
-  mx = mx & (!up | px);
-  my = my & (!up | py);
-  mz = mz & (!up | pz);
-  cnt[0] -= mx;
-  cnt[1] -= my;
-  cnt[2] -= mz;
-  const bool out = (mx & stop[0] & (cnt[0] == 0)) | (my & stop[1] & (cnt[1] == 0)) |
-                   (mz & stop[2] & (cnt[2] == 0));
-  w.fxy = (int32_t)((uint32_t)w.fxy + (mx ? (uint32_t)w.ad[1] : 0u) - (my ? (uint32_t)w.ad[0] : 0u));
-  w.fxz = (int32_t)((uint32_t)w.fxz + (mx ? (uint32_t)w.ad[2] : 0u) - (mz ? (uint32_t)w.ad[0] : 0u));
-  w.fyz = (int32_t)((uint32_t)w.fyz + (my ? (uint32_t)w.ad[2] : 0u) - (mz ? (uint32_t)w.ad[1] : 0u));
-  return out;
+// One step: sets which axes move; the walk has ended when walk_ended() after it.
+__device__ __forceinline__ void walk_step(Walk& w, bool& mx, bool& my, bool& mz) {
+  mx = (w.fxy < w.gxy) & (w.fxz < w.gxz);
+  my = (w.fxy >= 0) & (w.fyz < w.gyz);
+  mz = (w.fxz >= 0) & (w.fyz >= 0);
+  w.cnt[0] -= mx;
+  w.cnt[1] -= my;
+  w.cnt[2] -= mz;
+  // unsigned adds: a walk that has ended may drift on until its wave's end
+  const uint32_t a0 = (uint32_t)w.ad[0], a1 = (uint32_t)w.ad[1], a2 = (uint32_t)w.ad[2];
+  w.fxy = (int32_t)((uint32_t)w.fxy + (mx ? a1 : 0u) + (my ? 0u - a0 : 0u));
+  w.fxz = (int32_t)((uint32_t)w.fxz + (mx ? a2 : 0u) + (mz ? 0u - a0 : 0u));
+  w.fyz = (int32_t)((uint32_t)w.fyz + (my ? a2 : 0u) + (mz ? 0u - a1 : 0u));
 }
 
 // a * b + c on the 24-bit multiplier (operands below 2^24; b uniform across
@@ -312,12 +294,14 @@ __device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) 
   return r;
 }
 
-// col_base with 24-bit multiplies: brick coordinates < 2^11, nby <= 2048
-// and 16 nz <= 2048 keep every operand within 24 bits, and the index is
-// below 2^31 for every map the library accepts.
-__device__ __forceinline__ int32_t col_base24(const Dims& d, int32_t sx, int32_t sy) {
-  const uint32_t b = mad_u24((uint32_t)(sx >> 2), (uint32_t)d.nby, (uint32_t)(sy >> 2));
-  return (int32_t)mad_u24(b, (uint32_t)d.nz << 4, (uint32_t)(((sy & 3) << 2) | (sx & 3)));
+// Storage index of voxel (sx, sy, sz) from sx, 4 sy and 16 sz, with 24-bit
+// multiplies: brick coordinates < 2^11, nby <= 2048 and 16 nz <= 2048 keep every
+// operand within 24 bits, and the index is below 2^31 for every map the library
+// accepts.
+__device__ __forceinline__ int32_t index24(const Dims& d, int32_t sx, int32_t sy4, int32_t sz16) {
+  const uint32_t b = mad_u24((uint32_t)(sx >> 2), (uint32_t)d.nby, (uint32_t)(sy4 >> 4));
+  const uint32_t low = (((uint32_t)sx & 3u) | ((uint32_t)sy4 & 12u)) | (uint32_t)sz16;
+  return (int32_t)mad_u24(b, (uint32_t)d.nz << 4, low);
 }
 
 }  // namespace
