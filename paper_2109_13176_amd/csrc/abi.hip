@@ -450,16 +450,8 @@ bool grow(map_t* m, T** p, int64_t* cap, int64_t need, size_t elem) {
 // that stripe's waves can reserve (each wave at most one item per segment
 // its longest ray can have).  *need = wave items in all.
 void insert_layout(const map_t* m, int64_t ray_blocks, gvom::InsertArgs* a, int64_t* need) {
-  const int64_t per_ray = gvom::max_segments(m->d, m->seg_len);
-  int64_t tot = 0;
-  for (int t = 0; t < gvom::kStripes; t++) {
-    const int64_t blocks =
-        ray_blocks > t ? (ray_blocks - t + gvom::kStripes - 1) / gvom::kStripes : 0;
-    a->stripe_off[t] = tot;
-    a->stripe_cap[t] = blocks * (gvom::kRayBlock / 64) * per_ray;
-    tot += a->stripe_cap[t];
-  }
-  *need = tot;
+  a->block_items = (gvom::kRayBlock / 64) * gvom::max_segments(m->d, m->seg_len);
+  *need = ray_blocks * a->block_items;
 }
 
 // Everything of an insert but the per-scan buffers (a->rays, a->witems,
@@ -512,13 +504,16 @@ int32_t fill_insert(map_t* m, const float* xyz_dev, int64_t n, const float* pose
   // window cells centred on the sensor's voxel, moved inside the window
   const int32_t ext[3] = {gvom::kBoxXY, gvom::kBoxXY, gvom::kBoxZ};
   const int32_t dims[3] = {m->d.nx, m->d.ny, m->d.nz};
+  a->box_far = 0;
   for (int k = 0; k < 3; k++) {
     const int32_t e = ext[k] < dims[k] ? ext[k] : dims[k];
     int64_t lo = (int64_t)(S[k] >> 16) - m->origin[k] - ext[k] / 2;
     if (lo > dims[k] - e) lo = dims[k] - e;
     if (lo < 0) lo = 0;
     a->box_e[k] = e;
-    a->box_l[k] = (int32_t)lo;
+    const int64_t l = (int64_t)(S[k] >> 16) - m->origin[k];
+    const int64_t far = l - lo > lo + e - 1 - l ? l - lo : lo + e - 1 - l;
+    if (far > a->box_far) a->box_far = (int32_t)far;
     a->box_s[k] = (int32_t)((lo + m->d.ro[k]) % dims[k]);
   }
   a->box_rep = m->box_rep;

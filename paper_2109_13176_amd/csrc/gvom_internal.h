@@ -39,7 +39,7 @@ __host__ __device__ __forceinline__ int32_t col_base(const Dims& d, int32_t sx, 
 }
 
 constexpr int kStripes = 16;  // independent segment counters of the ray pass
-static_assert((kStripes & (kStripes - 1)) == 0, "the traversal binary-searches the stripes");
+static_assert(kStripes == 16, "the traversal scans the stripes in one row of lanes");
 
 // Sensor box of the segmented traversal: every ray starts in the sensor's
 // voxel, so the cells around it take the passes of thousands of waves and
@@ -71,10 +71,9 @@ struct InsertArgs {
   unsigned long long* part_rays;   // per ray block: nonfinite, range, hits, 0
   unsigned long long* part_trace;  // per trace block: passes, distinct passes, updates,
                                    // distinct hits
-  int4* rays;                  // per ray (ray-pass lane): {Qx, Qy, Qz, segments}
+  int4* rays;                  // per ray (ray-pass lane): {Qx, Qy, Qz, 4 segments + dominant axis}
   int2* witems;                // wave items {ray wave, segment index}, per stripe
-  int64_t stripe_off[kStripes];  // wave-item region of each stripe of ray blocks
-  int64_t stripe_cap[kStripes];
+  int64_t block_items;         // wave items one ray block has room for
   int32_t seg_len;             // dominant-axis voxels per segment
   int32_t trace_blocks;        // grid of the trace kernel (kTraceBlock threads per block
                                // for a single map, 256 in a batch)
@@ -83,7 +82,7 @@ struct InsertArgs {
   // (dx * kBoxXY + dy) * kBoxZ + dz
   int32_t box_s[3];
   int32_t box_e[3];
-  int32_t box_l[3];            // window-local coordinate of the box's first cell
+  int32_t box_far;             // most voxels along an axis from the sensor to a box cell
   int32_t* box_rep;            // [kBoxReps][kBoxCells], zero between inserts
 };
 

@@ -6,6 +6,8 @@
 #pragma once
 #include <math.h>
 
+#include <type_traits>
+
 #include "ray_common.h"
 
 namespace gvom {
@@ -28,7 +30,7 @@ namespace {
 //
 // The block then regroups its rays by segment count (most first; rays of
 // equal count keep their order, so neighbouring rays stay together) and
-// writes their records {Q, segments} in that order: a traversal wave holds
+// writes their records {Q, 4 segments + dominant axis} in that order: a traversal wave holds
 // segment j of 64 rays that all have it, instead of 64 neighbouring rays of
 // which the short ones ended long before j.  Each group of 64 records with at
 // most s segments publishes s wave items {group, j}.
@@ -60,6 +62,14 @@ __device__ __forceinline__ int block_excl_scan(int v, int* wtot) {
   return x - v + wtot[wv];
 }
 
+// First wave item of stripe t: the ray blocks t, t + kStripes, ... of the stripes
+// before it have room for block_items each.
+__device__ __forceinline__ int64_t stripe_off(const InsertArgs& a, const int t) {
+  const uint32_t blocks = ((uint32_t)a.n + kRayBlock - 1) / kRayBlock;
+  const uint32_t some = blocks % kStripes;
+  return (int64_t)a.block_items * ((uint32_t)t * (blocks / kStripes) + ((uint32_t)t < some ? t : some));
+}
+
 __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
   __shared__ unsigned int wcount[kRayWaves][4];
   __shared__ unsigned long long wbase[kRayWaves];
@@ -75,6 +85,7 @@ __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
   const bool nonfinite = pf.nonfinite, outrange = pf.outrange, hit = pf.hit;
 
   int nseg = 0;  // of a ray at least 1 (one that ends in the sensor's voxel has no steps)
+  int axis = 0;  // its dominant axis
   if (ray) {
     int32_t n[3];
 #pragma unroll
@@ -87,6 +98,7 @@ __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
     const int32_t lc = (Sd >> 16) - sel3(dom, a.O[0], a.O[1], a.O[2]);
     const int32_t room = sel3(dom, q[0], q[1], q[2]) > Sd ? sel3(dom, dims[0], dims[1], dims[2]) - 1 - lc : lc;
     nseg = min(sel3(dom, n[0], n[1], n[2]), room) / a.seg_len + 1;
+    axis = dom;
   }
 
   // ---- stable counting sort of the block's rays by bin (most segments first)
@@ -106,14 +118,14 @@ __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
   const int pre = block_excl_scan(bin_pre[threadIdx.x], wtot);
   bin_pre[threadIdx.x] = pre;  // every thread read its entry before the scan's barriers
   __syncthreads();
-  srec[bin_pre[bin * kRayWaves + wv] + rank] = make_int4(q[0], q[1], q[2], nseg);
+  srec[bin_pre[bin * kRayWaves + wv] + rank] = make_int4(q[0], q[1], q[2], nseg << 2 | axis);
   __syncthreads();
   const int4 rec = srec[threadIdx.x];
   a.rays[i] = rec;
 
   // ---- reserve the wave items: one returning atomic per block, group bases
   // from the block's prefix
-  int maxseg = rec.w;
+  int maxseg = rec.w >> 2;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) maxseg = max(maxseg, __shfl_xor(maxseg, o));
   const int c0 = __popcll(__ballot(nonfinite));
@@ -138,7 +150,7 @@ __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
     // blocks are spread over kStripes counters, each with its own item region
     const int st = blk % kStripes;
     const unsigned long long b = sum ? atomicAdd(&a.stats[8 + st], sum) : 0ull;
-    for (int w = 0; w < kRayWaves; w++) wbase[w] += b + a.stripe_off[st];
+    for (int w = 0; w < kRayWaves; w++) wbase[w] += b + stripe_off(a, st);
     unsigned long long* pr = a.part_rays + 4 * (size_t)blk;
     pr[0] = s0;
     pr[1] = s1;
@@ -152,6 +164,27 @@ __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
 }
 
 // ---------------------------------------------------------------------------
+// Inclusive prefix sums over the first kStripes = 16 lanes (one DPP row).
+__device__ __forceinline__ int64_t stripe_scan(int64_t v) {
+  const auto add = [&](auto c) {
+    constexpr int kRowShr = decltype(c)::value;
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)v, kRowShr, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), kRowShr, 0xf, 0xf, true);
+    v += (int64_t)((uint64_t)hi << 32 | lo);
+  };
+  add(std::integral_constant<int, 0x111>());
+  add(std::integral_constant<int, 0x112>());
+  add(std::integral_constant<int, 0x114>());
+  add(std::integral_constant<int, 0x118>());
+  return v;
+}
+
+__device__ __forceinline__ int64_t read_lane64(const int64_t v, const int lane) {
+  const uint32_t lo = __builtin_amdgcn_readlane((int)v, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(v >> 32), lane);
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
 // Pass 2: record the returns, one lane per ray, then, one lane per ray segment,
 // walk the segment voxel by voxel and add one pass to every window voxel before
 // the ray's end voxel.  (The returns' reads and atomics overlap the set-up of
@@ -177,12 +210,13 @@ __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
 // (about 15 on the 64-beam workload, against about 60 line requests when
 // every step adds its voxels straight to the map).  So each wave counts its
 // item in a private LDS line table: kWtSlots slots of one 64-byte storage
-// line each (16 counters of 16 bits, two per word: a voxel takes at most one
+// line each (16 counters of 8 bits, four per word: a voxel takes at most one
 // pass per lane of the item, so a counter stays below 65 while it is in the
 // table; and a tag = storage index >> 4), found by a hash of
-// the line with kWtProbe linear probes and claimed by compare-and-swap; a lane
-// remembers the slot of its current line, so it looks up only when its ray
-// enters another line.  When the item is done the wave adds every non-zero
+// the line with up to kWtProbe more probes and claimed by compare-and-swap.  A step
+// reads one tag, that of its lane's slot or, on another line, of the line's home
+// slot, and moves to the next voxel before it looks at it; only lanes that find
+// another line there search.  When the item is done the wave adds every non-zero
 // counter of its claimed slots to the map, 16 lanes per line (one line request
 // per line), and empties the table.  A line that finds no slot on its probe
 // path is added to the map directly.  With BOX, voxels in the sensor box add
@@ -190,14 +224,21 @@ __device__ __forceinline__ void rays_body(const InsertArgs& a, const int blk) {
 // its replica at the end (k_box_fold adds the replicas into the map).  Every
 // pass ends up in exactly one counter that reaches the map once, so the
 // result is the same integer sum whatever the claim order.
+//
+// On 512 x 512 x 64 with 131,072 points (150,000 steps of 11,000 items) the vector
+// instructions of a step (65) and an item's set-up (290) fill most of the kernel's
+// time; on 128 x 128 x 32 with 28,800 points, with one wave per SIMD, the chain of
+// LDS and memory round trips does.  With 16-bit counters, a search at every change
+// of line, coordinates, wraps and move counts in registers of their own, the stripes
+// searched in LDS and a set-up by divisions: 46.4 and 19.8 us, now 43.1 and 16.0.
 constexpr int kWtSlots = 64;     // slots per wave (one per lane at the flush)
-constexpr int kWtStride = 9;     // LDS words per slot: 8 counter pairs + 1 (bank spread)
+constexpr int kWtStride = 5;     // LDS words per slot: tag and 4 words of 4 counters
 constexpr int kWtProbe = 4;
 constexpr int32_t kWtEmpty = -1;
 
+
 struct WaveTable {
-  int32_t tag[kWtSlots];
-  uint32_t cnt[kWtSlots * kWtStride];
+  uint32_t slot[(kWtSlots + 1) * kWtStride];  // {tag, 4 words of counters}; the last: see wt_claim
   int32_t lst[kWtSlots];
 };
 
@@ -208,23 +249,36 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Slot of storage line `line` in the wave's table, claiming an empty one on
-// its probe path; -1 when the path holds other lines only.  The first slot
-// is a multiplicative (Fibonacci) hash of the line's low 24 bits: the top six
-// bits of their product with 2^24 / golden ratio (Knuth, TAOCP vol. 3,
+// Byte offset in the block's tables (this wave's begins at `base`) of the slot where the search for storage line
+// `line` begins: a multiplicative (Fibonacci) hash of the line's low 24 bits, the
+// top six bits of their product with 2^24 / golden ratio (Knuth, TAOCP vol. 3,
 // 6.4), one 24-bit multiply.  Tags hold the whole line, so lines that share
 // low bits only share a probe path.
-__device__ __forceinline__ int wt_lookup(WaveTable& wt, const int32_t line) {
-  const uint32_t h = mad_u24((uint32_t)line & 0xFFFFFFu, 0x9E3779u, 0u);
-  const int s0 = (int)(h >> 26);
-#pragma unroll
-  for (int p = 0; p < kWtProbe; p++) {
-    const int s = (s0 + p) & (kWtSlots - 1);
-    int32_t t = wt.tag[s];
-    if (t == kWtEmpty) t = atomicCAS(&wt.tag[s], kWtEmpty, line);
-    if (t == kWtEmpty || t == line) return s;
+__device__ __forceinline__ uint32_t wt_home(const int32_t line, const uint32_t base) {
+  const uint32_t h = (uint32_t)__umul24((uint32_t)line, 0x9E3779u) >> 26;
+  return (uint32_t)__umul24(h, 4 * kWtStride) + base;
+}
+
+__device__ __forceinline__ uint32_t* wt_word(WaveTable* wtab, const uint32_t at) {
+  return (uint32_t*)((char*)wtab + at);
+}
+
+constexpr uint32_t kWtLast = 4 * kWtStride * (kWtSlots - 1);  // offset of the last slot
+
+// The slot of `line` whose home slot `at` holds the tag t, not that line: claims
+// an empty slot or finds the line's on the rest of its probe path, one
+// compare-and-swap per probe.  When the path holds other lines only, the slot
+// behind the table, which nothing reads and no line is found in.
+__device__ __forceinline__ uint32_t wt_claim(WaveTable* wtab, const uint32_t base,
+                                             const int32_t line, uint32_t at, const int32_t t) {
+  const auto next = [&](uint32_t x) { return x == base + kWtLast ? base : x + 4u * kWtStride; };
+  if (t != kWtEmpty) at = next(at);
+  for (int p = 0;;) {
+    const int32_t o = (int32_t)atomicCAS(wt_word(wtab, at), (uint32_t)kWtEmpty, (uint32_t)line);
+    if (o == kWtEmpty || o == line) return at;
+    if (++p == kWtProbe) return base + kWtLast + 4u * kWtStride;
+    at = next(at);
   }
-  return -1;
 }
 
 // box_cnt[kBoxCells] and wtab[NT / 64] are the block's LDS (the caller's).
@@ -232,42 +286,45 @@ template <bool DISTINCT, bool BOX, int NT>
 __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, const int nblk,
                                            int32_t* box_cnt, WaveTable* wtab) {
   const int lane = __lane_id();
-  WaveTable& wt = wtab[threadIdx.x >> 6];
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  WaveTable& wt = wtab[wave];
+  const uint32_t base = (uint32_t)(wave * sizeof(WaveTable));
   const int64_t slots = ((int64_t)a.n + kRayBlock - 1) / kRayBlock * kRayBlock;  // ray records
   const int slot0 = blk * NT + (int)threadIdx.x;
   int4 ray0 = make_int4(0, 0, 0, 0);
+  unsigned long long cnt0 = 0;  // items of stripe `lane`
+  if (lane < kStripes) cnt0 = a.stats[8 + lane];
   if (slot0 < slots) ray0 = a.rays[slot0];
-  wt.tag[lane] = kWtEmpty;
-  for (int i = lane; i < kWtSlots * kWtStride; i += 64) wt.cnt[i] = 0;
+  for (int i = lane; i < kWtSlots * kWtStride; i += 64) wt.slot[i] = 0;
+  wave_lds_sync();
+  wt.slot[lane * kWtStride] = (uint32_t)kWtEmpty;
   if (BOX) {
     for (int i = threadIdx.x; i < kBoxCells; i += NT) box_cnt[i] = 0;
   }
-  __syncthreads();
   const int nx = a.d.nx, ny = a.d.ny, nz = a.d.nz;
   const int32_t dims[3] = {nx, ny, nz};
-  // wave items of stripe t occupy [stripe_off[t], stripe_off[t] + cnt[t]); the
-  // loop runs over their concatenation.  The stripe prefix lives in LDS
-  // (in registers it would cost the kernel its last wave per SIMD).
-  __shared__ int64_t s_pre[kStripes + 1];
-  __shared__ int64_t s_base[kStripes];  // stripe_off[t] - s_pre[t]
+  // Wave items of stripe t: [stripe_off(t), stripe_off(t) + count), item u of all
+  // belongs to the last stripe whose prefix is <= u (empty stripes share their
+  // prefix).  Lane t < kStripes holds stripe t's prefix, and what takes u to its
+  // place in a.witems.
+  const int64_t stride = (int64_t)nblk * (NT / 64);
+  int64_t u = (int64_t)blk * (NT / 64) + wave;
+  const int64_t off = stripe_off(a, lane);
+  const int64_t mine = lane < kStripes ? min((int64_t)cnt0, stripe_off(a, lane + 1) - off) : 0;
+  const int64_t incl = stripe_scan(mine);
+  const int64_t pre = incl - mine, to_item = off - pre;
+  const int64_t count = read_lane64(incl, kStripes - 1);  // wave items
+  const auto find_item = [&](int64_t x) {
+    const int t = __popcll(__builtin_amdgcn_ballot_w64(lane < kStripes && x >= pre)) - 1;
+    return a.witems[read_lane64(to_item, t) + x];
+  };
+  int2 item = make_int2(0, 0);
+  if (u < count) item = find_item(u);
   const Hit hit0 = find_hit(a, ray0);
   const HitReads reads0 = record_hit_issue(a, hit0);
-  if (threadIdx.x == 0) {
-    int64_t p = 0;
-#pragma unroll
-    for (int t = 0; t < kStripes; t++) {
-      s_pre[t] = p;
-      s_base[t] = a.stripe_off[t] - p;
-      p += min((int64_t)a.stats[8 + t], a.stripe_cap[t]);
-    }
-    s_pre[kStripes] = p;
-  }
-  __syncthreads();
-  const int64_t count = s_pre[kStripes];  // wave items
-  const int64_t stride = (int64_t)nblk * (NT / 64);
   uint32_t* touch_p = DISTINCT ? a.touch + ((a.d.vs + 31) >> 5) : nullptr;
   int32_t* const passes = a.passes;  // kept in registers across the loop
-  int n_pass = 0, n_dpass = 0, n_upd = 0;  // n_pass is wave-uniform
+  int n_pass = 0, n_dpass = 0, n_upd = 0;
   int n_dhit = 0;
   record_hit_finish(a, hit0, reads0, ray0.z);
   if (DISTINCT) n_dhit += distinct_hit(a, hit0);
@@ -277,130 +334,101 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
     record_hit_finish(a, h, record_hit_issue(a, h), r.z);
     if (DISTINCT) n_dhit += distinct_hit(a, h);
   }
+  if (BOX) __syncthreads();  // the box is zero
 
-  for (int64_t u = (int64_t)blk * (NT / 64) + (threadIdx.x >> 6); u < count; u += stride) {
-    bool active = false, near = false, wraps = false;
+  bool touched = false;
+  for (; u < count; u += stride) {
+    const int j = __builtin_amdgcn_readfirstlane(item.y);
+    const int4 ray = a.rays[(int64_t)__builtin_amdgcn_readfirstlane(item.x) * 64 + lane];
+    bool active = false, wrap[3] = {false, false, false};
     Walk w = {};
-    // storage coordinates of the current voxel (sx, 4 sy, 16 sz), their steps
-    int32_t sc[3] = {0, 0, 0}, st[3] = {0, 0, 0};
     int32_t sidx = 0;
     {
-      // last stripe t with s_pre[t] <= u (empty stripes share their prefix)
-      int t = 0;
-#pragma unroll
-      for (int step = kStripes / 2; step >= 1; step >>= 1)
-        if (u >= s_pre[t + step]) t += step;
-      const int2 item = a.witems[s_base[t] + u];
-      const int4 ray = a.rays[(int64_t)item.x * 64 + lane];
       const int32_t q[3] = {ray.x, ray.y, ray.z};
-      const int j = item.y;
-      int32_t sv[3], n[3], sg[3], ad[3];
+      int32_t l[3], most[3];
+      bool up[3];
+      const bool inside = segment_init(a, q, ray.w & 3, j, w, l, up, most);
+      active = inside && j < ray.w >> 2 && !walk_ended(w);  // (j: the ray has segment j)
 #pragma unroll
       for (int k = 0; k < 3; k++) {
-        sv[k] = a.S[k] >> 16;
-        const int32_t ev = q[k] >> 16;
-        n[k] = ev > sv[k] ? ev - sv[k] : sv[k] - ev;
-        const int32_t dq = q[k] - a.S[k];
-        sg[k] = dq > 0 ? 1 : (dq < 0 ? -1 : 0);
-        ad[k] = dq < 0 ? -dq : dq;
+        const int32_t s = wrap_add(l[k] + a.d.ro[k], dims[k]);
+        wrap[k] = active && (up[k] ? s + most[k] >= dims[k] : s < most[k]);
+        w.pos[k] += s << (2 * k);
+        w.move[k] += up[k] ? 1 << (2 * k) : -(1 << (2 * k));
       }
-      const int dom = dominant_axis(n);
-      int32_t v[3] = {sv[0], sv[1], sv[2]};
-      bool inside = j < ray.w;  // the ray has segment j
-      const int32_t sgd = sel3(dom, sg[0], sg[1], sg[2]);
-      if (inside && j > 0)
-        entry_voxel(a.S, sg, ad, dom, sel3(dom, sv[0], sv[1], sv[2]) + sgd * j * a.seg_len, v);
-      int32_t l[3];
-#pragma unroll
-      for (int k = 0; k < 3; k++) {
-        l[k] = v[k] - a.O[k];
-        inside = inside && l[k] >= 0 && l[k] < dims[k];
-      }
-      if (inside) {
-        int32_t most[3];
-        walk_init(a, q, v, l, sg, ad, dom, w, most);
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-          const int32_t s = wrap_add(l[k] + a.d.ro[k], dims[k]);
-          wraps |= sg[k] > 0 ? s + most[k] >= dims[k] : s < most[k];
-          sc[k] = s << (2 * k);
-          st[k] = sg[k] * (1 << (2 * k));
-        }
-        sidx = index24(a.d, sc[0], sc[1], sc[2]);
-        active = !walk_ended(w);
-        if (BOX) {
-          // the segment's dominant-axis cells (window-local) against the box's
-          const int32_t c0 = sel3(dom, l[0], l[1], l[2]), c1 = c0 + sgd * (a.seg_len - 1);
-          const int32_t lo = c0 < c1 ? c0 : c1, hi = c0 < c1 ? c1 : c0;
-          const int32_t bl = sel3(dom, a.box_l[0], a.box_l[1], a.box_l[2]);
-          near = hi >= bl && lo < bl + sel3(dom, a.box_e[0], a.box_e[1], a.box_e[2]);
-        }
-      }
+      sidx = index24(a.d, w.pos);
     }
+    // the storage wrap only along axes where a walk of the wave can reach it
+    bool wrap_any[3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) wrap_any[k] = __builtin_amdgcn_ballot_w64(wrap[k]) != 0;
     // box lookups only in waves that can reach the box
-    const bool wnear = BOX && __any(near);
-
-    // the storage wrap only in waves where a walk can reach it
-    const bool wwrap = __any(wraps);
+    const bool wnear = BOX && j * a.seg_len <= a.box_far;
+    touched |= wnear;
     int32_t cur_line = kWtEmpty;  // this lane's current line and its slot
-    int cur_slot = -1;
-    for (;;) {
-      const unsigned long long ab = __ballot(active);
-      if (!ab) break;
-      n_pass += __popcll(ab);
-      // ---- one pass of the current voxel
-      if (active) {
+    uint32_t cur_at = 0;
+    const auto walk = [&](auto near_c) {
+      constexpr bool NEAR = decltype(near_c)::value;
+      do {
+        n_pass++;
+        // ---- the current voxel's slot (read while the step is computed)
+        const int32_t line = (int32_t)((uint32_t)sidx >> 4);
+        const uint32_t home = wt_home(line, base);
+        uint32_t at = line == cur_line ? cur_at : home;
+        const int32_t tag = (int32_t)*wt_word(wtab, at);
+        const int32_t idx = sidx;
         int bidx = -1;
-        if (BOX && wnear) {
+        if (NEAR) {
           // storage offsets from the box's first cell (unsigned: wrapped)
-          const uint32_t d0 = (uint32_t)wrap_add(sc[0] - a.box_s[0] + nx, nx);
-          const uint32_t d1 = (uint32_t)wrap_add((sc[1] >> 2) - a.box_s[1] + ny, ny);
-          const uint32_t d2 = (uint32_t)wrap_add((sc[2] >> 4) - a.box_s[2] + nz, nz);
+          const uint32_t d0 = (uint32_t)wrap_add(pos_x(w) - a.box_s[0] + nx, nx);
+          const uint32_t d1 = (uint32_t)wrap_add(pos_y(w) - a.box_s[1] + ny, ny);
+          const uint32_t d2 = (uint32_t)wrap_add(pos_z(w) - a.box_s[2] + nz, nz);
           if (d0 < (uint32_t)a.box_e[0] && d1 < (uint32_t)a.box_e[1] && d2 < (uint32_t)a.box_e[2])
             bidx = (int)((d0 * kBoxXY + d1) * kBoxZ + d2);
         }
-        if (BOX && bidx >= 0) {
+        // ---- step
+        walk_step(w);
+        if (wrap_any[0]) wrap_pos(w, 0, nx);
+        if (wrap_any[1]) wrap_pos(w, 1, ny);
+        if (wrap_any[2]) wrap_pos(w, 2, nz);
+        sidx = index24(a.d, w.pos);
+        // ---- one pass of the voxel
+        if (NEAR && bidx >= 0) {
           atomicAdd(&box_cnt[bidx], 1);
         } else {
-          const int32_t line = sidx >> 4;
-          if (line != cur_line) {
-            cur_line = line;
-            cur_slot = wt_lookup(wt, line);
-          }
-          if (cur_slot >= 0) {
-            // counter pair (sidx & 15) / 2, half sidx & 1 (a shift takes 5 bits)
-            atomicAdd(&wt.cnt[cur_slot * kWtStride + ((sidx & 15) >> 1)], 1u << ((sidx << 4) & 31));
-          } else {
-            n_upd++;
-            atomicAdd(&passes[sidx], 1);
-            if (DISTINCT) {
-              const uint32_t bit = 1u << (sidx & 31);
-              const uint32_t old = atomicOr(&touch_p[(uint32_t)sidx >> 5], bit);
-              n_dpass += !(old & bit);
+          cur_line = line;
+          if (tag != line) {
+            at = wt_claim(wtab, base, line, at, tag);
+            if (at == base + kWtLast + 4u * kWtStride) {
+              cur_line = kWtEmpty;
+              n_upd++;
+              atomicAdd(&passes[idx], 1);
+              if (DISTINCT) {
+                const uint32_t bit = 1u << (idx & 31);
+                const uint32_t old = atomicOr(&touch_p[(uint32_t)idx >> 5], bit);
+                n_dpass += !(old & bit);
+              }
             }
           }
+          cur_at = at;
+          // counter idx & 15 = byte idx & 3 of word (idx & 15) / 4 (a shift takes 5 bits)
+          atomicAdd(wt_word(wtab, at + 4 + (idx & 12)), 1u << ((idx << 3) & 31));
         }
-      }
-      // ---- step
-      bool mx, my, mz;
-      walk_step(w, mx, my, mz);
-      sc[0] += mx ? st[0] : 0;
-      sc[1] += my ? st[1] : 0;
-      sc[2] += mz ? st[2] : 0;
-      if (wwrap) {
-        sc[0] = sc[0] < 0 ? nx - 1 : sc[0] == nx ? 0 : sc[0];
-        sc[1] = sc[1] < 0 ? 4 * (ny - 1) : sc[1] == 4 * ny ? 0 : sc[1];
-        sc[2] = sc[2] < 0 ? 16 * (nz - 1) : sc[2] == 16 * nz ? 0 : sc[2];
-      }
-      sidx = index24(a.d, sc[0], sc[1], sc[2]);
-      active = active & !walk_ended(w);
+      } while (!walk_ended(w));
+    };
+    if (active) {
+      if (wnear)
+        walk(std::true_type());
+      else
+        walk(std::false_type());
     }
+    if (u + stride < count) item = find_item(u + stride);
     // ---- flush the wave's table: 16 lanes per claimed line
     wave_lds_sync();
-    const int32_t tg = wt.tag[lane];
-    const unsigned long long vm = __ballot(tg != kWtEmpty);
+    const int32_t tg = (int32_t)wt.slot[lane * kWtStride];
+    const unsigned long long vm = __builtin_amdgcn_ballot_w64(tg != kWtEmpty);
     if (vm) {
-      if (tg != kWtEmpty) wt.lst[__popcll(vm & ((1ull << lane) - 1ull))] = lane;
+      if (tg != kWtEmpty) wt.lst[__popcll(vm & ((1ull << lane) - 1ull))] = lane * kWtStride;
       wave_lds_sync();
       const int nv = __popcll(vm);
       const int w = lane & 15;
@@ -408,12 +436,12 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
         const int e = k + (lane >> 4);
         if (e < nv) {
           const int s = wt.lst[e];
-          const uint32_t pair = wt.cnt[s * kWtStride + (w >> 1)];
-          const int c = (int)((pair >> ((w & 1) << 4)) & 0xFFFFu);
-          // both lanes of a pair have read it before the even one clears it
-          if (pair && !(w & 1)) wt.cnt[s * kWtStride + (w >> 1)] = 0;
+          const uint32_t four = wt.slot[s + 1 + (w >> 2)];
+          const int c = (int)((four >> (8 * (w & 3))) & 0xFFu);
+          // the four lanes of a word have read it before the first clears it
+          if (four && !(w & 3)) wt.slot[s + 1 + (w >> 2)] = 0;
           if (c) {
-            const int32_t addr = (wt.tag[s] << 4) + w;
+            const int32_t addr = ((int32_t)wt.slot[s] << 4) + w;
             n_upd++;
             atomicAdd(&passes[addr], c);
             if (DISTINCT) {
@@ -425,23 +453,23 @@ __device__ __forceinline__ void trace_body(const InsertArgs& a, const int blk, c
         }
       }
       wave_lds_sync();
-      wt.tag[lane] = kWtEmpty;
+      wt.slot[lane * kWtStride] = (uint32_t)kWtEmpty;
       wave_lds_sync();
     }
   }
   if (BOX) {
     // flush the block's box counts into its replica (coalesced; zero cells
-    // are skipped)
-    __syncthreads();
+    // are skipped, and blocks none of whose items came near)
     int32_t* rep = a.box_rep + (size_t)(blk % kBoxReps) * kBoxCells;
-    for (int i = threadIdx.x; i < kBoxCells; i += NT) {
+    const bool any = __syncthreads_or(touched);
+    for (int i = any ? (int)threadIdx.x : kBoxCells; i < kBoxCells; i += NT) {
       const int32_t c = box_cnt[i];
       if (c) atomicAdd(&rep[i], c);
     }
   }
   // per-block counters, written without atomics (summed by the host)
   __shared__ int wsum[NT / 64][4];
-  const int c3 = n_pass;
+  const int c3 = wave_sum(n_pass);
   const int c5 = DISTINCT ? wave_sum(n_dhit) : 0;
   const int c4 = DISTINCT ? wave_sum(n_dpass) : 0;
   const int c6 = wave_sum(n_upd);

@@ -147,49 +147,6 @@ __device__ __forceinline__ int distinct_hit(const InsertArgs& a, const Hit& f) {
   return !(atomicOr(&a.touch[(uint32_t)f.e >> 5], bit) & bit);
 }
 
-// Voxel at which the ray S -> q enters world cell c along axis dm (c is not
-// the sensor's cell): see the traversal pass below for the tie rule.
-//
-// At that instant another axis k lies at X_k = (S_k |D| + s_k |D_k| num) / |D|
-// (Q units; D = the dominant component, s_k the sign along k, num = the
-// dominant-axis distance from the sensor to the cell's boundary), in cell
-// floor(X_k / 2^16).  A float estimate of that quotient is within 0.02 of it
-// (|S_k| < 2^31, the displacement along k is below 2^27, each float step
-// rounds to 2^-24 relative), so its floor is off by at most one and one
-// exact 64-bit remainder test each way settles it.  All three axes are
-// computed without branches (dm varies across a wave) and the dominant one
-// is replaced by c.
-__device__ __forceinline__ void entry_voxel(const int32_t S[3], const int32_t sg[3],
-                                            const int32_t ad[3], const int dm, const int32_t c,
-                                            int32_t v[3]) {
-  const int32_t Sd = sel3(dm, S[0], S[1], S[2]);
-  const int32_t dd = sel3(dm, ad[0], ad[1], ad[2]);
-  const int32_t sd = sel3(dm, sg[0], sg[1], sg[2]);
-  // |num| < 2^28 (the ray spans fewer than 2^11 cells); formed from the
-  // cell offset so that no intermediate overflows
-  const int32_t off = c - (Sd >> 16);
-  const int32_t num = sd > 0 ? (off << 16) - (Sd & 0xFFFF) : (Sd & 0xFFFF) - ((off + 1) << 16);
-  const int64_t den = (int64_t)dd << 16;
-  const float rden = __builtin_amdgcn_rcpf((float)dd * 65536.0f);
-  const float fdd = (float)dd, fnum = (float)num;
-#pragma unroll
-  for (int k = 0; k < 3; k++) {
-    const int32_t sad = sg[k] * ad[k];
-    const int64_t x = (int64_t)S[k] * dd + (int64_t)num * sad;
-    int64_t qe = (int64_t)floorf(__builtin_fmaf((float)S[k], fdd, fnum * (float)sad) * rden);
-    int64_t r = x - ((qe * dd) << 16);
-    if (r < 0) {
-      qe -= 1;
-      r += den;
-    } else if (r >= den) {
-      qe += 1;
-      r -= den;
-    }
-    if (r == 0 && sd < 0 && sg[k] < 0) qe -= 1;
-    v[k] = k == dm ? c : (int32_t)qe;
-  }
-}
-
 // Exact traversal state of one segment: which axis crosses into its next cell
 // first, and the moves left.
 //
@@ -207,81 +164,155 @@ __device__ __forceinline__ void entry_voxel(const int32_t S[3], const int32_t sg
 // zero: a steps iff f < g, b steps iff f >= 0.
 //
 // The next boundary of every axis lies within one cell of the current point,
-// so |E| <= 2^16 max(|D_a|, |D_b|) < 2^43 and f fits in 32 bits; an axis without
-// motion counts as one cell away for ever (num = 2^16).  An axis that has
+// so |E| <= 2^16 max(|D_a|, |D_b|) < 2^43 and f fits in 32 bits; against an axis
+// without motion (taken as moving up: its boundary lies ahead) E never changes and
+// has the sign that lets the other one step.  An axis that has
 // reached the end voxel's coordinate needs no check of its own: its next
 // crossing comes after the ray's end, at t > 1 (or, moving down with the end on
 // a boundary, at t = 1), while an axis with moves left crosses at t < 1 (moving
 // up, at t <= 1, which steps first in a tie).
 //
-// cnt: an axis whose moves to the end voxel reach the move that leaves the
+// pos holds cnt << 16 | storage coordinate, so that one addition counts a move and
+// makes it.  cnt: an axis whose moves to the end voxel reach the move that leaves the
 // window or the segment (the walk ends before that voxel) holds the moves
 // before that one, and ends the walk by going negative; any other axis holds
 // its moves to the end voxel, and they end the walk by all being zero, if no
-// axis of the first kind exists (thr: -1 with one, else 0).
+// axis of the first kind exists (thr: -1 with one, else 2^16 - 1).
 struct Walk {
   int32_t fxy, fxz, fyz, gxy, gxz, gyz;
-  int32_t ad[3], cnt[3], thr;
+  int32_t ad[3], na[2], thr;  // |D|, -|D_x| and -|D_y|
+  int32_t pos[3];   // cnt << 16 | storage coordinate (sx, 4 sy, 16 sz)
+  int32_t move[3];  // what a move adds to pos
 };
 
-__device__ __forceinline__ void pair_init(const int32_t num_a, const int32_t ad_a, const bool up_a,
-                                          const int32_t num_b, const int32_t ad_b, const bool up_b,
-                                          int32_t& f, int32_t& g) {
-  const int64_t e = (int64_t)num_a * ad_b - (int64_t)num_b * ad_a;
-  const bool exact = (e & 0xFFFF) == 0;
-  f = (int32_t)(e >> 16) - (exact & up_a & !up_b);
-  g = exact & (up_a == up_b);
-}
-
 __device__ __forceinline__ bool walk_ended(const Walk& w) {
-  return (w.cnt[0] | w.cnt[1] | w.cnt[2]) <= w.thr;
+  return (w.pos[0] | w.pos[1] | w.pos[2]) <= w.thr;
 }
 
-// Starts the walk of a ray to q at world voxel v (inside the window, local l).
-// sg, ad: signs and sizes of the ray's displacement.  most[k]: an upper bound
-// of the walk's moves along axis k (the dominant axis moves seg_len times at
-// most, another one no faster than twice as fast).
-__device__ __forceinline__ void walk_init(const InsertArgs& a, const int32_t q[3],
-                                          const int32_t v[3], const int32_t l[3],
-                                          const int32_t sg[3], const int32_t ad[3], const int dom,
-                                          Walk& w, int32_t most[3]) {
+// Starts the walk of segment j of the ray to q with dominant axis dom (j the same
+// for the whole wave): l = local coordinates of its first voxel; up[k]: the ray
+// does not move down along axis k; most[k]: an upper bound of the walk's moves
+// along axis k (the dominant axis moves seg_len times at most, another one no
+// faster than twice as fast).  False when the first voxel lies outside the window.
+//
+// Along axis k the ray reaches its (i + 1)-st boundary after h_k + 2^16 i Q units,
+// h_k the distance from the sensor to the first one.  Segment j > 0 starts when the
+// dominant axis (d) has moved num = h_d + 2^16 (J - 1), J = j seg_len, and has made
+// J moves; another axis k has then made the moves m whose boundaries it has
+// reached, h_k |D_d| + 2^16 (m - 1) |D_d| <= num |D_k| (< when it moves down and d up:
+// a shared boundary belongs to the upper cell).  That is the quotient of
+// y = num |D_k| + (2^16 - h_k) |D_d| by 2^16 |D_d|, and the remainder r of that
+// division is what the walk starts from: E_dk = r + 2^16 (|D_k| - |D_d|).  (With j = 0
+// the same holds for m = 0 and r = y, which then is no remainder.)
+//
+// The quotient is below 2^12; its float estimate is within 0.01 of it, so lowered
+// by 0.02 and truncated it is the quotient or one less, which one exact comparison of
+// the remainder settles.  For < instead of <=, the same is done with y - 1.
+//
+// Axes in the order d, b, c (the others in ascending order), only at the end
+// brought back to x, y, z: the quotients are taken for two axes instead of three,
+// and two of the three E need no product of their own.  (Three entry coordinates and
+// three E, each by its own products: 390 vector instructions and 27 wide multiplies
+// for a wave's segment, now 270 and 12.)
+__device__ __forceinline__ bool segment_init(const InsertArgs& a, const int32_t q[3], const int dom,
+                                             const int32_t j, Walk& w, int32_t l[3], bool up[3],
+                                             int32_t most[3]) {
   const int32_t dims[3] = {a.d.nx, a.d.ny, a.d.nz};
-  int32_t num[3];  // |num| < 2^28: v lies on the ray, which spans fewer than 2^11 cells
-  bool stopped = false;
+  const int32_t J = j * a.seg_len;
+  // (numbers that are never negative as unsigned: their products take one
+  // multiply-add; truth values as 0 / 1)
+  uint32_t ad[3], h[3], u[3];
+  int32_t n[3];
 #pragma unroll
   for (int k = 0; k < 3; k++) {
-    const int32_t ev = q[k] >> 16;
-    const int32_t rem = ev > v[k] ? ev - v[k] : v[k] - ev;
-    int32_t T = (sg[k] > 0 ? dims[k] - 1 - l[k] : l[k]) + 1;  // the move that leaves the window
-    T = k == dom ? min(T, a.seg_len) : T;                     // or the segment
-    const bool stop = rem >= T;
-    stopped |= stop;
-    w.cnt[k] = stop ? T - 1 : rem;
-    w.ad[k] = ad[k];
-    most[k] = min(stop ? T : rem, 2 * a.seg_len + 2);
-    const int32_t off = v[k] - (a.S[k] >> 16), fr = a.S[k] & 0xFFFF;
-    num[k] = sg[k] > 0 ? ((off + 1) << 16) - fr : fr - (off << 16);
-    num[k] = sg[k] == 0 ? 1 << 16 : num[k];
+    const int32_t dq = q[k] - a.S[k], dv = (q[k] >> 16) - (a.S[k] >> 16), fr = a.S[k] & 0xFFFF;
+    up[k] = dq >= 0;
+    u[k] = up[k];
+    ad[k] = (uint32_t)(up[k] ? dq : -dq);
+    w.ad[k] = (int32_t)ad[k];
+    n[k] = up[k] ? dv : -dv;
+    h[k] = (uint32_t)(up[k] ? 65536 - fr : fr);
   }
-  w.thr = stopped ? -1 : 0;
-  pair_init(num[0], ad[0], sg[0] > 0, num[1], ad[1], sg[1] > 0, w.fxy, w.gxy);
-  pair_init(num[0], ad[0], sg[0] > 0, num[2], ad[2], sg[2] > 0, w.fxz, w.gxz);
-  pair_init(num[1], ad[1], sg[1] > 0, num[2], ad[2], sg[2] > 0, w.fyz, w.gyz);
+  const bool d0 = dom == 0, d1 = dom == 1, d2 = dom == 2;
+  const uint32_t dd = d0 ? ad[0] : d1 ? ad[1] : ad[2], hd = d0 ? h[0] : d1 ? h[1] : h[2];
+  const uint32_t adk[2] = {d0 ? ad[1] : ad[0], d2 ? ad[1] : ad[2]};
+  const uint32_t hk[2] = {d0 ? h[1] : h[0], d2 ? h[1] : h[2]};
+  uint32_t m[2] = {0, 0}, xd[2];  // xd: E_dk is a multiple of 2^16
+  int32_t fd[2];
+  if (j > 0) {
+    const uint32_t ud = d0 ? u[0] : d1 ? u[1] : u[2];
+    const uint32_t uk[2] = {d0 ? u[1] : u[0], d2 ? u[1] : u[2]};
+    const uint32_t num = hd + ((uint32_t)(J - 1) << 16);
+    const float fdd = (float)dd, fnum = (float)num;
+    const float rden = __builtin_amdgcn_rcpf(fdd * 65536.0f);
+    const uint64_t den = (uint64_t)dd << 16;
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+      const uint32_t g = 65536 - hk[k], strict = ud & ~uk[k];
+      const float est = __builtin_fmaf(fnum, (float)adk[k], (float)g * fdd) * rden;
+      m[k] = (uint32_t)(int32_t)(est - 0.02f);
+      uint64_t r = (uint64_t)num * adk[k] + (uint64_t)g * dd - strict - (uint64_t)(m[k] << 16) * dd;
+      const bool more = r >= den;
+      m[k] += more;
+      r = r - (more ? den : 0) + strict;
+      xd[k] = ((uint32_t)r & 0xFFFF) == 0;
+      fd[k] = (int32_t)((uint32_t)(r >> 16) + adk[k] - dd);
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+      const uint64_t e = (uint64_t)hd * adk[k] - (uint64_t)hk[k] * dd;
+      xd[k] = ((uint32_t)e & 0xFFFF) == 0;
+      fd[k] = (int32_t)(e >> 16);
+    }
+  }
+  const uint64_t e = (uint64_t)(hk[0] + (m[0] << 16)) * adk[1] - (uint64_t)(hk[1] + (m[1] << 16)) * adk[0];
+  const int32_t fbc = (int32_t)(e >> 16);
+  const uint32_t xbc = ((uint32_t)e & 0xFFFF) == 0;
+  // floor(-E / 2^16)
+  const int32_t nb = ~fd[0] + (int32_t)xd[0], nc = ~fd[1] + (int32_t)xd[1];
+  const uint32_t xxy = d2 ? xbc : xd[0], xxz = d0 ? xd[1] : d1 ? xbc : xd[0], xyz = d0 ? xbc : xd[1];
+  w.fxy = (d0 ? fd[0] : d1 ? nb : fbc) - (int32_t)(xxy & u[0] & ~u[1]);
+  w.fxz = (d0 ? fd[1] : d1 ? fbc : nb) - (int32_t)(xxz & u[0] & ~u[2]);
+  w.fyz = (d0 ? fbc : d1 ? fd[1] : nc) - (int32_t)(xyz & u[1] & ~u[2]);
+  w.gxy = (int32_t)(xxy & ~(u[0] ^ u[1]));
+  w.gxz = (int32_t)(xxz & ~(u[0] ^ u[2]));
+  w.gyz = (int32_t)(xyz & ~(u[1] ^ u[2]));
+  const int32_t mv[3] = {d0 ? J : (int32_t)m[0], (int32_t)(d0 ? m[0] : d1 ? (uint32_t)J : m[1]),
+                         d2 ? J : (int32_t)m[1]};
+  bool inside = true, stopped = false;
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    const int32_t ls = (a.S[k] >> 16) - a.O[k];
+    l[k] = ls + (up[k] ? mv[k] : -mv[k]);
+    inside &= (uint32_t)l[k] < (uint32_t)dims[k];
+    // moves from the sensor's voxel to the one that leaves the window or the segment
+    int32_t T = up[k] ? dims[k] - ls : ls + 1;
+    T = k == dom ? min(T, J + a.seg_len) : T;
+    stopped |= n[k] >= T;
+    const int32_t cnt = min(n[k], T - 1) - mv[k];
+    w.pos[k] = (int32_t)((uint32_t)cnt << 16);
+    w.move[k] = -(1 << 16);
+    most[k] = min(cnt + 1, 2 * a.seg_len + 2);
+  }
+  w.thr = stopped ? -1 : 0xFFFF;
+  w.na[0] = -w.ad[0];
+  w.na[1] = -w.ad[1];
+  asm("" : "+v"(w.na[0]), "+v"(w.na[1]));  // kept: a sum of three, not a difference and a sum
+  return inside;
 }
 
-// One step: sets which axes move; the walk has ended when walk_ended() after it.
-__device__ __forceinline__ void walk_step(Walk& w, bool& mx, bool& my, bool& mz) {
-  mx = (w.fxy < w.gxy) & (w.fxz < w.gxz);
-  my = (w.fxy >= 0) & (w.fyz < w.gyz);
-  mz = (w.fxz >= 0) & (w.fyz >= 0);
-  w.cnt[0] -= mx;
-  w.cnt[1] -= my;
-  w.cnt[2] -= mz;
-  // unsigned adds: a walk that has ended may drift on until its wave's end
-  const uint32_t a0 = (uint32_t)w.ad[0], a1 = (uint32_t)w.ad[1], a2 = (uint32_t)w.ad[2];
-  w.fxy = (int32_t)((uint32_t)w.fxy + (mx ? a1 : 0u) + (my ? 0u - a0 : 0u));
-  w.fxz = (int32_t)((uint32_t)w.fxz + (mx ? a2 : 0u) + (mz ? 0u - a0 : 0u));
-  w.fyz = (int32_t)((uint32_t)w.fyz + (my ? a2 : 0u) + (mz ? 0u - a1 : 0u));
+// One step; the walk has ended when walk_ended() after it.
+__device__ __forceinline__ void walk_step(Walk& w) {
+  const bool mx = (w.fxy < w.gxy) & (w.fxz < w.gxz);
+  const bool my = (w.fxy >= 0) & (w.fyz < w.gyz);
+  const bool mz = (w.fxz >= 0) & (w.fyz >= 0);
+  w.pos[0] += mx ? w.move[0] : 0;
+  w.pos[1] += my ? w.move[1] : 0;
+  w.pos[2] += mz ? w.move[2] : 0;
+  w.fxy = w.fxy + (mx ? w.ad[1] : 0) + (my ? w.na[0] : 0);
+  w.fxz = w.fxz + (mx ? w.ad[2] : 0) + (mz ? w.na[0] : 0);
+  w.fyz = w.fyz + (my ? w.ad[2] : 0) + (mz ? w.na[1] : 0);
 }
 
 // a * b + c on the 24-bit multiplier (operands below 2^24; b uniform across
@@ -294,14 +325,30 @@ __device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) 
   return r;
 }
 
-// Storage index of voxel (sx, sy, sz) from sx, 4 sy and 16 sz, with 24-bit
-// multiplies: brick coordinates < 2^11, nby <= 2048 and 16 nz <= 2048 keep every
-// operand within 24 bits, and the index is below 2^31 for every map the library
-// accepts.
-__device__ __forceinline__ int32_t index24(const Dims& d, int32_t sx, int32_t sy4, int32_t sz16) {
-  const uint32_t b = mad_u24((uint32_t)(sx >> 2), (uint32_t)d.nby, (uint32_t)(sy4 >> 4));
-  const uint32_t low = (((uint32_t)sx & 3u) | ((uint32_t)sy4 & 12u)) | (uint32_t)sz16;
+// Storage index of the voxel at pos (Walk::pos), with 24-bit multiplies: brick
+// coordinates < 2^11, nby <= 2048 and 16 nz <= 2048 keep every operand within 24
+// bits, and the index is below 2^31 for every map the library accepts.
+__device__ __forceinline__ int32_t index24(const Dims& d, const int32_t pos[3]) {
+  const uint32_t x = (uint32_t)pos[0], y = (uint32_t)pos[1], z = (uint32_t)pos[2] & 0xFFFFu;
+  const uint32_t b = mad_u24((x >> 2) & 0x3FFFu, (uint32_t)d.nby, (y >> 4) & 0xFFFu);
+  uint32_t low;  // x's two low bits, y's others; the compiler finds no bit select in it
+  asm("v_bfi_b32 %0, 3, %1, %2" : "=v"(low) : "v"(x), "v"(y));
+  low = (low & 15u) | z;
   return (int32_t)mad_u24(b, (uint32_t)d.nz << 4, low);
+}
+
+__device__ __forceinline__ int32_t pos_x(const Walk& w) { return w.pos[0] & 0xFFFF; }
+__device__ __forceinline__ int32_t pos_y(const Walk& w) { return (w.pos[1] >> 2) & 0x3FFF; }
+__device__ __forceinline__ int32_t pos_z(const Walk& w) { return (w.pos[2] >> 4) & 0xFFF; }
+
+// Brings a coordinate along axis k that a move took past either end of the
+// storage (n voxels; read as an unsigned number -1 lies past the end too) to the
+// other end.
+__device__ __forceinline__ void wrap_pos(Walk& w, const int k, const int32_t n) {
+  const int32_t size = n << (2 * k);
+  const bool out = (w.pos[k] & 0xFFFF) >= size;
+  const int32_t by = (int16_t)w.move[k] < 0 ? size : -size;
+  w.pos[k] += out ? by : 0;
 }
 
 }  // namespace
