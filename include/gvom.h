@@ -258,7 +258,9 @@ int32_t map_sync(map_t* m);
  * groups its rays by segment count), counts its passes in an LDS table of
  * 64-byte map lines and adds each line to the map with one request; the
  * passes of a 17 x 17 x 9 box around the sensor are summed per block on chip
- * first.  seg_len: dominant-axis voxels per ray segment, 1..1024 (default 8);
+ * first.  seg_len: dominant-axis voxels per ray segment, 1..1024 (default 8,
+ * which also lets a single insert take 4 or 5 for scans of up to 49,152 or
+ * 196,608 points);
  * trace_waves_per_cu: resident waves per compute unit requested for the
  * traversal grid (blocks of four waves), 1..32 (default 28, the most that fit
  * a compute unit); surface_tile: edge in

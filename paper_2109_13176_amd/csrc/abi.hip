@@ -24,6 +24,7 @@ using gvom::Dims;
 
 namespace {
 
+constexpr int32_t kSegLen = 8;  // default of the segment length setting
 constexpr size_t kStatsBytes = (8 + gvom::kStripes) * 8;
 
 int64_t n_vox(const map_t* m) { return (int64_t)m->p.nx * m->p.ny * m->p.nz; }
@@ -287,7 +288,7 @@ int32_t map_create(const map_params_t* p, void* stream, map_t** out) {
     delete m;
     return MAP_E_DEVICE;
   }
-  m->seg_len = 8;
+  m->seg_len = kSegLen;
   m->trace_wpc = 28;
   m->surf_tile = 32;
   // traversal blocks (at most 32 waves per CU) + the sensor-box fold blocks
@@ -449,9 +450,24 @@ bool grow(map_t* m, T** p, int64_t* cap, int64_t need, size_t elem) {
 // items in the region of stripe b mod kStripes, sized for the most items
 // that stripe's waves can reserve (each wave at most one item per segment
 // its longest ray can have).  *need = wave items in all.
-void insert_layout(const map_t* m, int64_t ray_blocks, gvom::InsertArgs* a, int64_t* need) {
-  a->block_items = (gvom::kRayBlock / 64) * gvom::max_segments(m->d, m->seg_len);
+void insert_layout(const map_t* m, int64_t ray_blocks, int32_t seg_len, gvom::InsertArgs* a,
+                   int64_t* need) {
+  a->seg_len = seg_len;
+  a->block_items = (gvom::kRayBlock / 64) * gvom::max_segments(m->d, seg_len);
   *need = ray_blocks * a->block_items;
+}
+
+// Segment length of a lone insert of n points.  An item's steps are one chain of
+// LDS round trips, so a scan with fewer items than the device has waves ends sooner
+// when its rays are cut shorter; with many items the set-up of each costs more than
+// the chains.  Traversal time with 4 / 5 / 8 voxels on 512 x 512 x 64: 32,768 points
+// 25.9 / 26.2 / 29.7 us, 98,304 points 40.0 / 39.2 / 41.0, 131,072 points 49.5 / 47.0
+// / 48.1, 262,144 points 84.2 / 79.2 / 80.3, and on 1024 x 1024 x 96 126 / 121 / 114
+// (with the events that time it).  In a batch the maps fill the device together: the
+// setting as it is.  Any other setting than the default is taken as it is.
+int32_t lone_seg_len(const map_t* m, int64_t n) {
+  if (m->seg_len != kSegLen) return m->seg_len;
+  return n <= 49152 ? 4 : n <= 196608 ? 5 : kSegLen;
 }
 
 // Everything of an insert but the per-scan buffers (a->rays, a->witems,
@@ -494,7 +510,6 @@ int32_t fill_insert(map_t* m, const float* xyz_dev, int64_t n, const float* pose
   a->stats = m->stats;
   a->touch = m->touch;
   a->part_trace = m->part_trace;
-  a->seg_len = m->seg_len;
   const int64_t tpb = gvom::kTraceBlock;  // threads per traversal block
   const int64_t want = (need + tpb / 64 - 1) / (tpb / 64);  // one wave per item
   int64_t lim = (int64_t)m->n_cu * m->trace_wpc / (tpb / 64);
@@ -527,10 +542,10 @@ int32_t fill_insert(map_t* m, const float* xyz_dev, int64_t n, const float* pose
 // fills the kernel arguments.  Updates the host-side map state.
 int32_t prepare_insert(map_t* m, const float* xyz_dev, int64_t n, const float* pose,
                        uint32_t flags, const int32_t S[3], gvom::InsertArgs* a,
-                       gvom::ClearArgs* plan, bool* full) {
+                       gvom::ClearArgs* plan, bool* full, int32_t seg_len) {
   const int64_t ray_blocks = (n + gvom::kRayBlock - 1) / gvom::kRayBlock;
   int64_t need = 0;
-  insert_layout(m, ray_blocks, a, &need);
+  insert_layout(m, ray_blocks, seg_len, a, &need);
   if (!grow(m, &m->rays, &m->rays_cap, ray_blocks * gvom::kRayBlock, sizeof(int4)))
     return MAP_E_OOM;
   if (!grow(m, &m->witems, &m->witem_cap, need, sizeof(int2))) return MAP_E_OOM;
@@ -649,10 +664,10 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Bytes of the scratch an insert of n points needs (ray records, wave items,
 // per-block counters), each region 256-byte aligned.
-size_t static_insert_bytes(const map_t* m, int64_t n, int64_t* need) {
+size_t static_insert_bytes(const map_t* m, int64_t n, int32_t seg_len, int64_t* need) {
   const int64_t ray_blocks = (n + gvom::kRayBlock - 1) / gvom::kRayBlock;
   gvom::InsertArgs tmp;
-  insert_layout(m, ray_blocks, &tmp, need);
+  insert_layout(m, ray_blocks, seg_len, &tmp, need);
   return align256((size_t)ray_blocks * gvom::kRayBlock * sizeof(int4)) +
          align256((size_t)*need * sizeof(int2)) + align256((size_t)ray_blocks * 32);
 }
@@ -672,7 +687,7 @@ int32_t map_insert_scan(map_t* m, const float* xyz_dev, int64_t n, const float p
   m->ranked = false;
   m->version = gvom::next_version();
   const int pm0 = prof_begin(m, MAP_PROF_SCROLL);
-  st = prepare_insert(m, xyz_dev, n, pose, flags, S, &a, &plan, &full);
+  st = prepare_insert(m, xyz_dev, n, pose, flags, S, &a, &plan, &full, lone_seg_len(m, n));
   if (st) return st;
   // an empty map moves its window without clearing anything; the slabs of a
   // moved one are cleared beside the ray pass
@@ -712,14 +727,16 @@ int32_t map_insert_scan_static(map_t* m, const float* xyz_dev, int64_t n, const 
   int32_t st = check_insert(m, xyz_dev, n, pose, flags, S);
   if (st) return st;
   int64_t need = 0;
-  if (static_insert_bytes(m, n, &need) > kScratchBytes) return MAP_E_CAPACITY;
+  int32_t seg_len = lone_seg_len(m, n);
+  if (static_insert_bytes(m, n, seg_len, &need) > kScratchBytes) seg_len = m->seg_len;
+  if (static_insert_bytes(m, n, seg_len, &need) > kScratchBytes) return MAP_E_CAPACITY;
   unsigned char* base = device_scratch(m->device);
   if (!base) return MAP_E_DEVICE;  // nothing enqueued, the map is unchanged
   gvom::InsertArgs a;
   gvom::ClearArgs plan;
   bool full = false;
   const int64_t ray_blocks = (n + gvom::kRayBlock - 1) / gvom::kRayBlock;
-  insert_layout(m, ray_blocks, &a, &need);
+  insert_layout(m, ray_blocks, seg_len, &a, &need);
   a.rays = (int4*)base;
   base += align256((size_t)ray_blocks * gvom::kRayBlock * sizeof(int4));
   a.witems = (int2*)base;
@@ -1012,8 +1029,14 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
     map_t* m = b->maps[i];
     bool full = false;
     const int32_t s = prepare_insert(m, xyz_dev[i], n[i], poses + 12 * i, flags[i], S[i],
-                                     &t->ins[i], &t->clr[i], &full);
+                                     &t->ins[i], &t->clr[i], &full, m->seg_len);
     if (s) return s;  // allocation failure
+    // blocks take 256 points' rays each, from a queue (see k_b_trace)
+    const int64_t tb = (n[i] + gvom::kBatchTracePoints - 1) / gvom::kBatchTracePoints;
+    if (tb < t->ins[i].trace_blocks) {
+      m->last_trace_blocks -= t->ins[i].trace_blocks - tb;
+      t->ins[i].trace_blocks = (int32_t)tb;
+    }
     const bool lut = lut_dev && lut_dev[i];
     column_args(m, &out2d[i], lut, &t->col[i]);
     m->ranked = false;
@@ -1160,13 +1183,14 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
     lut = s2 > lut ? s2 : lut;
   }
   const int cu = b->n_cu;
-  // persistent grids; the bandwidth-bound column and table passes get eight
+  // persistent grids; the traversal's as many blocks as are resident (with eight per
+  // CU, one of them waiting for a place, 922 us instead of 770); the bandwidth-bound column and table passes get eight
   // blocks per CU (the table pass's LDS regions allow it)
-  b->grid = gvom::BatchGrid{cu * 4, cu * 8, cu * 8, cu * 2, cu * 8,
+  b->grid = gvom::BatchGrid{cu * 4, cu * gvom::kTraceWavesPerSimd, cu * 8, cu * 2, cu * 8,
                             k * gvom::box_fold_blocks(), surf, lut};
   hipError_t e = gvom::dev_alloc((void**)&b->dtab, sizeof(gvom::BatchTables));
   if (e == hipSuccess) e = hipHostMalloc((void**)&b->htab, sizeof(gvom::BatchTables), 0);
-  if (e == hipSuccess) e = gvom::dev_alloc((void**)&b->dstamps, (gvom::kMaxBatch + 1) * 8);
+  if (e == hipSuccess) e = gvom::dev_alloc((void**)&b->dstamps, (gvom::kMaxBatch + 2) * 8);
   if (e == hipSuccess) e = hipHostMalloc((void**)&b->hstamps, (gvom::kMaxBatch + 1) * 8, 0);
   if (e != hipSuccess) {
     (void)hipGetLastError();

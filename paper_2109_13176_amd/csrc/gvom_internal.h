@@ -93,6 +93,10 @@ constexpr int kRayBlock = 512;    // threads per block of the ray pass (rays reg
 // CU (LDS and registers), and the walk is bound by per-wave latency
 constexpr int kTraceBlock = 256;
 constexpr int kTraceWavesPerSimd = 7;
+// Points per traversal block of a batch: 32 maps of 20,000-330,000 points take 725 us
+// with 64, 654 with 128, 648 with 256, 688 with 384 (a block's set-up and flush take as
+// long as about 60 points' rays; large blocks leave waves idle at the end).
+constexpr int kBatchTracePoints = 256;
 
 // Blocks of the sensor-box fold that follows the segmented traversal.
 int box_fold_blocks();

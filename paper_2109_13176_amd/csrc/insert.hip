@@ -58,6 +58,7 @@ __global__ __launch_bounds__(kRayBlock) void k_b_rays(const BatchTables* __restr
     if (threadIdx.x == 0) stamps[0] = wall_clock64();
     // per-map completion maxima, taken by the last stages
     for (int i = threadIdx.x; i < n; i += kRayBlock) stamps[1 + i] = 0;
+    if (threadIdx.x == 0) stamps[1 + kMaxBatch] = 0;  // the traversal's queue
   }
   for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {
     const int m = find_map(t->st.pre_rays, n, vb);
@@ -72,16 +73,27 @@ __global__ __launch_bounds__(kRayBlock) void k_b_rays(const BatchTables* __restr
   }
 }
 
+// The blocks' work differs by an order of magnitude (segments per ray, line tables that
+// fill up), so each takes its next virtual block from a queue (cleared by the ray pass);
+// the answer has the block's time to arrive.  Fixed shares of 1792 virtual blocks per
+// map: 922 us for 32 maps, with the queue and fewer of them 648.  (Single items from a
+// queue in the single-map kernel, over eight counters: 43 -> 55 us, the counters'
+// atomics queue up.)
 __global__ __launch_bounds__(kTraceBlock, kTraceWavesPerSimd) void k_b_trace(
-    const BatchTables* __restrict__ t) {
+    const BatchTables* __restrict__ t, unsigned long long* queue) {
   __shared__ int32_t box_cnt[kBoxCells];
   __shared__ WaveTable wtab[kTraceBlock / 64];
   const int n = t->st.nmaps;
   const int total = t->st.pre_trace[n];
-  for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {
+  __shared__ int next;
+  for (int vb = blockIdx.x; vb < total; vb = next) {
+    // (the answer is needed after the block)
+    unsigned long long taken = 0;
+    if (threadIdx.x == 0) taken = atomicAdd(queue, 1ull);
     const int m = find_map(t->st.pre_trace, n, vb);
     trace_body<false, true, kTraceBlock>(t->ins[m], vb - t->st.pre_trace[m],
                                          t->ins[m].trace_blocks, box_cnt, wtab);
+    if (threadIdx.x == 0) next = (int)(gridDim.x + taken);
     __syncthreads();
   }
 }
@@ -127,7 +139,8 @@ hipError_t launch_clear(const ClearArgs& a, hipStream_t s) {
 hipError_t launch_batch_insert(const BatchTables* tab, const BatchGrid& g,
                                unsigned long long* stamps, hipStream_t s) {
   hipLaunchKernelGGL(k_b_rays, dim3(g.rays), dim3(kRayBlock), 0, s, tab, stamps);
-  hipLaunchKernelGGL(k_b_trace, dim3(g.trace), dim3(kTraceBlock), 0, s, tab);
+  hipLaunchKernelGGL(k_b_trace, dim3(g.trace), dim3(kTraceBlock), 0, s, tab,
+                     stamps + 1 + kMaxBatch);
   hipLaunchKernelGGL(k_b_box_fold, dim3(g.fold), dim3(kBlock), 0, s, tab);
   return hipGetLastError();
 }
