@@ -248,10 +248,19 @@ __global__ __launch_bounds__(TR * 64) void k_conv_mfma(const uint16_t* __restric
 // A operands of rows 2..15 are zero); each wave keeps its nine A operands
 // in registers.  Block = 8 rows x 64 pixels, one wave per row, the input
 // tile with its halo staged in LDS.
+//
+// LOSS (training): the prediction stays in registers; out receives the loss
+// gradient dz = sign(pred - label) on defined label entries, 0 elsewhere (the
+// 1/count scale is applied to the reduced gradients), part the block's |error|
+// sum and entry count.  (A loss pass of its own and a launch that totalled its
+// 2,048 partials took 4.9 + 4.4 us at 512 x 512; k_reduce_grad totals the 512.)
+template <bool LOSS>
 __global__ __launch_bounds__(512) void k_conv_out(const uint16_t* __restrict__ x,
                                                   const uint16_t* __restrict__ w,
                                                   const float* __restrict__ bias,
-                                                  float* __restrict__ out, int H, int W) {
+                                                  const float* __restrict__ label,
+                                                  float* __restrict__ out,
+                                                  double* __restrict__ part, int H, int W) {
   constexpr int TR = 8, CIN = 32, PS = CIN + kPad, Q = CIN / 8;
   __shared__ __attribute__((aligned(16))) uint16_t sx[(TR + 2) * (kTC + 2) * PS];
   const int r0 = blockIdx.y * TR, c0 = blockIdx.x * kTC;
@@ -263,6 +272,19 @@ __global__ __launch_bounds__(512) void k_conv_out(const uint16_t* __restrict__ x
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
     if (lr < 2) v = *(const uint4*)(w + (lr * 9 + tap) * CIN + 8 * lk);
     aw[tap] = __builtin_bit_cast(v8bf, v);
+  }
+  // result lane: pixel column lr, rows (channels) 4 lk + e: the two channels
+  // sit in the lanes with lk = 0
+  const int r = r0 + wv;
+  float2 lab[4];
+  if constexpr (LOSS) {
+#pragma unroll
+    for (int nt = 0; nt < 4; nt++) {
+      const int col = c0 + nt * 16 + lr;
+      lab[nt] = make_float2(NAN, NAN);
+      const float* const q = label + ((int64_t)r * W + col) * 2;  // (may be 4-byte aligned)
+      if (lk == 0 && r < H && col < W) lab[nt] = make_float2(q[0], q[1]);
+    }
   }
   stage16<(TR + 2) * (kTC + 2) * Q, 512>(
       [&](int i) {
@@ -287,84 +309,55 @@ __global__ __launch_bounds__(512) void k_conv_out(const uint16_t* __restrict__ x
       acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[tap], b, acc[nt], 0, 0, 0);
     }
   }
-  // result lane: pixel column lr, rows (channels) 4 lk + e: the two channels
-  // sit in the lanes with lk = 0
-  const int r = r0 + wv;
-  if (r >= H || lk != 0) return;
   const float b0 = bias[0], b1 = bias[1];
+  if constexpr (!LOSS) {
+    if (r >= H || lk != 0) return;
 #pragma unroll
-  for (int nt = 0; nt < 4; nt++) {
-    const int col = c0 + nt * 16 + lr;
-    if (col < W) *(float2*)(out + ((int64_t)r * W + col) * 2) = make_float2(acc[nt][0] + b0, acc[nt][1] + b1);
-  }
-}
-
-
-// ------------------------------------------------------------------ loss
-// dz = sign(pred - label) on defined label entries (the 1/count scale is
-// applied to the reduced gradients); per-block |error| sums and counts.
-__global__ __launch_bounds__(256) void k_loss(const float* out, const float* label, int64_t n,
-                                              float* dz, double* part) {
-  double ls = 0.0, cnt = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const float l = label[i];
-    float g = 0.0f;
-    if (!isnan(l)) {
-      const float d = out[i] - l;
-      ls += fabs((double)d);
-      cnt += 1.0;
-      g = d > 0.0f ? 1.0f : (d < 0.0f ? -1.0f : 0.0f);
+    for (int nt = 0; nt < 4; nt++) {
+      const int col = c0 + nt * 16 + lr;
+      if (col < W) *(float2*)(out + ((int64_t)r * W + col) * 2) = make_float2(acc[nt][0] + b0, acc[nt][1] + b1);
     }
-    dz[i] = g;
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    ls += __shfl_xor(ls, o);
-    cnt += __shfl_xor(cnt, o);
-  }
-  __shared__ double s[2][4];
-  if (__lane_id() == 0) {
-    s[0][threadIdx.x >> 6] = ls;
-    s[1][threadIdx.x >> 6] = cnt;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = s[0][0] + s[0][1] + s[0][2] + s[0][3];
-    part[2 * blockIdx.x + 1] = s[1][0] + s[1][1] + s[1][2] + s[1][3];
-  }
-}
-
-// one block: total loss and 1/count -> scal[0] = loss, scal[1] = 1/count
-__global__ __launch_bounds__(256) void k_loss_total(const double* part, int nb, double* scal) {
-  __shared__ double s[2][256];
-  double a = 0.0, b = 0.0;
-  // a thread's pairs i = t, t + 256, ... summed in that order; sixteen
-  // 16-byte loads in flight per round (clamped in-bounds loads, masked adds)
-  constexpr int U = 16;
-  for (int i0 = threadIdx.x; i0 < nb; i0 += 256 * U) {
-    double2 v[U];
+  } else {
+    double ls = 0.0, cnt = 0.0;
 #pragma unroll
-    for (int u = 0; u < U; u++) v[u] = ((const double2*)part)[min(i0 + 256 * u, nb - 1)];
+    for (int nt = 0; nt < 4; nt++) {
+      const int col = c0 + nt * 16 + lr;
+      const float pred[2] = {acc[nt][0] + b0, acc[nt][1] + b1}, l[2] = {lab[nt].x, lab[nt].y};
+      float g[2];
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-      if (i0 + 256 * u < nb) {
-        a += v[u].x;
-        b += v[u].y;
+      for (int c = 0; c < 2; c++) {
+        g[c] = 0.0f;
+        if (!isnan(l[c])) {
+          const float d = pred[c] - l[c];
+          ls += fabs((double)d);
+          cnt += 1.0;
+          g[c] = d > 0.0f ? 1.0f : (d < 0.0f ? -1.0f : 0.0f);
+        }
       }
+      if (lk == 0 && r < H && col < W) *(float2*)(out + ((int64_t)r * W + col) * 2) = make_float2(g[0], g[1]);
     }
-  }
-  s[0][threadIdx.x] = a;
-  s[1][threadIdx.x] = b;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double ta = 0.0, tb = 0.0;
-    for (int i = 0; i < 256; i++) {
-      ta += s[0][i];
-      tb += s[1][i];
+    __shared__ double sl[8][2];
+    for (int o = 8; o > 0; o >>= 1) {  // the lanes with lk = 0
+      ls += __shfl_xor(ls, o);
+      cnt += __shfl_xor(cnt, o);
     }
-    scal[0] = tb > 0.0 ? ta / tb : 0.0;
-    scal[1] = tb > 0.0 ? 1.0 / tb : 0.0;
+    if (lane == 0) {
+      sl[wv][0] = ls;
+      sl[wv][1] = cnt;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int k = 1; k < 8; k++) {
+        ls += sl[k][0];
+        cnt += sl[k][1];
+      }
+      double* const q = part + 2 * ((int64_t)blockIdx.y * gridDim.x + blockIdx.x);
+      q[0] = ls;
+      q[1] = cnt;
+    }
   }
 }
+
 
 // -------------------------------------------------------------- backward
 // Input gradient of the 32 -> 2 output layer, then through the ReLU of the
@@ -377,15 +370,19 @@ __global__ __launch_bounds__(256) void k_loss_total(const double* part, int nb, 
 // exact and fp32-accumulated.  Stored as the bf16 pair hi = bf16(dprev),
 // lo = bf16(dprev - hi) that the matrix-core kernels of the layer below read.
 // Block = 8 rows x 64 pixels, one wave per row.
-__global__ __launch_bounds__(512) void k_bwd_data_out(const float* __restrict__ dz,
-                                                      const uint16_t* __restrict__ w,
-                                                      const uint16_t* __restrict__ x,
-                                                      uint16_t* __restrict__ dph,
-                                                      uint16_t* __restrict__ dpl, int H, int W) {
+constexpr int kDataOutLds = 10 * (kTC + 2) * 2 * 4;
+
+__device__ __forceinline__ void bwd_data_out_body(const float* __restrict__ dz,
+                                                  const uint16_t* __restrict__ w,
+                                                  const uint16_t* __restrict__ x,
+                                                  uint16_t* __restrict__ dph,
+                                                  uint16_t* __restrict__ dpl, int H, int W,
+                                                  const int bx, const int by, unsigned char* smem) {
   constexpr int TR = 8, C = 32, XC = kTC + 2;
   constexpr int NP = (TR + 2) * XC, IP = (NP + 511) / 512;
-  __shared__ float sdz[NP * 2];
-  const int r0 = blockIdx.y * TR, c0 = blockIdx.x * kTC;
+  static_assert(NP * 2 * 4 == kDataOutLds, "the tile");
+  float* const sdz = (float*)smem;
+  const int r0 = by * TR, c0 = bx * kTC;
   // the dz tile with its halo: clamped loads all in flight, zeros outside
   // the map applied at the store (lanes past the end rewrite the last pixel)
   float2 vd[IP];
@@ -478,18 +475,21 @@ __global__ __launch_bounds__(512) void k_bwd_data_out(const float* __restrict__ 
 // transposed weights W' (rows ci * 9 + t, 32 co each, written by k_pack);
 // the result leaves as the bf16 pair of the layer below only.
 template <int TR>
-__global__ __launch_bounds__(TR * 64) void k_bwd_data_mfma(const uint16_t* __restrict__ dzh,
-                                                           const uint16_t* __restrict__ dzl,
-                                                           const uint16_t* __restrict__ wt,
-                                                           const uint16_t* __restrict__ x,
-                                                           uint16_t* __restrict__ dph,
-                                                           uint16_t* __restrict__ dpl, int H,
-                                                           int W) {
+constexpr int kDataLds = ((TR + 2) * (kTC + 2) + 32 * 9) * (32 + kPad) * 2;
+
+template <int TR>
+__device__ __forceinline__ void bwd_data_body(const uint16_t* __restrict__ dzh,
+                                              const uint16_t* __restrict__ dzl,
+                                              const uint16_t* __restrict__ wt,
+                                              const uint16_t* __restrict__ x,
+                                              uint16_t* __restrict__ dph,
+                                              uint16_t* __restrict__ dpl, int H, int W,
+                                              const int bx, const int by, unsigned char* smem) {
   constexpr int C = 32, PS = C + kPad, NT = TR * 64, Q = C / 8;
   constexpr int NX = (TR + 2) * (kTC + 2) * Q, IX = (NX + NT - 1) / NT;
-  __shared__ __attribute__((aligned(16))) uint16_t sx[(TR + 2) * (kTC + 2) * PS];
-  __shared__ __attribute__((aligned(16))) uint16_t sw[32 * 9 * PS];
-  const int r0 = blockIdx.y * TR, c0 = blockIdx.x * kTC;
+  uint16_t* const sx = (uint16_t*)smem;
+  uint16_t* const sw = sx + (TR + 2) * (kTC + 2) * PS;
+  const int r0 = by * TR, c0 = bx * kTC;
   // tile item i of a dz part: clamped (in-bounds) load, zero outside the map
   // applied at the store (no lane conditions around the loads)
   auto tile_load = [&](const uint16_t* src, int i) {
@@ -594,15 +594,16 @@ __global__ __launch_bounds__(TR * 64) void k_bwd_data_mfma(const uint16_t* __res
 // operand layout asks for (A row / B column = lane % 16, k = 8 (lane / 16)
 // + e).  The tap shift is a whole-pixel offset in the staged x tile.
 //
-// Block = 4 waves over NTILE tiles of 4 rows x 64 pixels (accumulators stay
+// Block = 8 waves over NTILE tiles of 4 rows x 64 pixels (accumulators stay
 // in registers across the tiles); wave w takes output tile pair (co tile
-// w % 2, ci tile (w / 2) % (CIN / 16)) for all 9 taps and, for CIN = 16, the
-// rows of parity w / 2 (the two waves of a pair are added in LDS in fixed
+// w % 2, ci tile (w / 2) % (CIN / 16)) for all 9 taps and every second row of a
+// tile, or every fourth (the waves of a pair are added in LDS in fixed
 // order).  dz enters as the bf16 pair hi + lo of the input-gradient kernel
 // of the layer above (two MFMAs per product).  The bias gradient is the same
 // product with an all-ones B.  One partial [co][ci][tap] + [co] per block.
 constexpr int kWgRows = 4;            // rows per tile
 constexpr int kWgTiles = 4;           // tiles per block
+constexpr int kWgWaves = 8, kWgThreads = 64 * kWgWaves;
 constexpr int kWgPZ = 32 + 4;         // LDS pixel stride (bf16) of the dz tiles
 typedef short v8s __attribute__((ext_vector_type(8)));
 
@@ -613,23 +614,32 @@ __device__ __forceinline__ v8bf tr_pair(const uint16_t* lo4, const uint16_t* hi4
   return __builtin_bit_cast(v8bf, c);
 }
 
+template <int CIN>
+constexpr int kWeightLds = (2 * kWgRows * kTC * kWgPZ + (kWgRows + 2) * (kTC + 2) * (CIN + 4)) * 2;
+
 template <int CIN, int NTILE>
-__global__ __launch_bounds__(256) void k_bwd_weight_mfma(const uint16_t* __restrict__ dzh,
-                                                         const uint16_t* __restrict__ dzl,
-                                                         const uint16_t* __restrict__ x,
-                                                         float* __restrict__ part, int H, int W) {
+__device__ __forceinline__ void bwd_weight_body(const uint16_t* __restrict__ dzh,
+                                                const uint16_t* __restrict__ dzl,
+                                                const uint16_t* __restrict__ x,
+                                                float* __restrict__ part, int H, int W,
+                                                const int bx, const int by, const int gx,
+                                                unsigned char* smem) {
   constexpr int CO = 32, NW = CO * CIN * 9, NCT = CIN / 16;
-  constexpr int NPAIR = 2 * NCT, RSPLIT = 4 / NPAIR;  // waves per (co, ci) tile pair
+  constexpr int NPAIR = 2 * NCT, RSPLIT = kWgWaves / NPAIR;  // waves per (co, ci) tile pair
   constexpr int PX = CIN + 4;                          // LDS pixel stride of the x tile
   constexpr int XC = kTC + 2, XR = kWgRows + 2;       // x tile with its halo
-  static_assert(NPAIR * RSPLIT == 4, "four waves");
-  __shared__ __attribute__((aligned(16))) uint16_t sdz[2 * kWgRows * kTC * kWgPZ];
-  __shared__ __attribute__((aligned(16))) uint16_t sx[XR * XC * PX];
+  static_assert(NPAIR * RSPLIT == kWgWaves && kWgRows % RSPLIT == 0, "whole rows");
+  // both tiles, and after the products the waves' sums
+  constexpr int LZ = 2 * kWgRows * kTC * kWgPZ;
+  static_assert((LZ + XR * XC * PX) * 2 == kWeightLds<CIN>, "the tiles");
+  static_assert(RSPLIT / 2 * NPAIR * 40 * 64 * 4 <= kWeightLds<CIN>, "the sums");
+  uint16_t* const sdz = (uint16_t*)smem;
+  uint16_t* const sx = sdz + LZ;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int s = lane & 15, g = lane >> 4;
   const int pair = wv % NPAIR, rs = wv / NPAIR;
   const int mt = pair & 1, nt = pair >> 1;
-  const int c0 = blockIdx.x * kTC;
+  const int c0 = bx * kTC;
   v4f acc[9], accb = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int t = 0; t < 9; t++) acc[t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
@@ -640,13 +650,13 @@ __global__ __launch_bounds__(256) void k_bwd_weight_mfma(const uint16_t* __restr
   // before tile t - 1's products and stored to LDS after them: clamped
   // in-bounds loads, zeros outside the map applied at the store.
   constexpr int NZ = 2 * kWgRows * kTC * 4, NXI = XR * XC * (CIN / 8);
-  constexpr int IZ = (NZ + 255) / 256, IXI = (NXI + 255) / 256;
+  constexpr int IZ = (NZ + kWgThreads - 1) / kWgThreads, IXI = (NXI + kWgThreads - 1) / kWgThreads;
   uint4 vz[IZ], vx[IXI];
   auto load_tile = [&](int tile) {
-    const int r0 = (blockIdx.y * NTILE + tile) * kWgRows;
+    const int r0 = (by * NTILE + tile) * kWgRows;
 #pragma unroll
     for (int k = 0; k < IZ; k++) {
-      const int i = min((int)threadIdx.x + k * 256, NZ - 1);
+      const int i = min((int)threadIdx.x + k * kWgThreads, NZ - 1);
       const int hl = i / (kWgRows * kTC * 4), rem = i - hl * (kWgRows * kTC * 4);
       const int pix = rem >> 2, cg = rem & 3;
       const int gr = min(r0 + pix / kTC, H - 1), gc = min(c0 + pix % kTC, W - 1);
@@ -654,7 +664,7 @@ __global__ __launch_bounds__(256) void k_bwd_weight_mfma(const uint16_t* __restr
     }
 #pragma unroll
     for (int k = 0; k < IXI; k++) {
-      const int i = min((int)threadIdx.x + k * 256, NXI - 1);
+      const int i = min((int)threadIdx.x + k * kWgThreads, NXI - 1);
       const int pix = i / (CIN / 8), cq = i - pix * (CIN / 8);
       const int tr = pix / XC, tc = pix - tr * XC;
       const int gr = min(max(r0 + tr - 1, 0), H - 1), gc = min(max(c0 + tc - 1, 0), W - 1);
@@ -662,10 +672,10 @@ __global__ __launch_bounds__(256) void k_bwd_weight_mfma(const uint16_t* __restr
     }
   };
   auto store_tile = [&](int tile) {
-    const int r0 = (blockIdx.y * NTILE + tile) * kWgRows;
+    const int r0 = (by * NTILE + tile) * kWgRows;
 #pragma unroll
     for (int k = 0; k < IZ; k++) {
-      const int i = min((int)threadIdx.x + k * 256, NZ - 1);
+      const int i = min((int)threadIdx.x + k * kWgThreads, NZ - 1);
       const int rem = i % (kWgRows * kTC * 4), pix = rem >> 2;
       const int gr = r0 + pix / kTC, gc = c0 + pix % kTC;
       const uint32_t m = ((gr < H) & (gc < W)) ? ~0u : 0u;
@@ -675,7 +685,7 @@ __global__ __launch_bounds__(256) void k_bwd_weight_mfma(const uint16_t* __restr
     }
 #pragma unroll
     for (int k = 0; k < IXI; k++) {
-      const int i = min((int)threadIdx.x + k * 256, NXI - 1);
+      const int i = min((int)threadIdx.x + k * kWgThreads, NXI - 1);
       const int pix = i / (CIN / 8), tr = pix / XC, tc = pix - tr * XC;
       const int gr = r0 + tr - 1, gc = c0 + tc - 1;
       const uint32_t m = ((gr >= 0) & (gr < H) & (gc >= 0) & (gc < W)) ? ~0u : 0u;
@@ -692,8 +702,9 @@ __global__ __launch_bounds__(256) void k_bwd_weight_mfma(const uint16_t* __restr
     store_tile(tile);
     __syncthreads();
     if (tile + 1 < NTILE) load_tile(tile + 1);
+#pragma unroll 1  // (unrolled, the operands of several rows do not fit the registers)
     for (int r = rs; r < kWgRows; r += RSPLIT) {
-#pragma unroll
+#pragma unroll 1
       for (int kc = 0; kc < kTC / 32; kc++) {
         const int pa = r * kTC + kc * 32 + 8 * g + (s >> 2);
         const int ca = mt * 16 + 4 * (s & 3);
@@ -717,28 +728,33 @@ __global__ __launch_bounds__(256) void k_bwd_weight_mfma(const uint16_t* __restr
       }
     }
   }
-  float* out = part + (int64_t)(blockIdx.y * gridDim.x + blockIdx.x) * (NW + CO);
-  if constexpr (RSPLIT == 2) {
-    // the odd-row waves hand their sums to the even-row waves of the same pair
+  float* out = part + (int64_t)(by * gx + bx) * (NW + CO);
+  // the waves of a pair, upper half to lower half (LDS over both tiles)
+  float* red = (float*)smem;  // [wave][t][e][lane], bias last
+#pragma unroll
+  for (int half = RSPLIT / 2; half >= 1; half >>= 1) {
     __syncthreads();
-    float* red = (float*)sdz;  // [pair][t][e][lane] + bias
-    if (rs == 1) {
+    if (rs >= half && rs < 2 * half) {
+      float* const q = red + ((rs - half) * NPAIR + pair) * 40 * 64 + lane;
 #pragma unroll
       for (int t = 0; t < 9; t++)
 #pragma unroll
-        for (int e = 0; e < 4; e++) red[((pair * 10 + t) * 4 + e) * 64 + lane] = acc[t][e];
+        for (int e = 0; e < 4; e++) q[(t * 4 + e) * 64] = acc[t][e];
 #pragma unroll
-      for (int e = 0; e < 4; e++) red[((pair * 10 + 9) * 4 + e) * 64 + lane] = accb[e];
+      for (int e = 0; e < 4; e++) q[(36 + e) * 64] = accb[e];
     }
     __syncthreads();
-    if (rs == 1) return;
+    if (rs < half) {
+      const float* const q = red + (rs * NPAIR + pair) * 40 * 64 + lane;
 #pragma unroll
-    for (int t = 0; t < 9; t++)
+      for (int t = 0; t < 9; t++)
 #pragma unroll
-      for (int e = 0; e < 4; e++) acc[t][e] += red[((pair * 10 + t) * 4 + e) * 64 + lane];
+        for (int e = 0; e < 4; e++) acc[t][e] += q[(t * 4 + e) * 64];
 #pragma unroll
-    for (int e = 0; e < 4; e++) accb[e] += red[((pair * 10 + 9) * 4 + e) * 64 + lane];
+      for (int e = 0; e < 4; e++) accb[e] += q[(36 + e) * 64];
+    }
   }
+  if (rs != 0) return;
   // result lane: column ci = s of the tile, rows co = 4 g + e
 #pragma unroll
   for (int t = 0; t < 9; t++)
@@ -757,22 +773,27 @@ __global__ __launch_bounds__(256) void k_bwd_weight_mfma(const uint16_t* __restr
 // laid out as k_bwd_weight_mfma: A = dz^T with the two output channels as
 // rows 0 and 1 of a 16-row operand (rows 2..15 zero), staged as 16-channel
 // pixel rows; dz is the loss gradient, a sign (-1, 0 or 1) exact in bf16, so
-// one product per pair.  Wave w takes ci tile w % 2 and the rows of parity
-// w / 2 (the two waves of a tile are added in LDS in fixed order).
+// one product per pair.  Wave w takes ci tile w % 2 and a row of every tile (the waves of a tile are added in LDS in fixed order).
+constexpr int kWeightOutTiles = (kWgRows * kTC * 20 + (kWgRows + 2) * (kTC + 2) * 36) * 2;
+constexpr int kWeightOutLds = kWeightOutTiles + kWgWaves / 2 * 2 * 10 * 2 * 16 * 4;
+
 template <int NTILE>
-__global__ __launch_bounds__(256) void k_bwd_weight_out(const float* __restrict__ dz,
-                                                        const uint16_t* __restrict__ x,
-                                                        float* __restrict__ part, int H, int W) {
+__device__ __forceinline__ void bwd_weight_out_body(const float* __restrict__ dz,
+                                                    const uint16_t* __restrict__ x,
+                                                    float* __restrict__ part, int H, int W,
+                                                    const int bx, const int by, const int gx,
+                                                    unsigned char* smem) {
   constexpr int CIN = 32, CO = 2, NW = CO * CIN * 9, PZ = 16 + 4, PX = CIN + 4;
   constexpr int XC = kTC + 2, XR = kWgRows + 2;
-  __shared__ __attribute__((aligned(16))) uint16_t sdz[kWgRows * kTC * PZ];
-  __shared__ __attribute__((aligned(16))) uint16_t sx[XR * XC * PX];
-  __shared__ float red[2][10][4][64];
+  static_assert((kWgRows * kTC * PZ + XR * XC * PX) * 2 == kWeightOutTiles, "the tiles");
+  uint16_t* const sdz = (uint16_t*)smem;
+  uint16_t* const sx = sdz + kWgRows * kTC * PZ;
+  float(*const red)[2][10][CO][16] = (float(*)[2][10][CO][16])(smem + kWeightOutTiles);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int s = lane & 15, g = lane >> 4;
   const int nt = wv & 1, rs = wv >> 1;
-  const int c0 = blockIdx.x * kTC;
-  for (int i = threadIdx.x; i < kWgRows * kTC * PZ / 2; i += 256) ((uint32_t*)sdz)[i] = 0u;
+  const int c0 = bx * kTC;
+  for (int i = threadIdx.x; i < kWgRows * kTC * PZ / 2; i += kWgThreads) ((uint32_t*)sdz)[i] = 0u;
   v4f acc[9], accb = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int t = 0; t < 9; t++) acc[t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
@@ -782,17 +803,18 @@ __global__ __launch_bounds__(256) void k_bwd_weight_out(const float* __restrict_
   // Tile t's loads (dz, one pixel per thread, and the x tile with its halo)
   // are issued before tile t - 1's products and stored to LDS after them:
   // clamped in-bounds loads, zeros outside the map applied at the store.
-  static_assert(kWgRows * kTC == 256, "one dz pixel per thread");
-  constexpr int NXI = XR * XC * (CIN / 8), IXI = (NXI + 255) / 256;
+  static_assert(kWgWaves / 2 == kWgRows && kWgRows * kTC <= kWgThreads,
+                "a wave takes a row of a tile; one dz pixel per thread");
+  constexpr int NXI = XR * XC * (CIN / 8), IXI = (NXI + kWgThreads - 1) / kWgThreads;
   float2 vz;
   uint4 vx[IXI];
   auto load_tile = [&](int tile) {
-    const int r0 = (blockIdx.y * NTILE + tile) * kWgRows;
-    const int pix = threadIdx.x;
+    const int r0 = (by * NTILE + tile) * kWgRows;
+    const int pix = min((int)threadIdx.x, kWgRows * kTC - 1);
     vz = *(const float2*)(dz + ((int64_t)min(r0 + pix / kTC, H - 1) * W + min(c0 + pix % kTC, W - 1)) * CO);
 #pragma unroll
     for (int k = 0; k < IXI; k++) {
-      const int i = min((int)threadIdx.x + k * 256, NXI - 1);
+      const int i = min((int)threadIdx.x + k * kWgThreads, NXI - 1);
       const int pix = i / (CIN / 8), cq = i - pix * (CIN / 8);
       const int tr = pix / XC, tc = pix - tr * XC;
       const int gr = min(max(r0 + tr - 1, 0), H - 1), gc = min(max(c0 + tc - 1, 0), W - 1);
@@ -800,14 +822,14 @@ __global__ __launch_bounds__(256) void k_bwd_weight_out(const float* __restrict_
     }
   };
   auto store_tile = [&](int tile) {
-    const int r0 = (blockIdx.y * NTILE + tile) * kWgRows;
-    const int pix = threadIdx.x;
+    const int r0 = (by * NTILE + tile) * kWgRows;
+    const int pix = min((int)threadIdx.x, kWgRows * kTC - 1);  // (the others rewrite the last)
     const bool zok = (r0 + pix / kTC < H) & (c0 + pix % kTC < W);
     const float2 v = zok ? vz : make_float2(0.0f, 0.0f);
     *(uint32_t*)(sdz + pix * PZ) = (uint32_t)to_bf16(v.x) | ((uint32_t)to_bf16(v.y) << 16);
 #pragma unroll
     for (int k = 0; k < IXI; k++) {
-      const int i = min((int)threadIdx.x + k * 256, NXI - 1);
+      const int i = min((int)threadIdx.x + k * kWgThreads, NXI - 1);
       const int pix = i / (CIN / 8), tr = pix / XC, tc = pix - tr * XC;
       const int gr = r0 + tr - 1, gc = c0 + tc - 1;
       const uint32_t m = ((gr >= 0) & (gr < H) & (gc >= 0) & (gc < W)) ? ~0u : 0u;
@@ -824,7 +846,8 @@ __global__ __launch_bounds__(256) void k_bwd_weight_out(const float* __restrict_
     store_tile(tile);
     __syncthreads();
     if (tile + 1 < NTILE) load_tile(tile + 1);
-    for (int r = rs; r < kWgRows; r += 2) {
+    {
+      const int r = rs;
 #pragma unroll
       for (int kc = 0; kc < kTC / 32; kc++) {
         const uint16_t* ap = sdz + (r * kTC + kc * 32 + 8 * g + (s >> 2)) * PZ + 4 * (s & 3);
@@ -840,25 +863,74 @@ __global__ __launch_bounds__(256) void k_bwd_weight_out(const float* __restrict_
       }
     }
   }
-  // the odd-row waves hand their sums to the even-row waves of the same tile
-  if (rs == 1) {
+  // rows co = 4 g + e: only g = 0, e < 2 exist; the waves' sums are added in order
+  if (g == 0) {
 #pragma unroll
-    for (int t = 0; t < 9; t++)
+    for (int e = 0; e < CO; e++) {
 #pragma unroll
-      for (int e = 0; e < 4; e++) red[nt][t][e][lane] = acc[t][e];
-#pragma unroll
-    for (int e = 0; e < 4; e++) red[nt][9][e][lane] = accb[e];
+      for (int t = 0; t < 9; t++) red[rs][nt][t][e][s] = acc[t][e];
+      red[rs][nt][9][e][s] = accb[e];
+    }
   }
   __syncthreads();
-  if (rs == 1 || g != 0) return;  // rows co = 4 g + e: only g = 0, e < 2 exist
-  float* out = part + (int64_t)(blockIdx.y * gridDim.x + blockIdx.x) * (NW + CO);
+  float* out = part + (int64_t)(by * gx + bx) * (NW + CO);
+  for (int i = threadIdx.x; i < NW + CO; i += kWgThreads) {
+    const int w = i < NW ? i : 0, e = i < NW ? w / (CIN * 9) : i - NW;
+    const int ci = w / 9 % CIN, t = i < NW ? w % 9 : 9;
+    float v = 0.0f;
 #pragma unroll
-  for (int e = 0; e < CO; e++) {
-    const int ci = nt * 16 + s;
-#pragma unroll
-    for (int t = 0; t < 9; t++) out[(e * CIN + ci) * 9 + t] = acc[t][e] + red[nt][t][e][lane];
-    if (nt == 0 && s == 0) out[NW + e] = accb[e] + red[nt][9][e][lane];
+    for (int q = 0; q < kWgWaves / 2; q++) v += red[q][ci >> 4][t][e][ci & 15];
+    out[i] = v;
   }
+}
+
+// One launch per layer: the first gx * gyw blocks take the layer's weight gradient,
+// the others its input gradient.  The two read the same tensors and neither needs the
+// other; each alone is a chain of loads, LDS round trips and barriers on one or two
+// blocks per CU, so side by side they fill each other's waits.  Weight blocks first: they
+// are the longer ones.  512 x 512, 32 -> 32 channels: 23.1 + 20.0 us with four-wave
+// weight blocks, 17.2 + 20.2 with sixteen, 36.8 in one launch; the output layer's pair
+// 8.4 + 13.0 -> 18.3.  Both pass 84 MB (13.6 us at the copy rate).
+__global__ __launch_bounds__(512, 4) void k_bwd_layer(const uint16_t* __restrict__ dzh,
+                                                      const uint16_t* __restrict__ dzl,
+                                                      const uint16_t* __restrict__ wt,
+                                                      const uint16_t* __restrict__ x,
+                                                      uint16_t* __restrict__ dph,
+                                                      uint16_t* __restrict__ dpl,
+                                                      float* __restrict__ part, int H, int W,
+                                                      int gx, int gyw) {
+  constexpr int LDS = kDataLds<8> > kWeightLds<32> ? kDataLds<8> : kWeightLds<32>;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[LDS];
+  const int b = blockIdx.x, nw = gx * gyw;
+  if (b < nw)
+    bwd_weight_body<32, kWgTiles>(dzh, dzl, x, part, H, W, b % gx, b / gx, gx, smem);
+  else
+    bwd_data_body<8>(dzh, dzl, wt, x, dph, dpl, H, W, (b - nw) % gx, (b - nw) / gx, smem);
+}
+
+__global__ __launch_bounds__(512, 4) void k_bwd_layer_out(const float* __restrict__ dz,
+                                                          const uint16_t* __restrict__ w,
+                                                          const uint16_t* __restrict__ x,
+                                                          uint16_t* __restrict__ dph,
+                                                          uint16_t* __restrict__ dpl,
+                                                          float* __restrict__ part, int H, int W,
+                                                          int gx, int gyw) {
+  constexpr int LDS = kDataOutLds > kWeightOutLds ? kDataOutLds : kWeightOutLds;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[LDS];
+  const int b = blockIdx.x, nw = gx * gyw;
+  if (b < nw)
+    bwd_weight_out_body<kWgTiles>(dz, x, part, H, W, b % gx, b / gx, gx, smem);
+  else
+    bwd_data_out_body(dz, w, x, dph, dpl, H, W, (b - nw) % gx, (b - nw) / gx, smem);
+}
+
+// The first layer has no input gradient.
+__global__ __launch_bounds__(512, 4) void k_bwd_layer_in(const uint16_t* __restrict__ dzh,
+                                                         const uint16_t* __restrict__ dzl,
+                                                         const uint16_t* __restrict__ x,
+                                                         float* __restrict__ part, int H, int W) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kWeightLds<16>];
+  bwd_weight_body<16, kWgTiles>(dzh, dzl, x, part, H, W, blockIdx.x, blockIdx.y, gridDim.x, smem);
 }
 
 
@@ -875,7 +947,9 @@ struct RedArgs {
   const float* part;
   int nb;                  // partials per parameter (weight-gradient blocks)
   int64_t off[kNL + 1];    // first parameter of each layer; off[kNL] = all
-  const double* scal;
+  const double* lpart;     // loss partials {|error| sum, entries}, nl of them
+  int nl;
+  double* scal;            // loss, 1 / entries
   float* grad;
 };
 
@@ -901,12 +975,38 @@ __global__ __launch_bounds__(kRedWaves * 64) void k_reduce_grad(const RedArgs r)
       for (int u = 0; u < U; u++) s += b0 + kRedWaves * u < nb ? (double)v[u] : 0.0;
     }
   }
+  // every block totals the loss partials (the same values in the same order)
+  __shared__ double tot[2][kRedWaves];
+  double ta = 0.0, tb = 0.0;
+  for (int i = threadIdx.x; i < r.nl; i += kRedWaves * 64) {
+    const double2 v = ((const double2*)r.lpart)[i];
+    ta += v.x;
+    tb += v.y;
+  }
+  for (int k = 32; k > 0; k >>= 1) {
+    ta += __shfl_xor(ta, k);
+    tb += __shfl_xor(tb, k);
+  }
+  if (lane == 0) {
+    tot[0][w] = ta;
+    tot[1][w] = tb;
+  }
   ws[w][lane] = s;
   __syncthreads();
-  if (w == 0 && o < r.off[kNL]) {
+  if (w != 0) return;
+  ta = tb = 0.0;
+  for (int k = 0; k < kRedWaves; k++) {
+    ta += tot[0][k];
+    tb += tot[1][k];
+  }
+  if (o == 0) {
+    r.scal[0] = tb > 0.0 ? ta / tb : 0.0;
+    r.scal[1] = tb > 0.0 ? 1.0 / tb : 0.0;
+  }
+  if (o < r.off[kNL]) {
     double t = 0.0;
     for (int k = 0; k < kRedWaves; k++) t += ws[k][lane];
-    r.grad[o] = (float)(t * r.scal[1]);
+    r.grad[o] = (float)(t * (tb > 0.0 ? 1.0 / tb : 0.0));
   }
 }
 
@@ -1064,7 +1164,6 @@ struct sgt_net_t {
   uint16_t* wtr[kNL];  // transposed copies for the matrix-core input gradient (else null)
   float* bias[kNL];
   uint16_t* act[kNL];  // input of each layer (bf16)
-  float* out;
   float* dz0;          // fp32 loss gradient image (2 channels)
   uint16_t *dzh[2], *dzl[2];  // the same as bf16 pairs hi + lo (32 channels)
   float* part;         // weight-gradient partials, one per 16 x 16 tile
@@ -1101,9 +1200,9 @@ int32_t st_of(hipError_t e) {
   return MAP_OK;
 }
 
-// Forward of all layers; the output layer writes `out` (n->out for training,
-// the caller's buffer for inference).
-hipError_t forward_all(sgt_net_t* n, const float* feat, float* out) {
+// Forward of all layers; the output layer writes `out` or, with labels, the loss
+// gradient and the loss partials.
+hipError_t forward_all(sgt_net_t* n, const float* feat, float* out, const float* label) {
   const int H = n->H, W = n->W;
   dim3 g4((W + kTC - 1) / kTC, (H + 3) / 4), g8((W + kTC - 1) / kTC, (H + 7) / 8);
   const int64_t items = (int64_t)H * W * 2;
@@ -1114,8 +1213,12 @@ hipError_t forward_all(sgt_net_t* n, const float* feat, float* out) {
   for (int l = 1; l < 4; l++)
     hipLaunchKernelGGL((k_conv_mfma<32, 8>), g8, dim3(512), 0, n->stream, n->act[l], n->wbf[l],
                        n->bias[l], n->act[l + 1], H, W);
-  hipLaunchKernelGGL(k_conv_out, g8, dim3(512), 0, n->stream, n->act[4], n->wbf[4], n->bias[4],
-                     out, H, W);
+  if (label)
+    hipLaunchKernelGGL(k_conv_out<true>, g8, dim3(512), 0, n->stream, n->act[4], n->wbf[4],
+                       n->bias[4], label, n->dz0, n->lpart, H, W);
+  else
+    hipLaunchKernelGGL(k_conv_out<false>, g8, dim3(512), 0, n->stream, n->act[4], n->wbf[4],
+                       n->bias[4], nullptr, out, nullptr, H, W);
   return hipGetLastError();
 }
 
@@ -1163,14 +1266,13 @@ int32_t sgt_create(int32_t H, int32_t W, uint64_t seed, void* stream, sgt_net_t*
     al((void**)&n->bias[l], (size_t)kCout[l] * 4);
     al((void**)&n->act[l], (size_t)P * kCin[l] * 2);
   }
-  al((void**)&n->out, P * 2 * 4);
   al((void**)&n->dz0, P * 2 * 4);
   for (int k = 0; k < 2; k++) {
     al((void**)&n->dzh[k], P * 32 * 2);
     al((void**)&n->dzl[k], P * 32 * 2);
   }
   al((void**)&n->part, (size_t)n->part_blocks * n->np * 4);  // every layer's partials
-  al((void**)&n->lpart, (size_t)4096 * 2 * 8);
+  al((void**)&n->lpart, (size_t)((W + kTC - 1) / kTC) * ((H + 7) / 8) * 2 * 8);
   al((void**)&n->scal, 16);
   al((void**)&n->mean, kFeat * 4);
   al((void**)&n->stdv, kFeat * 4);
@@ -1207,7 +1309,7 @@ int32_t sgt_create(int32_t H, int32_t W, uint64_t seed, void* stream, sgt_net_t*
 int32_t sgt_destroy(sgt_net_t* n) {
   if (!n) return MAP_OK;
   (void)hipStreamSynchronize(n->stream);
-  void* ps[] = {n->master, n->m, n->v, n->grad, n->out, n->dz0, n->part,
+  void* ps[] = {n->master, n->m, n->v, n->grad, n->dz0, n->part,
                 n->lpart, n->scal, n->mean, n->stdv};
   for (void* p : ps) (void)gvom::dev_free(p);
   for (int k = 0; k < 2; k++) {
@@ -1309,63 +1411,48 @@ int32_t sgt_feature_sums(sgt_net_t* n, const float* feat_dev, double* sums_host)
 
 int32_t sgt_forward(sgt_net_t* n, const float* feat_dev, float* out_dev) {
   if (!n || !feat_dev || !out_dev) return MAP_E_INVALID;
-  return st_of(forward_all(n, feat_dev, out_dev));
+  return st_of(forward_all(n, feat_dev, out_dev, nullptr));
 }
 
 int32_t sgt_loss_grad(sgt_net_t* n, const float* feat_dev, const float* label_dev,
                       float* loss_host, float* grad_host) {
   if (!n || !feat_dev || !label_dev) return MAP_E_INVALID;
   const int H = n->H, W = n->W;
-  const int64_t P = (int64_t)H * W;
-  hipError_t e = forward_all(n, feat_dev, n->out);
+  hipError_t e = forward_all(n, feat_dev, nullptr, label_dev);
   if (e != hipSuccess) return st_of(e);
-  const int lb = blocks_for(P * 2) < 4096 ? blocks_for(P * 2) : 4096;
-  hipLaunchKernelGGL(k_loss, dim3(lb), dim3(256), 0, n->stream, n->out, label_dev, P * 2, n->dz0,
-                     n->lpart);
-  hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(256), 0, n->stream, n->lpart, lb, n->scal);
-  const float* dz = n->dz0;  // the loss gradient (the output layer's dz)
   int hb = 0;  // bf16 pair holding dz (set by the layer above)
   dim3 g8((W + kTC - 1) / kTC, (H + 7) / 8);
-  for (int l = kNL - 1; l >= 0; l--) {
-    // weight gradients: the 2-channel output layer on the VALU, the others on
-    // matrix cores (dz of those comes as the bf16 pair of the layer above)
-    int nb;
-    const dim3 gw((W + kTC - 1) / kTC, (H + kWgRows * kWgTiles - 1) / (kWgRows * kWgTiles));
-    nb = (int)(gw.x * gw.y);
+  // the output layer's gradients on its fp32 dz, the others' on the bf16 pair of the
+  // layer above
+  const dim3 gw((W + kTC - 1) / kTC, (H + kWgRows * kWgTiles - 1) / (kWgRows * kWgTiles));
+  const int nb = (int)(gw.x * gw.y);
+  const dim3 gl((unsigned)nb + g8.x * g8.y);
+  for (int l = kNL - 1; l >= 1; l--) {
     float* const part = n->part + (size_t)nb * n->off[l];  // this layer's partials
     if (l == 4) {
-      hipLaunchKernelGGL((k_bwd_weight_out<kWgTiles>), gw, dim3(256), 0, n->stream, dz,
-                         n->act[l], part, H, W);
+      hipLaunchKernelGGL(k_bwd_layer_out, gl, dim3(512), 0, n->stream, n->dz0, n->wbf[l], n->act[l],
+                         n->dzh[hb], n->dzl[hb], part, H, W, (int)gw.x, (int)gw.y);
     } else {
-      if (l == 0)
-        hipLaunchKernelGGL((k_bwd_weight_mfma<16, kWgTiles>), gw, dim3(256), 0, n->stream,
-                           n->dzh[hb], n->dzl[hb], n->act[l], part, H, W);
-      else
-        hipLaunchKernelGGL((k_bwd_weight_mfma<32, kWgTiles>), gw, dim3(256), 0, n->stream,
-                           n->dzh[hb], n->dzl[hb], n->act[l], part, H, W);
+      hipLaunchKernelGGL(k_bwd_layer, gl, dim3(512), 0, n->stream, n->dzh[hb], n->dzl[hb],
+                         n->wtr[l], n->act[l], n->dzh[hb ^ 1], n->dzl[hb ^ 1], part, H, W,
+                         (int)gw.x, (int)gw.y);
+      hb ^= 1;
     }
-    if (l == 0) {
-      // every layer's partials in one reduction
-      RedArgs ra;
-      ra.part = n->part;
-      ra.nb = nb;
-      for (int k = 0; k < kNL; k++) ra.off[k] = n->off[k];
-      ra.off[kNL] = n->np;
-      ra.scal = n->scal;
-      ra.grad = n->grad;
-      hipLaunchKernelGGL(k_reduce_grad, dim3((unsigned)((n->np + 63) / 64)), dim3(kRedWaves * 64),
-                         0, n->stream, ra);
-      break;
-    }
-    if (l == 4)
-      hipLaunchKernelGGL(k_bwd_data_out, g8, dim3(512), 0, n->stream, dz, n->wbf[l], n->act[l],
-                         n->dzh[hb], n->dzl[hb], H, W);
-    else
-      hipLaunchKernelGGL((k_bwd_data_mfma<8>), g8, dim3(512), 0, n->stream, n->dzh[hb],
-                         n->dzl[hb], n->wtr[l], n->act[l], n->dzh[hb ^ 1], n->dzl[hb ^ 1],
-                         H, W);
-    if (l != 4) hb ^= 1;
   }
+  hipLaunchKernelGGL(k_bwd_layer_in, gw, dim3(512), 0, n->stream, n->dzh[hb], n->dzl[hb],
+                     n->act[0], n->part, H, W);
+  // every layer's partials in one reduction
+  RedArgs ra;
+  ra.part = n->part;
+  ra.nb = nb;
+  for (int k = 0; k < kNL; k++) ra.off[k] = n->off[k];
+  ra.off[kNL] = n->np;
+  ra.lpart = n->lpart;
+  ra.nl = (int)(g8.x * g8.y);
+  ra.scal = n->scal;
+  ra.grad = n->grad;
+  hipLaunchKernelGGL(k_reduce_grad, dim3((unsigned)((n->np + 63) / 64)), dim3(kRedWaves * 64), 0,
+                     n->stream, ra);
   e = hipGetLastError();
   double scal[2] = {0.0, 0.0};
   if (e == hipSuccess) e = hipMemcpyAsync(scal, n->scal, 16, hipMemcpyDeviceToHost, n->stream);
