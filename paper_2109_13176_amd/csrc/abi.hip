@@ -317,6 +317,7 @@ int32_t map_create(const map_params_t* p, void* stream, map_t** out) {
   if (e == hipSuccess) e = dmalloc(&m->stats, kStatsBytes);
   if (e == hipSuccess) e = dmalloc(&m->err, 4);
   if (e == hipSuccess) e = dmalloc(&m->nocc, 8);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&m->host, 8, 0);
   if (e == hipSuccess) e = dmalloc(&m->part_trace, m->part_trace_cap * 32);
   if (e == hipSuccess) e = dmalloc(&m->box_rep, (int64_t)gvom::kBoxReps * gvom::kBoxCells * 4);
   if (e == hipSuccess)
@@ -357,6 +358,7 @@ int32_t map_destroy(map_t* m) {
   (void)gvom::dev_free(m->stats);
   (void)gvom::dev_free(m->err);
   (void)gvom::dev_free(m->nocc);
+  (void)hipHostFree(m->host);
   (void)gvom::dev_free(m->touch);
   (void)gvom::dev_free(m->rays);
   (void)gvom::dev_free(m->witems);
@@ -807,11 +809,11 @@ int32_t map_export_voxels(map_t* m, int32_t* lut_dev, map_voxel_t* data_dev, int
   if (!m || !n_occupied) return MAP_E_INVALID;
   int32_t s = map_export_voxels_async(m, lut_dev, data_dev, cap, m->nocc, origin_vox);
   if (s) return s;
-  int64_t count = 0;
-  hipError_t e = hipMemcpyAsync(&count, m->nocc, 8, hipMemcpyDeviceToHost, m->stream);
+  hipError_t e = hipMemcpyAsync(m->host, m->nocc, 8, hipMemcpyDeviceToHost, m->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
   s = dev_status(m, e);
   if (s) return s;
+  const int64_t count = *m->host;
   *n_occupied = count;
   return count > cap ? MAP_E_CAPACITY : MAP_OK;
 }
@@ -858,14 +860,14 @@ int32_t map_import_voxels(map_t* m, const int32_t* lut_dev, const map_voxel_t* d
   m->ranked = false;
   m->empty = false;
   m->version = gvom::next_version();
-  int32_t err = 0;
   hipError_t e = hipMemsetAsync(m->err, 0, 4, m->stream);
   if (e == hipSuccess)
     e = gvom::launch_import(m->d, lut_dev, data_dev, n_data, m->hits, m->passes, m->minqz,
                             m->occ, m->origin[2], m->err, m->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(&err, m->err, 4, hipMemcpyDeviceToHost, m->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(m->host, m->err, 4, hipMemcpyDeviceToHost, m->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
   if (e != hipSuccess) return dev_status(m, e);
+  const int32_t err = *(const int32_t*)m->host;
   m->wild = (err & 2) != 0;
   if (err & 1) {
     m->wild = false;

@@ -25,6 +25,9 @@ struct map_t {
   unsigned long long* stats;  // 8 counters
   int32_t* err;
   int64_t* nocc;              // occupied-voxel count of a synchronous table export
+  // pinned: where the small readbacks of a call land (into ordinary memory each copy
+  // passed through a buffer of the runtime's, 7 us more)
+  int64_t* host;
   uint32_t* touch;            // distinct-voxel bitmaps, allocated on first use
   int4* rays;                 // per-ray records of the current insert
   int2* witems;               // its wave items

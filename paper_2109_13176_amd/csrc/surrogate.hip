@@ -1169,13 +1169,16 @@ struct sgt_net_t {
   float* part;         // weight-gradient partials, one per 16 x 16 tile
   int part_blocks;
   double* lpart;
-  double* scal;
+  double* scal;        // behind the gradient, so that one copy brings both to the host
+  unsigned char* host; // pinned, for that copy
   float* mean;
   float* stdv;
   int64_t t;           // Adam step
 };
 
 namespace {
+
+size_t grad_bytes(const sgt_net_t* n) { return ((size_t)n->np * 4 + 15) & ~(size_t)15; }
 
 hipError_t pack_all(sgt_net_t* n) {
   PackArgs pa;
@@ -1259,7 +1262,7 @@ int32_t sgt_create(int32_t H, int32_t W, uint64_t seed, void* stream, sgt_net_t*
   al((void**)&n->master, n->np * 4);
   al((void**)&n->m, n->np * 4);
   al((void**)&n->v, n->np * 4);
-  al((void**)&n->grad, n->np * 4);
+  al((void**)&n->grad, grad_bytes(n) + 16);
   for (int l = 0; l < kNL; l++) {
     al((void**)&n->wbf[l], (size_t)kCout[l] * kCin[l] * 9 * 2);
     if (l >= 1 && l <= 3) al((void**)&n->wtr[l], (size_t)kCout[l] * kCin[l] * 9 * 2);
@@ -1273,7 +1276,8 @@ int32_t sgt_create(int32_t H, int32_t W, uint64_t seed, void* stream, sgt_net_t*
   }
   al((void**)&n->part, (size_t)n->part_blocks * n->np * 4);  // every layer's partials
   al((void**)&n->lpart, (size_t)((W + kTC - 1) / kTC) * ((H + 7) / 8) * 2 * 8);
-  al((void**)&n->scal, 16);
+  if (e == hipSuccess) n->scal = (double*)((unsigned char*)n->grad + grad_bytes(n));
+  if (e == hipSuccess) e = hipHostMalloc((void**)&n->host, grad_bytes(n) + 16, 0);
   al((void**)&n->mean, kFeat * 4);
   al((void**)&n->stdv, kFeat * 4);
   if (e != hipSuccess) {
@@ -1310,8 +1314,9 @@ int32_t sgt_destroy(sgt_net_t* n) {
   if (!n) return MAP_OK;
   (void)hipStreamSynchronize(n->stream);
   void* ps[] = {n->master, n->m, n->v, n->grad, n->dz0, n->part,
-                n->lpart, n->scal, n->mean, n->stdv};
+                n->lpart, n->mean, n->stdv};
   for (void* p : ps) (void)gvom::dev_free(p);
+  (void)hipHostFree(n->host);
   for (int k = 0; k < 2; k++) {
     (void)gvom::dev_free(n->dzh[k]);
     (void)gvom::dev_free(n->dzl[k]);
@@ -1455,10 +1460,15 @@ int32_t sgt_loss_grad(sgt_net_t* n, const float* feat_dev, const float* label_de
                      n->stream, ra);
   e = hipGetLastError();
   double scal[2] = {0.0, 0.0};
-  if (e == hipSuccess) e = hipMemcpyAsync(scal, n->scal, 16, hipMemcpyDeviceToHost, n->stream);
-  if (e == hipSuccess && grad_host)
-    e = hipMemcpyAsync(grad_host, n->grad, n->np * 4, hipMemcpyDeviceToHost, n->stream);
+  const size_t skip = grad_host ? 0 : grad_bytes(n), bytes = grad_bytes(n) + 16 - skip;
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(n->host + skip, (unsigned char*)n->grad + skip, bytes, hipMemcpyDeviceToHost,
+                       n->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(n->stream);
+  if (e == hipSuccess) {
+    memcpy(scal, n->host + grad_bytes(n), 16);
+    if (grad_host) memcpy(grad_host, n->host, n->np * 4);
+  }
   if (loss_host) *loss_host = (float)scal[0];
   return st_of(e);
 }
