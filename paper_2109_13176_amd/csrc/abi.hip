@@ -1170,8 +1170,12 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
     khz = 100000;
   b->clock_khz = khz;
   size_t surf = 0, lut = 0;
-  int64_t t64 = 0;
-  for (int i = 0; i < k; i++) t64 += tiles64(maps[i]);
+  int64_t t64 = 0, cols = 0, units = 0;  // virtual blocks of the column and the table pass
+  for (int i = 0; i < k; i++) {
+    t64 += tiles64(maps[i]);
+    cols += (n_col(maps[i]) + 255) / 256;
+    units += (int64_t)((maps[i]->p.nx + 3) / 4) * ((maps[i]->d.nby + 3) / 4);
+  }
   for (int i = 0; i < k; i++) {
     const map_t* m = maps[i];
     const int H = m->c.search_d > m->c.half_fit ? m->c.search_d : m->c.half_fit;
@@ -1185,11 +1189,15 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
     lut = s2 > lut ? s2 : lut;
   }
   const int cu = b->n_cu;
-  // persistent grids; the traversal's as many blocks as are resident (with eight per
-  // CU, one of them waiting for a place, 922 us instead of 770); the bandwidth-bound column and table passes get eight
-  // blocks per CU (the table pass's LDS regions allow it)
-  b->grid = gvom::BatchGrid{cu * 4, cu * gvom::kTraceWavesPerSimd, cu * 8, cu * 2, cu * 8,
-                            k * gvom::box_fold_blocks(), surf, lut};
+  // Grids, no larger than the maps' virtual blocks.  The traversal's as many blocks as
+  // are resident (with eight per CU, one of them waiting for a place, 922 us instead of
+  // 770).  The bandwidth-bound column and table passes 64 per CU: a block that goes on
+  // to its next virtual block starts that one's chain of loads only behind the last
+  // one's stores, a new block at once (32 maps, with 8 / 16 / 64 / 128 / 512 per CU: table
+  // 626 / 659 / 583 / 573 / 726 us, column 96 / 90 / 86 / 86 / 103).
+  const auto at_most = [](int64_t a, int64_t c) { return (int)(a < c ? a : c); };
+  b->grid = gvom::BatchGrid{cu * 4, cu * gvom::kTraceWavesPerSimd, at_most(cu * 64, cols), cu * 2,
+                            at_most(cu * 64, units), k * gvom::box_fold_blocks(), surf, lut};
   hipError_t e = gvom::dev_alloc((void**)&b->dtab, sizeof(gvom::BatchTables));
   if (e == hipSuccess) e = hipHostMalloc((void**)&b->htab, sizeof(gvom::BatchTables), 0);
   if (e == hipSuccess) e = gvom::dev_alloc((void**)&b->dstamps, (gvom::kMaxBatch + 2) * 8);
