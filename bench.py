@@ -42,11 +42,12 @@ def phase_bytes(params, st, n_occ):
     nx, ny, nz = params["nx"], params["ny"], params["nz"]
     V, C, W = nx * ny * nz, nx * ny, (nz + 63) // 64
     return {
-        # points read; hits and min height read+write per distinct hit voxel
-        "rays": 12 * st["n_points"] + 16 * st["n_distinct_hit"],
-        # passes read+write per distinct passed voxel
-        "trace": 8 * st["n_distinct_pass"],
-        "scroll": 12 * st["n_cleared"],
+        # points read; the voxels that left the window cleared
+        "rays": 12 * st["n_points"] + 12 * st["n_cleared"],
+        # hits and min height read+write per distinct hit voxel; passes read+write
+        # per distinct passed voxel
+        "trace": 16 * st["n_distinct_hit"] + 8 * st["n_distinct_pass"],
+        "scroll": 0,  # (whole-window clears only: none on this workload)
         # occupancy word, ground-voxel height, outputs (height, density, flags, Q height)
         "column": C * (8 * W + 4 + 13),
         # Q heights + flags in; slope, roughness, flags out
@@ -311,10 +312,11 @@ def voxel_outputs(args, params, scans, poses, flags):
     m.close()
     V = params["nx"] * params["ny"] * params["nz"]
     C = params["nx"] * params["ny"]
-    # density reads hits and passes and writes one float per voxel; the
-    # costmap reads 4 floats + 1 flag byte and writes 1 float per pixel
-    res["density_bytes"] = 12 * V
-    res["density_gbps"] = 12 * V / (res["density_us"] * 1e-6) / 1e9
+    # density reads the occupancy words and passes (hits only where a voxel is
+    # occupied) and writes one float per voxel; the costmap reads 4 floats + 1 flag
+    # byte and writes 1 float per pixel
+    res["density_bytes"] = 8 * V + 8 * C * ((params["nz"] + 63) // 64)
+    res["density_gbps"] = res["density_bytes"] / (res["density_us"] * 1e-6) / 1e9
     res["density_frac"] = res["density_gbps"] / HBM_PEAK_GBS
     res["costmap_bytes"] = 21 * C
     res["costmap_gbps"] = 21 * C / (res["costmap_us"] * 1e-6) / 1e9
