@@ -38,7 +38,7 @@ def log(*a):
 
 
 def phase_bytes(params, st, n_occ):
-    """Algorithmic HBM bytes per launch of each phase (see DESIGN.md)."""
+    """Algorithmic HBM bytes per launch of each phase."""
     nx, ny, nz = params["nx"], params["ny"], params["nz"]
     V, C, W = nx * ny * nz, nx * ny, (nz + 63) // 64
     return {
