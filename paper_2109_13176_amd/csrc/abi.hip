@@ -550,7 +550,12 @@ int32_t prepare_insert(map_t* m, const float* xyz_dev, int64_t n, const float* p
   insert_layout(m, ray_blocks, seg_len, a, &need);
   if (!grow(m, &m->rays, &m->rays_cap, ray_blocks * gvom::kRayBlock, sizeof(int4)))
     return MAP_E_OOM;
-  if (!grow(m, &m->witems, &m->witem_cap, need, sizeof(int2))) return MAP_E_OOM;
+  if (!grow(m, &m->witems, &m->witem_cap, need, sizeof(int2))) {
+    // no room for the items of shorter segments: the setting's length
+    if (seg_len == m->seg_len) return MAP_E_OOM;
+    insert_layout(m, ray_blocks, m->seg_len, a, &need);
+    if (!grow(m, &m->witems, &m->witem_cap, need, sizeof(int2))) return MAP_E_OOM;
+  }
   if (!grow(m, &m->part_rays, &m->part_rays_cap, ray_blocks, 32)) return MAP_E_OOM;
   a->rays = m->rays;
   a->witems = m->witems;
