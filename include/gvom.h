@@ -258,17 +258,17 @@ int32_t map_sync(map_t* m);
  * groups its rays by segment count), counts its passes in an LDS table of
  * 64-byte map lines and adds each line to the map with one request; the
  * passes of a 17 x 17 x 9 box around the sensor are summed per block on chip
- * first.  seg_len: dominant-axis voxels per ray segment, 1..1024 (default 8,
- * which also lets a single insert take 4 or 5 for scans of up to 49,152 or
- * 196,608 points);
+ * first.  seg_len: dominant-axis voxels per ray segment, 1..1024 (8 until it is
+ * set; a single insert of up to 49,152 or 196,608 points then takes 4 or 5);
  * trace_waves_per_cu: resident waves per compute unit requested for the
  * traversal grid (blocks of four waves), 1..32 (default 28, the most that fit
  * a compute unit); surface_tile: edge in
  * pixels of the tiles of the slope / roughness / negative-obstacle pass, 16
- * or 32 (default 32, which also lets the library take tiles of 16 or 64 where
- * the launch has very few or very many; other positive values are
- * MAP_E_INVALID).  A field
- * <= 0 keeps the current value.  The batch autotuner sets all three. */
+ * or 32 (32 until it is set; a launch with very few or very many tiles then
+ * takes 16 or 64; other positive values are MAP_E_INVALID).  A value that was
+ * set is what runs.  A field <= 0 keeps the current value.  map_get_tuning
+ * reports 8 and 32 where nothing was set.  The batch autotuner sets all three;
+ * a surface_tile of 32 among them leaves the tile to each launch again. */
 typedef struct {
   int32_t seg_len;
   int32_t trace_waves_per_cu;
@@ -396,8 +396,8 @@ int32_t map_batch_latency(const map_batch_t* b, double* ms);
 int32_t map_batch_set_graph(map_batch_t* b, int32_t enable);
 
 /* Autotuner: times every candidate tuning (seg_len 6/8/16 x
- * trace_waves_per_cu 16/28 x surface_tile 16/32) on this step's inputs with
- * batch steps, applies
+ * trace_waves_per_cu 16/28 x surface_tile 16/32, where 32 stands for the tile
+ * the batch takes by itself) on this step's inputs with batch steps, applies
  * the fastest to all maps and appends it to the text cache `cache_path`
  * (NULL: no cache).  A cached entry for the same device, map shapes and
  * point-count range is applied without timing.  The maps are left empty

@@ -24,7 +24,6 @@ using gvom::Dims;
 
 namespace {
 
-constexpr int32_t kSegLen = 8;  // default of the segment length setting
 constexpr size_t kStatsBytes = (8 + gvom::kStripes) * 8;
 
 int64_t n_vox(const map_t* m) { return (int64_t)m->p.nx * m->p.ny * m->p.nz; }
@@ -288,9 +287,10 @@ int32_t map_create(const map_params_t* p, void* stream, map_t** out) {
     delete m;
     return MAP_E_DEVICE;
   }
-  m->seg_len = kSegLen;
+  m->seg_len = 8;
   m->trace_wpc = 28;
   m->surf_tile = 32;
+  m->seg_auto = m->tile_auto = true;
   // traversal blocks (at most 32 waves per CU) + the sensor-box fold blocks
   m->part_trace_cap = (int64_t)m->n_cu * 32 / 4 + gvom::box_fold_blocks() + 1;
   m->d.nx = p->nx;
@@ -466,10 +466,10 @@ void insert_layout(const map_t* m, int64_t ray_blocks, int32_t seg_len, gvom::In
 // 25.9 / 26.2 / 29.7 us, 98,304 points 40.0 / 39.2 / 41.0, 131,072 points 49.5 / 47.0
 // / 48.1, 262,144 points 84.2 / 79.2 / 80.3, and on 1024 x 1024 x 96 126 / 121 / 114
 // (with the events that time it).  In a batch the maps fill the device together: the
-// setting as it is.  Any other setting than the default is taken as it is.
+// setting as it is.  A length that was set is taken as it is.
 int32_t lone_seg_len(const map_t* m, int64_t n) {
-  if (m->seg_len != kSegLen) return m->seg_len;
-  return n <= 49152 ? 4 : n <= 196608 ? 5 : kSegLen;
+  if (!m->seg_auto) return m->seg_len;
+  return n <= 49152 ? 4 : n <= 196608 ? 5 : m->seg_len;
 }
 
 // Everything of an insert but the per-scan buffers (a->rays, a->witems,
@@ -586,6 +586,15 @@ void column_args(const map_t* m, const map_2d_t* out, bool ranks, gvom::ColumnAr
 
 int64_t tiles64(const map_t* m) {
   return (int64_t)((m->p.nx + 63) / 64) * ((m->p.ny + 63) / 64);
+}
+
+int32_t surf_halo(const map_t* m) {
+  return m->c.search_d > m->c.half_fit ? m->c.search_d : m->c.half_fit;
+}
+
+// Tile edge of the surface pass in a launch of t64 64-pixel tiles.
+int32_t surf_tile(const map_t* m, int64_t t64) {
+  return m->tile_auto ? gvom::surface_tile_for(surf_halo(m), t64, m->n_cu) : m->surf_tile;
 }
 
 // ranks: the launch also sums the group counts of the column pass
@@ -782,9 +791,7 @@ int32_t map_export_2d(map_t* m, const map_2d_t* out) {
     gvom::SurfaceArgs sa;
     surface_args(m, out, true, &sa);
     pm = prof_begin(m, MAP_PROF_SURFACE);
-    const int H = sa.search_d > sa.half_fit ? sa.search_d : sa.half_fit;
-    const int tile = gvom::surface_tile_for(H, m->surf_tile, tiles64(m), m->n_cu);
-    e = gvom::launch_surface(sa, tile, m->stream);
+    e = gvom::launch_surface(sa, surf_tile(m, tiles64(m)), m->stream);
     prof_end(m, pm);
     m->ranked = e == hipSuccess;
   }
@@ -941,12 +948,18 @@ int32_t map_sync(map_t* m) {
 int32_t map_set_tuning(map_t* m, const map_tuning_t* t) {
   if (!m || !t) return MAP_E_INVALID;
   if (t->seg_len > 1024 || t->trace_waves_per_cu > 32) return MAP_E_INVALID;
-  if (!(t->surface_tile <= 0 || t->surface_tile == 16 || t->surface_tile == 32 ))
+  if (!(t->surface_tile <= 0 || t->surface_tile == 16 || t->surface_tile == 32))
     return MAP_E_INVALID;
   // the wave-item buffer is sized for the segment length at the next insert
-  if (t->seg_len > 0) m->seg_len = t->seg_len;
+  if (t->seg_len > 0) {
+    m->seg_len = t->seg_len;
+    m->seg_auto = false;
+  }
   if (t->trace_waves_per_cu > 0) m->trace_wpc = t->trace_waves_per_cu;
-  if (t->surface_tile > 0) m->surf_tile = t->surface_tile;
+  if (t->surface_tile > 0) {
+    m->surf_tile = t->surface_tile;
+    m->tile_auto = false;
+  }
   return MAP_OK;
 }
 
@@ -1020,6 +1033,13 @@ void batch_fail(map_batch_t* b, hipError_t e = hipSuccess) {
   for (int i = 0; i < b->k; i++) b->maps[i]->sticky = MAP_E_DEVICE;
 }
 
+void drop_graph(map_batch_t* b) {
+  if (!b->captured) return;
+  (void)hipGraphExecDestroy(b->exec);
+  (void)hipGraphDestroy(b->graph);
+  b->captured = false;
+}
+
 // Fills the step table; the caller has checked every request.
 int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t* n,
                       const float* poses, const uint32_t* flags, const map_2d_t* out2d,
@@ -1031,6 +1051,7 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
   st.pre_rays[0] = st.pre_trace[0] = st.pre_col[0] = st.pre_surf[0] = 0;
   st.pre_lwrite[0] = 0;
   int64_t t64 = 0;
+  size_t surf_lds = 0;
   for (int i = 0; i < b->k; i++) t64 += tiles64(b->maps[i]);
   for (int i = 0; i < b->k; i++) {
     map_t* m = b->maps[i];
@@ -1056,9 +1077,11 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
     }
     const int64_t C = (int64_t)m->p.nx * m->p.ny;
     const int ray_blocks = (int)((n[i] + gvom::kRayBlock - 1) / gvom::kRayBlock);
-    st.surf_H[i] = m->c.search_d > m->c.half_fit ? m->c.search_d : m->c.half_fit;
-    const int tile = gvom::surface_tile_for(st.surf_H[i], m->surf_tile, t64, b->n_cu);
+    st.surf_H[i] = surf_halo(m);
+    const int tile = surf_tile(m, t64);
     st.surf_tile[i] = tile;
+    const size_t lds = gvom::surface_lds(st.surf_H[i], tile);
+    surf_lds = lds > surf_lds ? lds : surf_lds;
     const int tiles_y = (m->p.ny + tile - 1) / tile;
     const int tiles = ((m->p.nx + tile - 1) / tile) * tiles_y;
     const int lw_by = (m->d.nby + 3) / 4;
@@ -1074,6 +1097,12 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
     st.nz_magic[i] = gvom::nz_magic(m->p.nz);
     st.last_is_lut[i] = lut ? 1 : 0;
     (void)full;  // a whole-window clear is the plan's single full box
+  }
+  // the recorded launches hold the surface pass's LDS: once it changes (a tile was
+  // set), they are recorded anew
+  if (surf_lds != b->grid.surf_lds) {
+    drop_graph(b);
+    b->grid.surf_lds = surf_lds;
   }
   return MAP_OK;
 }
@@ -1174,24 +1203,13 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
   if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0)
     khz = 100000;
   b->clock_khz = khz;
-  size_t surf = 0, lut = 0;
-  int64_t t64 = 0, cols = 0, units = 0;  // virtual blocks of the column and the table pass
+  size_t lut = 0;
+  int64_t cols = 0, units = 0;  // virtual blocks of the column and the table pass
   for (int i = 0; i < k; i++) {
-    t64 += tiles64(maps[i]);
+    const size_t s = gvom::lut_lds(maps[i]->p.nz);
+    lut = s > lut ? s : lut;
     cols += (n_col(maps[i]) + 255) / 256;
     units += (int64_t)((maps[i]->p.nx + 3) / 4) * ((maps[i]->d.nby + 3) / 4);
-  }
-  for (int i = 0; i < k; i++) {
-    const map_t* m = maps[i];
-    const int H = m->c.search_d > m->c.half_fit ? m->c.search_d : m->c.half_fit;
-    // any tile size (the maps' tuning may change before a step)
-    const size_t s2 = gvom::lut_lds(m->p.nz);
-    for (int tile = 16; tile <= 32; tile *= 2) {
-      const int t = gvom::surface_tile_for(H, tile, t64, b->n_cu);
-      const size_t s1 = gvom::surface_lds(H, t);
-      surf = s1 > surf ? s1 : surf;
-    }
-    lut = s2 > lut ? s2 : lut;
   }
   const int cu = b->n_cu;
   // Grids, no larger than the maps' virtual blocks.  The traversal's as many blocks as
@@ -1202,7 +1220,7 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
   // 626 / 659 / 583 / 573 / 726 us, column 96 / 90 / 86 / 86 / 103).
   const auto at_most = [](int64_t a, int64_t c) { return (int)(a < c ? a : c); };
   b->grid = gvom::BatchGrid{cu * 4, cu * gvom::kTraceWavesPerSimd, at_most(cu * 64, cols), cu * 2,
-                            at_most(cu * 64, units), k * gvom::box_fold_blocks(), surf, lut};
+                            at_most(cu * 64, units), k * gvom::box_fold_blocks(), 0, lut};
   hipError_t e = gvom::dev_alloc((void**)&b->dtab, sizeof(gvom::BatchTables));
   if (e == hipSuccess) e = hipHostMalloc((void**)&b->htab, sizeof(gvom::BatchTables), 0);
   if (e == hipSuccess) e = gvom::dev_alloc((void**)&b->dstamps, (gvom::kMaxBatch + 2) * 8);
@@ -1220,10 +1238,7 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
 int32_t map_batch_destroy(map_batch_t* b) {
   if (!b) return MAP_OK;
   (void)hipStreamSynchronize(b->stream);
-  if (b->captured) {
-    (void)hipGraphExecDestroy(b->exec);
-    (void)hipGraphDestroy(b->graph);
-  }
+  drop_graph(b);
   (void)gvom::dev_free(b->dtab);
   (void)hipHostFree(b->htab);
   (void)gvom::dev_free(b->dstamps);
@@ -1280,6 +1295,12 @@ int32_t map_batch_autotune(map_batch_t* b, const float* const* xyz_dev, const in
   }
   for (char& c : key)
     if (c == ' ') c = '_';
+  // a surface tile of 32 stands for the library's choice (32, in a large launch 64)
+  const auto apply = [&](const map_tuning_t& t) {
+    for (int i = 0; i < b->k; i++)
+      if (map_set_tuning(b->maps[i], &t) == MAP_OK && t.surface_tile == 32)
+        b->maps[i]->tile_auto = true;
+  };
   map_tuning_t best{0, 0, 0};
   bool cached = false;
   if (cache_path) {
@@ -1308,7 +1329,7 @@ int32_t map_batch_autotune(map_batch_t* b, const float* const* xyz_dev, const in
       for (int wi = 0; wi < 2; wi++)
         for (int ti = 0; ti < 2; ti++) {
         const map_tuning_t t{segs[si], wpcs[wi], tiles[ti]};
-        for (int i = 0; i < b->k; i++) map_set_tuning(b->maps[i], &t);
+        apply(t);
         float tot = 0.0f;
         for (int rep = 0; rep < 3; rep++) {
           for (int i = 0; i < b->k; i++) map_reset(b->maps[i]);
@@ -1340,10 +1361,8 @@ int32_t map_batch_autotune(map_batch_t* b, const float* const* xyz_dev, const in
       }
     }
   }
-  for (int i = 0; i < b->k; i++) {
-    map_set_tuning(b->maps[i], &best);
-    map_reset(b->maps[i]);
-  }
+  apply(best);
+  for (int i = 0; i < b->k; i++) map_reset(b->maps[i]);
   if (chosen) *chosen = best;
   return MAP_OK;
 }

@@ -481,8 +481,7 @@ uint32_t nz_magic(int nz) {
 // of 16 / 32 / 64, with the events' ~3 us): 128 x 128, D = 13 10.0 / 12.0 / 24.5;
 // 354 x 278, D = 20 12.7 / 14.0 / 33; 512 x 512, D = 25 24.3 / 15.8 / 37;
 // 640 x 640, D = 50 45 / 35 / 53; 1024 x 1024, D = 50 97 / 72 / 55.
-int surface_tile_for(int H, int tile, int64_t tiles64, int n_cu) {
-  if (tile != 32) return tile;
+int surface_tile_for(int H, int64_t tiles64, int n_cu) {
   if (8 * tiles64 <= n_cu) return 16;
   return tiles64 >= n_cu && surface_lds(H, 64) <= 160 * 1024 ? 64 : 32;
 }

@@ -269,9 +269,9 @@ hipError_t launch_batch_insert(const BatchTables* tab, const BatchGrid& g,
 hipError_t launch_batch_export(const BatchTables* tab, const BatchGrid& g,
                                unsigned long long* stamps, hipStream_t s);
 size_t surface_lds(int H, int tile);
-// Tile edge of the surface pass for a map tuned to `tile`; tiles64 = tiles of
-// 64 pixels in the launch.
-int surface_tile_for(int H, int tile, int64_t tiles64, int n_cu);
+// The library's choice of the surface pass's tile edge; tiles64 = tiles of 64
+// pixels in the launch.
+int surface_tile_for(int H, int64_t tiles64, int n_cu);
 size_t lut_lds(int nz);
 uint32_t nz_magic(int nz);
 

@@ -36,9 +36,12 @@ struct map_t {
   unsigned long long* part_trace;  // per-block counters of the traversal pass
   int64_t part_rays_cap, part_trace_cap;
   int64_t last_ray_blocks, last_trace_blocks;
+  // settings; the segment length and the surface tile (16 or 32) stand for a choice
+  // of the library's, made at each launch, until one is set
   int32_t seg_len;
   int32_t trace_wpc;
-  int32_t surf_tile;           // 16 or 32
+  int32_t surf_tile;
+  bool seg_auto, tile_auto;
   int32_t* box_rep;           // sensor-box replicas of the segmented traversal
   int32_t n_cu;
   int32_t sticky;

@@ -1,0 +1,98 @@
+"""Launch tuning: a value the caller sets is what runs, and where the library
+chooses (a map whose tuning was never set) results are the oracle's on both sides
+of its lines (needs an MI355X).  Integers and height bits are compared exactly, by
+the comparison rules of the other parity tests."""
+import numpy as np
+import pytest
+import torch
+
+from conftest import params
+from parity_util import Pair, compare_2d, compare_all, compare_2d_arrays, host_2d
+
+pytestmark = pytest.mark.gpu
+
+POSE = np.concatenate([np.eye(3, dtype=np.float32),
+                       np.array([[0.1], [0.2], [0.3]], np.float32)], 1).reshape(12)
+
+
+def _cloud(n, radius, seed):
+    rng = np.random.default_rng(seed)
+    return rng.uniform(-radius, radius, (n, 3)).astype(np.float32)
+
+
+def _insert_bytes(dims, n, seg_len):
+    """Bytes of the work buffers of a map's first insert: a 16-byte record per ray of
+    every block of 512, 8 bytes for every wave item a block's 8 waves can have (one per
+    segment of the window's longest axis), 32 bytes of counters per block."""
+    blocks = (n + 511) // 512
+    return blocks * (512 * 16 + 8 * ((max(dims) - 1) // seg_len + 1) * 8 + 32)
+
+
+# a map's own choice: 4 up to 49,152 points, 5 up to 196,608, then 8
+@pytest.mark.parametrize("n,set_len,runs", [
+    (1500, 8, 8), (131072, 8, 8), (131072, 5, 5), (200000, 3, 3),
+    (49152, 0, 4), (49153, 0, 5), (196608, 0, 5), (196609, 0, 8),
+])
+def test_segment_length_that_runs(n, set_len, runs):
+    from paper_2109_13176_amd import gvom
+    dims = (64, 48, 16)
+    pair = Pair(params(*dims, 0.5), set_len)
+    try:
+        used = gvom.lib().map_device_memory_in_use()
+        assert pair.insert(_cloud(n, 20.0, n), POSE) == 0
+        assert gvom.lib().map_device_memory_in_use() - used == _insert_bytes(dims, n, runs)
+        compare_all(pair)
+        assert gvom.map_get_tuning(pair.g.h)[1]["seg_len"] == (set_len or 8)
+    finally:
+        pair.close()
+
+
+# windows where the library takes 16, 32 and 64 pixels by itself; 31 rings and more
+@pytest.mark.parametrize("nx,ny,res", [(62, 98, 0.1), (258, 250, 0.2), (642, 514, 0.1),
+                                       (1030, 1026, 0.2)])
+def test_surface_tiles_set_and_chosen(nx, ny, res):
+    from paper_2109_13176_amd import gvom
+    pair = Pair(params(nx, ny, 16, res, szv=8))
+    try:
+        pts = _cloud(20000, 0.4 * nx * res, nx)
+        pts[:, 2] *= 0.02
+        assert pair.insert(pts, POSE, 1) == 0
+        _, ref = compare_2d(pair)
+        for tile in (32, 16):
+            assert gvom.map_set_tuning(pair.g.h, surface_tile=tile) == 0
+            out = pair.g.export_2d()
+            torch.cuda.synchronize()
+            compare_2d_arrays(host_2d(out), ref, res)
+            assert gvom.map_get_tuning(pair.g.h)[1]["surface_tile"] == tile
+    finally:
+        pair.close()
+
+
+def test_batch_follows_tuning_set_between_steps():
+    """A batch whose maps' surface tile is set after its first step (its recorded
+    launches then no longer fit): every step equals the single-map calls."""
+    from paper_2109_13176_amd import gvom
+    ps = [params(64, 48, 16, 0.5), params(98, 62, 16, 0.1)]
+    maps, ref = [gvom.VoxelMap(p) for p in ps], [gvom.VoxelMap(p) for p in ps]
+    batch = gvom.MapBatch(maps)
+    try:
+        for k, tile in enumerate((0, 32, 16, 32)):
+            if tile:
+                for m in maps:
+                    assert gvom.map_set_tuning(m.h, surface_tile=tile) == 0
+            xyz = [torch.as_tensor(_cloud(3000, 6.0, 10 * k + i), device="cuda") for i in range(2)]
+            for x in xyz:
+                x[:, 2] *= 0.05
+            batch.step(xyz, [POSE, POSE], [1, 1], [True, False])
+            torch.cuda.synchronize()
+            for i, m in enumerate(ref):
+                assert gvom.map_insert_scan(m.h, xyz[i], POSE, 1) == 0
+                want = m.export_2d()
+                torch.cuda.synchronize()
+                for key in want:
+                    assert torch.equal(maps[i].out2d[key].view(torch.uint8), want[key].view(torch.uint8)), \
+                        (k, i, key)
+    finally:
+        batch.close()
+        for m in maps + ref:
+            m.close()
