@@ -182,6 +182,8 @@ int32_t map_insert_scan(map_t* m, const float* xyz_dev, int64_t n, const float p
  * than the array holds: about 16 + 8 * ceil(max(nx, ny, nz) / seg_len) / 64
  * bytes per point, so 2.7 M points on a 512 x 512 x 64 window at the default
  * seg_len of 8.
+ * A graph that captured the call replays it on the voxels the map then holds, in
+ * the window of the capture (replays do not move the map's window).
  * MAP_STATS_DISTINCT is not accepted (MAP_E_INVALID): its bitmaps are
  * allocated on first use.  map_get_stats reports the call's counters until
  * the next insert into the same map. */
@@ -209,7 +211,10 @@ int32_t map_export_voxels(map_t* m, int32_t* lut_dev, map_voxel_t* data_dev, int
 /* The same export without waiting: M goes to the DEVICE int64
  * n_occupied_dev (valid once the stream has been synchronised) and a data
  * array that is too small is not reported (the caller compares M with cap).
- * For pipelines that keep the host off the critical path. */
+ * For pipelines that keep the host off the critical path.  May be captured: a
+ * replay exports the map as it then is.  (The voxel counts of a 2D export just
+ * before are used where both were captured into one graph, or no call on the map
+ * ever was; otherwise the export counts by itself.) */
 int32_t map_export_voxels_async(map_t* m, int32_t* lut_dev, map_voxel_t* data_dev, int64_t cap,
                                 int64_t* n_occupied_dev, int32_t origin_vox[3]);
 

@@ -88,6 +88,19 @@ void set_empty_origin(map_t* m, const int32_t o[3]) {
   if (m->empty) set_origin(m, o);
 }
 
+uint64_t capture_of(map_t* m) {
+  if (!m->stream) return 0;  // the null stream is never captured
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  if (hipStreamGetCaptureInfo(m->stream, &st, &id) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  if (st == hipStreamCaptureStatusNone) return 0;
+  m->replays = true;
+  return id;
+}
+
 uint64_t next_version() {
   static std::atomic<uint64_t> counter{0};
   return ++counter;
@@ -700,6 +713,7 @@ int32_t map_insert_scan(map_t* m, const float* xyz_dev, int64_t n, const float p
   gvom::InsertArgs a;
   gvom::ClearArgs plan;
   bool full = false;
+  (void)gvom::capture_of(m);
   m->ranked = false;
   m->version = gvom::next_version();
   const int pm0 = prof_begin(m, MAP_PROF_SCROLL);
@@ -758,6 +772,7 @@ int32_t map_insert_scan_static(map_t* m, const float* xyz_dev, int64_t n, const 
   a.witems = (int2*)base;
   base += align256((size_t)need * sizeof(int2));
   a.part_rays = (unsigned long long*)base;
+  (void)gvom::capture_of(m);
   m->ranked = false;
   m->version = gvom::next_version();
   st = fill_insert(m, xyz_dev, n, pose, flags, S, &a, &plan, &full, need);
@@ -782,6 +797,7 @@ int32_t map_insert_scan_static(map_t* m, const float* xyz_dev, int64_t n, const 
 int32_t map_export_2d(map_t* m, const map_2d_t* out) {
   if (!m || !valid_2d(out)) return MAP_E_INVALID;
   if (m->sticky) return m->sticky;
+  m->rank_capture = gvom::capture_of(m);
   gvom::ColumnArgs ca;
   column_args(m, out, true, &ca);
   int pm = prof_begin(m, MAP_PROF_COLUMN);
@@ -806,10 +822,13 @@ int32_t map_export_voxels_async(map_t* m, int32_t* lut_dev, map_voxel_t* data_de
   gvom::LutArgs a;
   lut_args(m, lut_dev, data_dev, cap, n_occupied_dev, &a);
   const int pm = prof_begin(m, MAP_PROF_LUT);
-  // the ranks of a 2D export since the last change of the map are used once: an
-  // export on its own always makes them, so that a captured one replays on
-  // whatever the map then holds
-  hipError_t e = gvom::launch_lut(a, m->ranked, m->stream);
+  // The ranks of a 2D export since the last change of the map are used once, and only
+  // where both exports run together: both captured into one graph, or neither in any
+  // and no call on the map ever captured (a replay between them, which the host does
+  // not see, may change the map or the ranks).  Any other export makes its own.
+  const uint64_t capture = gvom::capture_of(m);
+  const bool ranked = m->ranked && capture == m->rank_capture && (capture || !m->replays);
+  hipError_t e = gvom::launch_lut(a, ranked, m->stream);
   m->ranked = false;
   prof_end(m, pm);
   for (int i = 0; i < 3; i++) origin_vox[i] = m->origin[i];

@@ -939,6 +939,7 @@ int32_t map_buffer_combine(map_buffer_t* b, map_t* out) {
   hipError_t e = hipStreamWaitEvent(out->stream, b->pushed, 0);
   const map_buffer_t::Slot& nw = slot_of(b, b->npush - 1);
   gvom::set_origin(out, nw.origin);
+  (void)gvom::capture_of(out);
   out->ranked = false;
   out->empty = false;
   out->wild = false;  // (an update in place starts from a combination)

@@ -981,7 +981,7 @@ __device__ __forceinline__ void lut_write_body(const LutArgs& a, const uint32_t 
     int r, z;
     const int t = region_voxel(rc, o, r, z);
     const int32_t rank = sbase[t] + r;
-    if (rank < a.cap) {
+    if (rank >= 0 && rank < a.cap) {
       const int64_t idx = rc.base[t] + ((int64_t)wrap_add(z + roz, nz) << 4);
       map_voxel_t d;
       d.hits = a.hits[idx];

@@ -54,6 +54,10 @@ struct map_t {
   // the last 2D export left the table export's ranks (colpre, group_cnt,
   // super_sum) for the current map state; any change of the map clears it
   bool ranked;
+  uint64_t rank_capture;      // the stream capture that export belongs to (0: none)
+  // a call on this map was captured: its replays change the map or the ranks, and
+  // the host does not see them
+  bool replays;
   // every voxel is empty and every occupancy word zero (a recentring then
   // needs no clears)
   bool empty;
@@ -76,6 +80,9 @@ namespace gvom {
 void set_origin(map_t* m, const int32_t o[3]);
 // Same, for a map whose state is empty (no clears are needed).
 void set_empty_origin(map_t* m, const int32_t o[3]);
+// Identity of the stream capture that a call on m enqueued now becomes part of, 0
+// outside one.  For every call that changes the map's voxels or ranks.
+uint64_t capture_of(map_t* m);
 // Next value of the process-wide state version counter (never 0).
 uint64_t next_version();
 }  // namespace gvom

@@ -1359,6 +1359,7 @@ int32_t sgt_set_norm(sgt_net_t* n, const float* mean, const float* stdv) {
 int32_t sgt_thin(map_t* m, const uint8_t* thin_dev) {
   if (!m || !thin_dev) return MAP_E_INVALID;
   if (m->sticky) return m->sticky;
+  (void)gvom::capture_of(m);
   m->ranked = false;
   m->version = gvom::next_version();
   return st_of(gvom::launch_thin(m->d, thin_dev, m->hits, m->passes, m->minqz, m->occ, m->stream));
