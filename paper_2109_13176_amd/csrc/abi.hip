@@ -328,7 +328,7 @@ int32_t map_create(const map_params_t* p, void* stream, map_t** out) {
   if (e == hipSuccess) e = dmalloc(&m->colpre, C * 4);
   if (e == hipSuccess) e = dmalloc(&m->super_sum, (nb + 63) / 64 * 4);
   if (e == hipSuccess) e = dmalloc(&m->stats, kStatsBytes);
-  if (e == hipSuccess) e = dmalloc(&m->err, 4);
+  if (e == hipSuccess) e = dmalloc(&m->imported, 4);
   if (e == hipSuccess) e = dmalloc(&m->nocc, 8);
   if (e == hipSuccess) e = hipHostMalloc((void**)&m->host, 8, 0);
   if (e == hipSuccess) e = dmalloc(&m->part_trace, m->part_trace_cap * 32);
@@ -345,6 +345,7 @@ int32_t map_create(const map_params_t* p, void* stream, map_t** out) {
   m->empty = true;
   m->version = gvom::next_version();
   if (e == hipSuccess) e = hipMemsetAsync(m->stats, 0, kStatsBytes, m->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(m->imported, 0, 4, m->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -369,7 +370,7 @@ int32_t map_destroy(map_t* m) {
   (void)gvom::dev_free(m->colpre);
   (void)gvom::dev_free(m->super_sum);
   (void)gvom::dev_free(m->stats);
-  (void)gvom::dev_free(m->err);
+  (void)gvom::dev_free(m->imported);
   (void)gvom::dev_free(m->nocc);
   (void)hipHostFree(m->host);
   (void)gvom::dev_free(m->touch);
@@ -401,6 +402,7 @@ int32_t map_reset(map_t* m) {
   m->empty = true;
   m->wild = false;
   if (e == hipSuccess) e = hipMemsetAsync(m->stats, 0, kStatsBytes, m->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(m->imported, 0, 4, m->stream);
   // an insert that failed between the traversal and the fold leaves counts
   if (e == hipSuccess)
     e = hipMemsetAsync(m->box_rep, 0, (size_t)gvom::kBoxReps * gvom::kBoxCells * 4, m->stream);
@@ -619,7 +621,7 @@ void surface_args(const map_t* m, const map_2d_t* out, bool ranks, gvom::Surface
   sa->ny = m->p.ny;
   sa->hq = m->hq;
   sa->defbits = (const uint32_t*)m->defbits;
-  sa->wild = m->wild;
+  sa->imported = m->imported;
   sa->half_fit = m->c.half_fit;
   sa->search_d = m->c.search_d;
   sa->tau_q = m->c.tau_neg_q;
@@ -891,19 +893,21 @@ int32_t map_import_voxels(map_t* m, const int32_t* lut_dev, const map_voxel_t* d
   m->ranked = false;
   m->empty = false;
   m->version = gvom::next_version();
-  hipError_t e = hipMemsetAsync(m->err, 0, 4, m->stream);
+  hipError_t e = hipMemsetAsync(m->imported, 0, 4, m->stream);
   if (e == hipSuccess)
     e = gvom::launch_import(m->d, lut_dev, data_dev, n_data, m->hits, m->passes, m->minqz,
-                            m->occ, m->origin[2], m->err, m->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(m->host, m->err, 4, hipMemcpyDeviceToHost, m->stream);
+                            m->occ, m->origin[2], m->imported, m->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(m->host, m->imported, 4, hipMemcpyDeviceToHost, m->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
   if (e != hipSuccess) return dev_status(m, e);
   const int32_t err = *(const int32_t*)m->host;
-  m->wild = (err & 2) != 0;
-  if (err & 1) {
+  m->wild = (err & gvom::kWild) != 0;
+  if (err & gvom::kBadContent) {
     m->wild = false;
     initial_origin(m);
     e = clear_all(m);
+    if (e == hipSuccess) e = hipMemsetAsync(m->imported, 0, 4, m->stream);
     m->empty = true;
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
     if (e != hipSuccess) return dev_status(m, e);

@@ -942,7 +942,10 @@ int32_t map_buffer_combine(map_buffer_t* b, map_t* out) {
   (void)gvom::capture_of(out);
   out->ranked = false;
   out->empty = false;
-  out->wild = false;  // (an update in place starts from a combination)
+  if (out->wild) {  // (an update in place starts from a combination)
+    if (e == hipSuccess) e = gvom::launch_fill_i32(out->imported, 0, 1, out->stream);
+    out->wild = false;
+  }
   gvom::CombineArgs a;
   a.d = out->d;
   for (int i = 0; i < 3; i++) a.O[i] = nw.origin[i];

@@ -262,8 +262,8 @@ __global__ __launch_bounds__(kBlock) void k_costmap(CostArgs a) {
 // into the LDS rows, then the region is written in storage order, the records
 // of occupied voxels gathered on the way.  Hits and lowest returns are written
 // where the old or the new map has an occupied voxel (they are empty
-// elsewhere).  err: bit 0 = invalid content (the caller empties the map), bit
-// 1 = a lowest return outside its voxel.
+// elsewhere).  err receives kBadContent (the caller then empties the map) and
+// kWild.
 //
 // Bound: HBM, 4 V read + 4 V written.  Measured at 512 x 512 x 64: 237 us (a
 // lane per voxel of a column, each storing to lines of its own) -> 38.7 us.
@@ -340,12 +340,12 @@ __global__ __launch_bounds__(kBlock) void k_import(Dims d, const int32_t* __rest
           mq[e] = r.min_qz;
           write = true;
           atomicOr(&neww[zs >> 6][t + 16 * e], 1ull << (zs & 63));
-          if (r.min_qz >> 16 != origin_z + lz) atomicOr(err, 2);
+          if (r.min_qz >> 16 != origin_z + lz) atomicOr(err, kWild);
         } else {
-          atomicOr(err, 1);
+          atomicOr(err, kBadContent);
         }
       } else if (v == INT32_MIN) {
-        atomicOr(err, 1);
+        atomicOr(err, kBadContent);
       } else {
         p[e] = -1 - v;
       }

@@ -595,6 +595,7 @@ __device__ __forceinline__ void surface_body(const SurfaceArgs& a, const int H, 
   const int gx0 = bx * TILE - H, gy0 = by * TILE - H;
   const int lane = __lane_id(), wv = threadIdx.x >> 6;
   const int h = a.half_fit, D = a.search_d;
+  const bool wild = *a.imported & kWild;
 
   // ---- heights and row masks
   if (gx0 >= 0 && gy0 >= 0 && gx0 + T <= a.nx && gy0 + T <= a.ny)
@@ -691,7 +692,7 @@ __device__ __forceinline__ void surface_body(const SurfaceArgs& a, const int H, 
       const int32_t* tc = th + tx * TS + ty;
       PlaneSums s;
       bool ok;
-      if (h == 2 && !a.wild) {
+      if (h == 2 && !wild) {
         plane_sums5(tc, TS, *tc, s);
         ok = plane_solve<int32_t>(s, a.q2m, slope, rough);
       } else {

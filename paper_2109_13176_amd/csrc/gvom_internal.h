@@ -129,7 +129,7 @@ struct SurfaceArgs {
   int32_t nx, ny;
   const int32_t* hq;
   const uint32_t* defbits;  // the column pass's bits, as 32-bit words
-  int32_t wild;           // heights may lie outside the window (imported data)
+  const int32_t* imported;  // kWild set: heights may lie outside the window
   int32_t half_fit;
   int32_t search_d;
   int64_t tau_q;
@@ -143,6 +143,10 @@ struct SurfaceArgs {
   int32_t rank_n;
   int32_t* rank_sum;
 };
+
+// What an import found: content it refuses; a lowest return outside its voxel, which
+// the map then holds until it is emptied or combined anew.
+constexpr int32_t kBadContent = 1, kWild = 2;
 
 struct LutArgs {
   Dims d;

@@ -23,7 +23,7 @@ struct map_t {
   int32_t* colpre;
   int32_t* super_sum;
   unsigned long long* stats;  // 8 counters
-  int32_t* err;
+  int32_t* imported;          // what the map's last import found (kBadContent, kWild)
   int64_t* nocc;              // occupied-voxel count of a synchronous table export
   // pinned: where the small readbacks of a call land (into ordinary memory each copy
   // passed through a buffer of the runtime's, 7 us more)
@@ -61,8 +61,9 @@ struct map_t {
   // every voxel is empty and every occupancy word zero (a recentring then
   // needs no clears)
   bool empty;
-  // an import brought a lowest return that lies outside its voxel: ground
-  // heights may then differ by more than the window's height
+  // `imported` may hold kWild: ground heights may then differ by more than the
+  // window's height.  (The surface pass reads the device's word, so that a captured
+  // one replays on what the map then holds.)
   bool wild;
   // a fresh value (from a process-wide counter) whenever the voxel state may
   // change: a combine can tell that a map still holds its previous result

@@ -137,3 +137,49 @@ def test_both_exports_in_one_graph_and_apart(dims):
             compare_2d_arrays(host_2d(r.m.out2d), r.o.export_2d(), 0.5)
     finally:
         r.close()
+
+
+def test_captured_2d_export_and_imported_heights():
+    """A graph of the 2D export made while every height lay in its voxel, replayed on
+    imported heights of up to 2^28 (4,096 voxels; 32-bit sums of a 5 x 5 window's first
+    moments, up to 30 times that, do not hold them), and back."""
+    from paper_2109_13176_amd import gvom
+    r = Rig(SMALL)
+    nx, ny, nz = SMALL
+    try:
+        r.insert(r.cloud())
+        g = r.capture(r.m.export_2d)
+        org = np.array([-nx // 2, -ny // 2, -nz // 2], np.int32)
+        for k, top in enumerate((2 ** 28, 2 ** 16, 2 ** 28, None)):
+            lut = np.full((nx * ny, nz), -1, np.int32)
+            known = np.flatnonzero(r.rng.uniform(size=nx * ny) < 0.7)
+            z = r.rng.integers(0, nz, len(known))
+            lut[known, z] = np.arange(len(known))
+            data = np.ones((len(known), 3), np.int32)
+            data[:, 2] = (org[2] + z << 16) + r.rng.integers(0, 65536, len(known))
+            if top == 2 ** 28:
+                data[:, 2] = r.rng.integers(-top, top, len(known))
+            if top is None:  # refused: the map is empty afterwards
+                data[3, 0] = 0
+            lut = lut.reshape(-1)
+            st = gvom.map_import_voxels(r.m.h, torch.from_numpy(lut).cuda(),
+                                        torch.from_numpy(data).cuda(), org)
+            assert st == (0 if top else gvom.MAP_E_INVALID)
+            assert (r.o.import_voxels(lut, data, org) == oracle.OK) == (top is not None)
+            if top is None:
+                r.o.close()
+                r.o = oracle.OracleMap(r.p)
+            if k == 2:  # emptied and filled by scans alone
+                assert gvom.map_reset(r.m.h) == 0
+                r.o.close()
+                r.o = oracle.OracleMap(r.p)
+                r.insert(r.cloud())
+            ref = r.o.export_2d()
+            for _ in range(2):
+                r.replay(g)
+                compare_2d_arrays(host_2d(r.m.out2d), ref, 0.5)
+                r.m.export_2d()
+                torch.cuda.synchronize()
+                compare_2d_arrays(host_2d(r.m.out2d), ref, 0.5)
+    finally:
+        r.close()
