@@ -168,3 +168,34 @@ def test_scrolled_window_keeps_and_clears(nx, ny, nz):
         assert m.stats()["n_cleared"] == o.stats()["n_cleared"], k
     m.close()
     o.close()
+
+
+def test_import_time_does_not_follow_the_heights():
+    """A table given another origin in z, so that every lowest return lies outside its
+    voxel, is imported about as fast as one with all of them inside (a factor of 4
+    leaves room for noise; one global update per such voxel took 12)."""
+    import time
+    from paper_2109_13176_amd import gvom
+    nx, ny, nz = 512, 512, 64
+    p = dict(nx=nx, ny=ny, nz=nz, res_m=0.2, sensor_z_voxel=32, obs_min_m=0.4, obs_max_m=2.0,
+             dens_num=1, dens_den=2, fit_n=5, neg_thresh_m=0.5, neg_search_m=5.0)
+    rng = np.random.default_rng(0)
+    lut = np.full(nx * ny * nz, -1, np.int32)
+    occ = np.flatnonzero(rng.uniform(size=len(lut)) < 0.01)
+    lut[occ] = np.arange(len(occ))
+    data = np.ones((len(occ), 3), np.int32)
+    data[:, 2] = (occ % nz) << 16
+    lt, dt = torch.from_numpy(lut).cuda(), torch.from_numpy(data).cuda()
+    m = gvom.VoxelMap(p)
+    took = []
+    for oz in (0, 5):
+        org = np.array([0, 0, oz], np.int32)
+        t = []
+        for _ in range(20):
+            t0 = time.perf_counter()
+            assert gvom.map_import_voxels(m.h, lt, dt, org) == 0
+            t.append(time.perf_counter() - t0)
+        took.append(sorted(t)[len(t) // 2])
+    m.close()
+    print(f"import: heights inside {took[0] * 1e6:.0f} us, outside {took[1] * 1e6:.0f} us", flush=True)
+    assert took[1] < 4 * took[0]
