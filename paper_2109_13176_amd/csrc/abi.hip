@@ -562,14 +562,23 @@ int32_t prepare_insert(map_t* m, const float* xyz_dev, int64_t n, const float* p
                        gvom::ClearArgs* plan, bool* full, int32_t seg_len) {
   const int64_t ray_blocks = (n + gvom::kRayBlock - 1) / gvom::kRayBlock;
   int64_t need = 0;
-  insert_layout(m, ray_blocks, seg_len, a, &need);
   if (!grow(m, &m->rays, &m->rays_cap, ray_blocks * gvom::kRayBlock, sizeof(int4)))
     return MAP_E_OOM;
-  if (!grow(m, &m->witems, &m->witem_cap, need, sizeof(int2))) {
-    // no room for the items of shorter segments: the setting's length
+  // Where the items of shorter segments find no room, the setting's length; and as
+  // long as the buffer holds that one's items, no growing is tried again (each try
+  // waits for the stream, frees the buffer and allocates).
+  const auto fits = [&](int32_t len) {
+    insert_layout(m, ray_blocks, len, a, &need);
+    return need <= m->witem_cap;
+  };
+  if (seg_len != m->seg_len && !fits(seg_len) && m->short_oom && need >= m->short_oom &&
+      fits(m->seg_len))
+    seg_len = m->seg_len;
+  if (!fits(seg_len) && !grow(m, &m->witems, &m->witem_cap, need, sizeof(int2))) {
     if (seg_len == m->seg_len) return MAP_E_OOM;
-    insert_layout(m, ray_blocks, m->seg_len, a, &need);
-    if (!grow(m, &m->witems, &m->witem_cap, need, sizeof(int2))) return MAP_E_OOM;
+    m->short_oom = need;
+    if (!fits(m->seg_len) && !grow(m, &m->witems, &m->witem_cap, need, sizeof(int2)))
+      return MAP_E_OOM;
   }
   if (!grow(m, &m->part_rays, &m->part_rays_cap, ray_blocks, 32)) return MAP_E_OOM;
   a->rays = m->rays;
@@ -759,8 +768,9 @@ int32_t map_insert_scan_static(map_t* m, const float* xyz_dev, int64_t n, const 
   int32_t st = check_insert(m, xyz_dev, n, pose, flags, S);
   if (st) return st;
   int64_t need = 0;
-  int32_t seg_len = lone_seg_len(m, n);
-  if (static_insert_bytes(m, n, seg_len, &need) > kScratchBytes) seg_len = m->seg_len;
+  // (shorter segments of the library's choice always fit: at most 196,608 points, 44 MB
+  // on the longest window)
+  const int32_t seg_len = lone_seg_len(m, n);
   if (static_insert_bytes(m, n, seg_len, &need) > kScratchBytes) return MAP_E_CAPACITY;
   unsigned char* base = device_scratch(m->device);
   if (!base) return MAP_E_DEVICE;  // nothing enqueued, the map is unchanged

@@ -32,6 +32,7 @@ struct map_t {
   int4* rays;                 // per-ray records of the current insert
   int2* witems;               // its wave items
   int64_t rays_cap, witem_cap;
+  int64_t short_oom;          // wave items of shorter segments that found no memory (0: none)
   unsigned long long* part_rays;   // per-block counters of the ray pass
   unsigned long long* part_trace;  // per-block counters of the traversal pass
   int64_t part_rays_cap, part_trace_cap;

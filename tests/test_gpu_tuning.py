@@ -47,6 +47,37 @@ def test_segment_length_that_runs(n, set_len, runs):
         pair.close()
 
 
+def test_no_memory_for_shorter_segments():
+    """Under a memory limit that admits the work buffers of segments of 8 but not of
+    5, the length of a scan of 131,072 points: 8 runs, and goes on running without
+    another try while its buffers hold; a larger scan grows them again."""
+    from paper_2109_13176_amd import gvom
+    L = gvom.lib()
+    dims, n = (64, 48, 16), 131072
+    pair = Pair(params(*dims, 0.5))
+    try:
+        pts = _cloud(n, 20.0, 1)
+        used = L.map_device_memory_in_use()
+        assert L.map_set_device_memory_limit(used + _insert_bytes(dims, n, 8) - 1024) == 0
+        x = torch.as_tensor(pts, device="cuda")
+        assert gvom.map_insert_scan(pair.g.h, x, POSE, 0) == gvom.MAP_E_OOM
+        assert pair.g.export_voxels()[2] == 0
+        assert L.map_set_device_memory_limit(used + _insert_bytes(dims, n, 8) + 1024) == 0
+        for k in range(3):
+            assert pair.insert(_cloud(n, 20.0, k), POSE) == 0
+            assert L.map_device_memory_in_use() - used == _insert_bytes(dims, n, 8)
+            if k == 1:
+                assert L.map_set_device_memory_limit(0) == 0
+        compare_all(pair)
+        for m in (1000, 150000, n):
+            assert pair.insert(_cloud(m, 20.0, m), POSE) == 0
+        assert L.map_device_memory_in_use() - used > _insert_bytes(dims, 150000, 5)
+        compare_all(pair)
+    finally:
+        L.map_set_device_memory_limit(0)
+        pair.close()
+
+
 # windows where the library takes 16, 32 and 64 pixels by itself; 31 rings and more
 @pytest.mark.parametrize("nx,ny,res", [(62, 98, 0.1), (258, 250, 0.2), (642, 514, 0.1),
                                        (1030, 1026, 0.2)])
