@@ -1107,6 +1107,7 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
     if (lut) {
       lut_args(m, lut_dev[i], data_dev ? data_dev[i] : nullptr, cap ? cap[i] : 0,
                n_occupied_dev[i], &t->lut[i]);
+      t->lut[i].scanned = t->lut[i].nsuper > gvom::kWaveSupers;
     }
     const int64_t C = (int64_t)m->p.nx * m->p.ny;
     const int ray_blocks = (int)((n[i] + gvom::kRayBlock - 1) / gvom::kRayBlock);
@@ -1237,10 +1238,12 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
     khz = 100000;
   b->clock_khz = khz;
   size_t lut = 0;
+  bool scan = false;
   int64_t cols = 0, units = 0;  // virtual blocks of the column and the table pass
   for (int i = 0; i < k; i++) {
     const size_t s = gvom::lut_lds(maps[i]->p.nz);
     lut = s > lut ? s : lut;
+    scan |= n_col(maps[i]) > 4096 * (int64_t)gvom::kWaveSupers;
     cols += (n_col(maps[i]) + 255) / 256;
     units += (int64_t)((maps[i]->p.nx + 3) / 4) * ((maps[i]->d.nby + 3) / 4);
   }
@@ -1253,7 +1256,8 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
   // 626 / 659 / 583 / 573 / 726 us, column 96 / 90 / 86 / 86 / 103).
   const auto at_most = [](int64_t a, int64_t c) { return (int)(a < c ? a : c); };
   b->grid = gvom::BatchGrid{cu * 4, cu * gvom::kTraceWavesPerSimd, at_most(cu * 64, cols), cu * 2,
-                            at_most(cu * 64, units), k * gvom::box_fold_blocks(), 0, lut};
+                            at_most(cu * 64, units), k * gvom::box_fold_blocks(),
+                            scan ? k : 0, 0, lut};
   hipError_t e = gvom::dev_alloc((void**)&b->dtab, sizeof(gvom::BatchTables));
   if (e == hipSuccess) e = hipHostMalloc((void**)&b->htab, sizeof(gvom::BatchTables), 0);
   if (e == hipSuccess) e = gvom::dev_alloc((void**)&b->dstamps, (gvom::kMaxBatch + 2) * 8);

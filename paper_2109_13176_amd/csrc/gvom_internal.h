@@ -144,6 +144,11 @@ struct SurfaceArgs {
   int32_t* rank_sum;
 };
 
+// Super groups of ranks whose sums every region of a table export scans by itself, in
+// a wave, 64 a round; more of them are scanned once before (k_lut_scan, k_b_lut_scan: a
+// launch of 5 us, which the rounds of 1,024 super groups in 65,536 regions outweigh).
+constexpr int kWaveSupers = 256;
+
 // What an import found: content it refuses; a lowest return outside its voxel, which
 // the map then holds until it is emptied or combined anew.
 constexpr int32_t kBadContent = 1, kWild = 2;
@@ -262,6 +267,7 @@ struct BatchTables {
 struct BatchGrid {
   int rays, trace, col, surf, lwrite;  // persistent grid sizes
   int fold;                                                   // maps x sensor-box fold blocks
+  int scan;                            // maps, if one has more than kWaveSupers super groups
   size_t surf_lds, lut_lds;
 };
 
