@@ -9,6 +9,7 @@
 
 #include <stdio.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <new>
@@ -1055,7 +1056,7 @@ hipError_t enqueue_batch(map_batch_t* b) {
   if (e == hipSuccess) e = gvom::launch_batch_insert(b->dtab, b->grid, b->dstamps, b->stream);
   if (e == hipSuccess) e = gvom::launch_batch_export(b->dtab, b->grid, b->dstamps, b->stream);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(b->hstamps, b->dstamps, (b->k + 1) * sizeof(unsigned long long),
+    e = hipMemcpyAsync(b->hstamps, b->dstamps, gvom::kStampQueue * sizeof(unsigned long long),
                        hipMemcpyDeviceToHost, b->stream);
   return e;
 }
@@ -1167,8 +1168,12 @@ int32_t batch_run(map_batch_t* b) {
     batch_fail(b, e);
     return MAP_E_DEVICE;
   }
-  for (int i = 0; i < b->k; i++)
-    b->last_ms[i] = (double)(b->hstamps[1 + i] - b->hstamps[0]) / b->clock_khz;
+  for (int i = 0; i < b->k; i++) {
+    unsigned long long end = 0;
+    for (int t = 0; t < gvom::kStampSlots; t++)
+      end = std::max(end, b->hstamps[gvom::kStampEnds + t * gvom::kMaxBatch + i]);
+    b->last_ms[i] = (double)(end - b->hstamps[0]) / b->clock_khz;
+  }
   return MAP_OK;
 }
 
@@ -1253,15 +1258,15 @@ int32_t map_batch_create(map_t* const* maps, int32_t k, void* stream, map_batch_
   // 770).  The bandwidth-bound column and table passes 64 per CU: a block that goes on
   // to its next virtual block starts that one's chain of loads only behind the last
   // one's stores, a new block at once (32 maps, with 8 / 16 / 64 / 128 / 512 per CU: table
-  // 626 / 659 / 583 / 573 / 726 us, column 96 / 90 / 86 / 86 / 103).
+  // 562 / 546 / 521 / 500 / 473 us, column 63 / 61 / 60 / 61 / 61).
   const auto at_most = [](int64_t a, int64_t c) { return (int)(a < c ? a : c); };
   b->grid = gvom::BatchGrid{cu * 4, cu * gvom::kTraceWavesPerSimd, at_most(cu * 64, cols), cu * 2,
                             at_most(cu * 64, units), k * gvom::box_fold_blocks(),
                             scan ? k : 0, 0, lut};
   hipError_t e = gvom::dev_alloc((void**)&b->dtab, sizeof(gvom::BatchTables));
   if (e == hipSuccess) e = hipHostMalloc((void**)&b->htab, sizeof(gvom::BatchTables), 0);
-  if (e == hipSuccess) e = gvom::dev_alloc((void**)&b->dstamps, (gvom::kMaxBatch + 2) * 8);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&b->hstamps, (gvom::kMaxBatch + 1) * 8, 0);
+  if (e == hipSuccess) e = gvom::dev_alloc((void**)&b->dstamps, (gvom::kStampQueue + 1) * 8);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&b->hstamps, gvom::kStampQueue * 8, 0);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     map_batch_destroy(b);

@@ -398,7 +398,8 @@ struct Stamper {
     }
   }
   __device__ __forceinline__ void flush(unsigned long long* stamps) {
-    if (threadIdx.x == 0 && m >= 0) atomicMax(&stamps[1 + m], end);
+    if (threadIdx.x == 0 && m >= 0)
+      atomicMax(&stamps[kStampEnds + (blockIdx.x % kStampSlots) * kMaxBatch + m], end);
     m = -1;
   }
 };

@@ -236,6 +236,15 @@ struct ClearArgs {
 // ---- batches of maps ------------------------------------------------------
 constexpr int kMaxBatch = 64;
 
+// Clock values of a step, in device memory (64-bit words): its start, then kStampSlots
+// x kMaxBatch completion maxima of the maps, then the traversal's queue.  A map's blocks
+// spread over its slots, which lie in lines of their own: an atomic on one address costs
+// 46 ns behind the last one, so with one word per map the 16,384 blocks of the table pass
+// of four maps of 1024 x 1024 x 16 took 756 us, with the slots 127.
+constexpr int kStampSlots = 16;
+constexpr int kStampEnds = 8;  // (the start has a line of its own)
+constexpr int kStampQueue = kStampEnds + kStampSlots * kMaxBatch;
+
 // Per-step table of a batch: virtual-block prefixes of every stage (block b of
 // stage S belongs to the map m with pre[m] <= b < pre[m+1]) and per-map
 // launch constants.  Lives in device memory, uploaded once per step.
@@ -272,7 +281,7 @@ struct BatchGrid {
 };
 
 // Enqueues one batched step (all stages of all maps) reading `tab` (device).
-// stamps[0] = step start, stamps[1 + m] = completion of map m (wall clock:
+// stamps: see kStampSlots (wall clock:
 // the latest end of its last-stage blocks).
 hipError_t launch_batch_insert(const BatchTables* tab, const BatchGrid& g,
                                unsigned long long* stamps, hipStream_t s);

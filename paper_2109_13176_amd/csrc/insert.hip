@@ -57,8 +57,8 @@ __global__ __launch_bounds__(kRayBlock) void k_b_rays(const BatchTables* __restr
   if (blockIdx.x == 0) {
     if (threadIdx.x == 0) stamps[0] = wall_clock64();
     // per-map completion maxima, taken by the last stages
-    for (int i = threadIdx.x; i < n; i += kRayBlock) stamps[1 + i] = 0;
-    if (threadIdx.x == 0) stamps[1 + kMaxBatch] = 0;  // the traversal's queue
+    for (int i = kStampEnds + threadIdx.x; i < kStampQueue; i += kRayBlock) stamps[i] = 0;
+    if (threadIdx.x == 0) stamps[kStampQueue] = 0;
   }
   for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {
     const int m = find_map(t->st.pre_rays, n, vb);
@@ -145,7 +145,7 @@ hipError_t launch_batch_insert(const BatchTables* tab, const BatchGrid& g,
                                unsigned long long* stamps, hipStream_t s) {
   hipLaunchKernelGGL(k_b_rays, dim3(g.rays), dim3(kRayBlock), 0, s, tab, stamps);
   hipLaunchKernelGGL(k_b_trace, dim3(g.trace), dim3(kTraceBlock), 0, s, tab,
-                     stamps + 1 + kMaxBatch);
+                     stamps + kStampQueue);
   hipLaunchKernelGGL(k_b_box_fold, dim3(g.fold), dim3(kBlock), 0, s, tab);
   return hipGetLastError();
 }

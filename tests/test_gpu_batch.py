@@ -197,3 +197,41 @@ def test_batch_tables_beyond_256_super_groups():
         batch.close()
         for p in pairs:
             p.close()
+
+
+def test_batch_tables_cost_what_single_ones_do():
+    """The tables of four maps add to a step about what four single exports take (with
+    every block's completion stamp on one word per map they added five times as much;
+    2.5 leaves room for noise)."""
+    import time
+    from paper_2109_13176_amd import gvom
+    maps = [gvom.VoxelMap(params(1024, 1024, 16, 0.2)) for _ in range(4)]
+    batch = gvom.MapBatch(maps)
+    xyz = _cloud(np.random.default_rng(1), 3000, 60.0)
+    pose = scenegen.pose12(np.eye(3), [0.1, 0.2, 0.1])
+
+    def median_us(f):
+        t = []
+        for _ in range(25):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            f()
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - t0)
+        return sorted(t[5:])[10] * 1e6
+
+    def exports():
+        for m in maps:
+            m.export_voxels_async()
+    try:
+        step = [median_us(lambda: batch.step([xyz] * 4, [pose] * 4, [0] * 4, [v] * 4))
+                for v in (True, False)]
+        single = median_us(exports)
+        print(f"tables: {step[0] - step[1]:.0f} us in a step, {single:.0f} us by themselves", flush=True)
+        assert step[0] - step[1] < 2.5 * single
+        ms = batch.latency_ms()
+        assert (ms > 0).all() and (ms * 1e3 <= step[0] * 2).all()
+    finally:
+        batch.close()
+        for m in maps:
+            m.close()
