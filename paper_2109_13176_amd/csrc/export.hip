@@ -434,7 +434,7 @@ __global__ __launch_bounds__(kSurfThreads, 4) void k_b_surface(const BatchTables
 
 // Scans the sums of the super groups of every map that has many: block b = map b.
 // (Every region scanning all of them, a step of two maps of 4096 x 4096 x 4 took 4947 us,
-// with this launch 1629; of four of 2048 x 2048 x 16 1771, now 1543.)
+// with this launch 1629.)
 __global__ __launch_bounds__(1024) void k_b_lut_scan(const BatchTables* __restrict__ t) {
   const int m = blockIdx.x;
   if (m >= t->st.nmaps || !t->st.last_is_lut[m] || !t->lut[m].scanned) return;

@@ -717,9 +717,10 @@ __device__ __forceinline__ void surface_body(const SurfaceArgs& a, const int H, 
 // columns and each group its count, pass 2 sums the counts of every super
 // group of 64 groups (and makes them prefixes within it), pass 3 writes the
 // table and the data array region by region, scanning the sums of the super
-// groups in a wave.  After a 2D export the first two passes are already done, by its column pass and by one
-// wave in each of the first blocks of its surface pass: a scan of all groups in
-// a launch of its own took 5 us at 4,096 groups and 20 us at 16,384, and a
+// groups in a wave (many of them are scanned once before, see kWaveSupers).
+// After a 2D export the first two passes are already done, by its column pass and
+// by one wave in each of the first blocks of its surface pass: a scan of all groups
+// in a launch of its own took 5 us at 4,096 groups and 20 us at 16,384, and a
 // block more in the surface pass 7 us (a compute unit with two of its blocks).
 constexpr int kGroup = 64;
 
@@ -962,17 +963,11 @@ __device__ __forceinline__ void lut_write_body(const LutArgs& a, const uint32_t 
     int32_t base = c >= 0 ? cp + gp : 0;
     if (a.scanned) {
       base += s0;
-    } else {
-      int before = 0;
-      for (int k = 0; 64 * k < a.nsuper; k++) {
-        int v = k == 0 ? s0 : a.super_sum[min(64 * k + t, a.nsuper - 1)];
-        v = 64 * k + t < a.nsuper ? v : 0;
-        const int s = wave_scan(v);
-        const int e = __shfl(s - v, sg & 63);
-        base += sg >> 6 == k ? before + e : 0;
-        before += __builtin_amdgcn_readlane(s, 63);
-      }
-      if (bxr == 0 && byr == 0 && t == 0) *a.n_occupied = before;
+    } else {  // at most kWaveSupers: a lane each
+      const int v = t < a.nsuper ? s0 : 0;
+      const int s = wave_scan(v);
+      base += __shfl(s - v, sg);
+      if (bxr == 0 && byr == 0 && t == 63) *a.n_occupied = s;
     }
     sbase[t] = base;
   });

@@ -144,10 +144,13 @@ struct SurfaceArgs {
   int32_t* rank_sum;
 };
 
-// Super groups of ranks whose sums every region of a table export scans by itself, in
-// a wave, 64 a round; more of them are scanned once before (k_lut_scan, k_b_lut_scan: a
-// launch of 5 us, which the rounds of 1,024 super groups in 65,536 regions outweigh).
-constexpr int kWaveSupers = 256;
+// Super groups of ranks whose sums every region of a table export scans by itself, one a
+// lane; more of them are scanned once before (k_lut_scan, k_b_lut_scan), since every
+// further 64 cost each region a round.  Export after a 2D export, scanned in regions /
+// before: 512 x 512 x 64 (64 super groups) 31.3 / 33.8 us, 640 x 640 x 64 (100) 46.0 /
+// 45.4, 1024 x 1024 x 16 (256) 43.8 / 38.1, 1024 x 1024 x 96 191.9 / 184.5; a batched
+// step of 32 maps of 1024 x 1024 x 16 4394 / 3948.
+constexpr int kWaveSupers = 64;
 
 // What an import found: content it refuses; a lowest return outside its voxel, which
 // the map then holds until it is emptied or combined anew.

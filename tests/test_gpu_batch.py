@@ -167,23 +167,23 @@ def test_batch_rejects_bad_requests_without_change():
         m.close()
 
 
-def test_batch_tables_beyond_256_super_groups():
-    """Maps on both sides of the 256 super groups of ranks (4,096 columns each) that a
+def test_batch_tables_on_both_sides_of_64_super_groups():
+    """Maps on both sides of the 64 super groups of ranks (4,096 columns each) that a
     table export scans region by region, in one batch, against the oracle; tables of
-    either, both and none from step to step."""
+    some, all and none from step to step."""
     pairs = [Pair(params(*sh)) for sh in ((1026, 1030, 2, 0.5), (48, 40, 20, 0.5),
-                                          (1024, 1024, 2, 0.5))]
+                                          (512, 512, 2, 1.0), (514, 512, 2, 1.0))]
     from paper_2109_13176_amd import gvom
     batch = gvom.MapBatch([p.g for p in pairs])
     rng = np.random.default_rng(3)
     pose = scenegen.pose12(np.eye(3), [0.1, 0.2, 0.1])
+    T, F = True, False
     try:
-        for k, voxels in enumerate(([True, True, True], [False, True, False],
-                                    [True, False, False], [False] * 3, [True] * 3)):
-            xyzs = [_cloud(rng, 3000, r) for r in (250.0, 12.0, 250.0)]
+        for voxels in ([T, T, T, T], [F, T, T, F], [T, F, F, T], [F] * 4, [T] * 4):
+            xyzs = [_cloud(rng, 3000, r) for r in (250.0, 12.0, 250.0, 250.0)]
             for p in pairs:
                 p.g.lut.fill_(-7)
-            batch.step(xyzs, [pose] * 3, [0] * 3, voxels)
+            batch.step(xyzs, [pose] * 4, [0] * 4, voxels)
             for p, x, v in zip(pairs, xyzs, voxels):
                 assert p.o.insert_scan(x.cpu().numpy(), pose, 0) == 0
                 if v:
