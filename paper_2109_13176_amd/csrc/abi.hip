@@ -1085,16 +1085,23 @@ int32_t batch_prepare(map_batch_t* b, const float* const* xyz_dev, const int64_t
   st.pre_rays[0] = st.pre_trace[0] = st.pre_col[0] = st.pre_surf[0] = 0;
   st.pre_lwrite[0] = 0;
   int64_t t64 = 0;
+  int64_t all = 0;  // points
   size_t surf_lds = 0;
-  for (int i = 0; i < b->k; i++) t64 += tiles64(b->maps[i]);
+  for (int i = 0; i < b->k; i++) {
+    t64 += tiles64(b->maps[i]);
+    all += n[i];
+  }
+  // (see kBatchTracePoints; the grid is what the device holds)
+  const int64_t fill = all / (b->grid.trace / 2);
+  const int64_t points = fill < 1 ? 1 : std::min<int64_t>(fill, gvom::kBatchTracePoints);
   for (int i = 0; i < b->k; i++) {
     map_t* m = b->maps[i];
     bool full = false;
     const int32_t s = prepare_insert(m, xyz_dev[i], n[i], poses + 12 * i, flags[i], S[i],
                                      &t->ins[i], &t->clr[i], &full, m->seg_len);
     if (s) return s;  // allocation failure
-    // blocks take 256 points' rays each, from a queue (see k_b_trace)
-    const int64_t tb = (n[i] + gvom::kBatchTracePoints - 1) / gvom::kBatchTracePoints;
+    // blocks take `points` points' rays each, from a queue (see k_b_trace)
+    const int64_t tb = (n[i] + points - 1) / points;
     if (tb < t->ins[i].trace_blocks) {
       m->last_trace_blocks -= t->ins[i].trace_blocks - tb;
       t->ins[i].trace_blocks = (int32_t)tb;

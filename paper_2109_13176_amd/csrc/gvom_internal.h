@@ -94,9 +94,13 @@ constexpr int kRayBlock = 512;    // threads per block of the ray pass (rays reg
 // 131,072 points, 16.0 -> 18.4 at 28,800)
 constexpr int kTraceBlock = 256;
 constexpr int kTraceWavesPerSimd = 7;
-// Points per traversal block of a batch: 32 maps of 20,000-330,000 points take 725 us
+// Points per traversal block of a batch, at most: 32 maps of 20,000-330,000 points take 725 us
 // with 64, 654 with 128, 648 with 256, 688 with 384 (a block's set-up and flush take as
-// long as about 60 points' rays; large blocks leave waves idle at the end).
+// long as about 60 points' rays; large blocks leave waves idle at the end).  A step of few
+// points takes fewer, so that its blocks take at least every second place on the device:
+// one map of 512 x 512 x 64 with 3,000 points, the whole step with 256 points a block
+// 351 us, with a block for every eighth / fourth / second / each place 125 / 130 / 133 /
+// 132; of 1024 x 1024 x 16 with 60,000 points 586, 585 / 498 / 487 / 473.
 constexpr int kBatchTracePoints = 256;
 
 // Blocks of the sensor-box fold that follows the segmented traversal.

@@ -235,3 +235,39 @@ def test_batch_tables_cost_what_single_ones_do():
         batch.close()
         for m in maps:
             m.close()
+
+
+def test_batch_of_few_points_costs_what_single_calls_do():
+    """A step of one map with 3,000 points against the single calls (its traversal in
+    twelve blocks of 256 points took the step to nearly four times their time; 2.5
+    leaves room for noise)."""
+    import time
+    from paper_2109_13176_amd import gvom
+    m, one = (gvom.VoxelMap(params(512, 512, 64, 0.2)) for _ in range(2))
+    batch = gvom.MapBatch([m])
+    xyz = _cloud(np.random.default_rng(1), 3000, 45.0)
+    pose = scenegen.pose12(np.eye(3), [0.1, 0.2, 0.1])
+
+    def single():
+        one.insert(xyz, pose)
+        one.export_2d()
+        one.export_voxels_async()
+        one.sync()
+
+    def median_us(f):
+        t = []
+        for _ in range(25):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            f()
+            t.append(time.perf_counter() - t0)
+        return sorted(t[5:])[10] * 1e6
+    try:
+        got = median_us(lambda: batch.step([xyz], [pose], [0], [True])), median_us(single)
+        print(f"one map, 3,000 points: step {got[0]:.0f} us, single calls {got[1]:.0f} us", flush=True)
+        assert got[0] < 2.5 * got[1]
+        assert torch.equal(m.export_voxels()[0], one.export_voxels()[0])
+    finally:
+        batch.close()
+        m.close()
+        one.close()
