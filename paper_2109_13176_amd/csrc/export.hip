@@ -19,8 +19,9 @@ __device__ __forceinline__ void surface_rank_sums(const SurfaceArgs& a, const in
 
 template <int TILE>
 __global__ __launch_bounds__(kSurfThreads, 8) void k_surface(SurfaceArgs a, int H) {
+  const bool wild = *a.imported & kWild;  // (before any store: a scalar load)
   surface_rank_sums(a, blockIdx.x * gridDim.y + blockIdx.y);
-  surface_body<kSurfThreads, TILE>(a, H, blockIdx.x, blockIdx.y);
+  surface_body<kSurfThreads, TILE>(a, wild, H, blockIdx.x, blockIdx.y);
 }
 
 __global__ __launch_bounds__(kBlock) void k_lut_count(LutArgs a) { lut_count_body(a, blockIdx.x); }
@@ -421,11 +422,12 @@ __global__ __launch_bounds__(kSurfThreads, 4) void k_b_surface(const BatchTables
   for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {
     const int m = find_map_e(t->st.pre_surf, n, vb);
     const int b = vb - t->st.pre_surf[m];
+    const bool wild = *t->sur[m].imported & kWild;
     surface_rank_sums(t->sur[m], b);
     const int ty = t->st.surf_tiles_y[m], H = t->st.surf_H[m], tile = t->st.surf_tile[m];
-    if (tile == 64) surface_body<kSurfThreads, 64>(t->sur[m], H, b / ty, b % ty);
-    else if (tile == 32) surface_body<kSurfThreads, 32>(t->sur[m], H, b / ty, b % ty);
-    else surface_body<kSurfThreads, 16>(t->sur[m], H, b / ty, b % ty);
+    if (tile == 64) surface_body<kSurfThreads, 64>(t->sur[m], wild, H, b / ty, b % ty);
+    else if (tile == 32) surface_body<kSurfThreads, 32>(t->sur[m], wild, H, b / ty, b % ty);
+    else surface_body<kSurfThreads, 16>(t->sur[m], wild, H, b / ty, b % ty);
     __syncthreads();
     sp.done(m, !t->st.last_is_lut[m], stamps);
   }

@@ -574,8 +574,8 @@ __device__ __forceinline__ int64_t cone_spread(const int32_t* th, const uint32_t
 }
 
 template <int NT, int TILE>
-__device__ __forceinline__ void surface_body(const SurfaceArgs& a, const int H, const int bx,
-                                             const int by) {
+__device__ __forceinline__ void surface_body(const SurfaceArgs& a, const bool wild, const int H,
+                                             const int bx, const int by) {
   constexpr int kPix = TILE * TILE;  // tile pixels
   constexpr int kWaves = NT / 64;    // waves of the block
   constexpr int kPer = kPix > NT ? kPix / NT : 1;  // tile pixels per thread
@@ -595,7 +595,6 @@ __device__ __forceinline__ void surface_body(const SurfaceArgs& a, const int H, 
   const int gx0 = bx * TILE - H, gy0 = by * TILE - H;
   const int lane = __lane_id(), wv = threadIdx.x >> 6;
   const int h = a.half_fit, D = a.search_d;
-  const bool wild = *a.imported & kWild;
 
   // ---- heights and row masks
   if (gx0 >= 0 && gy0 >= 0 && gx0 + T <= a.nx && gy0 + T <= a.ny)
@@ -977,7 +976,7 @@ __device__ __forceinline__ void lut_write_body(const LutArgs& a, const uint32_t 
     int r, z;
     const int t = region_voxel(rc, o, r, z);
     const int32_t rank = sbase[t] + r;
-    if (rank >= 0 && rank < a.cap) {
+    if ((uint64_t)(int64_t)rank < (uint64_t)a.cap) {  // (0 <= rank < cap)
       const int64_t idx = rc.base[t] + ((int64_t)wrap_add(z + roz, nz) << 4);
       map_voxel_t d;
       d.hits = a.hits[idx];
