@@ -192,8 +192,12 @@ __device__ __forceinline__ bool walk_ended(const Walk& w) {
 // Starts the walk of segment j of the ray to q with dominant axis dom (j the same
 // for the whole wave): l = local coordinates of its first voxel; up[k]: the ray
 // does not move down along axis k; most[k]: an upper bound of the walk's moves
-// along axis k (the dominant axis moves seg_len times at most, another one no
-// faster than twice as fast).  False when the first voxel lies outside the window.
+// along axis k: those left to the end voxel and one past it, or, where the segment is
+// shorter, those of a segment.  The dominant axis d, which has the most voxel steps n_d,
+// moves seg_len times in it; another axis k moves at |D_k| / |D_d| < (n_k + 1) / (n_d - 1)
+// times its speed.  For n_d >= 3 that is at most 2: 2 seg_len + 2 moves.  For n_d <= 2 it
+// may be any number, but then the first bound is at most 3 moves, and the other one 4.
+// False when the first voxel lies outside the window.
 //
 // Along axis k the ray reaches its (i + 1)-st boundary after h_k + 2^16 i Q units,
 // h_k the distance from the sensor to the first one.  Segment j > 0 starts when the

@@ -47,3 +47,27 @@ def test_lattice_rays(dims, seg_len, frac, distinct):
             compare_all(pair, distinct=distinct)
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("seg_len", [1, 2])
+def test_short_rays_over_the_storage_wrap(seg_len):
+    """Rays whose dominant axis makes one or two moves while another makes as many, so
+    that the other runs up to any number of times faster between them, at every offset
+    of the storage's ring: sensors close to a voxel's faces, returns close to faces one
+    and two voxels away."""
+    nx, ny, nz, res = 6, 10, 5, 0.25
+    rng = np.random.default_rng(seg_len)
+    eps = 2.0 ** -16  # one unit of the fixed-point coordinates
+    pair = Pair(params(nx, ny, nz, res, szv=2), seg_len)
+    try:
+        for k in range(2 * ny):
+            cell = np.array([k % nx, k, -k % nz]) + (rng.integers(-2, 3, 3) if k % 3 == 0 else 0)
+            face = rng.choice([eps, 0.0, 0.5, 1 - eps], 3)
+            s = (cell + face) * res
+            step = rng.integers(-2, 3, (400, 3))
+            end = cell + step + rng.choice([0.0, eps, 2 * eps, 0.5, 1 - eps], (400, 3))
+            pts = (end * res - s).astype(np.float32)
+            assert pair.insert(pts, _pose(s), 1) == 0
+        compare_all(pair)
+    finally:
+        pair.close()
