@@ -588,7 +588,8 @@ int32_t prepare_insert(map_t* m, const float* xyz_dev, int64_t n, const float* p
   return fill_insert(m, xyz_dev, n, pose, flags, S, a, plan, full, need);
 }
 
-// ranks: also write the table export's per-column ranks (single-map export)
+// ranks: also write the table export's per-column ranks (in a batch where it exports
+// the map's table)
 void column_args(const map_t* m, const map_2d_t* out, bool ranks, gvom::ColumnArgs* ca) {
   ca->d = m->d;
   ca->hits = m->hits;

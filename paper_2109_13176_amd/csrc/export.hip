@@ -490,6 +490,7 @@ size_t surface_lds(int H, int tile) {
 
 size_t lut_lds(int nz) { return (size_t)kRegCols * lut_row(nz) * 4; }
 
+// b / nz == umulhi(b, ceil(2^32 / nz)) for every b < 2^20 (here b < 4 * 128)
 uint32_t nz_magic(int nz) {
   return nz > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint64_t)nz - 1) / (uint64_t)nz) : 0u;
 }
@@ -534,9 +535,6 @@ hipError_t launch_lut(const LutArgs& args, bool ranked, hipStream_t s) {
   LutArgs a = args;
   const int C = a.d.nx * a.d.ny;
   const int ng = (C + kGroup - 1) / kGroup;
-  // b / nz == umulhi(b, ceil(2^32 / nz)) for every b < 2^20 (here b < 4 * 128)
-  const uint32_t magic =
-      a.d.nz > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint64_t)a.d.nz - 1) / (uint64_t)a.d.nz) : 0u;
   const size_t lds = lut_lds(a.d.nz);
   if (!ranked) {
     hipLaunchKernelGGL(k_lut_count, dim3((C + kBlock - 1) / kBlock), dim3(kBlock), 0, s, a);
@@ -548,7 +546,7 @@ hipError_t launch_lut(const LutArgs& args, bool ranked, hipStream_t s) {
     a.scanned = 1;
   }
   dim3 g((a.d.nx + 3) / 4, (a.d.nby + 3) / 4);
-  hipLaunchKernelGGL(k_lut_write, g, dim3(kBlock), lds, s, a, magic);
+  hipLaunchKernelGGL(k_lut_write, g, dim3(kBlock), lds, s, a, nz_magic(a.d.nz));
   return hipGetLastError();
 }
 

@@ -192,7 +192,6 @@ __device__ __forceinline__ void column_body(const ColumnArgs& a, const int blk) 
 // from the staged heights, distances read ring by ring in a layout whose
 // column reads met in the same LDS banks, cones and their cells one after the
 // other, and 64-bit normal sums in every cell.
-constexpr int kTile = 32;
 constexpr int kSurfThreads = 1024;
 constexpr int kMaxMaskWords = 3;  // staged edge <= 192 cells
 

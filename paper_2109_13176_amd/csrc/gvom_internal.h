@@ -75,8 +75,7 @@ struct InsertArgs {
   int2* witems;                // wave items {ray wave, segment index}, per stripe
   int64_t block_items;         // wave items one ray block has room for
   int32_t seg_len;             // dominant-axis voxels per segment
-  int32_t trace_blocks;        // grid of the trace kernel (kTraceBlock threads per block
-                               // for a single map, 256 in a batch)
+  int32_t trace_blocks;        // (virtual) blocks of the traversal, kTraceBlock threads each
   // sensor box (segmented traversal): storage coordinate of its first cell
   // and extent per axis; cell (dx, dy, dz) has box index
   // (dx * kBoxXY + dy) * kBoxZ + dz
@@ -105,8 +104,6 @@ constexpr int kBatchTracePoints = 256;
 
 // Blocks of the sensor-box fold that follows the segmented traversal.
 int box_fold_blocks();
-// Replica groups of the fold (each fold block sums one group of replicas).
-int box_fold_groups();
 
 // Segments one ray can produce at most.
 int64_t max_segments(const Dims& d, int32_t seg_len);

@@ -9,8 +9,6 @@ namespace gvom {
 
 namespace {
 
-
-
 // Blocks [0, ray_blocks): the ray pass; the others clear the moved window.
 __global__ __launch_bounds__(kRayBlock) void k_rays(InsertArgs a, ClearArgs c, int ray_blocks) {
   const int b = (int)blockIdx.x - ray_blocks;
@@ -184,7 +182,7 @@ hipError_t launch_trace(const InsertArgs& a, bool distinct, hipStream_t s) {
 }
 
 int box_fold_blocks() { return kFoldCellBlocks * kFoldGroups; }
-int box_fold_groups() { return kFoldGroups; }
+
 // Sums the ray pass's per-block counters (4 per block) into out[0..3]: one
 // block, each thread a strided share of the blocks, then a fixed-order sum
 // over the threads (no atomics).

@@ -770,10 +770,11 @@ __device__ __forceinline__ void bwd_weight_body(const uint16_t* __restrict__ dzh
 }
 
 // Weight (and bias) gradient of the 32 -> 2 output layer on matrix cores,
-// laid out as k_bwd_weight_mfma: A = dz^T with the two output channels as
+// laid out as in bwd_weight_body: A = dz^T with the two output channels as
 // rows 0 and 1 of a 16-row operand (rows 2..15 zero), staged as 16-channel
 // pixel rows; dz is the loss gradient, a sign (-1, 0 or 1) exact in bf16, so
-// one product per pair.  Wave w takes ci tile w % 2 and a row of every tile (the waves of a tile are added in LDS in fixed order).
+// one product per pair.  Wave w takes ci tile w % 2 and a row of every tile (the
+// waves of a tile are added in LDS in fixed order).
 constexpr int kWeightOutTiles = (kWgRows * kTC * 20 + (kWgRows + 2) * (kTC + 2) * 36) * 2;
 constexpr int kWeightOutLds = kWeightOutTiles + kWgWaves / 2 * 2 * 10 * 2 * 16 * 4;
 
