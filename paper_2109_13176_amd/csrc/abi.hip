@@ -475,17 +475,26 @@ void insert_layout(const map_t* m, int64_t ray_blocks, int32_t seg_len, gvom::In
   *need = ray_blocks * a->block_items;
 }
 
-// Segment length of a lone insert of n points.  An item's steps are one chain of
-// LDS round trips, so a scan with fewer items than the device has waves ends sooner
-// when its rays are cut shorter; with many items the set-up of each costs more than
-// the chains.  Traversal time with 4 / 5 / 8 voxels on 512 x 512 x 64: 32,768 points
-// 25.9 / 26.2 / 29.7 us, 98,304 points 40.0 / 39.2 / 41.0, 131,072 points 49.5 / 47.0
-// / 48.1, 262,144 points 84.2 / 79.2 / 80.3, and on 1024 x 1024 x 96 126 / 121 / 114
-// (with the events that time it).  In a batch the maps fill the device together: the
-// setting as it is.  A length that was set is taken as it is.
+// Segment length of a lone insert of n points, where none was set.  An item's steps are
+// one chain of LDS round trips, so a scan with fewer items than the device has waves
+// ends sooner when its rays are cut shorter; with more items their set-up and the flush
+// of their lines cost more than the chains.  The items grow with the points and with the
+// voxels a ray can cross (n x the window's longer side); on windows beyond 512 a far
+// segment has most lines to itself, so cutting it again adds flushes.  Whole insert with
+// 4 / 5 / 8 voxels (events included), 64-beam scans and every k-th point of them:
+//   256 x 256 x 48: 65,536 points 34.4 / 35.2 / 37.3 us, 131,072 50.6 / 48.7 / 51.2,
+//     196,608 66.9 / 62.5 / 63.0, 262,144 81.8 / 77.8 / 76.6
+//   512 x 512 x 64: 32,768 31.5 / 31.5 / 34.4, 65,536 46.7 / 43.4 / 44.5, 131,072 75.1 /
+//     74.8 / 77.1, 196,608 95.8 / 94.4 / 97.5, 262,144 125.3 / 123.4 / 123.9
+//   1024 x 1024 x 96: 16,384 32.6 / 32.7 / 36.8, 32,768 44.6 / 40.9 / 39.6, 49,152 60.2 /
+//     55.9 / 54.3, 131,072 132 / 133 / 134, 196,608 175 / 166 / 159
+// (The shorter segments cost traffic: on the 64-beam scan 0.35 M instead of 0.23 M line
+// requests.)  In a batch the maps fill the device together: 8.
 int32_t lone_seg_len(const map_t* m, int64_t n) {
+  const int64_t side = std::max(m->p.nx, m->p.ny);
   if (!m->seg_auto) return m->seg_len;
-  return n <= 49152 ? 4 : n <= 196608 ? 5 : m->seg_len;
+  if (n * side <= (int64_t)1 << 24) return 4;
+  return side <= 512 && n <= 196608 ? 5 : m->seg_len;
 }
 
 // Everything of an insert but the per-scan buffers (a->rays, a->witems,
@@ -770,8 +779,7 @@ int32_t map_insert_scan_static(map_t* m, const float* xyz_dev, int64_t n, const 
   int32_t st = check_insert(m, xyz_dev, n, pose, flags, S);
   if (st) return st;
   int64_t need = 0;
-  // (shorter segments of the library's choice always fit: at most 196,608 points, 44 MB
-  // on the longest window)
+  // (shorter segments of the library's choice always fit: 6 MB at most)
   const int32_t seg_len = lone_seg_len(m, n);
   if (static_insert_bytes(m, n, seg_len, &need) > kScratchBytes) return MAP_E_CAPACITY;
   unsigned char* base = device_scratch(m->device);

@@ -28,14 +28,18 @@ def _insert_bytes(dims, n, seg_len):
     return blocks * (512 * 16 + 8 * ((max(dims) - 1) // seg_len + 1) * 8 + 32)
 
 
-# a map's own choice: 4 up to 49,152 points, 5 up to 196,608, then 8
-@pytest.mark.parametrize("n,set_len,runs", [
-    (1500, 8, 8), (131072, 8, 8), (131072, 5, 5), (200000, 3, 3),
-    (49152, 0, 4), (49153, 0, 5), (196608, 0, 5), (196609, 0, 8),
+# a map's own choice: 4 up to 2^24 points x longer side, 5 up to sides of 512 and 196,608
+# points, then 8
+@pytest.mark.parametrize("dims,n,set_len,runs", [
+    ((64, 48, 16), 1500, 8, 8), ((512, 12, 16), 131072, 8, 8), ((512, 12, 16), 131072, 5, 5),
+    ((64, 48, 16), 200000, 3, 3),
+    ((64, 48, 16), 1500, 0, 4), ((64, 48, 16), 262144, 0, 4), ((64, 48, 16), 262145, 0, 8),
+    ((512, 12, 16), 32768, 0, 4), ((512, 12, 16), 32769, 0, 5), ((12, 512, 16), 32769, 0, 5),
+    ((512, 12, 16), 196608, 0, 5), ((512, 12, 16), 196609, 0, 8),
+    ((514, 12, 16), 32640, 0, 4), ((514, 12, 16), 32641, 0, 8),
 ])
-def test_segment_length_that_runs(n, set_len, runs):
+def test_segment_length_that_runs(dims, n, set_len, runs):
     from paper_2109_13176_amd import gvom
-    dims = (64, 48, 16)
     pair = Pair(params(*dims, 0.5), set_len)
     try:
         used = gvom.lib().map_device_memory_in_use()
@@ -53,7 +57,7 @@ def test_no_memory_for_shorter_segments():
     another try while its buffers hold; a larger scan grows them again."""
     from paper_2109_13176_amd import gvom
     L = gvom.lib()
-    dims, n = (64, 48, 16), 131072
+    dims, n = (512, 12, 16), 131072
     pair = Pair(params(*dims, 0.5))
     try:
         pts = _cloud(n, 20.0, 1)
