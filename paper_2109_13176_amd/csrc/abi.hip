@@ -488,8 +488,9 @@ void insert_layout(const map_t* m, int64_t ray_blocks, int32_t seg_len, gvom::In
 //     74.8 / 77.1, 196,608 95.8 / 94.4 / 97.5, 262,144 125.3 / 123.4 / 123.9
 //   1024 x 1024 x 96: 16,384 32.6 / 32.7 / 36.8, 32,768 44.6 / 40.9 / 39.6, 49,152 60.2 /
 //     55.9 / 54.3, 131,072 132 / 133 / 134, 196,608 175 / 166 / 159
-// (The shorter segments cost traffic: on the 64-beam scan 0.35 M instead of 0.23 M line
-// requests.)  In a batch the maps fill the device together: 8.
+// (The shorter segments cost traffic: at 131,072 points on 512 x 512 x 64 the traversal
+// makes 0.311 M line requests and moves 26.4 MB with 5, 0.265 M and 23.8 MB with 8.)  In a
+// batch the maps fill the device together: 8.
 int32_t lone_seg_len(const map_t* m, int64_t n) {
   const int64_t side = std::max(m->p.nx, m->p.ny);
   if (!m->seg_auto) return m->seg_len;

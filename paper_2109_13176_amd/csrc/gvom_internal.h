@@ -89,8 +89,9 @@ constexpr int kBlock = 256;       // threads per block of the plain kernels
 constexpr int kRayBlock = 512;    // threads per block of the ray pass (rays regrouped per block)
 // threads per block of the traversal (single map and batch): four waves
 // share one LDS copy of the sensor box; seven of them fit a CU (72 registers a
-// thread; with 64, eight fit, but nine values go to scratch: 43.1 -> 43.8 us at
-// 131,072 points, 16.0 -> 18.4 at 28,800)
+// thread, for which one value goes to scratch, in the batch's kernel four; with 64
+// registers eight fit, but nine go: 43.1 -> 43.8 us at 131,072 points, 16.0 -> 18.4 at
+// 28,800)
 constexpr int kTraceBlock = 256;
 constexpr int kTraceWavesPerSimd = 7;
 // Points per traversal block of a batch, at most: 32 maps of 20,000-330,000 points take 725 us

@@ -225,12 +225,13 @@ __device__ __forceinline__ int64_t read_lane64(const int64_t v, const int lane) 
 // pass ends up in exactly one counter that reaches the map once, so the
 // result is the same integer sum whatever the claim order.
 //
-// On 512 x 512 x 64 with 131,072 points (150,000 steps of 11,000 items) the vector
-// instructions of a step (65) and an item's set-up (290) fill most of the kernel's
-// time; on 128 x 128 x 32 with 28,800 points, with one wave per SIMD, the chain of
-// LDS and memory round trips does.  With 16-bit counters, a search at every change
-// of line, coordinates, wraps and move counts in registers of their own, the stripes
-// searched in LDS and a set-up by divisions: 46.4 and 19.8 us, now 43.1 and 16.0.
+// On 512 x 512 x 64 with 131,072 points the walk makes 150,000 wave steps (three lanes of
+// four active) in 16,800 items of segments of 5 voxels, or 146,000 in 10,700 of 8: 17.9 M
+// and 16.0 M vector instructions in all.  Their issue fills two thirds of the kernel's
+// time; on 128 x 128 x 32 with 28,800 points, with one wave per SIMD, the chain of LDS
+// and memory round trips does.  With 16-bit counters, a search at every change of line,
+// coordinates, wraps and move counts in registers of their own, the stripes searched in
+// LDS and a set-up by divisions: 46.4 and 19.8 us, then 43.1 and 16.0 (segments of 8).
 constexpr int kWtSlots = 64;     // slots per wave (one per lane at the flush)
 constexpr int kWtStride = 5;     // LDS words per slot: tag and 4 words of 4 counters
 constexpr int kWtProbe = 4;

@@ -216,8 +216,8 @@ __device__ __forceinline__ bool walk_ended(const Walk& w) {
 // Axes in the order d, b, c (the others in ascending order), only at the end
 // brought back to x, y, z: the quotients are taken for two axes instead of three,
 // and two of the three E need no product of their own.  (Three entry coordinates and
-// three E, each by its own products: 390 vector instructions and 27 wide multiplies
-// for a wave's segment, now 270 and 12.)
+// three E, each by its own products: 390 vector instructions in the code and 27 wide
+// multiplies, so 270 and 12.)
 __device__ __forceinline__ bool segment_init(const InsertArgs& a, const int32_t q[3], const int dom,
                                              const int32_t j, Walk& w, int32_t l[3], bool up[3],
                                              int32_t most[3]) {

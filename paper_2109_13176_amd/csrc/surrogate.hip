@@ -890,8 +890,10 @@ __device__ __forceinline__ void bwd_weight_out_body(const float* __restrict__ dz
 // other; each alone is a chain of loads, LDS round trips and barriers on one or two
 // blocks per CU, so side by side they fill each other's waits.  Weight blocks first: they
 // are the longer ones.  512 x 512, 32 -> 32 channels: 23.1 + 20.0 us with four-wave
-// weight blocks, 17.2 + 20.2 with sixteen, 36.8 in one launch; the output layer's pair
-// 8.4 + 13.0 -> 18.3.  Both pass 84 MB (13.6 us at the copy rate).
+// weight blocks in a launch of their own, 17.2 + 20.2 with sixteen-wave ones, 36.7 in
+// one launch, where both kinds have eight (at two blocks per CU, 128 registers a thread,
+// the weight block spills 13 of them, which neither launch by itself did); the output
+// layer's pair 8.4 + 13.0 -> 18.3.  Both pass 84 MB (13.6 us at the copy rate).
 __global__ __launch_bounds__(512, 4) void k_bwd_layer(const uint16_t* __restrict__ dzh,
                                                       const uint16_t* __restrict__ dzl,
                                                       const uint16_t* __restrict__ wt,
