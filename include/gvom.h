@@ -264,8 +264,9 @@ int32_t map_sync(map_t* m);
  * 64-byte map lines and adds each line to the map with one request; the
  * passes of a 17 x 17 x 9 box around the sensor are summed per block on chip
  * first.  seg_len: dominant-axis voxels per ray segment, 1..1024 (8 until it is
- * set; a single insert then takes 4 if points x the window's longer side are at
- * most 2^24, and 5 on sides of up to 512 with up to 196,608 points);
+ * set; a single insert then takes 4 if points x the window's longer side, which
+ * counts as 1024 at most, are up to 2^24, and 5 on sides of up to 512 with up to
+ * 196,608 points);
  * trace_waves_per_cu: resident waves per compute unit requested for the
  * traversal grid (blocks of four waves), 1..32 (default 28, the most that fit
  * a compute unit); surface_tile: edge in

@@ -401,9 +401,10 @@ int32_t map_reset(map_t* m) {
   m->last_trace_blocks = 0;
   hipError_t e = intact ? clear_all(m) : fill_all(m);
   m->empty = true;
+  const bool told = m->wild || !intact;  // the import's word may not be zero
   m->wild = false;
   if (e == hipSuccess) e = hipMemsetAsync(m->stats, 0, kStatsBytes, m->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(m->imported, 0, 4, m->stream);
+  if (e == hipSuccess && told) e = hipMemsetAsync(m->imported, 0, 4, m->stream);
   // an insert that failed between the traversal and the fold leaves counts
   if (e == hipSuccess)
     e = hipMemsetAsync(m->box_rep, 0, (size_t)gvom::kBoxReps * gvom::kBoxCells * 4, m->stream);
@@ -488,13 +489,15 @@ void insert_layout(const map_t* m, int64_t ray_blocks, int32_t seg_len, gvom::In
 //     74.8 / 77.1, 196,608 95.8 / 94.4 / 97.5, 262,144 125.3 / 123.4 / 123.9
 //   1024 x 1024 x 96: 16,384 32.6 / 32.7 / 36.8, 32,768 44.6 / 40.9 / 39.6, 49,152 60.2 /
 //     55.9 / 54.3, 131,072 132 / 133 / 134, 196,608 175 / 166 / 159
+//   4096 x 4096 x 4, short rays: 5,000 30.7 / - / 36.9 (beyond 1024 a window is longer
+//     than most rays, so it counts as 1024)
 // (The shorter segments cost traffic: at 131,072 points on 512 x 512 x 64 the traversal
 // makes 0.311 M line requests and moves 26.4 MB with 5, 0.265 M and 23.8 MB with 8.)  In a
 // batch the maps fill the device together: 8.
 int32_t lone_seg_len(const map_t* m, int64_t n) {
   const int64_t side = std::max(m->p.nx, m->p.ny);
   if (!m->seg_auto) return m->seg_len;
-  if (n * side <= (int64_t)1 << 24) return 4;
+  if (n * std::min<int64_t>(side, 1024) <= (int64_t)1 << 24) return 4;
   return side <= 512 && n <= 196608 ? 5 : m->seg_len;
 }
 

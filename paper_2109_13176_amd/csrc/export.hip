@@ -181,7 +181,13 @@ __global__ __launch_bounds__(kBlock) void k_features(FeatArgs a, uint32_t nz_mag
 // Bound: HBM, 4 V read.  Measured at 512 x 512 x 64: half the columns 141 us
 // (4-byte stores to every voxel) -> 14.5 us; the whole map 3 x 18.3 us (three
 // fills) -> 14.5 us.
-__global__ __launch_bounds__(kBlock) void k_thin(Dims d, const uint8_t* thin, int32_t* hits,
+//
+// NT: threads per block.  A region of nz levels has 16 nz words, so one wave takes those
+// of few levels (with four, most do nothing but be launched).  The whole map by calls,
+// 256 / 64 threads: 4096 x 4096 x 4 250 / 104 us, 2048 x 2048 x 16 95 / 62, 512 x 512 x 32
+// 22.9 / 23.4, 512 x 512 x 64 28.4 / 32.1.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_thin(Dims d, const uint8_t* thin, int32_t* hits,
                                                  int32_t* passes, int32_t* minqz,
                                                  unsigned long long* occ, uint32_t nz_magic) {
   __shared__ unsigned long long lo[kRegCols], hi[kRegCols];  // storage z order, marked columns
@@ -209,14 +215,14 @@ __global__ __launch_bounds__(kBlock) void k_thin(Dims d, const uint8_t* thin, in
   __syncthreads();
   const unsigned long long mk = marked;
   if (!mk) return;
-  for (int k0 = 0; k0 < nv4; k0 += kLutLoads * kBlock) {
+  for (int k0 = 0; k0 < nv4; k0 += kLutLoads * NT) {
     int4 v[kLutLoads];
 #pragma unroll
     for (int u = 0; u < kLutLoads; u++)
-      v[u] = ((const int4*)(passes + r0))[min(k0 + u * kBlock + tid, nv4 - 1)];
+      v[u] = ((const int4*)(passes + r0))[min(k0 + u * NT + tid, nv4 - 1)];
 #pragma unroll
     for (int u = 0; u < kLutLoads; u++) {
-      const int k4 = k0 + u * kBlock + tid;
+      const int k4 = k0 + u * NT + tid;
       if (k4 >= nv4) continue;
       int zs;
       const int t = region_word(k4, nz, nz_magic, zs);
@@ -566,8 +572,12 @@ hipError_t launch_features(const FeatArgs& a, hipStream_t s) {
 
 hipError_t launch_thin(const Dims& d, const uint8_t* thin, int32_t* hits, int32_t* passes,
                        int32_t* minqz, unsigned long long* occ, hipStream_t s) {
-  hipLaunchKernelGGL(k_thin, region_grid(d), dim3(kBlock), 0, s, d, thin, hits, passes, minqz, occ,
-                     nz_magic(d.nz));
+  if (d.nz <= 16)
+    hipLaunchKernelGGL(k_thin<64>, region_grid(d), dim3(64), 0, s, d, thin, hits, passes, minqz,
+                       occ, nz_magic(d.nz));
+  else
+    hipLaunchKernelGGL(k_thin<256>, region_grid(d), dim3(256), 0, s, d, thin, hits, passes, minqz,
+                       occ, nz_magic(d.nz));
   return hipGetLastError();
 }
 

@@ -84,6 +84,12 @@ def test_region_kernels_match_oracle(nx, ny, nz, origin):
     o.close()
 
 
+@pytest.mark.parametrize("nx,ny,nz,origin", [(30, 22, 16, (3, -9, 5)), (22, 30, 17, (-8, 5, 9))])
+def test_region_kernels_around_sixteen_levels(nx, ny, nz, origin):
+    """The line between one and four waves per region of the thinning and the reset."""
+    test_region_kernels_match_oracle(nx, ny, nz, origin)
+
+
 def test_import_of_invalid_content_empties_the_map():
     from paper_2109_13176_amd import gvom
     nx, ny, nz = 34, 18, 9

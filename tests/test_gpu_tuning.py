@@ -28,8 +28,8 @@ def _insert_bytes(dims, n, seg_len):
     return blocks * (512 * 16 + 8 * ((max(dims) - 1) // seg_len + 1) * 8 + 32)
 
 
-# a map's own choice: 4 up to 2^24 points x longer side, 5 up to sides of 512 and 196,608
-# points, then 8
+# a map's own choice: 4 up to 2^24 points x longer side (1024 at most), 5 up to sides of 512
+# and 196,608 points, then 8
 @pytest.mark.parametrize("dims,n,set_len,runs", [
     ((64, 48, 16), 1500, 8, 8), ((512, 12, 16), 131072, 8, 8), ((512, 12, 16), 131072, 5, 5),
     ((64, 48, 16), 200000, 3, 3),
@@ -37,6 +37,7 @@ def _insert_bytes(dims, n, seg_len):
     ((512, 12, 16), 32768, 0, 4), ((512, 12, 16), 32769, 0, 5), ((12, 512, 16), 32769, 0, 5),
     ((512, 12, 16), 196608, 0, 5), ((512, 12, 16), 196609, 0, 8),
     ((514, 12, 16), 32640, 0, 4), ((514, 12, 16), 32641, 0, 8),
+    ((4096, 6, 8), 16384, 0, 4), ((4096, 6, 8), 16385, 0, 8),
 ])
 def test_segment_length_that_runs(dims, n, set_len, runs):
     from paper_2109_13176_amd import gvom
