@@ -84,14 +84,23 @@ __global__ __launch_bounds__(kBlock) void k_density(DensityArgs a, uint32_t nz_m
 //
 // Bound: HBM, 4 V read + 64 C written.  Measured at 512 x 512 x 64: 87 us (one
 // lane per column, hits and passes of every voxel in 4-byte reads 16 bytes
-// apart) -> 22.8 us.
+// apart) -> 22.8 us.  With few levels the round trips of a region bound it, so the 2D
+// maps are loaded beside the region's words: 2048 x 2048 x 8 227 us (a lane per column),
+// 189 (2D maps last), 155; 4096 x 4096 x 4 596, 688, 624; 4096 x 4096 x 1 376, 680, 596.
 __global__ __launch_bounds__(kBlock) void k_features(FeatArgs a, uint32_t nz_magic) {
   extern __shared__ __attribute__((aligned(16))) int32_t lpass[];  // [64][lut_row(nz)]
   __shared__ RegionCols rc;
   __shared__ unsigned long long sh[kRegCols], sq[kRegCols];  // sums of hits, of lowest returns
   __shared__ int32_t top_q[kRegCols], bot_h[kRegCols], bot_p[kRegCols];
   static_assert(kBlock == 4 * kRegCols, "four threads per column");
-  const int nx = a.d.nx, ny = a.d.ny, nz = a.d.nz, nzp = lut_row(nz);
+  const int ny = a.d.ny, nz = a.d.nz, nzp = lut_row(nz);
+  const int t = threadIdx.x >> 2, part = threadIdx.x & 3;
+  // the 2D maps of the thread's column, beside the region's loads
+  int32_t sxc, syc;
+  const int32_t c0 = max(region_col(a.d, blockIdx.x, blockIdx.y, t, sxc, syc), 0);
+  const float m0 = (part == 2 ? a.density : a.height)[c0], m1 = a.slope[c0], m2 = a.rough[c0];
+  const uint8_t fl0 = a.flags[c0];
+  const bool thin0 = a.thin && a.thin[c0];
   region_load(a.d, a.passes, a.occ, nz_magic, blockIdx.x, blockIdx.y, lpass, rc,
               [&](int t, int32_t) { sh[t] = sq[t] = 0ull; });
   __syncthreads();
@@ -109,7 +118,6 @@ __global__ __launch_bounds__(kBlock) void k_features(FeatArgs a, uint32_t nz_mag
     }
     if (o + 1 == rc.pre[t + 1]) top_q[t] = q;
   }
-  const int t = threadIdx.x >> 2, part = threadIdx.x & 3;
   int64_t sp = 0;
   for (int q = part; 4 * q < nz; q += 4) {
     const int4 v = *(const int4*)(lpass + t * nzp + 4 * q);
@@ -124,12 +132,11 @@ __global__ __launch_bounds__(kBlock) void k_features(FeatArgs a, uint32_t nz_mag
   const int32_t c = rc.col[t];
   if (c < 0) return;
   const int x = c / ny, y = c - x * ny;
-  (void)nx;
   const int cnt = rc.pre[t + 1] - rc.pre[t];
-  const bool thinned = a.thin && a.thin[c];
+  const bool thinned = thin0;
   const double q2m = a.res / 65536.0;
   float f[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  const uint8_t fl = thinned ? 0 : a.flags[c];
+  const uint8_t fl = thinned ? 0 : fl0;
   if (part == 0) {
     if (!thinned) {
       f[0] = (float)(double)(int64_t)sh[t];
@@ -139,7 +146,7 @@ __global__ __launch_bounds__(kBlock) void k_features(FeatArgs a, uint32_t nz_mag
     }
   } else if (part == 1) {
     if (fl & 1) {
-      f[0] = a.height[c];
+      f[0] = m0;
       f[3] = 1.0f;
     }
     if (!thinned && cnt > 0) {
@@ -151,17 +158,17 @@ __global__ __launch_bounds__(kBlock) void k_features(FeatArgs a, uint32_t nz_mag
       const double hb = bot_h[t], pb = bot_p[t];
       f[0] = (float)(hb / (hb + pb));
     }
-    if (fl & 2) f[1] = a.density[c];
+    if (fl & 2) f[1] = m0;
     if (fl & 32) {
-      f[2] = a.slope[c];
-      f[3] = a.rough[c];
+      f[2] = m1;
+      f[3] = m2;
     }
   } else {
     if (fl & 32) f[0] = 1.0f;
     const double cx = ((double)(a.O[0] + x) + 0.5) * a.res - a.sx;
     const double cy = ((double)(a.O[1] + y) + 0.5) * a.res - a.sy;
     f[1] = (float)sqrt(cx * cx + cy * cy);
-    if (fl & 1) f[2] = (float)(a.sz - (double)a.height[c]);
+    if (fl & 1) f[2] = (float)(a.sz - (double)m0);
     if (thinned) f[3] = 1.0f;
   }
   float* o = a.feat + (int64_t)c * 16 + 4 * part;
